@@ -96,6 +96,10 @@ hipError_t launch_attn_generic(const AttnGenericArgs& a, bool is_bf16, hipStream
 // act[m][i] (T) = silu(gu[m][i]) * gu[m][I + i];  gu: f32 [M][2I]
 hipError_t launch_swiglu(const float* gu, void* act, int M, int I, bool is_bf16, hipStream_t s);
 
+// the same from the partial products of the packed gate/up projection (tile columns 0..7 gate, 8..15 the matching up
+// columns), act bf16: parts f32 [n_parts][M][2I], slot s at parts + s * part_stride, summed in slot order
+hipError_t launch_swiglu_parts(const float* parts, int n_parts, size_t part_stride, bf16_t* act, int M, int I, hipStream_t s);
+
 // ---- generation head ----------------------------------------------------------------------------
 // x_out[r][:] = table[tokens[r]][:]  (T [rows][H]); an id outside [0, vocab) reads the nearest valid row and sets
 // *bad_id (host-visible memory, may be null) to 1
@@ -185,12 +189,18 @@ struct GemmArgs {
   const bf16_t* peers;     // bf16 [n_peers][peer_stride], row stride N; or null
   int n_peers;
   size_t peer_stride;      // elements
-  float* ssq_part;         // f32 [gemm_ssq_parts()][M] (at most ceil(N / 64) blocks), or null
+  float* ssq_part;         // f32 [gemm_ssq_parts()][M] (at most ceil(N / 32) blocks), or null
   // every epilogue: if non-null, row m of the product is multiplied by row_scale[m] first (the 1/rms of an
   // RMSNorm whose gain the producer of x has already applied: the factor commutes with the product)
   const float* row_scale;
+  // epilogue 0 only: workgroups along K; split ks leaves its partial product in out + ks * out_stride (0 or 1: no split)
+  int ksplit;
+  size_t out_stride;       // elements
 };
 hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s);
+// epilogue 0: the number of workgroups along K (1 .. max_split) that suits an M x N x K product
+// (extra_us: what taking a split at all costs beside the product)
+int gemm_ksplit(int M, int N, int K, int max_split, float extra_us);
 int gemm_ssq_parts(const GemmArgs& a);   // epilogue 3: the number of column blocks that launch_gemm_mfma(a) leaves in ssq_part
 // rs_a[m] (and rs_b[m] if non-null) = 1 / sqrt(sum_p ssq_part[p][m] / H + eps), p < n_part, fixed summation order
 hipError_t launch_row_rms(const float* ssq_part, int n_part, int M, int H, float eps, float* rs_a, float* rs_b, hipStream_t s);

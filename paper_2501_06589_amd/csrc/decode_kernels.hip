@@ -45,7 +45,8 @@ hipError_t launch_repack_tiles(const bf16_t* src, void* dst, int K, int N, int N
 }
 
 // ------------------------------------------------------------------------------------------------
-// Weight-streaming skinny GEMM  out[m][n] = sum_k x[m][k] W[k][n]  for M <= 16*MT rows.
+// Weight-streaming skinny GEMM  out[m][n] = sum_k x[m][k] W[k][n]  for M <= 16 rows
+// (more rows: gemm_ring_kernel, prefill_kernels.hip).
 // HBM-bound: every weight byte is read once, as one coalesced 1 KiB tile per wavefront load
 // (non-temporal: the stream must not evict x from the caches), and goes straight into the A operand
 // of a 16x16x32 bf16 MFMA; the B operand is the matching 16 rows x 32 k slice of x (rows >= M zeroed),
@@ -199,13 +200,10 @@ static hipError_t launch_gemv_mt(const GemvArgs& a, const GemvPlan& p, hipStream
 }
 
 hipError_t launch_gemv(const GemvArgs& a, hipStream_t s) {
-  if (a.M <= 0 || a.M > 64 || (a.N & 31) || (a.K & 31)) return hipErrorInvalidValue;
+  if (a.M <= 0 || a.M > 16 || (a.N & 31) || (a.K & 31)) return hipErrorInvalidValue;
   GemvPlan p = gemv_plan(a.M, a.N, a.K, a.epilogue == 0);
   if (a.ksplit != p.ksplit) return hipErrorInvalidValue;  // the caller sizes its slots from the same plan
-  const int mt = (a.M + 15) / 16;
-  if (mt == 1) return launch_gemv_mt<1>(a, p, s);
-  if (mt == 2) return launch_gemv_mt<2>(a, p, s);
-  return launch_gemv_mt<4>(a, p, s);
+  return launch_gemv_mt<1>(a, p, s);
 }
 
 // ------------------------------------------------------------------------------------------------

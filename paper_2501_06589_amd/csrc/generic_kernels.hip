@@ -286,6 +286,33 @@ hipError_t launch_swiglu(const float* gu, void* act, int M, int I, bool is_bf16,
   return hipGetLastError();
 }
 
+// Four activations per thread; the gate columns of eight activations and the matching up columns are neighbours.
+__global__ __launch_bounds__(256) void swiglu_parts_kernel(const float* __restrict__ parts, int n_parts, size_t part_stride,
+                                                           bf16_t* __restrict__ act, int M, int I) {
+  const long long gid = (long long)blockIdx.x * 256 + threadIdx.x;
+  const int i4 = I >> 2;
+  if (gid >= (long long)M * i4) return;
+  const int m = (int)(gid / i4), i = (int)(gid % i4) * 4;
+  const float* p = parts + (size_t)m * 2 * I + 16 * (i >> 3) + (i & 7);
+  float g[4] = {}, u[4] = {}, a[4];
+  for (int s = 0; s < n_parts; ++s) {
+    float t[4];
+    load4<float>(p + s * part_stride, t);
+    for (int e = 0; e < 4; ++e) g[e] += t[e];
+    load4<float>(p + s * part_stride + 8, t);
+    for (int e = 0; e < 4; ++e) u[e] += t[e];
+  }
+  for (int e = 0; e < 4; ++e) a[e] = g[e] / (1.0f + __expf(-g[e])) * u[e];
+  store4<bf16_t>(act + (size_t)m * I + i, a);
+}
+
+hipError_t launch_swiglu_parts(const float* parts, int n_parts, size_t part_stride, bf16_t* act, int M, int I, hipStream_t s) {
+  const long long total = (long long)M * (I >> 2);
+  if (total <= 0) return hipSuccess;
+  hipLaunchKernelGGL(swiglu_parts_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, parts, n_parts, part_stride, act, M, I);
+  return hipGetLastError();
+}
+
 // ------------------------------------------------------------------------------------------------
 // Caller-made cache content [B][nkv][S][d] -> K cache rows, V cache transposed.
 // ------------------------------------------------------------------------------------------------

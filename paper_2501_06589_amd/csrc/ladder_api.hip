@@ -322,7 +322,7 @@ int consumers_of(const ladder_ctx* c, int m, int out[2]) {
   return nc;
 }
 
-// Wide calls (more than 64 rows) of the packed-weight path with one real shard: the residual update of module m
+// Wide calls (more than FEW_ROWS rows) of the packed-weight path with one real shard: the residual update of module m
 // (Algorithm 1: the module's reduced output joins the stream; the AllReduce as a sum over rank partial sums, Eq. 2) is the
 // epilogue of the module's last GEMM instead of a kernel of its own, which saves a round trip of the fp32
 // product through memory.  The epilogue leaves the new rows, times the reading module's gain, as bf16 for the
@@ -354,6 +354,67 @@ int finish_residual(ladder_ctx* c, const GemmArgs& a, int rows, int nc, const in
   return LADDER_OK;
 }
 
+// Calls of at most this many rows: the projections may be split along K over workgroups (every CU gets some, whatever the
+// number of columns) and leave partial products, which the next kernel (rotary + append, SwiGLU, reduce + norm) adds up.
+// Beyond, the residual update is an epilogue (fuse_residual).  Measured with the line at 128 / 256 / 512 / 1024 rows (two
+// layers, us): 8B shape 200 rows 470 / 401 / 401 / 401, 1000 rows 1040 / 1040 / 1040 / 1018; 70B R = 8 shard 300 rows 465 /
+// 466 / 387 / 387, 1000 rows 892 / 892 / 891 / 818; 1.2B 400 rows 282 / 282 / 258 / 258, 1000 rows 404 / 404 / 404 / 420 (a
+// rule by module, fused where K is not worth a split, was no better: 70B R = 8 at 1000 rows 893).
+// FEW_ROWS_SLOTS slots per buffer up to 256 rows, as many as fit the same buffer beyond.
+constexpr int FEW_ROWS = 1024, FEW_ROWS_SLOTS = 8;
+constexpr float SPLIT_KERNEL_US = 4.0f;   // a kernel of its own that adds up partial products, where the epilogue would do
+
+size_t row_slots_of(const ladder_config& g) {
+  const size_t rows = (size_t)g.max_batch * g.max_tokens;
+  return std::max(rows, FEW_ROWS_SLOTS * std::min<size_t>(rows, 256));
+}
+
+int max_slots(const ladder_config& g, int rows) { return (int)std::min<size_t>(FEW_ROWS_SLOTS, row_slots_of(g) / (size_t)rows); }
+
+// one projection of a call of at most FEW_ROWS rows: out[slot][rows][N], returns the number of slots written
+int run_few_rows(ladder_ctx* c, const char* x, int ldx, const char* wp, int rows, int K, int N, float* out, hipStream_t s,
+                 int* slots, const float* row_scale = nullptr) {
+  if (rows <= 16) {
+    GemvArgs a{};
+    a.x = (const bf16_t*)x; a.ldx = ldx; a.wp = wp; a.M = rows; a.K = K; a.N = N;
+    a.ksplit = gemv_plan(rows, N, K, true).ksplit;
+    a.out = out; a.out_stride = (size_t)rows * N; a.slot0 = 0; a.epilogue = 0;
+    *slots = a.ksplit;
+    HIP_TRY(c, timed(c, LADDER_K_GEMV, s, [&] { return launch_gemv(a, s); }));
+    return LADDER_OK;
+  }
+  GemmArgs a{};
+  a.x = (const bf16_t*)x; a.ldx = ldx; a.wp = wp; a.M = rows; a.K = K; a.N = N; a.out = out; a.epilogue = 0; a.row_scale = row_scale;
+  a.ksplit = gemm_ksplit(rows, N, K, max_slots(c->cfg, rows), 0.f);
+  a.out_stride = (size_t)rows * N;
+  *slots = a.ksplit;
+  HIP_TRY(c, timed(c, LADDER_K_GEMM, s, [&] { return launch_gemm_mfma(a, s); }));
+  return LADDER_OK;
+}
+
+// the last projection of module m: (fuse) the residual update, or the partial products in out[slot][rows][hidden]
+int run_last_projection(ladder_ctx* c, int m, const char* x, const char* wp, int rows, int K, float* out, bool fuse, float* x_copy,
+                        hipStream_t s, int* slots) {
+  if (rows <= FEW_ROWS && !fuse) {
+    int n = 0;
+    const int rc = run_few_rows(c, x, K, wp, rows, K, c->cfg.hidden, out, s, &n);
+    *slots += n;
+    return rc;
+  }
+  GemmArgs a{};
+  a.x = (const bf16_t*)x; a.ldx = K; a.wp = wp; a.M = rows; a.K = K; a.N = c->cfg.hidden; a.out = out; a.epilogue = 0;
+  int cons[2], nc = 0;
+  if (fuse) nc = fuse_residual(c, a, m, x_copy, cons);
+  HIP_TRY(c, timed(c, LADDER_K_GEMM, s, [&] { return launch_gemm_mfma(a, s); }));
+  *slots += 1;
+  return fuse ? finish_residual(c, a, rows, nc, cons, s) : LADDER_OK;
+}
+
+// splits of the gate/up projection (its partial products have a buffer of their own, sized for the largest of these)
+int gate_up_ksplit(const ladder_config& g, int rows) {
+  return rows > 16 && rows <= FEW_ROWS ? gemm_ksplit(rows, 2 * g.inter, g.hidden, 4, SPLIT_KERNEL_US) : 1;
+}
+
 // ---------------------------------------------------------------------------------------------
 // one module's compute on the main stream; writes parts[m%2] and returns the number of slots written, or (fuse)
 // updates the residual itself and returns -1 slots: then no reduce follows
@@ -366,7 +427,7 @@ int run_module(ladder_ctx* c, int m, int B, int T, int pos0, hipStream_t s, int*
   const char* yin = c->y[par];
   float* pout = c->parts[par];
   const size_t pstride = (size_t)rows * H;
-  const bool skinny = rows <= 64;
+  const bool few = rows <= FEW_ROWS;
   const bool dev_pos = c->fast && T == 1;  // decode kernels of the bf16 path read the position from device memory
   int slots = 0;
   for (int r = 0; r < g.n_real_shards; ++r) {
@@ -378,13 +439,9 @@ int run_module(ladder_ctx* c, int m, int B, int T, int pos0, hipStream_t s, int*
         HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_gemm_generic(yin, L.wq, c->qkv, rows, nqd, H, c->nqkv, 0, c->bf16, s); }));
         HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_gemm_generic(yin, L.wk, c->qkv, rows, nkd, H, c->nqkv, nqd, c->bf16, s); }));
         HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_gemm_generic(yin, L.wv, c->qkv, rows, nkd, H, c->nqkv, nqd + nkd, c->bf16, s); }));
-      } else if (skinny) {
-        GemvArgs a{};
-        a.x = (const bf16_t*)yin; a.ldx = H; a.wp = L.pqkv; a.M = rows; a.K = H; a.N = c->nqkv;
-        a.ksplit = gemv_plan(rows, c->nqkv, H, true).ksplit;
-        a.out = c->qkv; a.out_stride = (size_t)rows * c->nqkv; a.slot0 = 0; a.epilogue = 0;
-        qkv_slots = a.ksplit;
-        HIP_TRY(c, timed(c, LADDER_K_GEMV, s, [&] { return launch_gemv(a, s); }));
+      } else if (few && (dev_pos || rows <= 16 || gemm_ksplit(rows, c->nqkv, H, max_slots(g, rows), SPLIT_KERNEL_US) > 1)) {
+        const int rc = run_few_rows(c, yin, H, L.pqkv, rows, H, c->nqkv, c->qkv, s, &qkv_slots, c->y_scale[par]);
+        if (rc) return rc;
       } else {
         GemmArgs a{};
         a.x = (const bf16_t*)yin; a.ldx = H; a.wp = L.pqkv; a.M = rows; a.K = H; a.N = c->nqkv; a.row_scale = c->y_scale[par];
@@ -430,21 +487,9 @@ int run_module(ladder_ctx* c, int m, int B, int T, int pos0, hipStream_t s, int*
       if (!c->fast) {
         HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_gemm_generic(c->obuf, L.wo, pout + slots * pstride, rows, H, nqd, H, 0, c->bf16, s); }));
         slots += 1;
-      } else if (skinny) {
-        GemvArgs a{};
-        a.x = (const bf16_t*)c->obuf; a.ldx = nqd; a.wp = L.po; a.M = rows; a.K = nqd; a.N = H;
-        a.ksplit = gemv_plan(rows, H, nqd, true).ksplit;
-        a.out = pout; a.out_stride = pstride; a.slot0 = slots; a.epilogue = 0;
-        HIP_TRY(c, timed(c, LADDER_K_GEMV, s, [&] { return launch_gemv(a, s); }));
-        slots += a.ksplit;
       } else {
-        GemmArgs a{};
-        a.x = (const bf16_t*)c->obuf; a.ldx = nqd; a.wp = L.po; a.M = rows; a.K = nqd; a.N = H; a.out = pout + slots * pstride; a.epilogue = 0;
-        int cons[2], nc = 0;
-        if (fuse) nc = fuse_residual(c, a, m, x_copy, cons);
-        HIP_TRY(c, timed(c, LADDER_K_GEMM, s, [&] { return launch_gemm_mfma(a, s); }));
-        if (fuse) { const int rc = finish_residual(c, a, rows, nc, cons, s); if (rc) return rc; }
-        slots += 1;
+        const int rc = run_last_projection(c, m, c->obuf, L.po, rows, nqd, pout + slots * pstride, fuse, x_copy, s, &slots);
+        if (rc) return rc;
       }
     } else {
       if (!c->fast) {
@@ -453,29 +498,23 @@ int run_module(ladder_ctx* c, int m, int B, int T, int pos0, hipStream_t s, int*
         HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_swiglu(c->gu, c->act, rows, I, c->bf16, s); }));
         HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_gemm_generic(c->act, L.wd, pout + slots * pstride, rows, H, I, H, 0, c->bf16, s); }));
         slots += 1;
-      } else if (skinny) {
-        GemvArgs a{};
-        a.x = (const bf16_t*)yin; a.ldx = H; a.wp = L.pgu; a.M = rows; a.K = H; a.N = 2 * I; a.ksplit = 1;
-        a.act = (bf16_t*)c->act; a.epilogue = 1;
-        HIP_TRY(c, timed(c, LADDER_K_GEMV, s, [&] { return launch_gemv(a, s); }));
-        GemvArgs b{};
-        b.x = (const bf16_t*)c->act; b.ldx = I; b.wp = L.pd; b.M = rows; b.K = I; b.N = H;
-        b.ksplit = gemv_plan(rows, H, I, true).ksplit;
-        b.out = pout; b.out_stride = pstride; b.slot0 = slots; b.epilogue = 0;
-        HIP_TRY(c, timed(c, LADDER_K_GEMV, s, [&] { return launch_gemv(b, s); }));
-        slots += b.ksplit;
       } else {
-        GemmArgs a{};
-        a.x = (const bf16_t*)yin; a.ldx = H; a.wp = L.pgu; a.M = rows; a.K = H; a.N = 2 * I; a.act = (bf16_t*)c->act; a.epilogue = 1;
-        a.row_scale = c->y_scale[par];
-        HIP_TRY(c, timed(c, LADDER_K_GEMM, s, [&] { return launch_gemm_mfma(a, s); }));
-        GemmArgs b{};
-        b.x = (const bf16_t*)c->act; b.ldx = I; b.wp = L.pd; b.M = rows; b.K = I; b.N = H; b.out = pout + slots * pstride; b.epilogue = 0;
-        int cons[2], nc = 0;
-        if (fuse) nc = fuse_residual(c, b, m, x_copy, cons);
-        HIP_TRY(c, timed(c, LADDER_K_GEMM, s, [&] { return launch_gemm_mfma(b, s); }));
-        if (fuse) { const int rc = finish_residual(c, b, rows, nc, cons, s); if (rc) return rc; }
-        slots += 1;
+        if (rows <= 16) {
+          GemvArgs a{};
+          a.x = (const bf16_t*)yin; a.ldx = H; a.wp = L.pgu; a.M = rows; a.K = H; a.N = 2 * I; a.ksplit = 1;
+          a.act = (bf16_t*)c->act; a.epilogue = 1;
+          HIP_TRY(c, timed(c, LADDER_K_GEMV, s, [&] { return launch_gemv(a, s); }));
+        } else {
+          GemmArgs a{};
+          a.x = (const bf16_t*)yin; a.ldx = H; a.wp = L.pgu; a.M = rows; a.K = H; a.N = 2 * I; a.row_scale = c->y_scale[par];
+          const int gu_slots = gate_up_ksplit(g, rows);
+          if (gu_slots > 1) { a.out = c->gu; a.epilogue = 0; a.ksplit = gu_slots; a.out_stride = (size_t)rows * 2 * I; }
+          else { a.act = (bf16_t*)c->act; a.epilogue = 1; }
+          HIP_TRY(c, timed(c, LADDER_K_GEMM, s, [&] { return launch_gemm_mfma(a, s); }));
+          if (gu_slots > 1) HIP_TRY(c, timed(c, LADDER_K_OTHER, s, [&] { return launch_swiglu_parts(c->gu, gu_slots, (size_t)rows * 2 * I, (bf16_t*)c->act, rows, I, s); }));
+        }
+        const int rc = run_last_projection(c, m, c->act, L.pd, rows, I, pout + slots * pstride, fuse, x_copy, s, &slots);
+        if (rc) return rc;
       }
     }
   }
@@ -609,9 +648,9 @@ int forward_body(ladder_ctx* c, const void* x_in, int B, int T, int pos0, void* 
   hipStream_t s0 = c->s_attn;
   auto module_stream = [&](int m) { return (overlap && (m & 1) == 0) ? c->s_mlp : s0; };
   auto reduce_stream = [&](int m) { return m == 0 ? s0 : (overlap ? module_stream(m) : (side ? c->side : s0)); };
-  // (the skinny kernels have no such epilogue, several real shards would each add to the residual, and the
+  // (calls of few rows split K over workgroups, whose partial products the reduce adds up; several real shards would each add to the residual, and the
   // emulated collective latency wants the reduce as a step of its own)
-  const bool fuse = c->fast && rows > 64 && c->cfg.n_real_shards == 1 && c->cfg.reduce_delay_us == 0;
+  const bool fuse = c->fast && rows > FEW_ROWS && c->cfg.n_real_shards == 1 && c->cfg.reduce_delay_us == 0;
   int rc = st ? run_stage_in(c, *st, rows, s0) : run_reduce(c, 0, rows, 0, x_in, c->n_mod == 0 ? (float*)x_out : nullptr, s0);
   if (rc) return rc;
   const size_t x_bytes = (size_t)rows * c->cfg.hidden * 4;
@@ -1526,11 +1565,9 @@ static int init_impl(const ladder_config* cfg, void* hip_stream, ladder_ctx** ou
   if (c->err_word) c->err_word[0] = c->err_word[1] = 0u;
   INIT_HIP(hipHostGetDevicePointer((void**)&c->err_word_dev, c->err_word, 0));
   // workspaces
-  // rows x slots of the partial-sum buffers: a skinny call (rows <= 64) may use up to 8 split-K slots
-  // per shard, a wide call uses one
+  // rows x slots of the partial-sum buffers: a call of few rows may use up to 8 split-K slots per shard, a wide call uses one
   const size_t rows = (size_t)c->rows_cap;
-  const size_t skinny_rows = rows < 64 ? rows : 64;
-  const size_t row_slots = rows > 8 * skinny_rows ? rows : 8 * skinny_rows;
+  const size_t row_slots = row_slots_of(g);
   INIT_TRY(dev_alloc(c, (void**)&c->x, rows * H * 4, false));
   INIT_TRY(dev_alloc(c, (void**)&c->pos_dev, 256, true));
   INIT_TRY(dev_alloc(c, (void**)&c->emb_stage, (size_t)g.max_batch * H * esz, false));
@@ -1542,9 +1579,15 @@ static int init_impl(const ladder_config* cfg, void* hip_stream, ladder_ctx** ou
   INIT_TRY(dev_alloc(c, (void**)&c->qbuf, rows * nq * d * esz, false));
   INIT_TRY(dev_alloc(c, (void**)&c->obuf, rows * nq * d * esz, false));
   INIT_TRY(dev_alloc(c, (void**)&c->act, rows * I * esz, false));
-  if (!c->fast) INIT_TRY(dev_alloc(c, (void**)&c->gu, rows * 2 * I * 4, false));
+  // the SwiGLU inputs in fp32: the plain path keeps the whole product, the packed path the slots of a split projection
+  size_t gu_rows = c->fast ? 0 : rows;
+  for (int r = 17; c->fast && r <= FEW_ROWS && (size_t)r <= rows; ++r) {
+    const int n = gate_up_ksplit(g, r);
+    if (n > 1) gu_rows = std::max(gu_rows, (size_t)n * r);
+  }
+  if (gu_rows) INIT_TRY(dev_alloc(c, (void**)&c->gu, gu_rows * 2 * I * 4, false));
   if (c->fast) {
-    INIT_TRY(dev_alloc(c, (void**)&c->ssq_part, (size_t)((H + 63) / 64) * rows * 4, false));
+    INIT_TRY(dev_alloc(c, (void**)&c->ssq_part, (size_t)((H + 31) / 32) * rows * 4, false));
     for (int i = 0; i < 2; ++i) INIT_TRY(dev_alloc(c, (void**)&c->y_rs[i], rows * 4, false));
     const size_t chunks = (size_t)(c->s_cap / 32);
     const size_t gq = nq / nkv;
@@ -1938,7 +1981,7 @@ static int head_body(ladder_ctx* c, const float* x, int rows, char* y, float* lo
   HIP_TRY(c, launch_head_norm(x, c->head_gain, y, rows, H, g.rms_eps, c->bf16, s));
   if (!c->head_fast) {
     HIP_TRY(c, launch_gemm_generic(y, c->head_w, logits, rows, V, H, V, 0, c->bf16, s));
-  } else if (rows <= 64) {
+  } else if (rows <= 16 || (V & 31)) {
     GemvArgs a{};
     a.x = (const bf16_t*)y; a.ldx = H; a.wp = c->head_wp; a.M = rows; a.K = H; a.N = V; a.ksplit = 1;
     a.out = logits; a.out_stride = (size_t)rows * V; a.slot0 = 0; a.epilogue = 0;

@@ -7,10 +7,6 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4_t;
 
-// workgroup tile of the large-M GEMM: 16 row tiles (256 x 256) at one wave per SIMD, or 8 (128 x 256) at two
-#define GEMM_WM_LARGE 8
-#define GEMM_WAVES_LARGE 2
-
 __device__ __forceinline__ void unpack8(const uint4 v, float (&f)[8]) {
   f[0] = __uint_as_float(v.x << 16); f[1] = __uint_as_float(v.x & 0xFFFF0000u);
   f[2] = __uint_as_float(v.y << 16); f[3] = __uint_as_float(v.y & 0xFFFF0000u);
@@ -24,27 +20,16 @@ __device__ __forceinline__ f32x4_t mfma16(const uint4 a, const uint4 b, const f3
 }
 
 // ------------------------------------------------------------------------------------------------
-// C[M][N] = X[M][K] W[K][N].  Workgroup tile: BM = 16*WM rows x 256 columns, 4 wavefronts side by
-// side along N (64 columns = 4 weight tiles each).  The weights are the MFMA A operand and come
-// straight from global memory in their packed tile order (1 KiB coalesced per wave load, each tile
-// read by exactly one wave of the workgroup); the activations are the B operand, staged once per
-// workgroup through double-buffered LDS and shared by the 4 waves.  One k tile (32) per stage: the
-// next stage's weights and activations are requested before the MFMAs of the current one.
-// Output element (m, n) sits in lane (n%16)/4*16 + m%16, register n%4: a lane stores 4 consecutive
-// columns.
-// All global loads are unconditional (row / tile / k indices clamped into range): a guarded load makes
-// the compiler drain every outstanding load before the MFMAs.  What a clamped load brings in is
-// neutralised later: rows >= M become zeros when the X tile is written to LDS, columns >= N are never
-// stored, and the stage past the end is never multiplied.
+// C[M][N] = X[M][K] W[K][N] on the packed weight tiles: two kernels, gemm_lds_kernel (256 x 256 tiles) for calls whose
+// tiles fill the chip and gemm_ring_kernel (smaller tiles, optional split of K) for the others; gemm_plan chooses.
+// In both the weights are the MFMA A operand and the activations the B operand, so output element (m, n) sits in
+// lane (n%16)/4*16 + m%16, register n%4: a lane stores 4 consecutive columns.
+// Rows >= M and weight tiles >= N/16 are clamped on load: they only reach outputs that are not stored.
 // ------------------------------------------------------------------------------------------------
-#define GEMM_BK 32
-#define GEMM_LDS_STRIDE (GEMM_BK + 8)  // bf16 elements per LDS row: 80 bytes, conflict-free 16-byte reads
-#define GEMM_GROUP_M 16
-
-// Epilogue of a wavefront's 64-column x (16 WM)-row accumulator block: row base m0, first weight tile nt0.
+// Epilogue of a wavefront's (16 JT)-column x (16 WM)-row accumulator block: row base m0, first weight tile nt0.
 // Output element (m, n) sits in lane (n%16)/4*16 + m%16, register n%4: a lane stores 4 consecutive columns.
-template <int WM>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x4_t (&acc)[4][WM], int m0, int nt0, int NT, int lane) {
+template <int WM, int JT>
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x4_t (&acc)[JT][WM], int m0, int nt0, int NT, int lane) {
   const int b = lane & 15, q = lane >> 4;
   // row scale (1.0 where there is none: the multiplication is exact then), applied where an accumulator is read
   auto scale_of = [&](int mt) { return a.row_scale ? a.row_scale[min(m0 + mt * 16 + b, a.M - 1)] : 1.0f; };
@@ -55,7 +40,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x4_t (&acc)[
       const float rs = scale_of(mt);
       if (m >= a.M) continue;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
+      for (int j = 0; j < JT; ++j) {
         if (nt0 + j >= NT) continue;
         const int n = (nt0 + j) * 16 + 4 * q;
         *reinterpret_cast<float4*>(a.out + (size_t)m * a.N + n) =
@@ -65,7 +50,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x4_t (&acc)[
   } else if (a.epilogue == 3) {
     // residual update; the summation order per element is fixed: old value, product, peers 0, 1, ...
     // The operands (old values, the first three peers) of two column tiles are requested at once.
-    constexpr int PB = 3, JB = 2, JG = 4 / JB, STEPS = WM * JG;
+    constexpr int PB = 3, JB = JT < 2 ? 1 : 2, JG = JT / JB, STEPS = WM * JG;
     struct Operands { float4 xo[JB]; uint2 pk[JB][PB]; };
     Operands o;
     auto row_of = [&](int mt) { return (size_t)min(m0 + mt * 16 + b, a.M - 1) * a.N; };
@@ -122,10 +107,10 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x4_t (&acc)[
         }
         ss += v4[0] * v4[0] + v4[1] * v4[1] + v4[2] * v4[2] + v4[3] * v4[3];
       }
-      if (st % JG == JG - 1) {   // the row block is complete: its rows' sums of squares over this wavefront's 64 columns
+      if (st % JG == JG - 1) {   // the row block is complete: its rows' sums of squares over this wavefront's columns
         ss += __shfl_xor(ss, 16, 64);
         ss += __shfl_xor(ss, 32, 64);
-        if (a.ssq_part && q == 0 && ok && nt0 < NT) a.ssq_part[(size_t)(nt0 >> 2) * a.M + m] = ss;
+        if (a.ssq_part && q == 0 && ok && nt0 < NT) a.ssq_part[(size_t)(nt0 / JT) * a.M + m] = ss;
         ss = 0.f;
       }
     }
@@ -139,7 +124,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x4_t (&acc)[
       if (m >= a.M) continue;
       const int seq = m / a.T, pos = a.pos0 + m % a.T;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
+      for (int j = 0; j < JT; ++j) {
         if (nt0 + j >= NT) continue;
         const int col = (nt0 + j) * 16 + 4 * q;
         const int head = col / a.d, dim = col % a.d;
@@ -176,7 +161,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x4_t (&acc)[
       const int m = m0 + mt * 16 + b;
       const float rs = scale_of(mt);   // (lane + 32 holds the same row)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
+      for (int j = 0; j < JT; ++j) {
         float r4[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -195,113 +180,24 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x4_t (&acc)[
   }
 }
 
-template <int WM, int MIN_WAVES>
-__global__ __launch_bounds__(256, MIN_WAVES) void gemm_mfma_kernel(GemmArgs a) {
-  constexpr int BM = 16 * WM;
-  constexpr int XV = BM * 4 / 256;  // 16-byte segments per thread per stage of the X tile (BM rows x 64 bytes)
-  static_assert(XV >= 1, "tile too small");
-  extern __shared__ __attribute__((aligned(16))) bf16_t xs_raw[];   // [2][BM][GEMM_LDS_STRIDE]
-  bf16_t (*xs)[BM][GEMM_LDS_STRIDE] = reinterpret_cast<bf16_t (*)[BM][GEMM_LDS_STRIDE]>(xs_raw);
-
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int b = lane & 15, q = lane >> 4;
-  const int KT = a.K >> 5, NT = a.N >> 4;
-  const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + 255) / 256;
-  // Workgroups are handed to the 8 XCDs round robin by block index and every XCD has its own L2: block
-  // index i is mapped to position (i % 8) * (n / 8) + i / 8 of the tile order, so that each XCD works
-  // through one contiguous eighth of it and neighbours in the order (which share operands) meet in one L2.
-  const int nblk = gridDim.x, nblk8 = nblk & ~7;
-  const int bid = (int)blockIdx.x < nblk8 ? ((int)blockIdx.x & 7) * (nblk8 >> 3) + ((int)blockIdx.x >> 3) : (int)blockIdx.x;
-  // grouped rasterisation: GROUP_M row blocks share one column block back to back
-  const int per_group = GEMM_GROUP_M * tiles_n;
-  const int group = bid / per_group, in_group = bid % per_group;
-  const int gm = min(GEMM_GROUP_M, tiles_m - group * GEMM_GROUP_M);
-  const int m_blk = group * GEMM_GROUP_M + in_group % gm;
-  const int n_blk = in_group / gm;
-  const int m0 = m_blk * BM;
-  const int nt0 = n_blk * 16 + wave * 4;
-
-  f32x4_t acc[4][WM];
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-#pragma unroll
-    for (int mt = 0; mt < WM; ++mt) acc[j][mt] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
-
-  // per-thread source addresses of the X tile (row clamped) and of the 4 weight tiles (tile clamped)
-  const bf16_t* xsrc[XV];
-  bool xok[XV];
-#pragma unroll
-  for (int i = 0; i < XV; ++i) {
-    const int idx = tid + i * 256, row = idx >> 2, seg = idx & 3;
-    xok[i] = m0 + row < a.M;
-    xsrc[i] = a.x + (size_t)min(m0 + row, a.M - 1) * a.ldx + seg * 8;
-  }
-  const u32x4_t* wsrc[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-    wsrc[j] = reinterpret_cast<const u32x4_t*>(a.wp) + (size_t)min(nt0 + j, NT - 1) * KT * 64 + lane;
-
-  u32x4_t xg[XV], w0[4], w1[4];
-  auto load_stage = [&](u32x4_t (&w)[4], int kt) {
-    const int ktc = min(kt, KT - 1);
-#pragma unroll
-    for (int i = 0; i < XV; ++i) xg[i] = *reinterpret_cast<const u32x4_t*>(xsrc[i] + (size_t)ktc * 32);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) w[j] = wsrc[j][(size_t)ktc * 64];
-  };
-  auto store_x = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < XV; ++i) {
-      const int idx = tid + i * 256, row = idx >> 2, seg = idx & 3;
-      *reinterpret_cast<u32x4_t*>(&xs[buf][row][seg * 8]) = xok[i] ? xg[i] : (u32x4_t){0u, 0u, 0u, 0u};
-    }
-  };
-  // LDS fragments are read two row tiles ahead of the MFMAs that consume them; the scheduling barriers
-  // keep that distance (left alone, the compiler hoists every read to the top and runs out of registers)
-  auto compute = [&](const u32x4_t (&w)[4], int buf) {
-    auto frag = [&](int mt) { return *reinterpret_cast<const u32x4_t*>(&xs[buf][mt * 16 + b][q * 8]); };
-    u32x4_t f0 = frag(0), f1 = frag(1), f2;
-#pragma unroll
-    for (int mt = 0; mt < WM; ++mt) {
-      f2 = frag(mt + 2 < WM ? mt + 2 : WM - 1);
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        acc[j][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w[j]),
-                                                            __builtin_bit_cast(bf16x8_t, f0), acc[j][mt], 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      f0 = f1;
-      f1 = f2;
-    }
-  };
-
-  load_stage(w0, 0);
-  store_x(0);
-  __syncthreads();
-  for (int kt = 0; kt < KT; kt += 2) {
-    load_stage(w1, kt + 1);
-    __builtin_amdgcn_sched_barrier(0);
-    compute(w0, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    store_x(1);
-    __syncthreads();
-    if (kt + 1 >= KT) break;
-    load_stage(w0, kt + 2);
-    __builtin_amdgcn_sched_barrier(0);
-    compute(w1, 1);
-    __builtin_amdgcn_sched_barrier(0);
-    store_x(0);
-    __syncthreads();
-  }
-
-  gemm_epilogue<WM>(a, acc, m0, nt0, NT, lane);
-}
-
-__global__ __launch_bounds__(256) void row_rms_kernel(const float* __restrict__ part, int n_part, int M, float h, float eps,
-                                                      float* __restrict__ rs_a, float* __restrict__ rs_b) {
-  const int m = blockIdx.x * 256 + threadIdx.x;
-  if (m >= M) return;
+// 64 rows per workgroup, the partial sums dealt out over its 16 wavefronts (a serial chain of loads otherwise: 64 parts x
+// 2048 rows 17 us); fixed order: every wavefront its parts in turn, then the wavefronts 0 .. 15
+__global__ __launch_bounds__(1024) void row_rms_kernel(const float* __restrict__ part, int n_part, int M, float h, float eps,
+                                                       float* __restrict__ rs_a, float* __restrict__ rs_b) {
+  __shared__ float sum[16][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int m = blockIdx.x * 64 + lane;
   float tot = 0.f;
-  for (int p = 0; p < n_part; ++p) tot += part[(size_t)p * M + m];
+  if (m < M) {
+#pragma unroll 4
+    for (int p = wave; p < n_part; p += 16) tot += part[(size_t)p * M + m];
+  }
+  sum[wave][lane] = tot;
+  __syncthreads();
+  if (wave > 0 || m >= M) return;
+  tot = 0.f;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) tot += sum[w][lane];
   const float rs = 1.0f / sqrtf(tot / h + eps);
   rs_a[m] = rs;
   if (rs_b) rs_b[m] = rs;
@@ -309,16 +205,7 @@ __global__ __launch_bounds__(256) void row_rms_kernel(const float* __restrict__ 
 
 hipError_t launch_row_rms(const float* ssq_part, int n_part, int M, int H, float eps, float* rs_a, float* rs_b, hipStream_t s) {
   if (M <= 0) return hipSuccess;
-  hipLaunchKernelGGL(row_rms_kernel, dim3((M + 255) / 256), dim3(256), 0, s, ssq_part, n_part, M, (float)H, eps, rs_a, rs_b);
-  return hipGetLastError();
-}
-
-template <int WM, int MIN_WAVES>
-static hipError_t launch_gemm_wm(const GemmArgs& a, hipStream_t s) {
-  constexpr int BM = 16 * WM;
-  const size_t lds = (size_t)2 * BM * GEMM_LDS_STRIDE * sizeof(bf16_t);
-  const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + 255) / 256;
-  hipLaunchKernelGGL((gemm_mfma_kernel<WM, MIN_WAVES>), dim3(tiles_m * tiles_n), dim3(256), lds, s, a);
+  hipLaunchKernelGGL(row_rms_kernel, dim3((M + 63) / 64), dim3(1024), 0, s, ssq_part, n_part, M, (float)H, eps, rs_a, rs_b);
   return hipGetLastError();
 }
 
@@ -343,14 +230,15 @@ static hipError_t launch_gemm_wm(const GemmArgs& a, hipStream_t s) {
 // issue its load cannot issue the MFMAs behind it either).
 // Rows >= M and weight tiles >= N/16 are clamped on load (they only reach outputs that are not stored).
 // K must be a multiple of 64.
-// Tile order: the XCD-aware order of gemm_mfma_kernel with groups of GEMM2_GROUP_M row blocks; the 32 CUs
-// of an XCD then work on 4 row blocks x 8 column blocks at a time (groups of 2 / 4 / 8 row blocks:
+// Tile order: workgroups are handed to the 8 XCDs round robin by block index and every XCD has its own L2, so block
+// index i is mapped to position (i % 8) * (n / 8) + i / 8 of the tile order: each XCD works through one contiguous
+// eighth of it and neighbours in the order (which share operands) meet in one L2.  GEMM2_GROUP_M row blocks share one
+// column block back to back; the 32 CUs of an XCD then work on 4 row blocks x 8 column blocks at a time (groups of 2 / 4 / 8 row blocks:
 // 1309 / 1335 / 1297 TFLOP/s on 32768 x 8192 x 14336).
-// Against gemm_mfma_kernel at 128 x 256 (two workgroups per CU): a third less operand traffic per CU
-// and no register staging; 971 -> 1129, 908 -> 993, 1098 -> 1271, 1158 -> 1338 TFLOP/s on the QKV / O / down /
-// gate-up shapes of the 70B R = 4 shard at 32768 rows.
+// 1129 / 993 / 1271 / 1338 TFLOP/s on the QKV / O / down / gate-up shapes of the 70B R = 4 shard at 32768 rows.
 // ------------------------------------------------------------------------------------------------
 #define GEMM2_GROUP_M 4
+#define RING_GROUP_M 8
 #define GEMM2_LDSP(p) ((__attribute__((address_space(3))) void*)(p))
 #define GEMM2_GLBP(p) ((const __attribute__((address_space(1))) void*)(p))
 
@@ -494,7 +382,7 @@ __global__ __launch_bounds__(512, 2) void gemm_lds_kernel(GemmArgs a) {
   const int wm = wave >> 2, wn = wave & 3;
   const int KT = a.K >> 5, KB = a.K >> 6, NT = a.N >> 4;
   const int tiles_m = (a.M + 255) / 256, tiles_n = (a.N + 255) / 256;
-  const int nblk = gridDim.x, nblk8 = nblk & ~7;   // XCD-aware order, as in gemm_mfma_kernel
+  const int nblk = gridDim.x, nblk8 = nblk & ~7;   // XCD-aware order
   const int bid = (int)blockIdx.x < nblk8 ? ((int)blockIdx.x & 7) * (nblk8 >> 3) + ((int)blockIdx.x >> 3) : (int)blockIdx.x;
   const int per_group = GEMM2_GROUP_M * tiles_n;
   const int group = bid / per_group, in_group = bid % per_group;
@@ -636,7 +524,7 @@ __global__ __launch_bounds__(512, 2) void gemm_lds_kernel(GemmArgs a) {
   // the clamped loads past the last k tile are still in flight into LDS: they must land before the workgroup ends
   gemm2_wait_and_meet<0>();
   if (a.epilogue == 3) gemm2_residual_epilogue(a, acc, g2_lds, m0, n_blk, wave, lane);
-  else gemm_epilogue<WM>(a, acc, m0 + wm * 128, nt0 + wn * 4, NT, lane);
+  else gemm_epilogue<WM, 4>(a, acc, m0 + wm * 128, nt0 + wn * 4, NT, lane);
 }
 
 static hipError_t launch_gemm_lds(const GemmArgs& a, hipStream_t s) {
@@ -655,15 +543,243 @@ static hipError_t launch_gemm_lds(const GemmArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-static bool gemm_takes_lds_kernel(const GemmArgs& a) {
-  // 256 x 256 tiles, one per CU, when they fill the chip at least once; else the smaller tiles
-  return (long)((a.M + 255) / 256) * ((a.N + 255) / 256) >= 256 && (a.K & 63) == 0 && a.K >= 256;
+// ------------------------------------------------------------------------------------------------
+// Few or ragged rows: BM x BN workgroup tile, WR x WC wavefronts, K in stages of 64 through a ring of S stages in LDS,
+// optionally split over ksplit workgroups whose partial products the caller's next kernel adds up.  With up to a few
+// hundred rows the product is bound by the one pass over the weights, so what counts is how many bytes of them are in
+// flight on how many CUs: S - 1 stages of direct-to-LDS loads per workgroup (64 - 120 KiB, one workgroup per CU) and, by
+// the split of K, a workgroup for every CU whatever N is.  Both operands are staged as in gemm_lds_kernel (weights: packed
+// tiles as they stand; activations: 8 rows x 64 k per load, XOR-swizzled).  K is a multiple of 32; an odd last k tile
+// half-fills its stage.
+// Measured (8B shape, us, weights from memory; against 64- or 128-row tiles with register-staged operands and no split):
+// 100 rows QKV 68 -> 15.4, O 68 -> 11, gate/up 81 -> 48, down 231 -> 25.5; 64 rows gate/up 84 -> 41.5 (5.7 TB/s), down
+// 248 -> 22.8; 2048 rows O 85 -> 63, down 276 -> 205 (1170 TFLOP/s, 128 x 256 tiles).  64 rows x 1280 columns of K 8192: 142 -> 7.3.
+// Non-temporal weight loads where one row block covers all rows: gate/up 46.6 -> 41.5 at 64 rows; with several row
+// blocks they are 5 - 13 % slower.  A rotated start of the K sweep: no change.
+// ------------------------------------------------------------------------------------------------
+// this wave's LDS reads are complete and at most N of its vector-memory operations in flight; then the workgroup meets
+template <int N>
+__device__ __forceinline__ void ring_meet() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_waitcnt(0x0070 | (N & 15) | ((N >> 4) << 14));
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
 }
 
-int gemm_ssq_parts(const GemmArgs& a) { return gemm_takes_lds_kernel(a) ? (a.N + 255) / 256 : (a.N + 63) / 64; }
+template <int BM, int BN, int WR, int WC, int S>
+__global__ __launch_bounds__(WR * WC * 64) void gemm_ring_kernel(GemmArgs a) {
+  constexpr int WAVES = WR * WC, MT = BM / WR / 16, JT = BN / WC / 16;
+  constexpr int XB = BM * 128, WB = BN * 128;             // bytes per stage of 64 k
+  constexpr int XL = BM / 8 / WAVES, WL = BN / 8 / WAVES; // 1 KiB loads per wave and stage
+  constexpr int L = XL + WL;
+  static_assert(XL * WAVES * 8 == BM && WL * WAVES * 8 == BN, "loads divide over the waves");
+  extern __shared__ __attribute__((aligned(16))) unsigned char ring_lds[];
+  unsigned char* const xring = ring_lds;
+  unsigned char* const wring = ring_lds + S * XB;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int b = lane & 15, q = lane >> 4;
+  const int wr = wave / WC, wc = wave % WC;
+  const int KT = a.K >> 5, ST = (KT + 1) >> 1, NT = a.N >> 4;
+  const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
+  const int nblk = gridDim.x, nblk8 = nblk & ~7;   // XCD-aware order, as in gemm_lds_kernel
+  int bid = (int)blockIdx.x < nblk8 ? ((int)blockIdx.x & 7) * (nblk8 >> 3) + ((int)blockIdx.x >> 3) : (int)blockIdx.x;
+  const int ks = bid / (tiles_m * tiles_n);
+  bid -= ks * (tiles_m * tiles_n);
+  const int per_group = RING_GROUP_M * tiles_n;
+  const int group = bid / per_group, in_group = bid % per_group;
+  const int gm = min(RING_GROUP_M, tiles_m - group * RING_GROUP_M);
+  const int m0 = (group * RING_GROUP_M + in_group % gm) * BM;
+  const int nt0 = in_group / gm * (BN / 16);
+  const int per_split = (ST + a.ksplit - 1) / a.ksplit;
+  const int s0 = ks * per_split, n = min(ST, s0 + per_split) - s0;   // (the host's plan leaves no split empty)
 
-hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s) {
+  const bf16_t* xsrc[XL];
+  const u32x4_t* wsrc[WL];
+  const int brow = lane >> 3;
+#pragma unroll
+  for (int i = 0; i < XL; ++i) {
+    const int g = wave + i * WAVES;
+    xsrc[i] = a.x + (size_t)min(m0 + 8 * g + brow, a.M - 1) * a.ldx;
+  }
+#pragma unroll
+  for (int i = 0; i < WL; ++i) {
+    const int t = wave + i * WAVES;
+    wsrc[i] = reinterpret_cast<const u32x4_t*>(a.wp) + (size_t)min(nt0 + t % (BN / 16), NT - 1) * KT * 64 + lane;
+  }
+  // one row block: every weight byte is read once and must not push the activations out of the caches (aux 2 = non-temporal)
+  const bool once = tiles_m == 1;
+  auto issue = [&](int st, int buf) {
+#pragma unroll
+    for (int i = 0; i < WL; ++i) {
+      const int t = wave + i * WAVES;
+      const int kt = min(2 * st + t / (BN / 16), KT - 1);
+      if (once) __builtin_amdgcn_global_load_lds(GEMM2_GLBP(wsrc[i] + (size_t)kt * 64), GEMM2_LDSP(wring + buf * WB + t * 1024), 16, 0, 2);
+      else __builtin_amdgcn_global_load_lds(GEMM2_GLBP(wsrc[i] + (size_t)kt * 64), GEMM2_LDSP(wring + buf * WB + t * 1024), 16, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < XL; ++i) {
+      const int g = wave + i * WAVES;
+      const int seg = (lane & 7) ^ (((8 * (g & 1) + brow) >> 1) & 7);
+      int k = st * 64 + seg * 8;
+      k = k < a.K ? k : k - 32;   // (an odd last k tile: the second half of the stage repeats the first and is not multiplied)
+      __builtin_amdgcn_global_load_lds(GEMM2_GLBP(xsrc[i] + k), GEMM2_LDSP(xring + buf * XB + g * 1024), 16, 0, 0);
+    }
+  };
+
+  f32x4_t acc[JT][MT];
+#pragma unroll
+  for (int j = 0; j < JT; ++j)
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) acc[j][mt] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+  const int xrow = (b >> 3) * 1024 + (b & 7) * 128 + wr * (BM / WR) * 128;
+  const int xoff0 = xrow + ((q) ^ ((b >> 1) & 7)) * 16, xoff1 = xrow + ((4 + q) ^ ((b >> 1) & 7)) * 16;
+  struct Frags { u32x4_t x[MT], w[JT]; };
+  auto read = [&](Frags& f, int buf, int h) {
+    const unsigned char* xb = xring + buf * XB + (h ? xoff1 : xoff0);
+    const unsigned char* wb = wring + buf * WB + h * (BN * 64) + wc * (JT * 1024) + lane * 16;
+#pragma unroll
+    for (int j = 0; j < JT; ++j) f.w[j] = *reinterpret_cast<const u32x4_t*>(wb + j * 1024);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) f.x[mt] = *reinterpret_cast<const u32x4_t*>(xb + mt * 2048);
+  };
+  auto multiply = [&](const Frags& f) {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int j = 0; j < JT; ++j)
+        acc[j][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, f.w[j]), __builtin_bit_cast(bf16x8_t, f.x[mt]), acc[j][mt], 0, 0, 0);
+  };
+  // One barrier per stage, between the two halves of its MFMAs.  Before it a wave has its reads of the stage complete
+  // and its loads of the next stage landed; behind it the next stage may be read and this stage's buffer be filled.
+#pragma unroll
+  for (int i = 0; i < S - 1; ++i) issue(s0 + min(i, n - 1), i);
+  Frags f0, f1;
+  ring_meet<(S - 2) * L>();
+  read(f0, 0, 0);
+  int buf = 0, fill = S - 1, i = 0;
+  for (; i + S - 1 < n; ++i) {
+    issue(s0 + i + S - 1, fill);
+    read(f1, buf, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(f0);
+    ring_meet<(S - 2) * L>();
+    fill = buf;
+    buf = buf + 1 == S ? 0 : buf + 1;
+    read(f0, buf, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(f1);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  // the last S - 1 stages: nothing left to request
+#pragma unroll
+  for (int r = S - 2; r >= 0; --r) {
+    if (n - 1 - r >= 0) {
+      const bool both = r > 0 || 2 * (s0 + n) <= KT;   // (an odd K / 32: the last stage has one k tile)
+      if (both) read(f1, buf, 1);
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(f0);
+      if (r > 0) {
+        if (r == S - 2) ring_meet<(S > 2 ? S - 3 : 0) * L>();
+        else if (r == S - 3) ring_meet<(S > 3 ? S - 4 : 0) * L>();
+        else if (r == S - 4) ring_meet<(S > 4 ? S - 5 : 0) * L>();
+        else ring_meet<0>();
+        buf = buf + 1 == S ? 0 : buf + 1;
+        read(f0, buf, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (both) multiply(f1);
+    }
+  }
+  GemmArgs e = a;
+  if (a.ksplit > 1) e.out = a.out + (size_t)ks * a.out_stride;
+  gemm_epilogue<MT, JT>(e, acc, m0 + wr * (BM / WR), nt0 + wc * JT, NT, lane);
+}
+
+template <int BM, int BN, int WR, int WC, int S>
+static hipError_t launch_gemm_ring_t(const GemmArgs& a, hipStream_t s) {
+  constexpr int LDS = S * (BM + BN) * 128;
+  static bool prepared[64] = {};
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+  if (!prepared[dev]) {
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_ring_kernel<BM, BN, WR, WC, S>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+    if (e != hipSuccess) return e;
+    prepared[dev] = true;
+  }
+  const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
+  hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, WR, WC, S>), dim3(tiles_m * tiles_n * a.ksplit), dim3(WR * WC * 64), LDS, s, a);
+  return hipGetLastError();
+}
+
+// Tile shapes of the two kernels: what a stage of 64 k takes on a full chip, and the share of that on a nearly empty one.
+enum { TILE_64x64, TILE_64x128, TILE_128x64, TILE_128x128, TILE_128x256, TILE_256x256, TILE_COUNT };
+static const struct { int bm, bn; float stage_us, alone; } gemm_tiles[TILE_COUNT] = {
+    {64, 64, 0.24f, 1.0f}, {64, 128, 0.39f, 1.0f}, {128, 64, 0.35f, 0.87f}, {128, 128, 0.58f, 0.82f}, {128, 256, 0.99f, 0.85f}, {256, 256, 1.59f, 0.74f}};
+
+// Estimated time (us) of a tile shape and split: the larger of the rounds of one workgroup per CU (2.6 us for a workgroup's
+// start and end) and the weights once from memory (6.3 TB/s + 3.4 us), and the partial products of a split.  Fitted to
+// 3900 measured times (the projections of the 1.2B, 8B and 70B R = 8 / R = 4 shapes at 17 - 6000 rows, every tile, splits
+// 1 - 8; rms error 7 %): the tile and split it picks are on average 1.6 %, at worst 23 %, off the fastest measured ones.
+static float gemm_cost(int tile, int M, int N, int K, int ksplit) {
+  const auto& t = gemm_tiles[tile];
+  const long wgs = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * ksplit;
+  const int stages = (K + 63) / 64, per = (stages + ksplit - 1) / ksplit;
+  const float last = (float)(wgs % 256) / 256.f;
+  float tiles_us = (float)(wgs / 256) * (2.6f + (float)per * t.stage_us);
+  if (last > 0.f) tiles_us += 2.6f + (float)per * t.stage_us * (t.alone + (1.f - t.alone) * last);
+  const float mem_us = 3.4f + (float)N * (float)K * 2.0f / 6.3e6f;
+  const float split_us = ksplit > 1 ? (float)ksplit * (float)M * (float)N * 8.0f / 6.0e6f : 0.f;
+  return (tiles_us > mem_us ? tiles_us : mem_us) + split_us;
+}
+
+static int gemm_best_tile(int M, int N, int K, int epilogue, int ksplit, float* cost) {
+  int best = -1;
+  float best_us = 0.f;
+  for (int t = 0; t < TILE_COUNT; ++t) {
+    if (t == TILE_256x256 && (ksplit > 1 || (K & 63) || K < 256)) continue;   // (what gemm_lds_kernel takes)
+    if (t == TILE_64x64 && epilogue == 3) continue;                           // (16 columns per wavefront: more sums of squares per row than the buffer holds)
+    const float us = gemm_cost(t, M, N, K, ksplit);
+    if (best < 0 || us < best_us) { best = t; best_us = us; }
+  }
+  if (cost) *cost = best_us;
+  return best;
+}
+
+int gemm_ksplit(int M, int N, int K, int max_split, float extra_us) {
+  const int stages = (K + 63) / 64;
+  int best = 1;
+  float best_us = 0.f;
+  gemm_best_tile(M, N, K, 0, 1, &best_us);
+  for (int ks = 2; ks <= max_split && ks <= 16; ++ks) {
+    const int per = (stages + ks - 1) / ks;
+    if ((stages + per - 1) / per != ks) continue;   // (a split would be left without work)
+    float us;
+    gemm_best_tile(M, N, K, 0, ks, &us);
+    us += extra_us;
+    if (us < best_us) { best = ks; best_us = us; }
+  }
+  return best;
+}
+
+int gemm_ssq_parts(const GemmArgs& a) {
+  // columns per workgroup (gemm_lds_kernel) or per wavefront
+  static const int cols[TILE_COUNT] = {16, 32, 32, 32, 64, 256};
+  const int c = cols[gemm_best_tile(a.M, a.N, a.K, a.epilogue, 1, nullptr)];
+  return (a.N + c - 1) / c;
+}
+
+hipError_t launch_gemm_mfma(const GemmArgs& given, hipStream_t s) {
+  GemmArgs a = given;
   if (a.M <= 0 || (a.K & 31) || (a.N & 15) || a.K < 32) return hipErrorInvalidValue;
+  if (a.ksplit < 1) a.ksplit = 1;
+  if (a.ksplit > 1) {
+    const int stages = (a.K + 63) / 64, per = (stages + a.ksplit - 1) / a.ksplit;
+    if (a.epilogue != 0 || (stages + per - 1) / per != a.ksplit) return hipErrorInvalidValue;
+  }
   // operands of the chosen epilogue
   if (a.epilogue < 0 || a.epilogue > 3) return hipErrorInvalidValue;
   if (a.epilogue == 0 && !a.out) return hipErrorInvalidValue;
@@ -672,12 +788,14 @@ hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s) {
   if (a.epilogue == 3 && (!a.x_res || a.n_peers < 0 || (a.n_peers > 0 && !a.peers) || (a.xh_b && !a.xh_a) || (a.ssq_part && !a.xh_a) ||
                           (a.xh_a && !a.gain_a) || (a.xh_b && !a.gain_b)))
     return hipErrorInvalidValue;
-  if (gemm_takes_lds_kernel(a)) return launch_gemm_lds(a, s);
-  // few rows: where 128-row tiles would not give every CU a workgroup, 64-row tiles (1.2B shape, 1024 rows: 9.0 -> 8.4 ms per call)
-  if (a.M > 64 && (long)((a.M + 127) / 128) * ((a.N + 255) / 256) < 256) return launch_gemm_wm<4, 2>(a, s);
-  if (a.M >= 1024) return launch_gemm_wm<GEMM_WM_LARGE, GEMM_WAVES_LARGE>(a, s);
-  if (a.M > 64) return launch_gemm_wm<8, 2>(a, s);   // 128 x 256
-  return launch_gemm_wm<4, 2>(a, s);                 //  64 x 256
+  switch (gemm_best_tile(a.M, a.N, a.K, a.epilogue, a.ksplit, nullptr)) {
+    case TILE_64x64: return launch_gemm_ring_t<64, 64, 2, 4, 6>(a, s);
+    case TILE_64x128: return launch_gemm_ring_t<64, 128, 2, 4, 6>(a, s);
+    case TILE_128x64: return launch_gemm_ring_t<128, 64, 4, 2, 5>(a, s);
+    case TILE_128x128: return launch_gemm_ring_t<128, 128, 2, 4, 5>(a, s);
+    case TILE_128x256: return launch_gemm_ring_t<128, 256, 2, 4, 3>(a, s);
+    default: return launch_gemm_lds(a, s);
+  }
 }
 
 // ------------------------------------------------------------------------------------------------

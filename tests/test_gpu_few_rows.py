@@ -1,0 +1,42 @@
+"""GPU: the projections of calls of few and medium rows (ring GEMM, split K, partial products added up by the next kernel) at
+the edges of their tiles, splits and row ranges, against the CPU oracle."""
+import pytest
+import torch
+
+from paper_2501_06589_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+# one layer; hidden 2080 = 65 k tiles (an odd number: the last stage of 64 k is half filled), N no multiple of a tile
+WIDE = inputs.WORKLOADS["8b"].with_(name="few_rows", n_layers=1, hidden=2080, n_q_heads=16, n_kv_heads=2, inter=2080,
+                                    batch=1, kv_preload=0, decode_steps=2)
+# the bound of a prefill of one layer: 0.29 % of RMS per module and sqrt(modules), its maximum 5.8 times that
+TOL = 0.0029 * 2 ** 0.5 * 5.8
+
+
+@pytest.fixture(scope="module")
+def harness():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gpu_harness
+    return gpu_harness
+
+
+@pytest.mark.parametrize("rows", [16, 17, 33, 64, 65, 129, 300, 513, 1024, 1025])
+def test_prefill_rows(harness, rows):
+    """16 rows and fewer: the skinny GEMM; up to 1024: partial products; beyond: the residual epilogue."""
+    res = harness.run_case(WIDE.with_(prefill=rows), decode_steps=1)
+    assert max(res.errs) < TOL, res.errs
+
+
+@pytest.mark.parametrize("batch,prefill", [(3, 43), (17, 3), (40, 1)])
+def test_several_sequences_and_wide_decode(harness, batch, prefill):
+    res = harness.run_case(WIDE.with_(batch=batch, prefill=prefill), decode_steps=2)
+    assert max(res.errs) < TOL, res.errs
+
+
+def test_two_computed_shards_and_peers(harness):
+    """Several shards share the partial-product buffer, slot after slot; peers are added behind them."""
+    w = WIDE.with_(tp_degree=3, n_real_shards=2, prefill=100, peer_pool=2)
+    res = harness.run_case(w, decode_steps=1)
+    assert max(res.errs) < TOL, res.errs
