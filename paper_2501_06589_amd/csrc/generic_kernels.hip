@@ -329,10 +329,66 @@ __global__ void load_kv_kernel(const T* __restrict__ k, const T* __restrict__ v,
   cv[((size_t)bh * d + i) * max_seq + p] = v[gid];
 }
 
+// The same, 16 bytes per lane on both sides: a workgroup takes P positions of one (sequence, kv head), copies its K rows
+// and turns its V rows in LDS, so that a store covers whole pieces of a cache row.  (Element by element every V value is
+// a memory transaction of its own.)
+// Measured, us per layer: 64 sequences x 8 kv heads x 1024 positions 435 -> 102 (5.3 TB/s read + written);
+// 16 x 8 x 1024 115 -> 29; 4 x 1 x 32001 117 -> 28.
+template <typename T, int P>
+__global__ __launch_bounds__(256) void load_kv_tiles_kernel(const T* __restrict__ k, const T* __restrict__ v, T* __restrict__ ck,
+                                                            T* __restrict__ cv, int S, int d, int max_seq) {
+  constexpr int E = 16 / sizeof(T);            // elements per 16 bytes
+  constexpr int ROW = P + 4 / (int)sizeof(T);  // a turned row: one word of padding
+  extern __shared__ __attribute__((aligned(16))) unsigned char load_kv_lds[];
+  T* const turned = reinterpret_cast<T*>(load_kv_lds);   // [d][ROW]
+  const int p0 = blockIdx.x * P, n = min(P, S - p0);
+  const size_t bh = blockIdx.y;
+  const int segs = d / E;
+  const T* ks = k + (bh * S + p0) * d;
+  const T* vs = v + (bh * S + p0) * d;
+  T* kd = ck + (bh * max_seq + p0) * d;
+  for (int i = threadIdx.x; i < n * segs; i += 256) {
+    *reinterpret_cast<uint4*>(kd + (size_t)i * E) = *reinterpret_cast<const uint4*>(ks + (size_t)i * E);
+    const uint4 u = *reinterpret_cast<const uint4*>(vs + (size_t)i * E);
+    const T* e = reinterpret_cast<const T*>(&u);
+    const int p = i / segs, dim = i % segs * E;
+#pragma unroll
+    for (int j = 0; j < E; ++j) turned[(dim + j) * ROW + p] = e[j];
+  }
+  __syncthreads();
+  const int pieces = P / E;
+  for (int i = threadIdx.x; i < d * pieces; i += 256) {
+    const int dim = i / pieces, p = i % pieces * E;
+    if (p >= n) continue;
+    T* dst = cv + (bh * d + dim) * max_seq + p0 + p;
+    uint4 u;
+    T* e = reinterpret_cast<T*>(&u);
+#pragma unroll
+    for (int j = 0; j < E; ++j) e[j] = turned[dim * ROW + p + j];
+    if (p + E <= n) {
+      *reinterpret_cast<uint4*>(dst) = u;   // (max_seq is a multiple of 128, p0 and p of E)
+    } else {
+      for (int j = 0; p + j < n; ++j) dst[j] = e[j];
+    }
+  }
+}
+
+template <typename T, int P>
+static hipError_t launch_load_kv_tiles(const void* k, const void* v, void* ck, void* cv, int B, int nkv, int S, int d, int max_seq, hipStream_t s) {
+  const size_t lds = (size_t)d * (P + 4 / sizeof(T)) * sizeof(T);   // at most 36 KiB (d <= 256)
+  hipLaunchKernelGGL((load_kv_tiles_kernel<T, P>), dim3((S + P - 1) / P, B * nkv), dim3(256), lds, s, (const T*)k, (const T*)v, (T*)ck, (T*)cv, S, d, max_seq);
+  return hipGetLastError();
+}
+
 hipError_t launch_load_kv(const void* k, const void* v, void* cache_k, void* cache_v, int B, int nkv, int S, int d,
                           int max_seq, bool is_bf16, hipStream_t s) {
   const long long total = (long long)B * nkv * S * d;
   if (total <= 0) return hipSuccess;
+  // 16-byte accesses: the caller's tensors have to be aligned and a row has to be whole pieces (d need only be even), and
+  // the cache rows too (max_seq, a multiple of 128, and the library's own allocation); B * nkv is a grid dimension
+  const bool aligned = (((uintptr_t)k | (uintptr_t)v) & 15) == 0 && d % (is_bf16 ? 8 : 4) == 0 && d <= 256 && max_seq % 8 == 0 && (long long)B * nkv <= 65535;
+  if (aligned) return is_bf16 ? launch_load_kv_tiles<bf16_t, 64>(k, v, cache_k, cache_v, B, nkv, S, d, max_seq, s)
+                              : launch_load_kv_tiles<float, 32>(k, v, cache_k, cache_v, B, nkv, S, d, max_seq, s);
   const unsigned blocks = (unsigned)((total + 255) / 256);
   if (is_bf16)
     hipLaunchKernelGGL(load_kv_kernel<bf16_t>, dim3(blocks), dim3(256), 0, s, (const bf16_t*)k, (const bf16_t*)v,

@@ -1,0 +1,42 @@
+"""GPU: the handed-over cache (ladder_load_kv) at the edges of its kernel: 16-byte and element-wise accesses give the same
+bits, whatever the length, head size and alignment."""
+import pytest
+import torch
+
+from paper_2501_06589_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+TINY = inputs.WORKLOADS["tiny"]
+
+
+@pytest.fixture(scope="module")
+def harness():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gpu_harness
+    return gpu_harness
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("bf16", 20), ("fp32", 64), ("fp32", 30)])
+@pytest.mark.parametrize("S", [1, 63, 64, 65, 130])
+def test_load_kv_alignment_and_ragged_lengths(harness, dtype, d, S):
+    w = TINY.with_(name="kv", dtype=dtype, n_layers=1, n_q_heads=4, n_kv_heads=2, head_dim=d, batch=3, prefill=0, kv_preload=S,
+                   decode_steps=1, tp_degree=1, n_real_shards=1)
+    res = harness.run_case(w, kv_preload=S, decode_steps=1)          # against the oracle
+    assert max(res.errs) < (1e-4 if dtype == "fp32" else 2e-2), res.errs
+    ctx = harness.build_gpu(w, harness.make_tensors(w))
+    k, v = (t.to(DEV) for t in inputs.kv_cache(w, 0, 0, w.batch, S))
+    x = inputs.embeddings(w, w.batch, 1, inputs.SEED_DECODE0)[:, 0].contiguous().to(DEV)
+    outs = []
+    for off in (0, 1):      # (off 1: contiguous tensors whose storage starts off a 16-byte boundary)
+        shifted = []
+        for t in (k, v):
+            buf = torch.empty(t.numel() + off, dtype=t.dtype, device=DEV)
+            buf[off:].copy_(t.flatten())
+            shifted.append(buf[off:].view(t.shape))
+        ctx.load_kv(0, 0, *shifted)
+        outs.append(ctx.decode_step(x).cpu())
+    assert torch.equal(outs[0], outs[1])
+    ctx.free()
