@@ -1,9 +1,10 @@
-"""GPU: the handed-over cache (ladder_load_kv) at the edges of its kernel: 16-byte and element-wise accesses give the same
-bits, whatever the length, head size and alignment."""
+"""GPU: the handed-over cache (ladder_load_kv) and the greedy token at the edges of their kernels: 16-byte and element-wise
+accesses give the same bits, whatever the length, head size and alignment; the first arg max whatever the row length."""
+import numpy as np
 import pytest
 import torch
 
-from paper_2501_06589_amd import inputs
+from paper_2501_06589_amd import inputs, ladder
 
 pytestmark = pytest.mark.gpu
 
@@ -40,3 +41,21 @@ def test_load_kv_alignment_and_ragged_lengths(harness, dtype, d, S):
         outs.append(ctx.decode_step(x).cpu())
     assert torch.equal(outs[0], outs[1])
     ctx.free()
+
+
+@pytest.mark.parametrize("V", [1, 3, 1023, 4096, 4100, 16389, 20000])
+def test_first_argmax_of_any_row_length(harness, V):
+    w = TINY.with_(name="head", n_layers=1, tp_degree=1, n_real_shards=1, batch=3)
+    hw = inputs.head_weights(w, max(V, 2), V, device=DEV)
+    x = torch.randn(3, w.hidden, generator=torch.Generator().manual_seed(V)).to(DEV)
+    for kind in ("random", "ties", "equal"):
+        ctx = ladder.Ladder(ladder.config_for(w))
+        w_lm = hw["w_lm"].clone()
+        if kind == "equal":
+            w_lm.zero_()
+        elif kind == "ties":      # every column twice, a stretch apart
+            w_lm[:, V // 2:2 * (V // 2)] = w_lm[:, :V // 2].clone()
+        ctx.load_head(hw["table"], hw["final_norm"], w_lm)
+        logits, toks = ctx.head(x)
+        assert np.array_equal(toks.cpu().numpy(), np.argmax(logits.cpu().numpy(), axis=-1)), (kind, V)
+        ctx.free()
