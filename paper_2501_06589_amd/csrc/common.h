@@ -147,14 +147,16 @@ struct AttnDecodeArgs {
   const bf16_t* q;         // [B][nq*d] rotated
   const bf16_t* cache_k;   // [B_cap][nkv][max_seq][d]
   const bf16_t* cache_v;   // [B_cap][nkv][d][max_seq]
-  float* part_o;           // [B][nkv][n_chunks][g][d]
-  float* part_ml;          // [B][nkv][n_chunks][g][2]
+  float* part_o;           // [B][nkv][n_splits][g][d]
+  float* part_ml;          // [B][nkv][n_splits][g][2]
   bf16_t* o;               // [B][nq*d]
   int B, nq, nkv, d, max_seq;
   int n_pos;               // visible positions (incl. the new one)
-  int chunk, n_chunks;     // chunk in {32, 64, 128}
+  int n_splits;            // workgroups per (sequence, kv head); attn_decode_splits()
   const int* pos_dev;      // if non-null: n_pos = *pos_dev + 1
 };
+#define ATTN_DECODE_MAX_SPLITS 512
+int attn_decode_splits(int B, int nkv, int max_seq);   // (the grid depends on the capacity, not on the position)
 hipError_t launch_attn_decode(const AttnDecodeArgs& a, hipStream_t s);
 
 // ---- prefill MFMA path ---------------------------------------------------------------------------

@@ -207,140 +207,168 @@ hipError_t launch_gemv(const GemvArgs& a, hipStream_t s) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// Decode attention, split over the cached positions.  Workgroup (chunk, kv head, sequence):
-// all G = nq/nkv query heads of the group share every K/V load.
-//   scores : D/8 lanes cover one K row with 16-byte loads (a wavefront load = whole rows, contiguous),
-//            the dot products are reduced over those lanes with wavefront shuffles;
-//   softmax: within the chunk, one wavefront per head;
-//   P*V    : V is cached transposed, CHUNK/8 lanes cover one dim's CHUNK positions with 16-byte loads,
-//            reduced over those lanes with shuffles.
-// (max, sum, unnormalised output) of the chunk go to the combine kernel.
+// Decode attention.  Workgroup (split, kv head, sequence): the positions are cut into at most n_splits runs of a multiple
+// of 128, computed from the position itself, so that the grid stays the same while the sequence grows; the 4 wavefronts
+// take 32-key blocks of the run round robin, each with its own running softmax, and merge through LDS.  It is bound by
+// the one pass over the cache: a wavefront has the 16 KiB of its next block in flight while it computes one, eight
+// wavefronts per CU.  All on the matrix cores, transposed so that nothing is shuffled:
+//   S^T[key][column] = K Q^T     A = 16 keys x 32 dims, straight from the K rows (row i of tile t is key 8 (i / 4) + 4 t +
+//                                i % 4 of the block, so that a lane ends up with eight neighbouring keys and its share of
+//                                V^T is 16 contiguous bytes); B: the q heads of the group twice, in columns 0..7 and 8..15;
+//   O^T[dim][column] = V^T P^T   A = 16 dims x 32 keys from the transposed V cache; B = the lane's own eight
+//                                probabilities, split: their bf16 rounding in columns 0..7 and what it left out, rounded in
+//                                turn, in 8..15 (16 significant bits); the two halves of O^T are added at the end.
+// With one split the workgroup writes the output, else the splits' (max, sum, unnormalised output) go to the combine kernel.
+// 64 sequences x 8 kv heads x 4 q heads x 1024 positions: 82 us + 9 for the combine -> 63 us by itself (4.2 TB/s); beside the
+// gate/up projection, with which it shares the memory, 113 + 27 -> 103.  (Vector units and chunks of 128 positions before.)
 // ------------------------------------------------------------------------------------------------
-__device__ __forceinline__ void unpack8(const uint4 v, float f[8]) {
-  f[0] = __uint_as_float(v.x << 16); f[1] = __uint_as_float(v.x & 0xFFFF0000u);
-  f[2] = __uint_as_float(v.y << 16); f[3] = __uint_as_float(v.y & 0xFFFF0000u);
-  f[4] = __uint_as_float(v.z << 16); f[5] = __uint_as_float(v.z & 0xFFFF0000u);
-  f[6] = __uint_as_float(v.w << 16); f[7] = __uint_as_float(v.w & 0xFFFF0000u);
-}
+__host__ __device__ __forceinline__ int attn_split_len(int n_pos, int n_splits) { return ((n_pos + n_splits - 1) / n_splits + 127) / 128 * 128; }
 
-template <int D, int G, int CHUNK>
-__global__ __launch_bounds__(256) void attn_decode_kernel(AttnDecodeArgs a) {
-  constexpr int LPR = D / 8;         // lanes per K row
-  constexpr int RPP = 256 / LPR;     // K rows per pass of the workgroup
-  constexpr int SEGS = CHUNK / 8;    // lanes per V^T row (8 positions each)
-  constexpr int DPP = 256 / SEGS;    // dims per pass
-  __shared__ float qs[G * D];
-  __shared__ float sc[G * CHUNK];
-  __shared__ float hmax[G], hsum[G];
-
+template <int D, int G>
+__global__ __launch_bounds__(256, 2) void attn_decode_kernel(AttnDecodeArgs a) {
+  constexpr int DS = D / 32, DT = D / 16;
+  __shared__ float osm[4][G][D];
+  __shared__ float msm[4][G], lsm[4][G];
   const int c = blockIdx.x, kvh = blockIdx.y, bi = blockIdx.z;
   const int n_pos = a.pos_dev ? (*a.pos_dev + 1) : a.n_pos;
-  const int p0 = c * CHUNK;
-  const int p1 = min(n_pos, p0 + CHUNK);
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const size_t part_idx = ((size_t)bi * a.nkv + kvh) * a.n_chunks + c;
-  if (p0 >= p1) {  // chunk beyond the visible range: neutral element for the combine
-    if (tid < G) {
-      a.part_ml[(part_idx * G + tid) * 2 + 0] = -INFINITY;
-      a.part_ml[(part_idx * G + tid) * 2 + 1] = 0.f;
-    }
-    return;
-  }
-  const int len = p1 - p0;
+  const int len = attn_split_len(n_pos, a.n_splits);
+  const int p0 = c * len, p1 = min(n_pos, p0 + len);
+  if (p0 >= p1) return;   // (the combine kernel looks at the splits that hold positions only)
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int b = lane & 15, q = lane >> 4;
+  const int nb = (p1 - p0 + 31) >> 5;
   const float scale = 1.0f / sqrtf((float)D);
-  const bf16_t* qg = a.q + (size_t)bi * a.nq * D + (size_t)kvh * G * D;
-  for (int i = tid; i < G * D; i += 256) qs[i] = bf16_to_f32(qg[i]) * scale;
-  for (int i = tid; i < G * CHUNK; i += 256) sc[i] = 0.f;
-  __syncthreads();
+  const int head = min(b & 7, G - 1);   // (columns without a head repeat one: finite, never stored)
+  const bf16_t* qg = a.q + (size_t)bi * a.nq * D + (size_t)(kvh * G + head) * D;
+  const bf16_t* kb = a.cache_k + (((size_t)bi * a.nkv + kvh) * a.max_seq + p0 + 8 * (b >> 2) + (b & 3)) * D + q * 8;
+  const bf16_t* vb = a.cache_v + (((size_t)bi * a.nkv + kvh) * D + b) * a.max_seq + p0 + 8 * q;
+  u32x4_t qr[DS];
+#pragma unroll
+  for (int s = 0; s < DS; ++s) qr[s] = *reinterpret_cast<const u32x4_t*>(qg + s * 32 + q * 8);
 
-  const bf16_t* kb = a.cache_k + (((size_t)bi * a.nkv + kvh) * a.max_seq + p0) * D;
-  const bf16_t* vb = a.cache_v + ((size_t)bi * a.nkv + kvh) * D * a.max_seq + p0;
-
-  // phase 1: scores
-  {
-    const int rsel = tid / LPR, csel = tid % LPR;  // row within a pass, 8-dim slice
-    for (int r0 = 0; r0 < len; r0 += RPP) {
-      const int r = r0 + rsel;
-      float kf[8];
-      if (r < len) {
-        unpack8(*reinterpret_cast<const uint4*>(kb + (size_t)r * D + csel * 8), kf);
-      } else {
+  f32x4_t o[DT];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) kf[e] = 0.f;
-      }
+  for (int t = 0; t < DT; ++t) o[t] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY, l = 0.f;
+  struct Block { u32x4_t k[2][DS], v[DT]; };
+  auto load = [&](Block& x, int blk) {   // unconditional: blk is clamped by the caller; the capacity is a multiple of 32
 #pragma unroll
-      for (int h = 0; h < G; ++h) {
-        float p = 0.f;
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) p = fmaf(qs[h * D + csel * 8 + e], kf[e], p);
+      for (int s = 0; s < DS; ++s)
+        x.k[t][s] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(kb + (size_t)(blk * 32 + 4 * t) * D + s * 32));
 #pragma unroll
-        for (int o = LPR / 2; o > 0; o >>= 1) p += __shfl_xor(p, o, 64);
-        if (csel == 0 && r < len) sc[h * CHUNK + r] = p;
-      }
-    }
-  }
-  __syncthreads();
-
-  // phase 2: softmax within the chunk, one wavefront per head (round robin); entries >= len stay 0
-  for (int h = wave; h < G; h += 4) {
-    float m = -INFINITY;
-    for (int r = lane; r < len; r += 64) m = fmaxf(m, sc[h * CHUNK + r]);
-    m = wave_max(m);
-    float l = 0.f;
-    for (int r = lane; r < len; r += 64) {
-      const float e = __expf(sc[h * CHUNK + r] - m);
-      sc[h * CHUNK + r] = e;
-      l += e;
-    }
-    l = wave_sum(l);
-    if (lane == 0) { hmax[h] = m; hsum[h] = l; }
-  }
-  __syncthreads();
-
-  // phase 3: unnormalised output  o[h][dim] = sum_r p[h][r] V^T[dim][r]
-  {
-    const int seg = tid % SEGS, dsel = tid / SEGS;
-    float pr[G][8];
+    for (int t = 0; t < DT; ++t)
+      x.v[t] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(vb + (size_t)t * 16 * a.max_seq + blk * 32));
+  };
+  auto compute = [&](const Block& x, int blk) {
+    f32x4_t st[2];
+    float sv[8], mloc = -INFINITY;
 #pragma unroll
-    for (int h = 0; h < G; ++h)
+    for (int t = 0; t < 2; ++t) {
+      st[t] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int e = 0; e < 8; ++e) pr[h][e] = sc[h * CHUNK + seg * 8 + e];
-    float* po = a.part_o + part_idx * G * D;
-    for (int d0 = 0; d0 < D; d0 += DPP) {
-      const int dim = d0 + dsel;
-      float vf[8];
-      unpack8(*reinterpret_cast<const uint4*>(vb + (size_t)dim * a.max_seq + seg * 8), vf);
+      for (int s = 0; s < DS; ++s)
+        st[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, x.k[t][s]), __builtin_bit_cast(bf16x8_t, qr[s]), st[t], 0, 0, 0);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) vf[e] = (seg * 8 + e < len) ? vf[e] : 0.f;  // never touch unwritten cache
-#pragma unroll
-      for (int h = 0; h < G; ++h) {
-        float s = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) s = fmaf(pr[h][e], vf[e], s);
-#pragma unroll
-        for (int o = SEGS / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-        if (seg == 0) po[h * D + dim] = s;
+      for (int r = 0; r < 4; ++r) {
+        const float v = p0 + blk * 32 + 8 * q + 4 * t + r < p1 ? st[t][r] * scale : -INFINITY;
+        sv[t * 4 + r] = v;
+        mloc = fmaxf(mloc, v);
       }
     }
+    mloc = fmaxf(mloc, __shfl_xor(mloc, 16, 64));
+    mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64));
+    const float mnew = fmaxf(m, mloc);    // finite: a block has at least one visible key
+    const float corr = __expf(m - mnew);
+    float psum = 0.f;
+    uint32_t pk[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float part[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const float p = __expf(sv[2 * e + h] - mnew);
+        psum += p;
+        const float high = bf16_to_f32(f32_to_bf16(p));
+        part[h] = b < 8 ? high : p - high;
+      }
+      pk[e] = (uint32_t)f32_to_bf16(part[0]) | ((uint32_t)f32_to_bf16(part[1]) << 16);
+    }
+    l = l * corr + psum;
+    m = mnew;
+    const u32x4_t pb = {pk[0], pk[1], pk[2], pk[3]};
+#pragma unroll
+    for (int t = 0; t < DT; ++t) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) o[t][r] *= corr;
+      o[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, x.v[t]), __builtin_bit_cast(bf16x8_t, pb), o[t], 0, 0, 0);
+    }
+  };
+  if (wave < nb) {
+    Block x0, x1;
+    load(x0, wave);
+    for (int blk = wave; blk < nb; blk += 8) {
+      load(x1, min(blk + 4, nb - 1));
+      __builtin_amdgcn_sched_barrier(0);
+      compute(x0, blk);
+      __builtin_amdgcn_sched_barrier(0);
+      load(x0, min(blk + 8, nb - 1));
+      __builtin_amdgcn_sched_barrier(0);
+      if (blk + 4 < nb) compute(x1, blk + 4);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   }
-  if (tid < G) {
-    a.part_ml[(part_idx * G + tid) * 2 + 0] = hmax[tid];
-    a.part_ml[(part_idx * G + tid) * 2 + 1] = hsum[tid];
+  l += __shfl_xor(l, 16, 64);
+  l += __shfl_xor(l, 32, 64);
+#pragma unroll
+  for (int t = 0; t < DT; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float v = o[t][r] + __shfl_xor(o[t][r], 8, 64);
+      if (b < G) osm[wave][b][t * 16 + 4 * q + r] = v;
+    }
+  if (q == 0 && b < G) { msm[wave][b] = m; lsm[wave][b] = l; }
+  __syncthreads();
+  const size_t part = (((size_t)bi * a.nkv + kvh) * a.n_splits + c) * G;
+  for (int i = tid; i < G * D; i += 256) {
+    const int h = i / D, dim = i % D;
+    float mm = msm[0][h];   // (wavefront 0 always has a block)
+#pragma unroll
+    for (int w = 1; w < 4; ++w) mm = fmaxf(mm, msm[w][h]);
+    float ll = 0.f, oo = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const float e = __expf(msm[w][h] - mm);
+      ll += lsm[w][h] * e;
+      oo += osm[w][h][dim] * e;
+    }
+    if (a.n_splits == 1) {
+      a.o[(size_t)bi * a.nq * D + (size_t)(kvh * G + h) * D + dim] = f32_to_bf16(oo / ll);
+    } else {
+      a.part_o[(part + h) * D + dim] = oo;
+      if (dim == 0) {
+        a.part_ml[(part + h) * 2 + 0] = mm;
+        a.part_ml[(part + h) * 2 + 1] = ll;
+      }
+    }
   }
 }
 
-// combine: one workgroup of D threads per (sequence, q head); the chunk statistics go through LDS
+// combine: one workgroup of D threads per (sequence, q head); the splits' statistics go through LDS
 // so that no thread walks a chain of dependent global loads
 template <int D>
 __global__ void attn_combine_kernel(AttnDecodeArgs a) {
-  __shared__ float wgt[512];
+  __shared__ float wgt[ATTN_DECODE_MAX_SPLITS];
   __shared__ float stat[2];
   const int h = blockIdx.x, bi = blockIdx.y, t = threadIdx.x;
   const int g = a.nq / a.nkv;
   const int kvh = h / g, hg = h % g;
   const int n_pos = a.pos_dev ? (*a.pos_dev + 1) : a.n_pos;
-  const int nc = min(a.n_chunks, (n_pos + a.chunk - 1) / a.chunk);   // chunks that hold visible positions
-  const size_t base = ((size_t)bi * a.nkv + kvh) * a.n_chunks;
+  const int len = attn_split_len(n_pos, a.n_splits);
+  const int nc = (n_pos + len - 1) / len;   // splits that hold visible positions
+  const size_t base = ((size_t)bi * a.nkv + kvh) * a.n_splits;
   for (int c = t; c < nc; c += D) wgt[c] = a.part_ml[((base + c) * g + hg) * 2];
   __syncthreads();
   if (t < 64) {   // first wavefront: max, then weights and the normaliser
@@ -363,22 +391,24 @@ __global__ void attn_combine_kernel(AttnDecodeArgs a) {
   a.o[(size_t)bi * a.nq * D + h * D + t] = f32_to_bf16(o / stat[0]);
 }
 
+// splits of a (sequence, kv head): enough workgroups for the chip (two per CU), of at least 128 positions each
+int attn_decode_splits(int B, int nkv, int max_seq) {
+  const int want = (512 + B * nkv - 1) / (B * nkv), most = (max_seq + 127) / 128;
+  const int n = want < most ? want : most;
+  return n < ATTN_DECODE_MAX_SPLITS ? n : ATTN_DECODE_MAX_SPLITS;
+}
+
 template <int D, int G>
 static hipError_t launch_attn_decode_t(const AttnDecodeArgs& a, hipStream_t s) {
-  const dim3 grid(a.n_chunks, a.nkv, a.B);
-  switch (a.chunk) {
-    case 32: hipLaunchKernelGGL((attn_decode_kernel<D, G, 32>), grid, dim3(256), 0, s, a); break;
-    case 64: hipLaunchKernelGGL((attn_decode_kernel<D, G, 64>), grid, dim3(256), 0, s, a); break;
-    case 128: hipLaunchKernelGGL((attn_decode_kernel<D, G, 128>), grid, dim3(256), 0, s, a); break;
-    default: return hipErrorInvalidValue;
-  }
+  hipLaunchKernelGGL((attn_decode_kernel<D, G>), dim3(a.n_splits, a.nkv, a.B), dim3(256), 0, s, a);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || a.n_splits == 1) return e;
   hipLaunchKernelGGL(attn_combine_kernel<D>, dim3(a.nq, a.B), dim3(D), 0, s, a);
   return hipGetLastError();
 }
 
 hipError_t launch_attn_decode(const AttnDecodeArgs& a, hipStream_t s) {
+  if (a.n_splits < 1 || a.n_splits > ATTN_DECODE_MAX_SPLITS || (a.max_seq & 31)) return hipErrorInvalidValue;
   const int g = a.nq / a.nkv;
   if (a.d == 128) {
     switch (g) {

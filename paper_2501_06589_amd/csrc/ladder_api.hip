@@ -470,13 +470,8 @@ int run_module(ladder_ctx* c, int m, int B, int T, int pos0, hipStream_t s, int*
         aa.part_o = c->att_o; aa.part_ml = c->att_ml; aa.o = (bf16_t*)c->obuf;
         aa.B = B; aa.nq = nq; aa.nkv = nkv; aa.d = d; aa.max_seq = c->s_cap; aa.n_pos = pos0 + 1;
         // launch shape fixed by the cache capacity (not the current position) so that a captured step
-        // stays valid as the sequence grows; workgroups past the visible range exit at once
-        int chunk = 32;
-        for (int cand : {128, 64}) {
-          if ((long long)B * nkv * ((g.max_seq + cand - 1) / cand) >= 256) { chunk = cand; break; }
-        }
-        while (chunk < 128 && (g.max_seq + chunk - 1) / chunk > 512) chunk *= 2;  // combine holds <= 512 chunk weights
-        aa.chunk = chunk; aa.n_chunks = (g.max_seq + chunk - 1) / chunk; aa.pos_dev = c->pos_dev;
+        // stays valid as the sequence grows
+        aa.n_splits = attn_decode_splits(B, nkv, g.max_seq); aa.pos_dev = c->pos_dev;
         HIP_TRY(c, timed(c, LADDER_K_ATTN_DECODE, s, [&] { return launch_attn_decode(aa, s); }));
       } else {
         AttnPrefillArgs aa{(const bf16_t*)c->qbuf, (const bf16_t*)L.cache_k, (const bf16_t*)L.cache_v,
@@ -1589,10 +1584,11 @@ static int init_impl(const ladder_config* cfg, void* hip_stream, ladder_ctx** ou
   if (c->fast) {
     INIT_TRY(dev_alloc(c, (void**)&c->ssq_part, (size_t)((H + 31) / 32) * rows * 4, false));
     for (int i = 0; i < 2; ++i) INIT_TRY(dev_alloc(c, (void**)&c->y_rs[i], rows * 4, false));
-    const size_t chunks = (size_t)(c->s_cap / 32);
+    size_t splits = 0;   // of all sequences together, the largest over the batch sizes
+    for (int B = 1; B <= g.max_batch; ++B) splits = std::max(splits, (size_t)B * attn_decode_splits(B, nkv, g.max_seq));
     const size_t gq = nq / nkv;
-    INIT_TRY(dev_alloc(c, (void**)&c->att_o, (size_t)g.max_batch * nkv * chunks * gq * d * 4, false));
-    INIT_TRY(dev_alloc(c, (void**)&c->att_ml, (size_t)g.max_batch * nkv * chunks * gq * 2 * 4, false));
+    INIT_TRY(dev_alloc(c, (void**)&c->att_o, splits * nkv * gq * d * 4, false));
+    INIT_TRY(dev_alloc(c, (void**)&c->att_ml, splits * nkv * gq * 2 * 4, false));
     c->fused = fused_usable(c);
     if (c->fused) {
       INIT_HIP(fused_decode_prepare(d, gq));

@@ -40,3 +40,14 @@ def test_two_computed_shards_and_peers(harness):
     w = WIDE.with_(tp_degree=3, n_real_shards=2, prefill=100, peer_pool=2)
     res = harness.run_case(w, decode_steps=1)
     assert max(res.errs) < TOL, res.errs
+
+
+@pytest.mark.parametrize("nq,nkv,d", [(2, 2, 64), (4, 2, 128), (4, 1, 64), (8, 1, 128)])
+@pytest.mark.parametrize("cached", [1, 31, 127, 128, 300, 1025])
+def test_wide_decode_attention(harness, nq, nkv, d, cached):
+    """Batches above 16: one and several splits, at the edges of a 32-key block, of a wavefront round and of a split, while
+    the position moves over them; every number of q heads per kv head."""
+    w = WIDE.with_(name="wide_attn", hidden=256, n_q_heads=nq, n_kv_heads=nkv, head_dim=d, inter=352, batch=17, prefill=0,
+                   kv_preload=cached, decode_steps=3)
+    res = harness.run_case(w, kv_preload=cached, decode_steps=3, max_tokens=1)
+    assert max(res.errs) < TOL, res.errs
