@@ -23,10 +23,10 @@
  *   - every pointer named "device" is a HIP device pointer of the current
  *     device; config / weight-descriptor structs are host memory.
  *   - calls are ordered on the stream given to ladder_init: the work runs on
- *     the context's own streams, which wait for that stream at entry and which
- *     that stream waits for before the call returns; calls return without
- *     synchronising; outputs are valid once the caller has synchronised the
- *     stream.
+ *     it, and where a call uses a stream of the context beside it, that stream
+ *     forks from it and joins it again before the call returns; calls return
+ *     without synchronising; outputs are valid once the caller has synchronised
+ *     the stream.
  *   - every entry point returns 0 or a negative LADDER_E_* code; nothing
  *     throws or aborts across the boundary; a failed call leaves the
  *     context's position unchanged.  ladder_last_error gives a text.

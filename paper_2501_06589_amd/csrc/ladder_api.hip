@@ -1,7 +1,8 @@
 // Host side of the C-ABI: configuration checks, memory plan, weight loading (repack into matrix-core
 // tiles), and the schedules of the Ladder-Residual forward (Algorithm 1 / Eq. 2).
 //
-// All work runs on the context's own streams; the caller's stream is fenced in and out with events.
+// Calls run on the caller's stream; a second module stream or a side stream (small calls of the per-operation schedule)
+// forks from it and joins it again with events.
 //
 // Per-operation schedule (forward_body: prefill, fp32, several computed shards).  Module m (1..2N)
 // writes its partial sums into parts[m%2].  "AsyncAllReduce(m)" = reduce_norm: it waits for the event
@@ -83,11 +84,11 @@ struct ladder_ctx {
   bool bf16 = false, fast = false;
   size_t esz = 4;
   int n_mod = 0, n_peers = 0, s_cap = 0, rows_cap = 0, nqkv = 0;
-  // caller's stream (fences only) and the internal streams: s_attn runs the attention modules (and
-  // everything else when nothing overlaps), s_mlp the MLP modules, side the reduces
-  hipStream_t main = nullptr, s_attn = nullptr, s_mlp = nullptr, side = nullptr;
+  // main: the caller's stream, on which calls run; s_mlp runs the MLP modules and side the reduces of small calls that
+  // overlap them; s_capture is only ever captured on (a decode step's graph is replayed on the caller's stream)
+  hipStream_t main = nullptr, s_capture = nullptr, s_mlp = nullptr, side = nullptr;
   hipEvent_t ev_mod[2] = {nullptr, nullptr}, ev_red[2] = {nullptr, nullptr};
-  hipEvent_t ev_begin = nullptr, ev_end = nullptr, ev_fork = nullptr;
+  hipEvent_t ev_fork = nullptr;
   int* pos_dev = nullptr;       // device copy of the position, read by the decode kernels
   char* emb_stage = nullptr;    // T [max_batch][H]: decode input staged for the captured graph
   hipGraphExec_t graph_exec = nullptr;
@@ -298,7 +299,6 @@ bool fast_shapes_ok(const ladder_config* g) {
 int collect_profile(ladder_ctx* c) {
   if (c->prof_pending.empty()) return LADDER_OK;
   HIP_TRY(c, hipStreamSynchronize(c->main));
-  HIP_TRY(c, hipStreamSynchronize(c->s_attn));
   HIP_TRY(c, hipStreamSynchronize(c->s_mlp));
   HIP_TRY(c, hipStreamSynchronize(c->side));
   for (auto& r : c->prof_pending) {
@@ -623,15 +623,15 @@ int run_reduce(ladder_ctx* c, int m, int rows, int n_slots, const void* emb, flo
   return LADDER_OK;
 }
 
-// the 2N modules and their reduces on the internal streams; does not touch the caller's stream.
+// the 2N modules and their reduces, from stream s0 and back to it.
 // Stream plan:
-//   overlap_modules: odd (attention) modules and their reduces on s_attn, even (MLP) modules and their
+//   overlap_modules: odd (attention) modules and their reduces on the call's stream s0, even (MLP) modules and their
 //     reduces on s_mlp.  Under the ladder wiring module m+1 needs only x_{m-1}, so it executes while
 //     module m and reduce(m) still run on the other stream; reduce(m) waits for reduce(m-1) (the
 //     residual is updated in place, in module order) through an event.
-//   else reduce_on_side_stream: all modules on s_attn, all reduces on the side stream.
-//   else (and for every call with more than 64 rows): everything in order on s_attn.
-int forward_body(ladder_ctx* c, const void* x_in, int B, int T, int pos0, void* x_out, const StageIo* st = nullptr) {
+//   else reduce_on_side_stream: all modules on s0, all reduces on the side stream.
+//   else (and for every call with more than 64 rows): everything in order on s0.
+int forward_body(ladder_ctx* c, const void* x_in, int B, int T, int pos0, void* x_out, hipStream_t s0, const StageIo* st = nullptr) {
   const int rows = B * T;
   // calls with more than 64 rows (prefill) run in order on one stream: each of their kernels fills the
   // chip, and the same work measured 4 % (reduce on the side stream) to 16 % (two module streams) slower
@@ -640,7 +640,6 @@ int forward_body(ladder_ctx* c, const void* x_in, int B, int T, int pos0, void* 
   const bool small = rows <= 64 && !st;
   const bool overlap = small && c->cfg.overlap_modules != 0;
   const bool side = small && !overlap && c->cfg.reduce_on_side_stream != 0;
-  hipStream_t s0 = c->s_attn;
   auto module_stream = [&](int m) { return (overlap && (m & 1) == 0) ? c->s_mlp : s0; };
   auto reduce_stream = [&](int m) { return m == 0 ? s0 : (overlap ? module_stream(m) : (side ? c->side : s0)); };
   // (calls of few rows split K over workgroups, whose partial products the reduce adds up; several real shards would each add to the residual, and the
@@ -1172,7 +1171,7 @@ int build_chain(ladder_ctx* c, int B) {
     return fail(c, LADDER_E_ARG, "chained step: the launch list is longer than the tables sized at init");
   std::vector<StepItem> flat((size_t)c->chain_slots * n_items);   // (zero items: kind 0 ends a list)
   for (size_t w = 0; w < slot.size(); ++w) std::copy(slot[w].begin(), slot[w].end(), flat.begin() + w * n_items);
-  HIP_TRY(c, hipStreamSynchronize(c->s_attn));   // (a step that reads the old tables may still be running)
+  HIP_TRY(c, hipStreamSynchronize(c->main));   // (a step that reads the old tables may still be running)
   HIP_TRY(c, hipMemcpy(c->chain_items_dev, flat.data(), flat.size() * sizeof(StepItem), hipMemcpyHostToDevice));
   HIP_TRY(c, hipMemcpy(c->chain_gemv_dev, gemv.data(), gemv.size() * sizeof(GemvJob), hipMemcpyHostToDevice));
   if (!attn.empty()) HIP_TRY(c, hipMemcpy(c->chain_attn_dev, attn.data(), attn.size() * sizeof(AttnJob), hipMemcpyHostToDevice));
@@ -1302,31 +1301,12 @@ int fused_body(ladder_ctx* c, const void* emb, int B, hipStream_t s, float* x_ou
   return LADDER_OK;
 }
 
-int fence_in(ladder_ctx* c) {
-  HIP_TRY(c, hipEventRecord(c->ev_begin, c->main));
-  HIP_TRY(c, hipStreamWaitEvent(c->s_attn, c->ev_begin, 0));
-  return LADDER_OK;
-}
-int fence_out(ladder_ctx* c) {
-  HIP_TRY(c, hipEventRecord(c->ev_end, c->s_attn));
-  HIP_TRY(c, hipStreamWaitEvent(c->main, c->ev_end, 0));
-  return LADDER_OK;
-}
-
-int forward(ladder_ctx* c, const void* x_in, int B, int T, int pos0, void* x_out, const StageIo* st = nullptr) {
-  int rc = fence_in(c);
-  if (rc) return rc;
-  rc = forward_body(c, x_in, B, T, pos0, x_out, st);
-  if (rc) return rc;
-  return fence_out(c);
-}
-
 // one decode step replayed from a captured graph: stage the input, launch, copy the result out
 int decode_graph_step(ladder_ctx* c, const void* x_in, void* x_out) {
   const int B = c->batch, H = c->cfg.hidden;
   if (!c->graph_exec || c->graph_batch != B || c->graph_stale) {
     if (c->graph_exec) {
-      HIP_TRY(c, hipStreamSynchronize(c->s_attn));   // (a replay may still be running)
+      HIP_TRY(c, hipStreamSynchronize(c->main));   // (a replay may still be running)
       HIP_TRY(c, hipGraphExecDestroy(c->graph_exec));
       c->graph_exec = nullptr;
     }
@@ -1337,17 +1317,17 @@ int decode_graph_step(ladder_ctx* c, const void* x_in, void* x_out) {
     }
     hipGraph_t graph = nullptr;
     DBG("capture: begin (batch %d)", B);
-    HIP_TRY(c, hipStreamBeginCapture(c->s_attn, hipStreamCaptureModeThreadLocal));
+    HIP_TRY(c, hipStreamBeginCapture(c->s_capture, hipStreamCaptureModeThreadLocal));
     int finished = 0;
-    int rc = c->fused ? fused_body(c, c->emb_stage, B, c->s_attn, nullptr, &finished) : forward_body(c, c->emb_stage, B, 1, 0, nullptr);
+    int rc = c->fused ? fused_body(c, c->emb_stage, B, c->s_capture, nullptr, &finished) : forward_body(c, c->emb_stage, B, 1, 0, nullptr, c->s_capture);
     DBG("capture: body recorded rc=%d", rc);
     if (rc == LADDER_OK && !(finished & FUSED_ADVANCED)) {
       DBG("capture: inc_pos");
-      hipLaunchKernelGGL(inc_pos_kernel, dim3(1), dim3(1), 0, c->s_attn, c->pos_dev);
+      hipLaunchKernelGGL(inc_pos_kernel, dim3(1), dim3(1), 0, c->s_capture, c->pos_dev);
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) rc = fail(c, LADDER_E_HIP, std::string("inc_pos: ") + hipGetErrorString(e));
     }
-    hipError_t ee = hipStreamEndCapture(c->s_attn, &graph);
+    hipError_t ee = hipStreamEndCapture(c->s_capture, &graph);
     DBG("capture: end -> %s", hipGetErrorString(ee));
     if (rc) {
       if (graph) (void)hipGraphDestroy(graph);
@@ -1363,34 +1343,30 @@ int decode_graph_step(ladder_ctx* c, const void* x_in, void* x_out) {
     }
     c->graph_batch = B;
   }
-  int rc = fence_in(c);
-  if (rc) return rc;
-  HIP_TRY(c, hipMemcpyAsync(c->emb_stage, x_in, (size_t)B * H * c->esz, hipMemcpyDeviceToDevice, c->s_attn));
+  HIP_TRY(c, hipMemcpyAsync(c->emb_stage, x_in, (size_t)B * H * c->esz, hipMemcpyDeviceToDevice, c->main));
   DBG("graph launch");
-  HIP_TRY(c, hipGraphLaunch(c->graph_exec, c->s_attn));
+  HIP_TRY(c, hipGraphLaunch(c->graph_exec, c->main));
   DBG("graph launched");
   const float* result = c->fused ? c->x_ring[(size_t)(c->n_mod % c->ring_n)] : c->x;
-  HIP_TRY(c, hipMemcpyAsync(x_out, result, (size_t)B * H * 4, hipMemcpyDeviceToDevice, c->s_attn));
-  return fence_out(c);
+  HIP_TRY(c, hipMemcpyAsync(x_out, result, (size_t)B * H * 4, hipMemcpyDeviceToDevice, c->main));
+  return LADDER_OK;
 }
 
 // one decode step of the fused path, launched eagerly (st: a pipeline stage's step, which takes and leaves its
 // three tensors instead of x_in / x_out)
 int decode_fused_step(ladder_ctx* c, const void* x_in, void* x_out, const StageIo* st = nullptr) {
   const int B = c->batch, H = c->cfg.hidden;
-  int rc = fence_in(c);
-  if (rc) return rc;
   int finished = 0;
-  rc = fused_body(c, x_in, B, c->s_attn, (float*)x_out, &finished, st);
+  const int rc = fused_body(c, x_in, B, c->main, (float*)x_out, &finished, st);
   if (rc) return rc;
   // (what the last launch has not done itself)
   if (!st && !(finished & FUSED_DELIVERED))
-    HIP_TRY(c, hipMemcpyAsync(x_out, c->x_ring[(size_t)(c->n_mod % c->ring_n)], (size_t)B * H * 4, hipMemcpyDeviceToDevice, c->s_attn));
+    HIP_TRY(c, hipMemcpyAsync(x_out, c->x_ring[(size_t)(c->n_mod % c->ring_n)], (size_t)B * H * 4, hipMemcpyDeviceToDevice, c->main));
   if (!(finished & FUSED_ADVANCED)) {
-    hipLaunchKernelGGL(inc_pos_kernel, dim3(1), dim3(1), 0, c->s_attn, c->pos_dev);
+    hipLaunchKernelGGL(inc_pos_kernel, dim3(1), dim3(1), 0, c->main, c->pos_dev);
     HIP_TRY(c, hipGetLastError());
   }
-  return fence_out(c);
+  return LADDER_OK;
 }
 
 // A kernel of an earlier call has raised the error word (its bounded in-launch wait gave up, so that call's
@@ -1476,11 +1452,9 @@ static int init_impl(const ladder_config* cfg, void* hip_stream, ladder_ctx** ou
     if (!c->dry && hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev_id) == hipSuccess && khz > 0) c->wall_khz = khz;
     INIT_HIP(resolve_static_scratch(dev_id, &c->static_scratch));
   }
-  INIT_HIP(hipStreamCreateWithFlags(&c->s_attn, hipStreamNonBlocking));
+  INIT_HIP(hipStreamCreateWithFlags(&c->s_capture, hipStreamNonBlocking));
   INIT_HIP(hipStreamCreateWithFlags(&c->s_mlp, hipStreamNonBlocking));
   INIT_HIP(hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
-  INIT_HIP(hipEventCreateWithFlags(&c->ev_begin, hipEventDisableTiming));
-  INIT_HIP(hipEventCreateWithFlags(&c->ev_end, hipEventDisableTiming));
   INIT_HIP(hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming));
   for (int i = 0; i < 2; ++i) {
     INIT_HIP(hipEventCreateWithFlags(&c->ev_mod[i], hipEventDisableTiming));
@@ -1770,7 +1744,7 @@ int ladder_prefill(ladder_ctx* c, const void* x_in, int32_t B, int32_t T, void* 
   if (rc) return rc;
   rc = all_loaded(c);
   if (rc) return rc;
-  rc = forward(c, x_in, B, T, 0, x_out);
+  rc = forward_body(c, x_in, B, T, 0, x_out, c->main);
   if (rc) return rc;
   for (auto& X : c->store) { X.kv_B = 0; X.kv_S = 0; }
   c->pos = T;
@@ -1797,7 +1771,7 @@ int ladder_decode_step(ladder_ctx* c, const void* x_in, void* x_out) {
     rc = decode_fused_step(c, x_in, x_out);
     if (rc) return rc;
   } else {
-    rc = forward(c, x_in, c->batch, 1, c->pos, x_out);
+    rc = forward_body(c, x_in, c->batch, 1, c->pos, x_out, c->main);
     if (rc) return rc;
     hipLaunchKernelGGL(inc_pos_kernel, dim3(1), dim3(1), 0, c->main, c->pos_dev);
     HIP_TRY(c, hipGetLastError());
@@ -1833,7 +1807,7 @@ int ladder_prefill_stage(ladder_ctx* c, const float* residual_in, const float* a
   if (rc) return rc;
   rc = all_loaded(c);
   if (rc) return rc;
-  rc = forward(c, nullptr, B, T, 0, nullptr, &st);
+  rc = forward_body(c, nullptr, B, T, 0, nullptr, c->main, &st);
   if (rc) return rc;
   for (auto& X : c->store) { X.kv_B = 0; X.kv_S = 0; }
   c->pos = T;
@@ -1861,7 +1835,7 @@ int ladder_decode_step_stage(ladder_ctx* c, const float* residual_in, const floa
     rc = decode_fused_step(c, nullptr, nullptr, &st);
     if (rc) return rc;
   } else {
-    rc = forward(c, nullptr, c->batch, 1, c->pos, nullptr, &st);
+    rc = forward_body(c, nullptr, c->batch, 1, c->pos, nullptr, c->main, &st);
     if (rc) return rc;
     hipLaunchKernelGGL(inc_pos_kernel, dim3(1), dim3(1), 0, c->main, c->pos_dev);
     HIP_TRY(c, hipGetLastError());
@@ -1873,15 +1847,13 @@ int ladder_decode_step_stage(ladder_ctx* c, const float* residual_in, const floa
 void ladder_free(ladder_ctx* c) {
   if (!c) return;
   (void)hipStreamSynchronize(c->main);
-  for (hipStream_t* st : {&c->s_attn, &c->s_mlp, &c->side}) {
+  for (hipStream_t* st : {&c->s_capture, &c->s_mlp, &c->side}) {
     if (*st) {
       (void)hipStreamSynchronize(*st);
       (void)hipStreamDestroy(*st);
     }
   }
   if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
-  if (c->ev_begin) (void)hipEventDestroy(c->ev_begin);
-  if (c->ev_end) (void)hipEventDestroy(c->ev_end);
   if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
   for (auto& r : c->prof_pending) {
     (void)hipEventDestroy(r.start);
@@ -2035,7 +2007,7 @@ int ladder_timeline_enable(ladder_ctx* c, int32_t on) {
     const int rc = dev_alloc(c, (void**)&c->chain_tl_dev, bytes, true);
     if (rc) return rc;
   }
-  HIP_TRY(c, hipStreamSynchronize(c->s_attn));
+  HIP_TRY(c, hipStreamSynchronize(c->main));
   c->timeline_on = on != 0;
   return LADDER_OK;
 }
@@ -2044,7 +2016,7 @@ int ladder_timeline_read(ladder_ctx* c, ladder_timeline_rec* out, int64_t cap, i
   if (!c || !n_out) return LADDER_E_ARG;
   if (!c->chain || !c->chain_tl_dev) return fail(c, LADDER_E_STATE, "no timeline: ladder_timeline_enable first");
   if (c->fused_plan.empty() || c->chain_items <= 0) return fail(c, LADDER_E_STATE, "no timeline: no decode step has run");
-  HIP_TRY(c, hipStreamSynchronize(c->s_attn));
+  HIP_TRY(c, hipStreamSynchronize(c->main));
   const size_t n_items = (size_t)c->chain_items;
   std::vector<unsigned long long> t((size_t)c->chain_slots * n_items * 3);
   HIP_TRY(c, hipMemcpy(t.data(), c->chain_tl_dev, t.size() * sizeof(unsigned long long), hipMemcpyDeviceToHost));
