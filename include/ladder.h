@@ -83,7 +83,9 @@ typedef struct {
                                     0: everything in order on one stream (same results).  Like
                                     overlap_modules it applies to calls of at most 64 rows that do not take
                                     the fused decode schedule; larger calls (prefill) always run in order:
-                                    their kernels fill the chip and measured slower when spread over streams */
+                                    their kernels fill the chip and measured slower when spread over streams;
+                                    so do calls of the plain kernels on layers of less than 32 MB, whose
+                                    kernels are shorter than the events between streams */
   int32_t peer_pool;      /* number of distinct synthetic peer sets; module m uses set m % peer_pool */
   int32_t peer_rows;      /* rows of each synthetic peer tensor (>= rows of any call), 0 if no peers */
   int32_t kernel_path;    /* LADDER_PATH_AUTO: MFMA/streaming kernels when dtype and sizes allow;

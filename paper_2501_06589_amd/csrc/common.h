@@ -61,9 +61,34 @@ struct ReduceNormArgs {
 };
 hipError_t launch_reduce_norm(const ReduceNormArgs& a, bool is_bf16, hipStream_t s);
 
-// out[m][col0 + n] (f32, row stride ldo) = sum_k x[m][k] * w[k][n];  x: T [M][K], w: T [K][N]
-hipError_t launch_gemm_generic(const void* x, const void* w, float* out, int M, int N, int K, int ldo,
-                               int col0, bool is_bf16, hipStream_t s);
+// Plain projections of the rows x (T [shard][M][K]) for all computed shards at once; w: T [K][N], a shard's matrices
+// w_stride BYTES behind the previous shard's, as are its caches (cache_stride); the other strides are elements per shard.
+enum { PLAIN_OUT = 0, PLAIN_SWIGLU = 1, PLAIN_QKV = 2 };
+struct PlainGemmArgs {
+  const void* x;
+  size_t x_stride;         // 0: every shard reads the same rows
+  int M, K, n_shards;
+  int n_mat;               // matrices: 1 (OUT), gate and up (SWIGLU, equal N), q, k and v (QKV)
+  const void* w[3];
+  int N[3];
+  size_t w_stride;
+  int epilogue;
+  float* out;              // OUT: f32 [shard][M][N]
+  size_t out_stride;
+  void* act;               // SWIGLU: T [shard][M][N] = silu(gate) * up
+  size_t act_stride;
+  // QKV: row b*T + t is token t of sequence b at position pos0 + t; q rotated -> T [shard][M][nq*d], k rotated and v -> the
+  // caches (layouts as below)
+  void* q_out;
+  size_t q_stride;
+  void* cache_k;
+  void* cache_v;
+  size_t cache_stride;
+  const float* cos_tab;    // [max_seq][d/2]
+  const float* sin_tab;
+  int T, pos0, nkv, d, max_seq;
+};
+hipError_t launch_plain_gemm(const PlainGemmArgs& a, bool is_bf16, hipStream_t s);
 
 // qkv: f32 [n_parts][rows][(nq+2nkv)*d] (slots summed).  rows = B*T, row = b*T + t, position = pos0 + t.
 // q -> T [rows][nq*d] rotated; k rotated -> cache_k T [B_cap][nkv][max_seq][d]; v -> cache_v kept
@@ -81,22 +106,21 @@ struct RopeAppendArgs {
   int B, T, pos0, nq, nkv, d, max_seq;
   const int* pos_dev;      // if non-null the position is read from device memory (pos0 ignored)
 };
-hipError_t launch_rope_append(const RopeAppendArgs& a, bool is_bf16, hipStream_t s);
+hipError_t launch_rope_append(const RopeAppendArgs& a, hipStream_t s);   // T = bf16
 
-// plain causal GQA attention over the cache: one wavefront per (row, q head).
+// plain causal GQA attention over the cache, all computed shards
 struct AttnGenericArgs {
-  const void* q;           // T [rows][nq*d]
+  const void* q;           // T [shard][rows][nq*d]
   const void* cache_k;     // T [B_cap][nkv][max_seq][d]
   const void* cache_v;     // T [B_cap][nkv][d][max_seq]
-  void* o;                 // T [rows][nq*d]
-  int B, T, pos0, nq, nkv, d, max_seq;
+  void* o;                 // T [shard][rows][nq*d]
+  int B, T, pos0, nq, nkv, d, max_seq, n_shards;
+  size_t q_stride;         // elements, of q and o
+  size_t cache_stride;     // bytes
 };
 hipError_t launch_attn_generic(const AttnGenericArgs& a, bool is_bf16, hipStream_t s);
 
-// act[m][i] (T) = silu(gu[m][i]) * gu[m][I + i];  gu: f32 [M][2I]
-hipError_t launch_swiglu(const float* gu, void* act, int M, int I, bool is_bf16, hipStream_t s);
-
-// the same from the partial products of the packed gate/up projection (tile columns 0..7 gate, 8..15 the matching up
+// act[m][i] = silu(gate) * up from the partial products of the packed gate/up projection (tile columns 0..7 gate, 8..15 the matching up
 // columns), act bf16: parts f32 [n_parts][M][2I], slot s at parts + s * part_stride, summed in slot order
 hipError_t launch_swiglu_parts(const float* parts, int n_parts, size_t part_stride, bf16_t* act, int M, int I, hipStream_t s);
 

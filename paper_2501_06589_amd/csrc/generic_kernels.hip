@@ -1,6 +1,6 @@
 // Plain kernels: any size, both storage types, fp32 arithmetic.  They are the whole path for the
-// fp32 storage type and the fallback of the bf16 one; reduce_norm and rope_append are also used by
-// the streaming / MFMA path.  gfx950 only.
+// fp32 storage type and the fallback of the bf16 one; reduce_norm is used by both paths, rope_append and
+// swiglu_parts by the streaming / MFMA path.  gfx950 only.
 #include "common.h"
 
 // ------------------------------------------------------------------------------------------------
@@ -94,68 +94,150 @@ hipError_t launch_reduce_norm(const ReduceNormArgs& a, bool is_bf16, hipStream_t
 }
 
 // ------------------------------------------------------------------------------------------------
-// Plain tiled GEMM, 64x64 output tile per workgroup, 4x4 per thread, fully bounds-checked.
+// Plain projections: any size, both storage types, weights [K][N] as they were given, fp32 arithmetic.  One launch is
+// one step of a module for ALL computed shards (grid z) and all the matrices that read the same rows (q | k | v, or gate
+// and up), with what follows as its epilogue: a decode step of a small model is a chain of launches, and what counts is how
+// many there are and how many memory round trips each one is long.  A workgroup takes MR rows x 64 columns and
+// the whole K: 16 lanes side by side cover the columns, four at a time, and 16 groups of lanes deal out K in fours; every
+// thread has 16 rows of the weights in flight before the activations are needed.  The groups' sums meet by lane
+// exchange, the wavefronts' in LDS, in a fixed order.
+// tiny fp32 model (hidden 256, 2 shards), one row: 22 us per matrix and shard (64 x 64 tiles, one k step of 16 in flight)
+// -> 5 us for all
+// of them; fp32 model of hidden 2048 (50 M weights a layer), 8 steps behind a prompt of 32: 23.9 -> 2.2 ms for 2 layers.
 // ------------------------------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void gemm_generic_kernel(const T* __restrict__ x, const T* __restrict__ w,
-                                                           float* __restrict__ out, int M, int N, int K,
-                                                           int ldo, int col0) {
-  __shared__ float xs[16][64 + 4];
-  __shared__ float ws[16][64 + 4];
-  const int t = threadIdx.x;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  const int ty = t >> 4, tx = t & 15;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    {
-      const int r = t >> 2, kq = (t & 3) * 4;
-      for (int e = 0; e < 4; ++e) {
-        const int m = m0 + r, k = k0 + kq + e;
-        xs[kq + e][r] = (m < M && k < K) ? load_f<T>(x + (size_t)m * K + k) : 0.f;
-      }
-      const int kr = t >> 4, nq4 = (t & 15) * 4;
-      for (int e = 0; e < 4; ++e) {
-        const int k = k0 + kr, n = n0 + nq4 + e;
-        ws[kr][nq4 + e] = (k < K && n < N) ? load_f<T>(w + (size_t)k * N + n) : 0.f;
-      }
-    }
+constexpr int PLAIN_KC = 256;   // k per pass
+
+template <typename T, bool VEC>
+__device__ __forceinline__ void plain_w4(const T* w, int k, int K, int n, int N, float v[4]) {
+  if (VEC) {   // (N is a multiple of 4: a thread's columns are all inside or all outside)
+    if (k < K && n < N) load4<T>(w + (size_t)k * N + n, v);
+    else v[0] = v[1] = v[2] = v[3] = 0.f;
+  } else {
+    for (int e = 0; e < 4; ++e) v[e] = k < K && n + e < N ? load_f<T>(w + (size_t)k * N + n + e) : 0.f;
+  }
+}
+
+// rows m0 .. m0 + MR - 1 of x times columns n .. n + 3 (per lane) of w; the sums over all K end up in `sum` [MR][64]
+template <typename T, int MR, bool VEC>
+__device__ __forceinline__ void plain_product(const T* x, int M, int K, int m0, const T* w, int N, int n0, float (*xs)[PLAIN_KC],
+                                              float (*red)[MR][64], float (*sum)[64]) {
+  const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
+  const int c4 = (lane & 15) * 4, kg = t >> 4;
+  float acc[MR][4] = {};
+  for (int k0 = 0; k0 < K; k0 += PLAIN_KC) {
+    float wv[4][4][4];   // [pass][k][column]
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) plain_w4<T, VEC>(w, k0 + i * 64 + kg * 4 + e, K, n0 + c4, N, wv[i][e]);
+    if (k0 > 0) __syncthreads();   // the previous pass has been read
+#pragma unroll
+    for (int m = 0; m < MR; ++m) xs[m][t] = m0 + m < M && k0 + t < K ? load_f<T>(x + (size_t)(m0 + m) * K + k0 + t) : 0.f;
     __syncthreads();
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float av[4], bv[4];
-      for (int i = 0; i < 4; ++i) av[i] = xs[kk][ty * 4 + i];
-      for (int j = 0; j < 4; ++j) bv[j] = ws[kk][tx * 4 + j];
-      for (int i = 0; i < 4; ++i)
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
-    }
-    __syncthreads();
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int m = 0; m < MR; ++m) {
+        const float4 xv = *reinterpret_cast<const float4*>(&xs[m][i * 64 + kg * 4]);
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          acc[m][c] = fmaf(xv.w, wv[i][3][c], fmaf(xv.z, wv[i][2][c], fmaf(xv.y, wv[i][1][c], fmaf(xv.x, wv[i][0][c], acc[m][c]))));
+      }
   }
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + ty * 4 + i;
-    if (m >= M) continue;
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx * 4 + j;
-      if (n < N) out[(size_t)m * ldo + col0 + n] = acc[i][j];
+#pragma unroll
+  for (int m = 0; m < MR; ++m)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      float v = acc[m][c];
+      v += __shfl_xor(v, 16, 64);
+      v += __shfl_xor(v, 32, 64);
+      if (lane < 16) red[wave][m][c4 + c] = v;
+    }
+  __syncthreads();
+  for (int i = t; i < MR * 64; i += 256) sum[i >> 6][i & 63] = red[0][i >> 6][i & 63] + red[1][i >> 6][i & 63] + red[2][i >> 6][i & 63] + red[3][i >> 6][i & 63];
+  __syncthreads();
+}
+
+template <typename T, int MR, bool VEC>
+__global__ __launch_bounds__(256) void plain_gemm_kernel(PlainGemmArgs a) {
+  __shared__ __attribute__((aligned(16))) float xs[MR][PLAIN_KC];
+  __shared__ float red[4][MR][64];
+  __shared__ float sum[2][MR][64];
+  const int t = threadIdx.x, shard = blockIdx.z, m0 = blockIdx.y * MR;
+  int blk = blockIdx.x, mat = 0;   // the matrices' column blocks side by side (SwiGLU: the gate's; the up matrix goes along)
+  while (a.epilogue != PLAIN_SWIGLU && mat + 1 < a.n_mat && blk >= (a.N[mat] + 63) / 64) { blk -= (a.N[mat] + 63) / 64; ++mat; }
+  const int n0 = blk * 64, N = a.N[mat];
+  const T* x = reinterpret_cast<const T*>(a.x) + shard * a.x_stride;
+  auto weights = [&](int i) { return reinterpret_cast<const T*>(reinterpret_cast<const char*>(a.w[i]) + shard * a.w_stride); };
+  plain_product<T, MR, VEC>(x, a.M, a.K, m0, weights(mat), N, n0, xs, red, sum[0]);
+  if (a.epilogue == PLAIN_SWIGLU) plain_product<T, MR, VEC>(x, a.M, a.K, m0, weights(1), N, n0, xs, red, sum[1]);
+  if (a.epilogue == PLAIN_OUT) {
+    for (int i = t; i < MR * 64; i += 256) {
+      const int m = m0 + (i >> 6), n = n0 + (i & 63);
+      if (m < a.M && n < N) a.out[shard * a.out_stride + (size_t)m * N + n] = sum[0][i >> 6][i & 63];
+    }
+  } else if (a.epilogue == PLAIN_SWIGLU) {
+    T* act = reinterpret_cast<T*>(a.act) + shard * a.act_stride;
+    for (int i = t; i < MR * 64; i += 256) {
+      const int m = m0 + (i >> 6), n = n0 + (i & 63);
+      const float g = sum[0][i >> 6][i & 63], u = sum[1][i >> 6][i & 63];
+      if (m < a.M && n < N) store_f<T>(act + (size_t)m * N + n, g / (1.0f + expf(-g)) * u);
+    }
+  } else {   // matrices q, k, v: rotary embedding of q and k (adjacent pairs), k and v to the cache (v transposed)
+    const int half = a.d >> 1;
+    for (int i = t; i < MR * 32; i += 256) {
+      const int m = m0 + (i >> 5), n = n0 + 2 * (i & 31);
+      if (m >= a.M || n >= N) continue;   // (N is a multiple of the even d)
+      float e = sum[0][i >> 5][2 * (i & 31)], o = sum[0][i >> 5][2 * (i & 31) + 1];
+      const int b = m / a.T, pos = a.pos0 + m % a.T, head = n / a.d, dim = n % a.d;
+      if (mat < 2) {
+        const float c = a.cos_tab[(size_t)pos * half + (dim >> 1)], sn = a.sin_tab[(size_t)pos * half + (dim >> 1)];
+        const float re = e * c - o * sn;
+        o = e * sn + o * c;
+        e = re;
+      }
+      if (mat == 0) {
+        T* q = reinterpret_cast<T*>(a.q_out) + shard * a.q_stride + (size_t)m * N + n;
+        store_f<T>(q, e);
+        store_f<T>(q + 1, o);
+      } else if (mat == 1) {
+        T* k = reinterpret_cast<T*>(reinterpret_cast<char*>(a.cache_k) + shard * a.cache_stride) + (((size_t)b * a.nkv + head) * a.max_seq + pos) * a.d + dim;
+        store_f<T>(k, e);
+        store_f<T>(k + 1, o);
+      } else {
+        T* v = reinterpret_cast<T*>(reinterpret_cast<char*>(a.cache_v) + shard * a.cache_stride) + (((size_t)b * a.nkv + head) * a.d + dim) * a.max_seq + pos;
+        store_f<T>(v, e);
+        store_f<T>(v + a.max_seq, o);
+      }
     }
   }
 }
 
-hipError_t launch_gemm_generic(const void* x, const void* w, float* out, int M, int N, int K, int ldo,
-                               int col0, bool is_bf16, hipStream_t s) {
-  if (M <= 0 || N <= 0) return hipSuccess;
-  dim3 grid((N + 63) / 64, (M + 63) / 64);
-  if (is_bf16)
-    hipLaunchKernelGGL(gemm_generic_kernel<bf16_t>, grid, dim3(256), 0, s, (const bf16_t*)x, (const bf16_t*)w, out,
-                       M, N, K, ldo, col0);
-  else
-    hipLaunchKernelGGL(gemm_generic_kernel<float>, grid, dim3(256), 0, s, (const float*)x, (const float*)w, out, M,
-                       N, K, ldo, col0);
+template <typename T, int MR>
+static hipError_t launch_plain_gemm_t(const PlainGemmArgs& a, bool vec, hipStream_t s) {
+  int blocks = 0;
+  for (int i = 0; i < (a.epilogue == PLAIN_SWIGLU ? 1 : a.n_mat); ++i) blocks += (a.N[i] + 63) / 64;
+  const dim3 grid(blocks, (a.M + MR - 1) / MR, a.n_shards);
+  if (vec) hipLaunchKernelGGL((plain_gemm_kernel<T, MR, true>), grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((plain_gemm_kernel<T, MR, false>), grid, dim3(256), 0, s, a);
   return hipGetLastError();
+}
+
+hipError_t launch_plain_gemm(const PlainGemmArgs& a, bool is_bf16, hipStream_t s) {
+  if (a.M <= 0 || a.n_shards <= 0) return hipSuccess;
+  // four weights per load where every row of every matrix starts on such a boundary
+  bool vec = (a.w_stride & 15) == 0;
+  for (int i = 0; i < a.n_mat; ++i) vec = vec && a.N[i] % 4 == 0 && ((uintptr_t)a.w[i] & 15) == 0;
+  // rows per workgroup: one for a single row; four for a few; more re-use of the weights beyond
+  const int mr = a.M == 1 ? 1 : a.M <= 64 ? 4 : 16;
+  if ((a.M + mr - 1) / mr > 65535) return hipErrorInvalidValue;
+  if (is_bf16) return mr == 1 ? launch_plain_gemm_t<bf16_t, 1>(a, vec, s) : mr == 4 ? launch_plain_gemm_t<bf16_t, 4>(a, vec, s) : launch_plain_gemm_t<bf16_t, 16>(a, vec, s);
+  return mr == 1 ? launch_plain_gemm_t<float, 1>(a, vec, s) : mr == 4 ? launch_plain_gemm_t<float, 4>(a, vec, s) : launch_plain_gemm_t<float, 16>(a, vec, s);
 }
 
 // ------------------------------------------------------------------------------------------------
 // Rotary embedding of q and k (adjacent pairs, angle = position * theta^(-2j/d), cos/sin from a
-// host-made table) and append of k, v to the cache.  One thread per pair.
+// host-made table) and append of k, v to the cache (packed-weight path, bf16).  One thread per pair.
 // ------------------------------------------------------------------------------------------------
 template <typename T>
 __global__ void rope_append_kernel(RopeAppendArgs a) {
@@ -203,89 +285,114 @@ __global__ void rope_append_kernel(RopeAppendArgs a) {
   store_f<T>(dst + 1, o);
 }
 
-hipError_t launch_rope_append(const RopeAppendArgs& a, bool is_bf16, hipStream_t s) {
+hipError_t launch_rope_append(const RopeAppendArgs& a, hipStream_t s) {
   const long long total = (long long)a.B * a.T * (a.nq + 2 * a.nkv) * (a.d / 2);
   if (total <= 0) return hipSuccess;
   const unsigned blocks = (unsigned)((total + 255) / 256);
-  if (is_bf16) hipLaunchKernelGGL(rope_append_kernel<bf16_t>, dim3(blocks), dim3(256), 0, s, a);
-  else hipLaunchKernelGGL(rope_append_kernel<float>, dim3(blocks), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(rope_append_kernel<bf16_t>, dim3(blocks), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
 // ------------------------------------------------------------------------------------------------
-// Plain attention: one wavefront per (row, q head), streaming softmax over the visible positions.
+// Plain attention, any even head size up to 256: one workgroup per (row, q head, shard).  Its 4 wavefronts take chunks of
+// 64 visible positions in turn, each with its own running softmax, and merge in LDS.  In a chunk a lane first owns a
+// position (it walks that K row, 16 bytes at a time) and then a dim (it walks that row of the transposed V cache), so that
+// every load is a whole piece of a row and a chunk is two memory round trips long, not one per position.
+// tiny fp32 model, one row behind 32 positions: 23 us per shard -> 5.7 for both.
 // ------------------------------------------------------------------------------------------------
-template <typename T>
+template <typename T, bool VEC>
 __global__ __launch_bounds__(256) void attn_generic_kernel(AttnGenericArgs a) {
+  __shared__ float qs[256];
+  __shared__ __attribute__((aligned(16))) float ps[4][64];
+  __shared__ float om[4][256], ms[4], ls[4];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const long long unit = (long long)blockIdx.x * 4 + wave;
-  const int rows = a.B * a.T;
-  if (unit >= (long long)rows * a.nq) return;
-  const int row = (int)(unit / a.nq), h = (int)(unit % a.nq);
+  const int row = blockIdx.x / a.nq, h = blockIdx.x % a.nq, shard = blockIdx.y;
   const int b = row / a.T, t = row % a.T;
   const int kvh = h / (a.nq / a.nkv);
   const int n_vis = a.pos0 + t + 1;
-  const T* q = reinterpret_cast<const T*>(a.q) + (size_t)row * a.nq * a.d + h * a.d;
-  const T* kb = reinterpret_cast<const T*>(a.cache_k) + ((size_t)b * a.nkv + kvh) * a.max_seq * a.d;
-  const T* vb = reinterpret_cast<const T*>(a.cache_v) + ((size_t)b * a.nkv + kvh) * a.max_seq * a.d;
-  float qr[4], acc[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int e = 0; e < 4; ++e) {
-    const int i = lane + 64 * e;
-    qr[e] = i < a.d ? load_f<T>(q + i) : 0.f;
-  }
+  const T* q = reinterpret_cast<const T*>(a.q) + shard * a.q_stride + (size_t)row * a.nq * a.d + h * a.d;
+  const T* kb = reinterpret_cast<const T*>(reinterpret_cast<const char*>(a.cache_k) + shard * a.cache_stride) + ((size_t)b * a.nkv + kvh) * a.max_seq * a.d;
+  const T* vb = reinterpret_cast<const T*>(reinterpret_cast<const char*>(a.cache_v) + shard * a.cache_stride) + ((size_t)b * a.nkv + kvh) * a.max_seq * a.d;
+  if ((int)threadIdx.x < a.d) qs[threadIdx.x] = load_f<T>(q + threadIdx.x);
+  __syncthreads();
   const float scale = 1.0f / sqrtf((float)a.d);
+  float acc[4] = {0.f, 0.f, 0.f, 0.f};
   float mx = -INFINITY, l = 0.f;
-  for (int j = 0; j < n_vis; ++j) {
-    float part = 0.f;
-    for (int e = 0; e < 4; ++e) {
-      const int i = lane + 64 * e;
-      if (i < a.d) part = fmaf(qr[e], load_f<T>(kb + (size_t)j * a.d + i), part);
+  for (int c0 = wave * 64; c0 < n_vis; c0 += 256) {
+    const int n = min(64, n_vis - c0);
+    float sc = -INFINITY;
+    if (lane < n) {
+      const T* kr = kb + (size_t)(c0 + lane) * a.d;
+      float part[4] = {0.f, 0.f, 0.f, 0.f};
+      if (VEC) {
+#pragma unroll 8
+        for (int i = 0; i < a.d; i += 4) {
+          float kv[4];
+          load4<T>(kr + i, kv);
+          for (int e = 0; e < 4; ++e) part[e] = fmaf(qs[i + e], kv[e], part[e]);
+        }
+      } else {
+        for (int i = 0; i < a.d; ++i) part[i & 3] = fmaf(qs[i], load_f<T>(kr + i), part[i & 3]);
+      }
+      sc = ((part[0] + part[1]) + (part[2] + part[3])) * scale;
     }
-    const float sc = wave_sum(part) * scale;
-    const float mn = fmaxf(mx, sc);
-    const float corr = expf(mx - mn), p = expf(sc - mn);
-    l = l * corr + p;
-    for (int e = 0; e < 4; ++e) {
-      const int i = lane + 64 * e;
-      if (i < a.d) acc[e] = acc[e] * corr + p * load_f<T>(vb + (size_t)i * a.max_seq + j);
-    }
+    const float mn = fmaxf(mx, wave_max(sc));   // finite: the chunk has a visible position
+    const float corr = expf(mx - mn), p = lane < n ? expf(sc - mn) : 0.f;
+    l = l * corr + wave_sum(p);
     mx = mn;
+    ps[wave][lane] = p;
+    __builtin_amdgcn_wave_barrier();   // (the wavefront's own LDS accesses stay in order)
+    for (int e = 0; e < 4; ++e) {
+      const int i = lane + 64 * e;
+      if (i >= a.d) break;
+      const T* vr = vb + (size_t)i * a.max_seq + c0;   // (the capacity and c0 are multiples of 64)
+      float o[4] = {0.f, 0.f, 0.f, 0.f};
+      int j = 0;
+#pragma unroll 8
+      for (; j + 4 <= n; j += 4) {
+        float v[4];
+        load4<T>(vr + j, v);
+        for (int u = 0; u < 4; ++u) o[u] = fmaf(ps[wave][j + u], v[u], o[u]);
+      }
+      for (; j < n; ++j) o[0] = fmaf(ps[wave][j], load_f<T>(vr + j), o[0]);
+      acc[e] = acc[e] * corr + ((o[0] + o[1]) + (o[2] + o[3]));
+    }
+    __builtin_amdgcn_wave_barrier();
   }
-  T* o = reinterpret_cast<T*>(a.o) + (size_t)row * a.nq * a.d + h * a.d;
-  for (int e = 0; e < 4; ++e) {
-    const int i = lane + 64 * e;
-    if (i < a.d) store_f<T>(o + i, acc[e] / l);
+  for (int e = 0; e < 4; ++e)
+    if (lane + 64 * e < a.d) om[wave][lane + 64 * e] = acc[e];
+  if (lane == 0) { ms[wave] = mx; ls[wave] = l; }
+  __syncthreads();
+  if ((int)threadIdx.x < a.d) {
+    const float m = fmaxf(fmaxf(ms[0], ms[1]), fmaxf(ms[2], ms[3]));   // (wavefront 0 always has a chunk)
+    float o = 0.f, tot = 0.f;
+    for (int w = 0; w < 4; ++w) {
+      const float f = expf(ms[w] - m);
+      o += om[w][threadIdx.x] * f;
+      tot += ls[w] * f;
+    }
+    store_f<T>(reinterpret_cast<T*>(a.o) + shard * a.q_stride + (size_t)row * a.nq * a.d + h * a.d + threadIdx.x, o / tot);
   }
 }
 
 hipError_t launch_attn_generic(const AttnGenericArgs& a, bool is_bf16, hipStream_t s) {
   const long long units = (long long)a.B * a.T * a.nq;
-  if (units <= 0) return hipSuccess;
-  const unsigned blocks = (unsigned)((units + 3) / 4);
-  if (is_bf16) hipLaunchKernelGGL(attn_generic_kernel<bf16_t>, dim3(blocks), dim3(256), 0, s, a);
-  else hipLaunchKernelGGL(attn_generic_kernel<float>, dim3(blocks), dim3(256), 0, s, a);
+  if (units <= 0 || a.n_shards <= 0) return hipSuccess;
+  if (units > 0x7fffffff || a.n_shards > 65535 || a.d > 256) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)units, a.n_shards);
+  const bool vec = a.d % 4 == 0;   // (a K row then starts on a boundary of four elements)
+  if (is_bf16) {
+    if (vec) hipLaunchKernelGGL((attn_generic_kernel<bf16_t, true>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((attn_generic_kernel<bf16_t, false>), grid, dim3(256), 0, s, a);
+  } else {
+    if (vec) hipLaunchKernelGGL((attn_generic_kernel<float, true>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((attn_generic_kernel<float, false>), grid, dim3(256), 0, s, a);
+  }
   return hipGetLastError();
 }
 
 // ------------------------------------------------------------------------------------------------
-template <typename T>
-__global__ void swiglu_kernel(const float* __restrict__ gu, T* __restrict__ act, int M, int I) {
-  const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gid >= (long long)M * I) return;
-  const int m = (int)(gid / I), i = (int)(gid % I);
-  const float g = gu[(size_t)m * 2 * I + i], u = gu[(size_t)m * 2 * I + I + i];
-  store_f<T>(act + gid, g / (1.0f + expf(-g)) * u);
-}
-
-hipError_t launch_swiglu(const float* gu, void* act, int M, int I, bool is_bf16, hipStream_t s) {
-  const long long total = (long long)M * I;
-  if (total <= 0) return hipSuccess;
-  const unsigned blocks = (unsigned)((total + 255) / 256);
-  if (is_bf16) hipLaunchKernelGGL(swiglu_kernel<bf16_t>, dim3(blocks), dim3(256), 0, s, gu, (bf16_t*)act, M, I);
-  else hipLaunchKernelGGL(swiglu_kernel<float>, dim3(blocks), dim3(256), 0, s, gu, (float*)act, M, I);
-  return hipGetLastError();
-}
-
+// SwiGLU of a split gate/up projection (packed-weight path).
 // Four activations per thread; the gate columns of eight activations and the matching up columns are neighbours.
 __global__ __launch_bounds__(256) void swiglu_parts_kernel(const float* __restrict__ parts, int n_parts, size_t part_stride,
                                                            bf16_t* __restrict__ act, int M, int I) {

@@ -97,6 +97,7 @@ struct ladder_ctx {
   std::vector<void*> allocs;
   size_t dev_bytes = 0;
   size_t weight_bytes = 0;      // of dev_bytes: the weight store
+  size_t shard_bytes = 0, shard_kv_bytes = 0;   // a shard's part of a layer: weights, caches
   bool dry = false;             // sizing pass: the memory plan is walked, no HIP call is made
   std::vector<LayerStore> store;  // [layer * n_real + shard]
   std::vector<char*> gain_attn, gain_mlp;  // per layer, T [H]
@@ -415,6 +416,34 @@ int gate_up_ksplit(const ladder_config& g, int rows) {
   return rows > 16 && rows <= FEW_ROWS ? gemm_ksplit(rows, 2 * g.inter, g.hidden, 4, SPLIT_KERNEL_US) : 1;
 }
 
+// one module of the plain path: three launches (attention) or two (MLP) for all computed shards, which leave a partial
+// sum each in out[shard][rows][hidden]
+int run_module_plain(ladder_ctx* c, int m, int B, int T, int pos0, float* out, hipStream_t s) {
+  const ladder_config& g = c->cfg;
+  const int rows = B * T, H = g.hidden, d = g.head_dim, nqd = g.n_q_heads * d, nkd = g.n_kv_heads * d, I = g.inter;
+  const LayerStore& L = c->store[(size_t)((m - 1) / 2) * g.n_real_shards];   // shard 0; the others lie at fixed strides behind it
+  PlainGemmArgs a{};
+  a.x = c->y[m & 1]; a.M = rows; a.K = H; a.n_shards = g.n_real_shards; a.w_stride = c->shard_bytes;
+  PlainGemmArgs last{};
+  last.M = rows; last.n_shards = g.n_real_shards; last.w_stride = c->shard_bytes; last.n_mat = 1; last.N[0] = H;
+  last.epilogue = PLAIN_OUT; last.out = out; last.out_stride = (size_t)rows * H;
+  if (m & 1) {
+    a.n_mat = 3; a.w[0] = L.wq; a.w[1] = L.wk; a.w[2] = L.wv; a.N[0] = nqd; a.N[1] = a.N[2] = nkd; a.epilogue = PLAIN_QKV;
+    a.q_out = c->qbuf; a.q_stride = (size_t)rows * nqd; a.cache_k = L.cache_k; a.cache_v = L.cache_v; a.cache_stride = c->shard_kv_bytes;
+    a.cos_tab = c->cos_tab; a.sin_tab = c->sin_tab; a.T = T; a.pos0 = pos0; a.nkv = g.n_kv_heads; a.d = d; a.max_seq = c->s_cap;
+    HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_plain_gemm(a, c->bf16, s); }));
+    AttnGenericArgs aa{c->qbuf, L.cache_k, L.cache_v, c->obuf, B, T, pos0, g.n_q_heads, g.n_kv_heads, d, c->s_cap, g.n_real_shards, (size_t)rows * nqd, c->shard_kv_bytes};
+    HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_attn_generic(aa, c->bf16, s); }));
+    last.x = c->obuf; last.x_stride = (size_t)rows * nqd; last.K = nqd; last.w[0] = L.wo;
+  } else {
+    a.n_mat = 2; a.w[0] = L.wg; a.w[1] = L.wu; a.N[0] = a.N[1] = I; a.epilogue = PLAIN_SWIGLU; a.act = c->act; a.act_stride = (size_t)rows * I;
+    HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_plain_gemm(a, c->bf16, s); }));
+    last.x = c->act; last.x_stride = (size_t)rows * I; last.K = I; last.w[0] = L.wd;
+  }
+  HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_plain_gemm(last, c->bf16, s); }));
+  return LADDER_OK;
+}
+
 // ---------------------------------------------------------------------------------------------
 // one module's compute on the main stream; writes parts[m%2] and returns the number of slots written, or (fuse)
 // updates the residual itself and returns -1 slots: then no reduce follows
@@ -427,19 +456,18 @@ int run_module(ladder_ctx* c, int m, int B, int T, int pos0, hipStream_t s, int*
   const char* yin = c->y[par];
   float* pout = c->parts[par];
   const size_t pstride = (size_t)rows * H;
+  if (!c->fast) {
+    *n_slots = g.n_real_shards;
+    return run_module_plain(c, m, B, T, pos0, pout, s);
+  }
   const bool few = rows <= FEW_ROWS;
-  const bool dev_pos = c->fast && T == 1;  // decode kernels of the bf16 path read the position from device memory
+  const bool dev_pos = T == 1;  // decode kernels of the bf16 path read the position from device memory
   int slots = 0;
   for (int r = 0; r < g.n_real_shards; ++r) {
     LayerStore& L = c->store[(size_t)layer * g.n_real_shards + r];
     if (is_attn) {
       int qkv_slots = 1;
-      if (!c->fast) {
-        const int nqd = nq * d, nkd = nkv * d;
-        HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_gemm_generic(yin, L.wq, c->qkv, rows, nqd, H, c->nqkv, 0, c->bf16, s); }));
-        HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_gemm_generic(yin, L.wk, c->qkv, rows, nkd, H, c->nqkv, nqd, c->bf16, s); }));
-        HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_gemm_generic(yin, L.wv, c->qkv, rows, nkd, H, c->nqkv, nqd + nkd, c->bf16, s); }));
-      } else if (few && (dev_pos || rows <= 16 || gemm_ksplit(rows, c->nqkv, H, max_slots(g, rows), SPLIT_KERNEL_US) > 1)) {
+      if (few && (dev_pos || rows <= 16 || gemm_ksplit(rows, c->nqkv, H, max_slots(g, rows), SPLIT_KERNEL_US) > 1)) {
         const int rc = run_few_rows(c, yin, H, L.pqkv, rows, H, c->nqkv, c->qkv, s, &qkv_slots, c->y_scale[par]);
         if (rc) return rc;
       } else {
@@ -460,11 +488,8 @@ int run_module(ladder_ctx* c, int m, int B, int T, int pos0, hipStream_t s, int*
       ra.q_out = c->qbuf; ra.cache_k = L.cache_k; ra.cache_v = L.cache_v;
       ra.cos_tab = c->cos_tab; ra.sin_tab = c->sin_tab;
       ra.B = B; ra.T = T; ra.pos0 = pos0; ra.nq = nq; ra.nkv = nkv; ra.d = d; ra.max_seq = c->s_cap; ra.pos_dev = dev_pos ? c->pos_dev : nullptr;
-      if (qkv_slots > 0) HIP_TRY(c, timed(c, LADDER_K_ROPE_APPEND, s, [&] { return launch_rope_append(ra, c->bf16, s); }));
-      if (!c->fast) {
-        AttnGenericArgs aa{c->qbuf, L.cache_k, L.cache_v, c->obuf, B, T, pos0, nq, nkv, d, c->s_cap};
-        HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_attn_generic(aa, c->bf16, s); }));
-      } else if (T == 1) {
+      if (qkv_slots > 0) HIP_TRY(c, timed(c, LADDER_K_ROPE_APPEND, s, [&] { return launch_rope_append(ra, s); }));
+      if (T == 1) {
         AttnDecodeArgs aa{};
         aa.q = (const bf16_t*)c->qbuf; aa.cache_k = (const bf16_t*)L.cache_k; aa.cache_v = (const bf16_t*)L.cache_v;
         aa.part_o = c->att_o; aa.part_ml = c->att_ml; aa.o = (bf16_t*)c->obuf;
@@ -479,38 +504,25 @@ int run_module(ladder_ctx* c, int m, int B, int T, int pos0, hipStream_t s, int*
         HIP_TRY(c, timed(c, LADDER_K_ATTN_PREFILL, s, [&] { return launch_attn_prefill(aa, s); }));
       }
       const int nqd = nq * d;
-      if (!c->fast) {
-        HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_gemm_generic(c->obuf, L.wo, pout + slots * pstride, rows, H, nqd, H, 0, c->bf16, s); }));
-        slots += 1;
-      } else {
-        const int rc = run_last_projection(c, m, c->obuf, L.po, rows, nqd, pout + slots * pstride, fuse, x_copy, s, &slots);
-        if (rc) return rc;
-      }
+      const int rc = run_last_projection(c, m, c->obuf, L.po, rows, nqd, pout + slots * pstride, fuse, x_copy, s, &slots);
+      if (rc) return rc;
     } else {
-      if (!c->fast) {
-        HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_gemm_generic(yin, L.wg, c->gu, rows, I, H, 2 * I, 0, c->bf16, s); }));
-        HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_gemm_generic(yin, L.wu, c->gu, rows, I, H, 2 * I, I, c->bf16, s); }));
-        HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_swiglu(c->gu, c->act, rows, I, c->bf16, s); }));
-        HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_gemm_generic(c->act, L.wd, pout + slots * pstride, rows, H, I, H, 0, c->bf16, s); }));
-        slots += 1;
+      if (rows <= 16) {
+        GemvArgs a{};
+        a.x = (const bf16_t*)yin; a.ldx = H; a.wp = L.pgu; a.M = rows; a.K = H; a.N = 2 * I; a.ksplit = 1;
+        a.act = (bf16_t*)c->act; a.epilogue = 1;
+        HIP_TRY(c, timed(c, LADDER_K_GEMV, s, [&] { return launch_gemv(a, s); }));
       } else {
-        if (rows <= 16) {
-          GemvArgs a{};
-          a.x = (const bf16_t*)yin; a.ldx = H; a.wp = L.pgu; a.M = rows; a.K = H; a.N = 2 * I; a.ksplit = 1;
-          a.act = (bf16_t*)c->act; a.epilogue = 1;
-          HIP_TRY(c, timed(c, LADDER_K_GEMV, s, [&] { return launch_gemv(a, s); }));
-        } else {
-          GemmArgs a{};
-          a.x = (const bf16_t*)yin; a.ldx = H; a.wp = L.pgu; a.M = rows; a.K = H; a.N = 2 * I; a.row_scale = c->y_scale[par];
-          const int gu_slots = gate_up_ksplit(g, rows);
-          if (gu_slots > 1) { a.out = c->gu; a.epilogue = 0; a.ksplit = gu_slots; a.out_stride = (size_t)rows * 2 * I; }
-          else { a.act = (bf16_t*)c->act; a.epilogue = 1; }
-          HIP_TRY(c, timed(c, LADDER_K_GEMM, s, [&] { return launch_gemm_mfma(a, s); }));
-          if (gu_slots > 1) HIP_TRY(c, timed(c, LADDER_K_OTHER, s, [&] { return launch_swiglu_parts(c->gu, gu_slots, (size_t)rows * 2 * I, (bf16_t*)c->act, rows, I, s); }));
-        }
-        const int rc = run_last_projection(c, m, c->act, L.pd, rows, I, pout + slots * pstride, fuse, x_copy, s, &slots);
-        if (rc) return rc;
+        GemmArgs a{};
+        a.x = (const bf16_t*)yin; a.ldx = H; a.wp = L.pgu; a.M = rows; a.K = H; a.N = 2 * I; a.row_scale = c->y_scale[par];
+        const int gu_slots = gate_up_ksplit(g, rows);
+        if (gu_slots > 1) { a.out = c->gu; a.epilogue = 0; a.ksplit = gu_slots; a.out_stride = (size_t)rows * 2 * I; }
+        else { a.act = (bf16_t*)c->act; a.epilogue = 1; }
+        HIP_TRY(c, timed(c, LADDER_K_GEMM, s, [&] { return launch_gemm_mfma(a, s); }));
+        if (gu_slots > 1) HIP_TRY(c, timed(c, LADDER_K_OTHER, s, [&] { return launch_swiglu_parts(c->gu, gu_slots, (size_t)rows * 2 * I, (bf16_t*)c->act, rows, I, s); }));
       }
+      const int rc = run_last_projection(c, m, c->act, L.pd, rows, I, pout + slots * pstride, fuse, x_copy, s, &slots);
+      if (rc) return rc;
     }
   }
   *n_slots = fuse ? -1 : slots;
@@ -637,7 +649,11 @@ int forward_body(ladder_ctx* c, const void* x_in, int B, int T, int pos0, void* 
   // chip, and the same work measured 4 % (reduce on the side stream) to 16 % (two module streams) slower
   // when spread over streams
   // (and so does a pipeline stage's call: its hand-over reads the stream between the last modules)
-  const bool small = rows <= 64 && !st;
+  // (and so do calls whose kernels are shorter than the events between two streams: a layer of the plain path under
+  // 32 MB of weights.  Measured, prompt of 32 and 8 steps, overlapped / in order, us: tiny model (2.8 MB) 1078 / 556, 10 MB
+  // 970 / 725, 41 MB 1246 / 1077 and at batch 4 1498 / 1688, 100 MB 1288 / 1534, 200 MB 2221 / 2732)
+  const bool brief = !c->fast && c->shard_bytes * (size_t)c->cfg.n_real_shards < (32u << 20);
+  const bool small = rows <= 64 && !st && !brief;
   const bool overlap = small && c->cfg.overlap_modules != 0;
   const bool side = small && !overlap && c->cfg.reduce_on_side_stream != 0;
   auto module_stream = [&](int m) { return (overlap && (m & 1) == 0) ? c->s_mlp : s0; };
@@ -1476,6 +1492,7 @@ static int init_impl(const ladder_config* cfg, void* hip_stream, ladder_ctx** ou
     per_shard = ((size_t)H * c->nqkv + (size_t)nq * d * H + 3 * (size_t)H * I) * esz;
     per_shard = (per_shard + 255) / 256 * 256;
   }
+  c->shard_bytes = per_shard;
   char* wbase = nullptr;
   INIT_TRY(dev_alloc(c, (void**)&wbase, per_shard * c->store.size(), false));
   c->weight_bytes = c->dev_bytes;
@@ -1484,6 +1501,7 @@ static int init_impl(const ladder_config* cfg, void* hip_stream, ladder_ctx** ou
   // KV cache: K rows [B][nkv][s_cap][d]; V transposed [B][nkv][d][s_cap]; zero-filled so that no
   // kernel ever reads an uninitialised bit pattern
   const size_t kv_one = (size_t)g.max_batch * nkv * c->s_cap * d * esz;
+  c->shard_kv_bytes = kv_one * 2;
   char* kvbase = nullptr;
   INIT_TRY(dev_alloc(c, (void**)&kvbase, kv_one * 2 * c->store.size(), true));
   for (size_t i = 0; i < c->store.size(); ++i) {
@@ -1544,12 +1562,13 @@ static int init_impl(const ladder_config* cfg, void* hip_stream, ladder_ctx** ou
   c->parts_cap = (size_t)g.n_real_shards * H * row_slots;
   for (int i = 0; i < 2; ++i) INIT_TRY(dev_alloc(c, (void**)&c->parts[i], c->parts_cap * 4, false));
   c->qkv_cap = (size_t)c->nqkv * row_slots;
-  INIT_TRY(dev_alloc(c, (void**)&c->qkv, c->qkv_cap * 4, false));
-  INIT_TRY(dev_alloc(c, (void**)&c->qbuf, rows * nq * d * esz, false));
-  INIT_TRY(dev_alloc(c, (void**)&c->obuf, rows * nq * d * esz, false));
-  INIT_TRY(dev_alloc(c, (void**)&c->act, rows * I * esz, false));
-  // the SwiGLU inputs in fp32: the plain path keeps the whole product, the packed path the slots of a split projection
-  size_t gu_rows = c->fast ? 0 : rows;
+  if (c->fast) INIT_TRY(dev_alloc(c, (void**)&c->qkv, c->qkv_cap * 4, false));
+  const size_t shards = c->fast ? 1 : (size_t)g.n_real_shards;   // (the plain path takes all computed shards in one launch)
+  INIT_TRY(dev_alloc(c, (void**)&c->qbuf, shards * rows * nq * d * esz, false));
+  INIT_TRY(dev_alloc(c, (void**)&c->obuf, shards * rows * nq * d * esz, false));
+  INIT_TRY(dev_alloc(c, (void**)&c->act, shards * rows * I * esz, false));
+  // the slots of a split gate/up projection
+  size_t gu_rows = 0;
   for (int r = 17; c->fast && r <= FEW_ROWS && (size_t)r <= rows; ++r) {
     const int n = gate_up_ksplit(g, r);
     if (n > 1) gu_rows = std::max(gu_rows, (size_t)n * r);
@@ -1948,7 +1967,9 @@ static int head_body(ladder_ctx* c, const float* x, int rows, char* y, float* lo
   hipStream_t s = c->main;
   HIP_TRY(c, launch_head_norm(x, c->head_gain, y, rows, H, g.rms_eps, c->bf16, s));
   if (!c->head_fast) {
-    HIP_TRY(c, launch_gemm_generic(y, c->head_w, logits, rows, V, H, V, 0, c->bf16, s));
+    PlainGemmArgs a{};
+    a.x = y; a.M = rows; a.K = H; a.n_shards = 1; a.n_mat = 1; a.w[0] = c->head_w; a.N[0] = V; a.epilogue = PLAIN_OUT; a.out = logits;
+    HIP_TRY(c, launch_plain_gemm(a, c->bf16, s));
   } else if (rows <= 16 || (V & 31)) {
     GemvArgs a{};
     a.x = (const bf16_t*)y; a.ldx = H; a.wp = c->head_wp; a.M = rows; a.K = H; a.N = V; a.ksplit = 1;
