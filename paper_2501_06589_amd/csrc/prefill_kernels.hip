@@ -98,8 +98,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x4_t (&acc)[
             const float g4[4] = {__uint_as_float(gk.x << 16), __uint_as_float(gk.x & 0xFFFF0000u),
                                  __uint_as_float(gk.y << 16), __uint_as_float(gk.y & 0xFFFF0000u)};
             uint2 pk;
-            pk.x = (uint32_t)f32_to_bf16(v4[0] * g4[0]) | ((uint32_t)f32_to_bf16(v4[1] * g4[1]) << 16);
-            pk.y = (uint32_t)f32_to_bf16(v4[2] * g4[2]) | ((uint32_t)f32_to_bf16(v4[3] * g4[3]) << 16);
+            pk.x = f32_to_bf16x2(v4[0] * g4[0], v4[1] * g4[1]);
+            pk.y = f32_to_bf16x2(v4[2] * g4[2], v4[3] * g4[3]);
             *reinterpret_cast<uint2*>(dst + off) = pk;
           };
           if (a.xh_a) store_gained(a.xh_a, a.gain_a);
@@ -140,8 +140,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x4_t (&acc)[
         }
         if (head < a.nq + a.nkv) {
           uint2 pk;
-          pk.x = (uint32_t)f32_to_bf16(v4[0]) | ((uint32_t)f32_to_bf16(v4[1]) << 16);
-          pk.y = (uint32_t)f32_to_bf16(v4[2]) | ((uint32_t)f32_to_bf16(v4[3]) << 16);
+          pk.x = f32_to_bf16x2(v4[0], v4[1]);
+          pk.y = f32_to_bf16x2(v4[2], v4[3]);
           bf16_t* dst = head < a.nq ? a.q_out + (size_t)m * a.nq * a.d + head * a.d + dim
                                     : a.cache_k + (((size_t)seq * a.nkv + (head - a.nq)) * a.max_seq + pos) * a.d + dim;
           *reinterpret_cast<uint2*>(dst) = pk;
@@ -171,8 +171,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x4_t (&acc)[
         }
         if (q < 2 && m < a.M && nt0 + j < NT) {
           uint2 pk;
-          pk.x = (uint32_t)f32_to_bf16(r4[0]) | ((uint32_t)f32_to_bf16(r4[1]) << 16);
-          pk.y = (uint32_t)f32_to_bf16(r4[2]) | ((uint32_t)f32_to_bf16(r4[3]) << 16);
+          pk.x = f32_to_bf16x2(r4[0], r4[1]);
+          pk.y = f32_to_bf16x2(r4[2], r4[3]);
           *reinterpret_cast<uint2*>(a.act + (size_t)m * I + (nt0 + j) * 8 + 4 * q) = pk;
         }
       }
@@ -348,10 +348,10 @@ __device__ __forceinline__ void gemm2_residual_epilogue(const GemmArgs& a, f32x4
           // the rows as the modules that read them want them: times their norm's gain (fp32 product, one rounding)
           auto store_gained = [&](bf16_t* dst, const float (&g8)[8]) {
             uint4 u;
-            u.x = (uint32_t)f32_to_bf16(v8[0] * g8[0]) | ((uint32_t)f32_to_bf16(v8[1] * g8[1]) << 16);
-            u.y = (uint32_t)f32_to_bf16(v8[2] * g8[2]) | ((uint32_t)f32_to_bf16(v8[3] * g8[3]) << 16);
-            u.z = (uint32_t)f32_to_bf16(v8[4] * g8[4]) | ((uint32_t)f32_to_bf16(v8[5] * g8[5]) << 16);
-            u.w = (uint32_t)f32_to_bf16(v8[6] * g8[6]) | ((uint32_t)f32_to_bf16(v8[7] * g8[7]) << 16);
+            u.x = f32_to_bf16x2(v8[0] * g8[0], v8[1] * g8[1]);
+            u.y = f32_to_bf16x2(v8[2] * g8[2], v8[3] * g8[3]);
+            u.z = f32_to_bf16x2(v8[4] * g8[4], v8[5] * g8[5]);
+            u.w = f32_to_bf16x2(v8[6] * g8[6], v8[7] * g8[7]);
             *reinterpret_cast<uint4*>(dst + off[r]) = u;
           };
           if (a.xh_a) store_gained(a.xh_a, ga8);
@@ -899,10 +899,10 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(AttnPrefillArgs a) {
       lrun[qt] = lrun[qt] * corr + psum;
       mrun[qt] = mnew;
       uint4 pb;
-      pb.x = (uint32_t)f32_to_bf16(pv[0]) | ((uint32_t)f32_to_bf16(pv[1]) << 16);
-      pb.y = (uint32_t)f32_to_bf16(pv[2]) | ((uint32_t)f32_to_bf16(pv[3]) << 16);
-      pb.z = (uint32_t)f32_to_bf16(pv[4]) | ((uint32_t)f32_to_bf16(pv[5]) << 16);
-      pb.w = (uint32_t)f32_to_bf16(pv[6]) | ((uint32_t)f32_to_bf16(pv[7]) << 16);
+      pb.x = f32_to_bf16x2(pv[0], pv[1]);
+      pb.y = f32_to_bf16x2(pv[2], pv[3]);
+      pb.z = f32_to_bf16x2(pv[4], pv[5]);
+      pb.w = f32_to_bf16x2(pv[6], pv[7]);
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) {
 #pragma unroll
@@ -923,24 +923,40 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(AttnPrefillArgs a) {
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) {
         uint2 pk;
-        pk.x = (uint32_t)f32_to_bf16(oacc[qt][dt][0] * inv) | ((uint32_t)f32_to_bf16(oacc[qt][dt][1] * inv) << 16);
-        pk.y = (uint32_t)f32_to_bf16(oacc[qt][dt][2] * inv) | ((uint32_t)f32_to_bf16(oacc[qt][dt][3] * inv) << 16);
+        pk.x = f32_to_bf16x2(oacc[qt][dt][0] * inv, oacc[qt][dt][1] * inv);
+        pk.y = f32_to_bf16x2(oacc[qt][dt][2] * inv, oacc[qt][dt][3] * inv);
         *reinterpret_cast<uint2*>(op + dt * 16 + 4 * q) = pk;
       }
     }
   }
 }
 
+// the largest of the four lanes that hold one query, 16, 32 and 48 lanes apart, by exchanging rows of 16 and halves
+__device__ __forceinline__ float max_over_rows(float v) {
+  typedef __attribute__((__vector_size__(2 * sizeof(unsigned)))) unsigned u32x2_t;
+  u32x2_t r = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false));
+  v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  r = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false));
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
 // ------------------------------------------------------------------------------------------------
 // The same computation with the K / V^T tiles of a 32-key block staged once per workgroup in LDS
 // (double buffered) and shared by its 4 wavefronts, each of which owns QT tiles of 16 queries of
 // one q head.  With grouped-query attention the wavefronts of a workgroup are HW = min(G, 4) q heads
-// of ONE kv head over the same query block, so they walk exactly the same keys.  Per block a
-// wavefront issues 64 matrix instructions against 16 KiB of LDS reads; the running-max rescale of the
-// output accumulators (the largest vector cost) is skipped for a tile whenever no lane's maximum moved.
+// of ONE kv head over the same query block, so they walk exactly the same keys.
+// What bounds it is the vector work of the softmax between the matrix instructions (a tile of 16 queries x 32 keys is 16
+// of those and eight probabilities per lane), so that is kept short: scores stay unscaled and scale and base-2 exponent
+// are one fused multiply-add; keys are masked only in the blocks that cross the diagonal; the maximum travels by row swaps
+// instead of through LDS; and the output is rescaled only where a maximum of the tile has grown.  (Letting it grow by 2^6
+// before rescaling would save another 0.5 % of a call, but the largest weight of a query is then no longer exactly 1 and its
+// bf16 rounding shows: attention output behind 4001 positions 1.297e-2 -> 1.312e-2 of its norm.)  The K rows are staged in the order that leaves a
+// lane eight neighbouring keys (row 16 t + i holds key 8 (i / 4) + 4 t + i % 4), so its share of V^T is one 16-byte read.
+// us per layer (before -> after): 16 x 2048 tokens, 16 q / 2 kv heads 556 -> 424 (650 TFLOP/s); 1 x 2048, 32 / 8 heads 156 -> 106;
+// 1 x 4001, 8 / 1 heads 202 -> 116; 1 x 100, 32 / 8 heads 12.8 -> 6.0 (direct kernel before).
 // ------------------------------------------------------------------------------------------------
 template <int D, int HW, int QT>
-__global__ __launch_bounds__(256, QT <= 3 ? 2 : 1) void attn_prefill_lds_kernel(AttnPrefillArgs a) {
+__global__ __launch_bounds__(256, 2) void attn_prefill_lds_kernel(AttnPrefillArgs a) {
   constexpr int DS = D / 32, DT = D / 16;
   constexpr int QW = 4 / HW;                 // query sub-blocks (of QT * 16) per workgroup
   constexpr int KROW = D * 2 + 16;           // bytes per staged K row (key): 16-byte pad, conflict-free b128 reads
@@ -955,8 +971,7 @@ __global__ __launch_bounds__(256, QT <= 3 ? 2 : 1) void attn_prefill_lds_kernel(
   const int h = blockIdx.y * HW + wave % HW, bi = blockIdx.z;
   const int kvh = h / (a.nq / a.nkv);
   const int t0 = (qblk * QW + wave / HW) * (QT * 16);       // this wavefront's first query
-  const float scale = 1.0f / sqrtf((float)D);
-  const uint4 zero4 = make_uint4(0, 0, 0, 0);
+  const float scale2 = 1.4426950408889634f / sqrtf((float)D);   // scores to exponents of 2
 
   uint4 qreg[QT][DS];
 #pragma unroll
@@ -998,7 +1013,8 @@ __global__ __launch_bounds__(256, QT <= 3 ? 2 : 1) void attn_prefill_lds_kernel(
 #pragma unroll
     for (int i = 0; i < SEGS; ++i) {
       const int seg = tid + 256 * i;
-      const int krow = seg / (D / 8), kcx = seg % (D / 8);
+      const int key = seg / (D / 8), kcx = seg % (D / 8);
+      const int krow = 16 * ((key >> 2) & 1) + 4 * (key >> 3) + (key & 3);
       *reinterpret_cast<u32x4_t*>(&lds[buf][krow * KROW + kcx * 16]) = kst[i];
       const int vrow = seg >> 2, vcx = seg & 3;
       *reinterpret_cast<u32x4_t*>(&lds[buf][KBYTES + vrow * VROW + vcx * 16]) = vst[i];
@@ -1029,48 +1045,40 @@ __global__ __launch_bounds__(256, QT <= 3 ? 2 : 1) void attn_prefill_lds_kernel(
       uint4 pb[QT];
 #pragma unroll
       for (int qt = 0; qt < QT; ++qt) {
-        const int qpos = a.pos0 + t0 + qt * 16 + b;
-        float sv[8];
-        float mloc = -INFINITY;
+        // st[t][r] is the score of this lane's query with key kb + 8 q + 4 t + r
+        if (kb + 31 > a.pos0 + t0 + qt * 16) {   // (uniform) the block crosses the diagonal of the tile
+          const int visible = a.pos0 + t0 + qt * 16 + b - kb - 8 * q;   // the lane's keys 0 .. visible are
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+          for (int t = 0; t < 2; ++t)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int key = kb + 16 * t + 4 * q + r;
-            const float v = key <= qpos ? st[qt][t][r] * scale : -INFINITY;
-            sv[t * 4 + r] = v;
-            mloc = fmaxf(mloc, v);
-          }
-        mloc = fmaxf(mloc, __shfl_xor(mloc, 16, 64));
-        mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64));
-        const float mnew = fmaxf(mrun[qt], mloc);   // finite from the first block on (key 0 is always visible)
-        const float corr = __expf(mrun[qt] - mnew);  // exactly 1 when the maximum did not move
-        float psum = 0.f;
-        float pv[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          pv[e] = __expf(sv[e] - mnew);
-          psum += pv[e];
+            for (int r = 0; r < 4; ++r) st[qt][t][r] = 4 * t + r <= visible ? st[qt][t][r] : -INFINITY;
         }
-        lrun[qt] = lrun[qt] * corr + psum;
-        mrun[qt] = mnew;
-        pb[qt].x = (uint32_t)f32_to_bf16(pv[0]) | ((uint32_t)f32_to_bf16(pv[1]) << 16);
-        pb[qt].y = (uint32_t)f32_to_bf16(pv[2]) | ((uint32_t)f32_to_bf16(pv[3]) << 16);
-        pb[qt].z = (uint32_t)f32_to_bf16(pv[4]) | ((uint32_t)f32_to_bf16(pv[5]) << 16);
-        pb[qt].w = (uint32_t)f32_to_bf16(pv[6]) | ((uint32_t)f32_to_bf16(pv[7]) << 16);
-        if (__any(corr != 1.0f)) {   // wave-uniform: some query of the tile has a new maximum
+        float mloc = fmaxf(fmaxf(fmaxf(st[qt][0][0], st[qt][0][1]), fmaxf(st[qt][0][2], st[qt][0][3])),
+                           fmaxf(fmaxf(st[qt][1][0], st[qt][1][1]), fmaxf(st[qt][1][2], st[qt][1][3])));
+        mloc = max_over_rows(mloc);   // (finite in the first block: key 0 is always visible)
+        if (__any(mloc > mrun[qt])) {   // uniform; the first block always
+          const float mnew = fmaxf(mrun[qt], mloc);
+          const float corr = __builtin_amdgcn_exp2f((mrun[qt] - mnew) * scale2);
+          lrun[qt] *= corr;
+          mrun[qt] = mnew;
 #pragma unroll
           for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
             for (int r = 0; r < 4; ++r) oacc[qt][dt][r] *= corr;
         }
+        const float base = -mrun[qt] * scale2;
+        float pv[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) pv[e] = __builtin_amdgcn_exp2f(fmaf(st[qt][e >> 2][e & 3], scale2, base));
+        lrun[qt] += ((pv[0] + pv[1]) + (pv[2] + pv[3])) + ((pv[4] + pv[5]) + (pv[6] + pv[7]));
+        pb[qt].x = f32_to_bf16x2(pv[0], pv[1]);
+        pb[qt].y = f32_to_bf16x2(pv[2], pv[3]);
+        pb[qt].z = f32_to_bf16x2(pv[4], pv[5]);
+        pb[qt].w = f32_to_bf16x2(pv[6], pv[7]);
       }
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) {
-        const unsigned char* vp = vl + (dt * 16 + b) * VROW + q * 8;
-        const uint2 lo = *reinterpret_cast<const uint2*>(vp);
-        const uint2 hi = *reinterpret_cast<const uint2*>(vp + 32);
-        const uint4 vf = make_uint4(lo.x, lo.y, hi.x, hi.y);
+        const uint4 vf = *reinterpret_cast<const uint4*>(vl + (dt * 16 + b) * VROW + q * 16);
 #pragma unroll
         for (int qt = 0; qt < QT; ++qt) oacc[qt][dt] = mfma16(vf, pb[qt], oacc[qt][dt]);
       }
@@ -1091,22 +1099,23 @@ __global__ __launch_bounds__(256, QT <= 3 ? 2 : 1) void attn_prefill_lds_kernel(
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) {
         uint2 pk;
-        pk.x = (uint32_t)f32_to_bf16(oacc[qt][dt][0] * inv) | ((uint32_t)f32_to_bf16(oacc[qt][dt][1] * inv) << 16);
-        pk.y = (uint32_t)f32_to_bf16(oacc[qt][dt][2] * inv) | ((uint32_t)f32_to_bf16(oacc[qt][dt][3] * inv) << 16);
+        pk.x = f32_to_bf16x2(oacc[qt][dt][0] * inv, oacc[qt][dt][1] * inv);
+        pk.y = f32_to_bf16x2(oacc[qt][dt][2] * inv, oacc[qt][dt][3] * inv);
         *reinterpret_cast<uint2*>(op + dt * 16 + 4 * q) = pk;
       }
     }
   }
 }
 
-#define ATTN_LDS_QT 3   // 16-query tiles per wavefront.  Measured on 16 x 2048 tokens, 16 q / 2 kv heads, d = 128:
-                        // 2 tiles 0.80 ms, 3 tiles 0.55 ms, 4 tiles 1.45 ms per layer (4 leaves one wavefront
-                        // per SIMD, which cannot hide the global -> LDS latency; 2 doubles the LDS reads per flop)
-template <int D>
+// 16-query tiles per wavefront: the fewest whose workgroups still fit the chip together (two per CU), because a call is
+// then as long as its longest workgroup; where even three tiles make more workgroups, three (the K / V^T reads from LDS
+// are shared by more queries; four leave one wavefront per SIMD and took 1.45 instead of 0.55 ms on 16 x 2048 tokens).
+// Whole layer, us, with 1 / 2 / 3: 70B R = 8 shard, 1 x 1000 374 / 388 / 395, 2 layers 1 x 4001 3223 / 3277 / 3315; 8B 2 layers
+// 1 x 2048 1845 / 1830 / 1862, 1 layer 1 x 4000 1740 / 1728 / 1720, 2 x 8000 7612 / 7245 / 7295.
+template <int D, int QT>
 static hipError_t launch_attn_prefill_lds(const AttnPrefillArgs& a, hipStream_t s) {
   const int g = a.nq / a.nkv;
   const int hw = g >= 4 && g % 4 == 0 ? 4 : (g % 2 == 0 ? 2 : 1);
-  constexpr int QT = ATTN_LDS_QT;
   const int qrows = (4 / hw) * QT * 16;
   const dim3 grid((a.T + qrows - 1) / qrows, a.nq / hw, a.B), block(256);
   if (hw == 4) hipLaunchKernelGGL((attn_prefill_lds_kernel<D, 4, QT>), grid, block, 0, s, a);
@@ -1115,10 +1124,20 @@ static hipError_t launch_attn_prefill_lds(const AttnPrefillArgs& a, hipStream_t 
   return hipGetLastError();
 }
 
+template <int D>
+static hipError_t launch_attn_prefill_lds(const AttnPrefillArgs& a, hipStream_t s) {
+  const int g = a.nq / a.nkv;
+  const int hw = g >= 4 && g % 4 == 0 ? 4 : (g % 2 == 0 ? 2 : 1);
+  int qt = 1;
+  while (qt < 3 && (long)((a.T + (4 / hw) * qt * 16 - 1) / ((4 / hw) * qt * 16)) * (a.nq / hw) * a.B > 512) ++qt;
+  return qt == 1 ? launch_attn_prefill_lds<D, 1>(a, s) : qt == 2 ? launch_attn_prefill_lds<D, 2>(a, s) : launch_attn_prefill_lds<D, 3>(a, s);
+}
+
 hipError_t launch_attn_prefill(const AttnPrefillArgs& a, hipStream_t s) {
-  // long prompts: the LDS-shared kernel (its reads run to the end of the last 32-key block, which the
-  // cache capacity, a multiple of 128, always covers); short ones keep more workgroups with the direct one
-  if (a.T >= 256 && (a.max_seq & 31) == 0) {
+  // the LDS-shared kernel (its reads run to the end of the last 32-key block, which the cache capacity, a multiple of 128,
+  // always covers); the direct one where a prompt is two key blocks at most and the staging costs more than it saves
+  // (8B shape, one layer, us, direct / shared: 60 tokens 123 / 129, 8 x 60 268 / 270, 100 132 / 125, 200 191 / 181)
+  if (a.T > 64 && (a.max_seq & 31) == 0) {
     if (a.d == 128) return launch_attn_prefill_lds<128>(a, s);
     if (a.d == 64) return launch_attn_prefill_lds<64>(a, s);
     return hipErrorInvalidValue;
