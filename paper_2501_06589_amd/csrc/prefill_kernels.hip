@@ -262,7 +262,8 @@ __device__ __forceinline__ void gemm2_wait_and_meet() {
 #define GEMM2_WSTAGES 4
 #define GEMM2_LDS_BYTES (GEMM2_XBLOCKS * GEMM2_XBLOCK_BYTES + GEMM2_WSTAGES * GEMM2_WSTAGE_BYTES)
 
-// Epilogue 3 of the 256 x 256 tile (see GemmArgs), with whole rows per memory instruction.  In the accumulator
+// Epilogue 3 of a tile of 32 MT rows x 256 columns whose wavefronts lie 2 x 4 (see GemmArgs), with whole rows per memory
+// instruction.  In the accumulator
 // layout a wavefront's load or store touches 16 rows, 64 (fp32) or 32 (bf16) bytes of each; this epilogue
 // moves 16 bytes per element through memory (the old row, three peers, the new row twice), and in that shape it
 // cost as much as the separate reduce kernel it replaces.  So the tile passes through LDS (free once the
@@ -272,7 +273,8 @@ __device__ __forceinline__ void gemm2_wait_and_meet() {
 // block: ssq_part[n_blk][m].  The summation order per element is fixed: old value, product, peers 0, 1, ...
 #define GEMM2_EPI_STRIDE 260   // floats per staged row: 256 + 4, so that the 16 rows of a write spread over the banks
 static_assert(64 * GEMM2_EPI_STRIDE * 4 <= GEMM2_LDS_BYTES, "staging area");
-__device__ __forceinline__ void gemm2_residual_epilogue(const GemmArgs& a, f32x4_t (&acc)[4][8], unsigned char* lds, int m0,
+template <int MT>
+__device__ __forceinline__ void gemm2_residual_epilogue(const GemmArgs& a, f32x4_t (&acc)[4][MT], unsigned char* lds, int m0,
                                                         int n_blk, int wave, int lane) {
   float* stage = reinterpret_cast<float*>(lds);
   const int b = lane & 15, q = lane >> 4;
@@ -291,7 +293,7 @@ __device__ __forceinline__ void gemm2_residual_epilogue(const GemmArgs& a, f32x4
     unpack8(zb, gb8);
   }
 #pragma unroll
-  for (int pass = 0; pass < 4; ++pass) {     // row blocks mt = 2 pass, 2 pass + 1 of both halves of the tile
+  for (int pass = 0; pass < MT / 2; ++pass) {   // row blocks mt = 2 pass, 2 pass + 1 of both halves of the tile
     if (pass > 0) __syncthreads();           // the previous pass has been read
 #pragma unroll
     for (int h = 0; h < 2; ++h)
@@ -310,7 +312,7 @@ __device__ __forceinline__ void gemm2_residual_epilogue(const GemmArgs& a, f32x4
 #pragma unroll
       for (int r = 0; r < RB; ++r) {
         const int lr = 2 * wave + 16 * (g * RB + r) + half;              // staged row: half lr / 32, row lr % 32 of the pass
-        mrow[r] = m0 + (lr >> 5) * 128 + pass * 32 + (lr & 31);
+        mrow[r] = m0 + (lr >> 5) * (MT * 16) + pass * 32 + (lr & 31);
         ok[r] = col_ok && mrow[r] < a.M;
         off[r] = (size_t)min(mrow[r], a.M - 1) * a.N + nc;
         xo[r][0] = *reinterpret_cast<const float4*>(a.x_res + off[r]);
@@ -523,7 +525,7 @@ __global__ __launch_bounds__(512, 2) void gemm_lds_kernel(GemmArgs a) {
   }
   // the clamped loads past the last k tile are still in flight into LDS: they must land before the workgroup ends
   gemm2_wait_and_meet<0>();
-  if (a.epilogue == 3) gemm2_residual_epilogue(a, acc, g2_lds, m0, n_blk, wave, lane);
+  if (a.epilogue == 3) gemm2_residual_epilogue<WM>(a, acc, g2_lds, m0, n_blk, wave, lane);
   else gemm_epilogue<WM, 4>(a, acc, m0 + wm * 128, nt0 + wn * 4, NT, lane);
 }
 
@@ -692,6 +694,13 @@ __global__ __launch_bounds__(WR * WC * 64) void gemm_ring_kernel(GemmArgs a) {
       if (both) multiply(f1);
     }
   }
+  if constexpr (BN == 256 && WR == 2) {   // (whole rows per memory instruction: 8B shape, 2 layers, 1100 rows 1265 -> 1251 us, 2048 1795 -> 1784)
+    if (a.epilogue == 3) {
+      ring_meet<0>();   // every wavefront is past its last read of the ring, whose memory stages the tile
+      gemm2_residual_epilogue<MT>(a, acc, ring_lds, m0, nt0 >> 4, wave, lane);
+      return;
+    }
+  }
   GemmArgs e = a;
   if (a.ksplit > 1) e.out = a.out + (size_t)ks * a.out_stride;
   gemm_epilogue<MT, JT>(e, acc, m0 + wr * (BM / WR), nt0 + wc * JT, NT, lane);
@@ -766,8 +775,8 @@ int gemm_ksplit(int M, int N, int K, int max_split, float extra_us) {
 }
 
 int gemm_ssq_parts(const GemmArgs& a) {
-  // columns per workgroup (gemm_lds_kernel) or per wavefront
-  static const int cols[TILE_COUNT] = {16, 32, 32, 32, 64, 256};
+  // columns per workgroup (256-column tiles) or per wavefront
+  static const int cols[TILE_COUNT] = {16, 32, 32, 32, 256, 256};
   const int c = cols[gemm_best_tile(a.M, a.N, a.K, a.epilogue, 1, nullptr)];
   return (a.N + c - 1) / c;
 }

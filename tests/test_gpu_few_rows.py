@@ -51,3 +51,11 @@ def test_wide_decode_attention(harness, nq, nkv, d, cached):
                    kv_preload=cached, decode_steps=3)
     res = harness.run_case(w, kv_preload=cached, decode_steps=3, max_tokens=1)
     assert max(res.errs) < TOL, res.errs
+
+
+def test_residual_epilogue_of_the_wide_ring_tile(harness):
+    """128 x 256 tiles with the residual update as epilogue, ragged in both directions, more peers than are requested at once;
+    the second layer reads the rows and the sums of squares that the epilogue left."""
+    w = WIDE.with_(name="wide_tile", n_layers=2, hidden=4128, prefill=1101, tp_degree=5, peer_pool=2)
+    res = harness.run_case(w, decode_steps=0, gen_device="cuda:0")
+    assert max(res.errs) < TOL * 2 ** 0.5, res.errs
