@@ -39,12 +39,13 @@ __device__ __forceinline__ float wave_max(float v) {
 // All return the hipError_t of the launch.
 // ---------------------------------------------------------------------------------------------
 
-// x (f32 [rows][H], in place) = (emb ? emb : x) + sum_{s<n_parts} parts[s] + sum_{j<n_peers} peers[j];
+// x (f32 [rows][H], in place) = (emb ? emb : x_src ? x_src : x) + sum_{s<n_parts} parts[s] + sum_{j<n_peers} peers[j];
 // then up to two normed copies out_a = rmsnorm(x) * gain_a, out_b likewise (T), and an optional
 // f32 copy x_out.  parts: f32, slot s at parts + s*part_stride; peers: T, peer j at peers + j*peer_stride.
 struct ReduceNormArgs {
   float* x;
   const void* emb;         // T [rows][H] or null
+  const float* x_src;      // f32 [rows][H] or null
   const float* parts;      // f32 or null
   int n_parts;
   size_t part_stride;      // elements

@@ -41,7 +41,7 @@ __global__ void reduce_norm_kernel(ReduceNormArgs a) {
   for (int i = threadIdx.x * 4; i < H; i += blockDim.x * 4) {
     float v[4], t[4];
     if (emb) load4<T>(emb + (size_t)row * H + i, v);
-    else load4<float>(xr + i, v);
+    else load4<float>(a.x_src ? a.x_src + (size_t)row * H + i : xr + i, v);
     for (int s = 0; s < a.n_parts; ++s) {
       load4<float>(a.parts + s * a.part_stride + (size_t)row * H + i, t);
       v[0] += t[0]; v[1] += t[1]; v[2] += t[2]; v[3] += t[3];

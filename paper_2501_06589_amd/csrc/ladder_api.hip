@@ -565,7 +565,7 @@ __global__ __launch_bounds__(256) void stage_out_kernel(const float4* x2, const 
                                                         float4* r, float4* a, float4* m, size_t n4) {
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (size_t)gridDim.x * 256) {
     const float4 v2 = x2[i], v1 = x1[i], v0 = x0[i];
-    r[i] = v2;
+    if (r != x2) r[i] = v2;   // (uniform; the stream may have been left there already)
     a[i] = make_float4(v1.x - v2.x, v1.y - v2.y, v1.z - v2.z, v1.w - v2.w);
     m[i] = make_float4(v0.x - v1.x, v0.y - v1.y, v0.z - v1.z, v0.w - v1.w);
   }
@@ -585,11 +585,11 @@ int launch_stage_out(ladder_ctx* c, const float* x2, const float* x1, const floa
 // stream; module 2 reads it); ladder wiring in both modules
 int run_stage_in(ladder_ctx* c, const StageIo& st, int rows, hipStream_t s) {
   const ladder_config& g = c->cfg;
-  HIP_TRY(c, hipMemcpyAsync(c->x, st.res, (size_t)rows * g.hidden * 4, hipMemcpyDeviceToDevice, s));
   for (int cm = 1; cm <= 2; ++cm) {
     ReduceNormArgs a{};
-    a.x = c->x; a.rows = rows; a.H = g.hidden; a.eps = g.rms_eps;
+    a.x = c->x; a.x_src = cm == 1 ? st.res : nullptr; a.rows = rows; a.H = g.hidden; a.eps = g.rms_eps;
     a.parts = cm == 1 ? st.att : st.mlp; a.n_parts = a.parts ? 1 : 0; a.part_stride = (size_t)rows * g.hidden;
+    if (cm == 2 && c->n_mod == 2) a.x_out = st.r_out;   // (a stage of one layer: x_0 is the stream it hands over)
     a.out_a = c->y[cm & 1];
     a.gain_a = cm == 1 ? (const void*)c->gain_attn[0] : (const void*)c->gain_mlp[0];
     c->y_scale[cm & 1] = nullptr;   // normed rows
@@ -663,7 +663,6 @@ int forward_body(ladder_ctx* c, const void* x_in, int B, int T, int pos0, void* 
   const bool fuse = c->fast && rows > FEW_ROWS && c->cfg.n_real_shards == 1 && c->cfg.reduce_delay_us == 0;
   int rc = st ? run_stage_in(c, *st, rows, s0) : run_reduce(c, 0, rows, 0, x_in, c->n_mod == 0 ? (float*)x_out : nullptr, s0);
   if (rc) return rc;
-  const size_t x_bytes = (size_t)rows * c->cfg.hidden * 4;
   if (overlap && c->n_mod >= 2) {  // fork: the MLP stream starts once x_0 and its normed copies exist
     HIP_TRY(c, hipEventRecord(c->ev_fork, s0));
     HIP_TRY(c, hipStreamWaitEvent(c->s_mlp, c->ev_fork, 0));
@@ -674,9 +673,11 @@ int forward_body(ladder_ctx* c, const void* x_in, int B, int T, int pos0, void* 
     const int src = m - lag_of(c, m);
     if (src >= 1 && reduce_stream(src) != sm) HIP_TRY(c, hipStreamWaitEvent(sm, c->ev_red[src & 1], 0));
     int n_slots = 0;
-    // (a stage's hand-over: the stream as it is before the last attention module's output joins it ...)
-    if (st && m == c->n_mod - 1) HIP_TRY(c, hipMemcpyAsync(st->r_out, c->x, x_bytes, hipMemcpyDeviceToDevice, s0));
-    rc = run_module(c, m, B, T, pos0, sm, &n_slots, fuse, m == c->n_mod ? (float*)x_out : nullptr);
+    // a copy of the stream x_m: the call's result, or of a stage's hand-over the stream before and after the last attention
+    // module's output joins it (the residual update writes the copy itself; the two outputs are the differences of
+    // consecutive streams)
+    float* copy = m == c->n_mod ? (float*)x_out : !st ? nullptr : m == c->n_mod - 2 ? st->r_out : m == c->n_mod - 1 ? st->a_out : nullptr;
+    rc = run_module(c, m, B, T, pos0, sm, &n_slots, fuse, copy);
     if (rc) return rc;
     if (n_slots >= 0) {   // (else the module has updated the residual itself: wide calls run on one stream)
       if (rs != sm) {
@@ -684,12 +685,10 @@ int forward_body(ladder_ctx* c, const void* x_in, int B, int T, int pos0, void* 
         HIP_TRY(c, hipStreamWaitEvent(rs, c->ev_mod[m & 1], 0));
       }
       if (m >= 2 && reduce_stream(m - 1) != rs) HIP_TRY(c, hipStreamWaitEvent(rs, c->ev_red[(m - 1) & 1], 0));
-      rc = run_reduce(c, m, rows, n_slots, nullptr, m == c->n_mod ? (float*)x_out : nullptr, rs);
+      rc = run_reduce(c, m, rows, n_slots, nullptr, copy, rs);
       if (rc) return rc;
       if (overlap || side) HIP_TRY(c, hipEventRecord(c->ev_red[m & 1], rs));
     }
-    // (... and after it has; the two outputs are the differences of consecutive streams)
-    if (st && m == c->n_mod - 1) HIP_TRY(c, hipMemcpyAsync(st->a_out, c->x, x_bytes, hipMemcpyDeviceToDevice, s0));
     if (st && m == c->n_mod) {
       rc = launch_stage_out(c, st->r_out, st->a_out, c->x, *st, rows, s0);
       if (rc) return rc;
