@@ -210,8 +210,10 @@ hipError_t launch_gemv(const GemvArgs& a, hipStream_t s) {
 // Decode attention.  Workgroup (split, kv head, sequence): the positions are cut into at most n_splits runs of a multiple
 // of 128, computed from the position itself, so that the grid stays the same while the sequence grows; the 4 wavefronts
 // take 32-key blocks of the run round robin, each with its own running softmax, and merge through LDS.  It is bound by
-// the one pass over the cache: a wavefront has the 16 KiB of its next block in flight while it computes one, eight
-// wavefronts per CU.  All on the matrix cores, transposed so that nothing is shuffled:
+// the one pass over the cache: a wavefront requests the 16 KiB of a block at once, and the wavefronts beside it compute
+// meanwhile (one register buffer, three wavefronts per SIMD; a second buffer for the next block left two and was slower:
+// 8B shape, batch 64, 1024 positions, whole case 3248 -> 2939 us, batch 40 2633 -> 2285, 70B R = 8 batch 64 2047 -> 1969; 1.2B
+// batch 32 1544 -> 1561).  All on the matrix cores, transposed so that nothing is shuffled:
 //   S^T[key][column] = K Q^T     A = 16 keys x 32 dims, straight from the K rows (row i of tile t is key 8 (i / 4) + 4 t +
 //                                i % 4 of the block, so that a lane ends up with eight neighbouring keys and its share of
 //                                V^T is 16 contiguous bytes); B: the q heads of the group twice, in columns 0..7 and 8..15;
@@ -219,13 +221,13 @@ hipError_t launch_gemv(const GemvArgs& a, hipStream_t s) {
 //                                probabilities, split: their bf16 rounding in columns 0..7 and what it left out, rounded in
 //                                turn, in 8..15 (16 significant bits); the two halves of O^T are added at the end.
 // With one split the workgroup writes the output, else the splits' (max, sum, unnormalised output) go to the combine kernel.
-// 64 sequences x 8 kv heads x 4 q heads x 1024 positions: 82 us + 9 for the combine -> 63 us by itself (4.2 TB/s); beside the
-// gate/up projection, with which it shares the memory, 113 + 27 -> 103.  (Vector units and chunks of 128 positions before.)
+// 64 sequences x 8 kv heads x 4 q heads x 1024 positions: 82 us + 9 for the combine -> 61 us by itself (4.4 TB/s).  (Vector units and chunks
+// of 128 positions before.)
 // ------------------------------------------------------------------------------------------------
 __host__ __device__ __forceinline__ int attn_split_len(int n_pos, int n_splits) { return ((n_pos + n_splits - 1) / n_splits + 127) / 128 * 128; }
 
 template <int D, int G>
-__global__ __launch_bounds__(256, 2) void attn_decode_kernel(AttnDecodeArgs a) {
+__global__ __launch_bounds__(256, 3) void attn_decode_kernel(AttnDecodeArgs a) {
   constexpr int DS = D / 32, DT = D / 16;
   __shared__ float osm[4][G][D];
   __shared__ float msm[4][G], lsm[4][G];
@@ -252,7 +254,7 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(AttnDecodeArgs a) {
   for (int t = 0; t < DT; ++t) o[t] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
   float m = -INFINITY, l = 0.f;
   struct Block { u32x4_t k[2][DS], v[DT]; };
-  auto load = [&](Block& x, int blk) {   // unconditional: blk is clamped by the caller; the capacity is a multiple of 32
+  auto load = [&](Block& x, int blk) {   // (whole blocks: the capacity is a multiple of 32)
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -306,19 +308,12 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(AttnDecodeArgs a) {
       o[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, x.v[t]), __builtin_bit_cast(bf16x8_t, pb), o[t], 0, 0, 0);
     }
   };
-  if (wave < nb) {
-    Block x0, x1;
-    load(x0, wave);
-    for (int blk = wave; blk < nb; blk += 8) {
-      load(x1, min(blk + 4, nb - 1));
-      __builtin_amdgcn_sched_barrier(0);
-      compute(x0, blk);
-      __builtin_amdgcn_sched_barrier(0);
-      load(x0, min(blk + 8, nb - 1));
-      __builtin_amdgcn_sched_barrier(0);
-      if (blk + 4 < nb) compute(x1, blk + 4);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+  for (int blk = wave; blk < nb; blk += 4) {
+    Block x;
+    load(x, blk);
+    __builtin_amdgcn_sched_barrier(0);
+    compute(x, blk);
+    __builtin_amdgcn_sched_barrier(0);
   }
   l += __shfl_xor(l, 16, 64);
   l += __shfl_xor(l, 32, 64);
@@ -391,10 +386,11 @@ __global__ void attn_combine_kernel(AttnDecodeArgs a) {
   a.o[(size_t)bi * a.nq * D + h * D + t] = f32_to_bf16(o / stat[0]);
 }
 
-// splits of a (sequence, kv head): enough workgroups for the chip (two per CU), of at least 128 positions each
+// splits of a (sequence, kv head): as many as give the chip two workgroups per CU and no more (a few workgroups of a second
+// round cost a round), of at least 128 positions each
 int attn_decode_splits(int B, int nkv, int max_seq) {
-  const int want = (512 + B * nkv - 1) / (B * nkv), most = (max_seq + 127) / 128;
-  const int n = want < most ? want : most;
+  const int want = 512 / (B * nkv), most = (max_seq + 127) / 128;
+  const int n = want < 1 ? 1 : want < most ? want : most;
   return n < ATTN_DECODE_MAX_SPLITS ? n : ATTN_DECODE_MAX_SPLITS;
 }
 
