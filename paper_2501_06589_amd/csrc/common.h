@@ -88,6 +88,7 @@ struct PlainGemmArgs {
   const float* cos_tab;    // [max_seq][d/2]
   const float* sin_tab;
   int T, pos0, nkv, d, max_seq;
+  int n_blocks;            // set by the launcher: column blocks of all matrices
 };
 hipError_t launch_plain_gemm(const PlainGemmArgs& a, bool is_bf16, hipStream_t s);
 

@@ -95,7 +95,7 @@ hipError_t launch_reduce_norm(const ReduceNormArgs& a, bool is_bf16, hipStream_t
 
 // ------------------------------------------------------------------------------------------------
 // Plain projections: any size, both storage types, weights [K][N] as they were given, fp32 arithmetic.  One launch is
-// one step of a module for ALL computed shards (grid z) and all the matrices that read the same rows (q | k | v, or gate
+// one step of a module for ALL computed shards (grid y) and all the matrices that read the same rows (q | k | v, or gate
 // and up), with what follows as its epilogue: a decode step of a small model is a chain of launches, and what counts is how
 // many there are and how many memory round trips each one is long.  A workgroup takes MR rows x 64 columns and
 // the whole K: 16 lanes side by side cover the columns, four at a time, and 16 groups of lanes deal out K in fours; every
@@ -163,8 +163,9 @@ __global__ __launch_bounds__(256) void plain_gemm_kernel(PlainGemmArgs a) {
   __shared__ __attribute__((aligned(16))) float xs[MR][PLAIN_KC];
   __shared__ float red[4][MR][64];
   __shared__ float sum[2][MR][64];
-  const int t = threadIdx.x, shard = blockIdx.z, m0 = blockIdx.y * MR;
-  int blk = blockIdx.x, mat = 0;   // the matrices' column blocks side by side (SwiGLU: the gate's; the up matrix goes along)
+  const int t = threadIdx.x, shard = blockIdx.y;
+  const int m0 = (int)(blockIdx.x / (unsigned)a.n_blocks) * MR;
+  int blk = (int)(blockIdx.x % (unsigned)a.n_blocks), mat = 0;   // the matrices' column blocks side by side (SwiGLU: the gate's; the up matrix goes along)
   while (a.epilogue != PLAIN_SWIGLU && mat + 1 < a.n_mat && blk >= (a.N[mat] + 63) / 64) { blk -= (a.N[mat] + 63) / 64; ++mat; }
   const int n0 = blk * 64, N = a.N[mat];
   const T* x = reinterpret_cast<const T*>(a.x) + shard * a.x_stride;
@@ -214,10 +215,12 @@ __global__ __launch_bounds__(256) void plain_gemm_kernel(PlainGemmArgs a) {
 }
 
 template <typename T, int MR>
-static hipError_t launch_plain_gemm_t(const PlainGemmArgs& a, bool vec, hipStream_t s) {
-  int blocks = 0;
-  for (int i = 0; i < (a.epilogue == PLAIN_SWIGLU ? 1 : a.n_mat); ++i) blocks += (a.N[i] + 63) / 64;
-  const dim3 grid(blocks, (a.M + MR - 1) / MR, a.n_shards);
+static hipError_t launch_plain_gemm_t(PlainGemmArgs a, bool vec, hipStream_t s) {
+  a.n_blocks = 0;
+  for (int i = 0; i < (a.epilogue == PLAIN_SWIGLU ? 1 : a.n_mat); ++i) a.n_blocks += (a.N[i] + 63) / 64;
+  const long long blocks = (long long)a.n_blocks * ((a.M + MR - 1) / MR);   // (rows and columns in one grid dimension: the others end at 65535)
+  if (blocks > 0x7fffffff || a.n_shards > 65535) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)blocks, a.n_shards);
   if (vec) hipLaunchKernelGGL((plain_gemm_kernel<T, MR, true>), grid, dim3(256), 0, s, a);
   else hipLaunchKernelGGL((plain_gemm_kernel<T, MR, false>), grid, dim3(256), 0, s, a);
   return hipGetLastError();
@@ -230,7 +233,6 @@ hipError_t launch_plain_gemm(const PlainGemmArgs& a, bool is_bf16, hipStream_t s
   for (int i = 0; i < a.n_mat; ++i) vec = vec && a.N[i] % 4 == 0 && ((uintptr_t)a.w[i] & 15) == 0;
   // rows per workgroup: one for a single row; four for a few; more re-use of the weights beyond
   const int mr = a.M == 1 ? 1 : a.M <= 64 ? 4 : 16;
-  if ((a.M + mr - 1) / mr > 65535) return hipErrorInvalidValue;
   if (is_bf16) return mr == 1 ? launch_plain_gemm_t<bf16_t, 1>(a, vec, s) : mr == 4 ? launch_plain_gemm_t<bf16_t, 4>(a, vec, s) : launch_plain_gemm_t<bf16_t, 16>(a, vec, s);
   return mr == 1 ? launch_plain_gemm_t<float, 1>(a, vec, s) : mr == 4 ? launch_plain_gemm_t<float, 4>(a, vec, s) : launch_plain_gemm_t<float, 16>(a, vec, s);
 }

@@ -59,3 +59,13 @@ def test_residual_epilogue_of_the_wide_ring_tile(harness):
     w = WIDE.with_(name="wide_tile", n_layers=2, hidden=4128, prefill=1101, tp_degree=5, peer_pool=2)
     res = harness.run_case(w, decode_steps=0, gen_device="cuda:0")
     assert max(res.errs) < TOL * 2 ** 0.5, res.errs
+
+
+def test_wide_decode_replayed_from_a_graph(harness):
+    """Every replay of a captured wide step against the eager steps, with eager work and a synchronisation between them."""
+    import numpy as np
+    w = WIDE.with_(name="wide_graph", hidden=256, inter=352, n_q_heads=4, batch=17, prefill=0, kv_preload=126, decode_steps=5)
+    eager = harness.run_case(w, kv_preload=126, decode_steps=5, gpu_only=True, max_tokens=1, decode_graph=0)
+    graph = harness.run_case(w, kv_preload=126, decode_steps=5, gpu_only=True, max_tokens=1, decode_graph=1)
+    for a, b in zip(eager.gpu, graph.gpu):      # (run_case copies every step's result to the host)
+        assert np.array_equal(a, b)
