@@ -119,6 +119,7 @@ struct ladder_ctx {
   size_t qkv_cap = 0;
   char *qbuf = nullptr, *obuf = nullptr, *act = nullptr;
   float* gu = nullptr;
+  size_t gu_rows = 0;
   float *att_o = nullptr, *att_ml = nullptr;
   // fused decode path: ring of three residual buffers (x_m lives in ring[m % 3]), arrival tickets, and
   // the launch list of one step
@@ -411,9 +412,10 @@ int run_last_projection(ladder_ctx* c, int m, const char* x, const char* wp, int
   return fuse ? finish_residual(c, a, rows, nc, cons, s) : LADDER_OK;
 }
 
-// splits of the gate/up projection (its partial products have a buffer of their own, sized for the largest of these)
-int gate_up_ksplit(const ladder_config& g, int rows) {
-  return rows > 16 && rows <= FEW_ROWS ? gemm_ksplit(rows, 2 * g.inter, g.hidden, 4, SPLIT_KERNEL_US) : 1;
+// splits of the gate/up projection: its partial products have a buffer of their own, of gu_rows rows (slots times rows)
+int gate_up_ksplit(const ladder_config& g, int rows, size_t gu_rows) {
+  if (rows <= 16 || rows > FEW_ROWS) return 1;
+  return gemm_ksplit(rows, 2 * g.inter, g.hidden, (int)std::min<size_t>(4, gu_rows / (size_t)rows), SPLIT_KERNEL_US);
 }
 
 // one module of the plain path: three launches (attention) or two (MLP) for all computed shards, which leave a partial
@@ -515,7 +517,7 @@ int run_module(ladder_ctx* c, int m, int B, int T, int pos0, hipStream_t s, int*
       } else {
         GemmArgs a{};
         a.x = (const bf16_t*)yin; a.ldx = H; a.wp = L.pgu; a.M = rows; a.K = H; a.N = 2 * I; a.row_scale = c->y_scale[par];
-        const int gu_slots = gate_up_ksplit(g, rows);
+        const int gu_slots = gate_up_ksplit(g, rows, c->gu_rows);
         if (gu_slots > 1) { a.out = c->gu; a.epilogue = 0; a.ksplit = gu_slots; a.out_stride = (size_t)rows * 2 * I; }
         else { a.act = (bf16_t*)c->act; a.epilogue = 1; }
         HIP_TRY(c, timed(c, LADDER_K_GEMM, s, [&] { return launch_gemm_mfma(a, s); }));
@@ -1566,13 +1568,13 @@ static int init_impl(const ladder_config* cfg, void* hip_stream, ladder_ctx** ou
   INIT_TRY(dev_alloc(c, (void**)&c->qbuf, shards * rows * nq * d * esz, false));
   INIT_TRY(dev_alloc(c, (void**)&c->obuf, shards * rows * nq * d * esz, false));
   INIT_TRY(dev_alloc(c, (void**)&c->act, shards * rows * I * esz, false));
-  // the slots of a split gate/up projection
-  size_t gu_rows = 0;
-  for (int r = 17; c->fast && r <= FEW_ROWS && (size_t)r <= rows; ++r) {
-    const int n = gate_up_ksplit(g, r);
-    if (n > 1) gu_rows = std::max(gu_rows, (size_t)n * r);
+  // the slots of a split gate/up projection: what the largest wants (looked up every 16 rows; a call in between that would
+  // want more takes a split less)
+  for (size_t r = 32; c->fast && r <= (size_t)FEW_ROWS && r < rows + 16; r += 16) {
+    const int n = gate_up_ksplit(g, (int)std::min(r, rows), (size_t)4 * FEW_ROWS);
+    if (n > 1) c->gu_rows = std::max(c->gu_rows, (size_t)n * std::min(r, rows));
   }
-  if (gu_rows) INIT_TRY(dev_alloc(c, (void**)&c->gu, gu_rows * 2 * I * 4, false));
+  if (c->gu_rows) INIT_TRY(dev_alloc(c, (void**)&c->gu, c->gu_rows * 2 * I * 4, false));
   if (c->fast) {
     INIT_TRY(dev_alloc(c, (void**)&c->ssq_part, (size_t)((H + 31) / 32) * rows * 4, false));
     for (int i = 0; i < 2; ++i) INIT_TRY(dev_alloc(c, (void**)&c->y_rs[i], rows * 4, false));
