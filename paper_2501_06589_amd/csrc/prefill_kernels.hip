@@ -694,6 +694,9 @@ __global__ __launch_bounds__(WR * WC * 64) void gemm_ring_kernel(GemmArgs a) {
       if (both) multiply(f1);
     }
   }
+  // with two stages or more, the wait in front of the last one was for everything; a single stage (K <= 64, or a last split of
+  // one) leaves the start's other requests, which repeat it, in flight into LDS: they must land before the workgroup ends
+  if (n == 1) ring_meet<0>();
   if constexpr (BN == 256 && WR == 2) {   // (whole rows per memory instruction: 8B shape, 2 layers, 1100 rows 1265 -> 1251 us, 2048 1795 -> 1784)
     if (a.epilogue == 3) {
       ring_meet<0>();   // every wavefront is past its last read of the ring, whose memory stages the tile

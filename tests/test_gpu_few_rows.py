@@ -69,3 +69,13 @@ def test_wide_decode_replayed_from_a_graph(harness):
     graph = harness.run_case(w, kv_preload=126, decode_steps=5, gpu_only=True, max_tokens=1, decode_graph=1)
     for a, b in zip(eager.gpu, graph.gpu):      # (run_case copies every step's result to the host)
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("rows", [17, 100, 300])
+@pytest.mark.parametrize("hidden,inter", [(448, 32), (448, 416), (32, 64)])
+def test_products_of_a_single_stage(harness, hidden, inter, rows):
+    """K of 64 and less (one 64-wide q head, 32 hidden or SwiGLU columns) and splits of K whose last one is a single stage
+    of 64 (448 in 3 and 416 in 3): the ring's start requests more stages than there are."""
+    w = WIDE.with_(name="one_stage", hidden=hidden, n_q_heads=1, n_kv_heads=1, head_dim=64, inter=inter, batch=1, prefill=rows)
+    res = harness.run_case(w, decode_steps=0)
+    assert max(res.errs) < TOL, res.errs
