@@ -264,7 +264,19 @@ __global__ __launch_bounds__(256, 3) void attn_decode_kernel(AttnDecodeArgs a) {
     for (int t = 0; t < DT; ++t)
       x.v[t] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(vb + (size_t)t * 16 * a.max_seq + blk * 32));
   };
-  auto compute = [&](const Block& x, int blk) {
+  auto compute = [&](Block& x, int blk) {
+    const int ahead = p1 - (p0 + blk * 32);
+    if (ahead < 32) {   // (uniform) the run's last block: a probability of 0 does not cancel an infinity or NaN that an earlier,
+                        // longer sequence left behind the run, so the V entries of the lane's keys ahead - 8 q .. 7 are cleared
+      const int keep = ahead - 8 * q;
+#pragma unroll
+      for (int t = 0; t < DT; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t mask = (2 * e < keep ? 0x0000FFFFu : 0u) | (2 * e + 1 < keep ? 0xFFFF0000u : 0u);
+          x.v[t][e] &= mask;
+        }
+    }
     f32x4_t st[2];
     float sv[8], mloc = -INFINITY;
 #pragma unroll
