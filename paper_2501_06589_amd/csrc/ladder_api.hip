@@ -450,7 +450,7 @@ int run_module_plain(ladder_ctx* c, int m, int B, int T, int pos0, float* out, h
 // one module's compute on the main stream; writes parts[m%2] and returns the number of slots written, or (fuse)
 // updates the residual itself and returns -1 slots: then no reduce follows
 // ---------------------------------------------------------------------------------------------
-int run_module(ladder_ctx* c, int m, int B, int T, int pos0, hipStream_t s, int* n_slots, bool fuse, float* x_copy) {
+int run_module(ladder_ctx* c, int m, int B, int T, int pos0, bool decode, hipStream_t s, int* n_slots, bool fuse, float* x_copy) {
   const ladder_config& g = c->cfg;
   const int rows = B * T, H = g.hidden, d = g.head_dim, nq = g.n_q_heads, nkv = g.n_kv_heads, I = g.inter;
   const int layer = (m - 1) / 2, par = m & 1;
@@ -463,24 +463,26 @@ int run_module(ladder_ctx* c, int m, int B, int T, int pos0, hipStream_t s, int*
     return run_module_plain(c, m, B, T, pos0, pout, s);
   }
   const bool few = rows <= FEW_ROWS;
-  const bool dev_pos = T == 1;  // decode kernels of the bf16 path read the position from device memory
+  // a decode step of the bf16 path reads the position from device memory, so that a captured one stays valid; a prefill of one
+  // token starts at position 0 wherever the context stood before
+  const int* pos_dev = decode ? c->pos_dev : nullptr;
   int slots = 0;
   for (int r = 0; r < g.n_real_shards; ++r) {
     LayerStore& L = c->store[(size_t)layer * g.n_real_shards + r];
     if (is_attn) {
       int qkv_slots = 1;
-      if (few && (dev_pos || rows <= 16 || gemm_ksplit(rows, c->nqkv, H, max_slots(g, rows), SPLIT_KERNEL_US) > 1)) {
+      if (few && (T == 1 || rows <= 16 || gemm_ksplit(rows, c->nqkv, H, max_slots(g, rows), SPLIT_KERNEL_US) > 1)) {
         const int rc = run_few_rows(c, yin, H, L.pqkv, rows, H, c->nqkv, c->qkv, s, &qkv_slots, c->y_scale[par]);
         if (rc) return rc;
       } else {
         GemmArgs a{};
         a.x = (const bf16_t*)yin; a.ldx = H; a.wp = L.pqkv; a.M = rows; a.K = H; a.N = c->nqkv; a.row_scale = c->y_scale[par];
-        if (!dev_pos) {
+        if (T != 1) {
           // rotary embedding and cache append are the GEMM's epilogue (no fp32 q|k|v round trip through memory)
           a.epilogue = 2; a.q_out = (bf16_t*)c->qbuf; a.cache_k = (bf16_t*)L.cache_k; a.cache_v = (bf16_t*)L.cache_v;
           a.cos_tab = c->cos_tab; a.sin_tab = c->sin_tab; a.T = T; a.pos0 = pos0; a.nq = nq; a.nkv = nkv; a.d = d; a.max_seq = c->s_cap;
           qkv_slots = 0;
-        } else {   // (a decode step of more than 64 sequences: the position lives in device memory)
+        } else {   // (one token for each of more than FEW_ROWS sequences: in a decode step the position lives in device memory)
           a.out = c->qkv; a.epilogue = 0;
         }
         HIP_TRY(c, timed(c, LADDER_K_GEMM, s, [&] { return launch_gemm_mfma(a, s); }));
@@ -489,7 +491,7 @@ int run_module(ladder_ctx* c, int m, int B, int T, int pos0, hipStream_t s, int*
       ra.qkv = c->qkv; ra.n_parts = qkv_slots; ra.part_stride = (size_t)rows * c->nqkv;
       ra.q_out = c->qbuf; ra.cache_k = L.cache_k; ra.cache_v = L.cache_v;
       ra.cos_tab = c->cos_tab; ra.sin_tab = c->sin_tab;
-      ra.B = B; ra.T = T; ra.pos0 = pos0; ra.nq = nq; ra.nkv = nkv; ra.d = d; ra.max_seq = c->s_cap; ra.pos_dev = dev_pos ? c->pos_dev : nullptr;
+      ra.B = B; ra.T = T; ra.pos0 = pos0; ra.nq = nq; ra.nkv = nkv; ra.d = d; ra.max_seq = c->s_cap; ra.pos_dev = pos_dev;
       if (qkv_slots > 0) HIP_TRY(c, timed(c, LADDER_K_ROPE_APPEND, s, [&] { return launch_rope_append(ra, s); }));
       if (T == 1) {
         AttnDecodeArgs aa{};
@@ -498,7 +500,7 @@ int run_module(ladder_ctx* c, int m, int B, int T, int pos0, hipStream_t s, int*
         aa.B = B; aa.nq = nq; aa.nkv = nkv; aa.d = d; aa.max_seq = c->s_cap; aa.n_pos = pos0 + 1;
         // launch shape fixed by the cache capacity (not the current position) so that a captured step
         // stays valid as the sequence grows
-        aa.n_splits = attn_decode_splits(B, nkv, g.max_seq); aa.pos_dev = c->pos_dev;
+        aa.n_splits = attn_decode_splits(B, nkv, g.max_seq); aa.pos_dev = pos_dev;
         HIP_TRY(c, timed(c, LADDER_K_ATTN_DECODE, s, [&] { return launch_attn_decode(aa, s); }));
       } else {
         AttnPrefillArgs aa{(const bf16_t*)c->qbuf, (const bf16_t*)L.cache_k, (const bf16_t*)L.cache_v,
@@ -645,7 +647,7 @@ int run_reduce(ladder_ctx* c, int m, int rows, int n_slots, const void* emb, flo
 //     residual is updated in place, in module order) through an event.
 //   else reduce_on_side_stream: all modules on s0, all reduces on the side stream.
 //   else (and for every call with more than 64 rows): everything in order on s0.
-int forward_body(ladder_ctx* c, const void* x_in, int B, int T, int pos0, void* x_out, hipStream_t s0, const StageIo* st = nullptr) {
+int forward_body(ladder_ctx* c, const void* x_in, int B, int T, int pos0, bool decode, void* x_out, hipStream_t s0, const StageIo* st = nullptr) {
   const int rows = B * T;
   // calls with more than 64 rows (prefill) run in order on one stream: each of their kernels fills the
   // chip, and the same work measured 4 % (reduce on the side stream) to 16 % (two module streams) slower
@@ -679,7 +681,7 @@ int forward_body(ladder_ctx* c, const void* x_in, int B, int T, int pos0, void* 
     // module's output joins it (the residual update writes the copy itself; the two outputs are the differences of
     // consecutive streams)
     float* copy = m == c->n_mod ? (float*)x_out : !st ? nullptr : m == c->n_mod - 2 ? st->r_out : m == c->n_mod - 1 ? st->a_out : nullptr;
-    rc = run_module(c, m, B, T, pos0, sm, &n_slots, fuse, copy);
+    rc = run_module(c, m, B, T, pos0, decode, sm, &n_slots, fuse, copy);
     if (rc) return rc;
     if (n_slots >= 0) {   // (else the module has updated the residual itself: wide calls run on one stream)
       if (rs != sm) {
@@ -1336,7 +1338,7 @@ int decode_graph_step(ladder_ctx* c, const void* x_in, void* x_out) {
     DBG("capture: begin (batch %d)", B);
     HIP_TRY(c, hipStreamBeginCapture(c->s_capture, hipStreamCaptureModeThreadLocal));
     int finished = 0;
-    int rc = c->fused ? fused_body(c, c->emb_stage, B, c->s_capture, nullptr, &finished) : forward_body(c, c->emb_stage, B, 1, 0, nullptr, c->s_capture);
+    int rc = c->fused ? fused_body(c, c->emb_stage, B, c->s_capture, nullptr, &finished) : forward_body(c, c->emb_stage, B, 1, 0, true, nullptr, c->s_capture);
     DBG("capture: body recorded rc=%d", rc);
     if (rc == LADDER_OK && !(finished & FUSED_ADVANCED)) {
       DBG("capture: inc_pos");
@@ -1764,7 +1766,7 @@ int ladder_prefill(ladder_ctx* c, const void* x_in, int32_t B, int32_t T, void* 
   if (rc) return rc;
   rc = all_loaded(c);
   if (rc) return rc;
-  rc = forward_body(c, x_in, B, T, 0, x_out, c->main);
+  rc = forward_body(c, x_in, B, T, 0, false, x_out, c->main);
   if (rc) return rc;
   for (auto& X : c->store) { X.kv_B = 0; X.kv_S = 0; }
   c->pos = T;
@@ -1791,7 +1793,7 @@ int ladder_decode_step(ladder_ctx* c, const void* x_in, void* x_out) {
     rc = decode_fused_step(c, x_in, x_out);
     if (rc) return rc;
   } else {
-    rc = forward_body(c, x_in, c->batch, 1, c->pos, x_out, c->main);
+    rc = forward_body(c, x_in, c->batch, 1, c->pos, true, x_out, c->main);
     if (rc) return rc;
     hipLaunchKernelGGL(inc_pos_kernel, dim3(1), dim3(1), 0, c->main, c->pos_dev);
     HIP_TRY(c, hipGetLastError());
@@ -1827,7 +1829,7 @@ int ladder_prefill_stage(ladder_ctx* c, const float* residual_in, const float* a
   if (rc) return rc;
   rc = all_loaded(c);
   if (rc) return rc;
-  rc = forward_body(c, nullptr, B, T, 0, nullptr, c->main, &st);
+  rc = forward_body(c, nullptr, B, T, 0, false, nullptr, c->main, &st);
   if (rc) return rc;
   for (auto& X : c->store) { X.kv_B = 0; X.kv_S = 0; }
   c->pos = T;
@@ -1855,7 +1857,7 @@ int ladder_decode_step_stage(ladder_ctx* c, const float* residual_in, const floa
     rc = decode_fused_step(c, nullptr, nullptr, &st);
     if (rc) return rc;
   } else {
-    rc = forward_body(c, nullptr, c->batch, 1, c->pos, nullptr, c->main, &st);
+    rc = forward_body(c, nullptr, c->batch, 1, c->pos, true, nullptr, c->main, &st);
     if (rc) return rc;
     hipLaunchKernelGGL(inc_pos_kernel, dim3(1), dim3(1), 0, c->main, c->pos_dev);
     HIP_TRY(c, hipGetLastError());

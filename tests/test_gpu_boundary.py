@@ -111,3 +111,37 @@ def test_peers_changed_under_a_captured_decode_step(harness, fused):
         assert err < 2e-2, (step, err)
         step += 1
     ctx.free()
+
+
+@pytest.mark.parametrize("dtype,batch", [("fp32", 2), ("bf16", 3), ("bf16", 17), ("bf16", 40)])
+@pytest.mark.parametrize("before", [5, 128])
+@pytest.mark.parametrize("stage", [False, True])
+def test_one_token_prefill_on_a_used_context(harness, dtype, batch, before, stage):
+    """A prefill resets the position to 0 wherever the context stood, also one of a single token per sequence, which runs the
+    decode kernels, and also on a full cache (128 of 128 positions): same bits as on a fresh context, and so are the steps
+    behind it."""
+    w = inputs.WORKLOADS["tiny"].with_(name="one_token", dtype=dtype, inter=352, n_q_heads=4, n_kv_heads=2, batch=batch,
+                                       prefill=1, kv_preload=before, decode_steps=2, tp_degree=1, n_real_shards=1)
+    tensors = harness.make_tensors(w)
+    g = torch.Generator().manual_seed(batch)
+    hands = [[torch.randn(batch, w.hidden, generator=g).to(DEV) for _ in range(3)] for _ in range(3)]
+    xs = [inputs.embeddings(w, batch, 1, inputs.SEED_DECODE0 + i).to(DEV) for i in range(3)]
+    outs = []
+    for used in (0, before):
+        ctx = harness.build_gpu(w, tensors, max_seq=128, max_tokens=1)
+        if used:
+            for i in range(w.n_layers):
+                ctx.load_kv(i, 0, *[t.to(DEV) for t in inputs.kv_cache(w, i, 0, batch, used)])
+            if used < 128:
+                ctx.decode_step(xs[2][:, 0].contiguous())
+        if stage:
+            got = list(ctx.prefill_stage([t[:, None].contiguous() for t in hands[0]]))
+        else:
+            got = [ctx.prefill(xs[0])]
+        assert ctx.position() == (1, batch)
+        for i in (1, 2):
+            got += list(ctx.decode_step_stage(hands[i])) if stage else [ctx.decode_step(xs[i][:, 0].contiguous())]
+        outs.append([t.cpu() for t in got])
+        ctx.free()
+    for a, b in zip(*outs):
+        assert torch.isfinite(a).all() and torch.equal(a, b)
