@@ -1973,7 +1973,7 @@ static int head_body(ladder_ctx* c, const float* x, int rows, char* y, float* lo
     PlainGemmArgs a{};
     a.x = y; a.M = rows; a.K = H; a.n_shards = 1; a.n_mat = 1; a.w[0] = c->head_w; a.N[0] = V; a.epilogue = PLAIN_OUT; a.out = logits;
     HIP_TRY(c, launch_plain_gemm(a, c->bf16, s));
-  } else if (rows <= 16 || (rows <= 64 && (V & 31))) {   // (up to 64 rows whole pairs of tiles are asked for: launch_gemv refuses others)
+  } else if (rows <= 16 && (V & 31) == 0 && gemv_plan(rows, V, H, true).ksplit == 1) {   // (what the skinny GEMM takes: whole pairs of tiles, and so many that K is not split)
     GemvArgs a{};
     a.x = (const bf16_t*)y; a.ldx = H; a.wp = c->head_wp; a.M = rows; a.K = H; a.N = V; a.ksplit = 1;
     a.out = logits; a.out_stride = (size_t)rows * V; a.slot0 = 0; a.epilogue = 0;

@@ -62,22 +62,23 @@ def test_first_argmax_of_any_row_length(harness, V):
 
 
 @pytest.mark.parametrize("rows", [1, 16, 17, 64, 65])
-@pytest.mark.parametrize("V", [48, 64, 1056])
-def test_head_rows(harness, rows, V):
-    """The packed head's three products: up to 16 rows, up to 64, beyond; an odd number of column tiles is taken beyond 64 rows only."""
-    w = TINY.with_(name="head_rows", dtype="bf16", inter=352, n_layers=1, tp_degree=1, n_real_shards=1, batch=rows)
+@pytest.mark.parametrize("hidden,V", [(256, 48), (256, 64), (256, 1056), (4096, 4000), (4096, 16)])
+def test_head_rows(harness, hidden, V, rows):
+    """The packed head's two products: the skinny GEMM for up to 16 rows where it takes the width, the tiled one for more rows,
+    an odd number of column tiles, and widths so narrow that the skinny one would split K."""
+    w = TINY.with_(name="head_rows", dtype="bf16", hidden=hidden, inter=352, n_layers=1, tp_degree=1, n_real_shards=1, batch=rows)
     hw = inputs.head_weights(w, V, V, device=DEV)
     ctx = ladder.Ladder(ladder.config_for(w))
     ctx.load_head(hw["table"], hw["final_norm"], hw["w_lm"])
     x = torch.randn(rows, w.hidden, generator=torch.Generator().manual_seed(V)).to(DEV)
-    if V % 32 and rows <= 64:
-        with pytest.raises(ladder.LadderError):
-            ctx.head(x)
-    else:
-        logits, toks = ctx.head(x)
-        y = x.double() / torch.sqrt((x.double() ** 2).mean(-1, keepdim=True) + w.rms_eps) * hw["final_norm"].double()
-        want = y @ hw["w_lm"].double()
-        # (the normed rows are rounded to bf16 once: 2^-9 of each term at most)
-        assert float((logits.double() - want).abs().max() / want.square().mean().sqrt()) < 2e-2
-        assert np.array_equal(toks.cpu().numpy(), np.argmax(logits.cpu().numpy(), axis=-1))
+    logits, toks = ctx.head(x)
+    y = x.double() / torch.sqrt((x.double() ** 2).mean(-1, keepdim=True) + w.rms_eps) * hw["final_norm"].double()
+    want = y @ hw["w_lm"].double()
+    # (the normed rows are rounded to bf16 once: 2^-9 of each term at most)
+    assert float((logits.double() - want).abs().max() / want.square().mean().sqrt()) < 2e-2
+    assert np.array_equal(toks.cpu().numpy(), np.argmax(logits.cpu().numpy(), axis=-1))
+    if rows <= 16:      # (LADDER_HEAD_STATIC_MAX_ROWS)
+        got = torch.full((rows,), -1, dtype=torch.int32, device=DEV)
+        ctx.head_static(x, got)
+        assert torch.equal(got, toks)
     ctx.free()
