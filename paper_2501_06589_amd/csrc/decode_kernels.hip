@@ -294,8 +294,9 @@ __global__ __launch_bounds__(256, 3) void attn_decode_kernel(AttnDecodeArgs a) {
     }
     mloc = fmaxf(mloc, __shfl_xor(mloc, 16, 64));
     mloc = fmaxf(mloc, __shfl_xor(mloc, 32, 64));
-    const float mnew = fmaxf(m, mloc);    // finite: a block has at least one visible key
-    const float corr = __expf(m - mnew);
+    const float mnew = fmaxf(m, mloc);
+    const float ref = mnew == -INFINITY ? 0.f : mnew;   // (scores that are all -inf weigh nothing, they must not become NaN)
+    const float corr = __expf(m - ref);
     float psum = 0.f;
     uint32_t pk[4];
 #pragma unroll
@@ -303,7 +304,7 @@ __global__ __launch_bounds__(256, 3) void attn_decode_kernel(AttnDecodeArgs a) {
       float part[2];
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const float p = __expf(sv[2 * e + h] - mnew);
+        const float p = __expf(sv[2 * e + h] - ref);
         psum += p;
         const float high = bf16_to_f32(f32_to_bf16(p));
         part[h] = b < 8 ? high : p - high;
@@ -344,10 +345,11 @@ __global__ __launch_bounds__(256, 3) void attn_decode_kernel(AttnDecodeArgs a) {
     float mm = msm[0][h];   // (wavefront 0 always has a block)
 #pragma unroll
     for (int w = 1; w < 4; ++w) mm = fmaxf(mm, msm[w][h]);
+    const float ref = mm == -INFINITY ? 0.f : mm;
     float ll = 0.f, oo = 0.f;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-      const float e = __expf(msm[w][h] - mm);
+      const float e = __expf(msm[w][h] - ref);
       ll += lsm[w][h] * e;
       oo += osm[w][h][dim] * e;
     }

@@ -338,8 +338,9 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(AttnGenericArgs a) {
       }
       sc = ((part[0] + part[1]) + (part[2] + part[3])) * scale;
     }
-    const float mn = fmaxf(mx, wave_max(sc));   // finite: the chunk has a visible position
-    const float corr = expf(mx - mn), p = lane < n ? expf(sc - mn) : 0.f;
+    const float mn = fmaxf(mx, wave_max(sc));
+    const float ref = mn == -INFINITY ? 0.f : mn;   // (scores that are all -inf weigh nothing, they must not become NaN)
+    const float corr = expf(mx - ref), p = lane < n ? expf(sc - ref) : 0.f;
     l = l * corr + wave_sum(p);
     mx = mn;
     ps[wave][lane] = p;

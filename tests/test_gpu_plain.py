@@ -35,3 +35,37 @@ def test_attention_chunks(harness, cached):
     w = BASE.with_(batch=2, prefill=0, kv_preload=cached, n_q_heads=4, n_kv_heads=2)
     res = harness.run_case(w, kv_preload=cached)
     assert max(res.errs) < 1e-4, res.errs
+
+
+@pytest.mark.parametrize("dtype,batch,nq,nkv,cached", [("fp32", 2, 2, 2, 300), ("fp32", 1, 4, 2, 700), ("bf16", 17, 2, 2, 300),
+                                                       ("bf16", 17, 4, 1, 1025)])
+def test_stretches_of_scores_of_minus_infinity(harness, dtype, batch, nq, nkv, cached):
+    """Cached keys whose scores are -inf, whole chunks of them (64 positions in the plain kernel, 32 in the one of wide bf16
+    batches, and whole splits of that): they weigh nothing, as keys with a huge negative score do; same bits."""
+    w = BASE.with_(name="minus_inf", dtype=dtype, tp_degree=1, n_real_shards=1, hidden=256, inter=352, n_q_heads=nq, n_kv_heads=nkv,
+                   head_dim=64, batch=batch, prefill=0, kv_preload=cached, decode_steps=1)
+    tensors = harness.make_tensors(w)
+    t = tensors[0][0]
+    k, v = inputs.kv_cache(w, 0, 0, batch, cached)
+    x = inputs.embeddings(w, batch, 1, inputs.SEED_DECODE0)[:, 0]
+    # the step's rotated queries, and for each kv head a dim in which its q heads agree in sign
+    xd = x.double()
+    y = xd / torch.sqrt((xd * xd).mean(-1, keepdim=True) + w.rms_eps) * t["attn_norm"].double()
+    q = (y @ t["wq"].double()).view(batch, nkv, nq // nkv, 32, 2)
+    ang = cached * w.rope_theta ** (-torch.arange(0, 64, 2, dtype=torch.float64) / 64)
+    q = torch.stack([q[..., 0] * ang.cos() - q[..., 1] * ang.sin(), q[..., 0] * ang.sin() + q[..., 1] * ang.cos()], -1).flatten(-2)
+    agree = torch.maximum(q.amin(2), -q.amax(2))                    # [batch][kv head][dim]: positive where the signs agree
+    dim = agree.argmax(-1, keepdim=True)
+    assert float(agree.gather(-1, dim).min()) > 0.02
+    sign = q[:, :, 0].gather(-1, dim).sign()
+    outs = []
+    for huge in (1e9, float("inf")):      # (1e9 x 0.02 / 8 = 2.5e6: the weight is exactly 0 as well)
+        kk = k.clone()
+        row = torch.zeros(batch, nkv, 64, dtype=k.dtype).scatter(-1, dim, (-huge * sign).to(k.dtype))
+        for a, b in ((32, 64), (96, 256), (640, 700), (384, 1020)):
+            kk[:, :, a:min(b, cached)] = row[:, :, None]
+        ctx = harness.build_gpu(w, tensors, max_tokens=1)
+        ctx.load_kv(0, 0, kk.cuda(), v.cuda())
+        outs.append(ctx.decode_step(x.contiguous().cuda()).cpu())
+        ctx.free()
+    assert torch.isfinite(outs[0]).all() and torch.equal(*outs)
