@@ -1,5 +1,6 @@
 """GPU: the plain kernels (fp32 storage, odd sizes, bf16 on request) at the edges of their tiles, passes and chunks, against
 the CPU oracle; all computed shards share a launch."""
+import numpy as np
 import pytest
 import torch
 
@@ -69,3 +70,18 @@ def test_stretches_of_scores_of_minus_infinity(harness, dtype, batch, nq, nkv, c
         outs.append(ctx.decode_step(x.contiguous().cuda()).cpu())
         ctx.free()
     assert torch.isfinite(outs[0]).all() and torch.equal(*outs)
+
+
+def test_overlapped_schedules_of_the_plain_path(harness):
+    """Layers of 32 MB and more run their modules on two streams, or the reduces on a side stream, smaller ones in order: the
+    schedules give the same bits, and the right ones."""
+    w = BASE.with_(name="overlap", n_layers=3, hidden=1024, n_q_heads=8, n_kv_heads=4, head_dim=128, inter=1409, tp_degree=4,
+                   n_real_shards=2, batch=2, prefill=9, decode_steps=3, peer_pool=2)
+    assert w.params_per_layer() * w.n_real_shards * 4 >= 32 << 20
+    tensors = harness.make_tensors(w, "cuda:0")
+    runs = [harness.run_case(w, tensors=tensors, gen_device="cuda:0", gpu_only=i > 0, overlap_modules=overlap, reduce_on_side_stream=side)
+            for i, (overlap, side) in enumerate(((0, 0), (1, 1), (0, 1)))]
+    assert max(runs[0].errs) < 1e-4, runs[0].errs
+    for r in runs[1:]:
+        for a, b in zip(runs[0].gpu, r.gpu):
+            assert np.array_equal(a, b)
