@@ -104,17 +104,40 @@ hipError_t launch_reduce_norm(const ReduceNormArgs& a, bool is_bf16, hipStream_t
 // tiny fp32 model (hidden 256, 2 shards), one row: 22 us per matrix and shard (64 x 64 tiles, one k step of 16 in flight)
 // -> 5 us for all
 // of them; fp32 model of hidden 2048 (50 M weights a layer), 8 steps behind a prompt of 32: 23.9 -> 2.2 ms for 2 layers.
+// Many rows, a layer of hidden 4096 and SwiGLU 11008, 64 x 64 tiles -> this, ms: fp32 128 / 512 / 2048 rows 4.6 / 7.5 / 39.8 ->
+// 1.7 / 6.5 / 30.4, bf16 4.5 / 6.9 / 36.5 -> 1.3 / 4.7 / 20.9 (8.5 at 512 rows with the weights converted as they are loaded).
 // ------------------------------------------------------------------------------------------------
 constexpr int PLAIN_KC = 256;   // k per pass
 
-template <typename T, bool VEC>
-__device__ __forceinline__ void plain_w4(const T* w, int k, int K, int n, int N, float v[4]) {
-  if (VEC) {   // (N is a multiple of 4: a thread's columns are all inside or all outside)
-    if (k < K && n < N) load4<T>(w + (size_t)k * N + n, v);
-    else v[0] = v[1] = v[2] = v[3] = 0.f;
-  } else {
-    for (int e = 0; e < 4; ++e) v[e] = k < K && n + e < N ? load_f<T>(w + (size_t)k * N + n + e) : 0.f;
+// four weights as they were loaded: converted where they are multiplied, because a conversion in front of the activations' loads
+// would wait for the weights first, one memory round trip after the other
+template <typename T, bool VEC> struct PlainW4;
+template <bool VEC> struct PlainW4<float, VEC> {
+  float v[4];
+  __device__ __forceinline__ void value(float (&f)[4]) const { for (int e = 0; e < 4; ++e) f[e] = v[e]; }
+};
+template <> struct PlainW4<bf16_t, true> {
+  uint2 v;
+  __device__ __forceinline__ void value(float (&f)[4]) const {
+    f[0] = __uint_as_float(v.x << 16); f[1] = __uint_as_float(v.x & 0xFFFF0000u);
+    f[2] = __uint_as_float(v.y << 16); f[3] = __uint_as_float(v.y & 0xFFFF0000u);
   }
+};
+template <> struct PlainW4<bf16_t, false> {
+  uint32_t v[4];
+  __device__ __forceinline__ void value(float (&f)[4]) const { for (int e = 0; e < 4; ++e) f[e] = __uint_as_float(v[e] << 16); }
+};
+
+template <typename T, bool VEC>
+__device__ __forceinline__ PlainW4<T, VEC> plain_w4(const T* w, int k, int K, int n, int N) {
+  PlainW4<T, VEC> r{};
+  if constexpr (VEC) {   // (N is a multiple of 4: a thread's columns are all inside or all outside)
+    if (k < K && n < N) r = *reinterpret_cast<const PlainW4<T, VEC>*>(__builtin_assume_aligned(w + (size_t)k * N + n, 4 * sizeof(T)));
+  } else {
+    for (int e = 0; e < 4; ++e)
+      if (k < K && n + e < N) r.v[e] = w[(size_t)k * N + n + e];
+  }
+  return r;
 }
 
 // rows m0 .. m0 + MR - 1 of x times columns n .. n + 3 (per lane) of w; the sums over all K end up in `sum` [MR][64]
@@ -125,24 +148,29 @@ __device__ __forceinline__ void plain_product(const T* x, int M, int K, int m0, 
   const int c4 = (lane & 15) * 4, kg = t >> 4;
   float acc[MR][4] = {};
   for (int k0 = 0; k0 < K; k0 += PLAIN_KC) {
-    float wv[4][4][4];   // [pass][k][column]
+    PlainW4<T, VEC> wr[4][4];   // [pass][k]
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) plain_w4<T, VEC>(w, k0 + i * 64 + kg * 4 + e, K, n0 + c4, N, wv[i][e]);
+      for (int e = 0; e < 4; ++e) wr[i][e] = plain_w4<T, VEC>(w, k0 + i * 64 + kg * 4 + e, K, n0 + c4, N);
     if (k0 > 0) __syncthreads();   // the previous pass has been read
 #pragma unroll
     for (int m = 0; m < MR; ++m) xs[m][t] = m0 + m < M && k0 + t < K ? load_f<T>(x + (size_t)(m0 + m) * K + k0 + t) : 0.f;
     __syncthreads();
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 4; ++i) {
+      float wv[4][4];   // [k][column]
+#pragma unroll
+      for (int e = 0; e < 4; ++e) wr[i][e].value(wv[e]);
 #pragma unroll
       for (int m = 0; m < MR; ++m) {
         const float4 xv = *reinterpret_cast<const float4*>(&xs[m][i * 64 + kg * 4]);
 #pragma unroll
         for (int c = 0; c < 4; ++c)
-          acc[m][c] = fmaf(xv.w, wv[i][3][c], fmaf(xv.z, wv[i][2][c], fmaf(xv.y, wv[i][1][c], fmaf(xv.x, wv[i][0][c], acc[m][c]))));
+          acc[m][c] = fmaf(xv.w, wv[3][c], fmaf(xv.z, wv[2][c], fmaf(xv.y, wv[1][c], fmaf(xv.x, wv[0][c], acc[m][c]))));
       }
+    }
   }
 #pragma unroll
   for (int m = 0; m < MR; ++m)
