@@ -119,7 +119,6 @@ struct ladder_ctx {
   size_t qkv_cap = 0;
   char *qbuf = nullptr, *obuf = nullptr, *act = nullptr;
   float* gu = nullptr;
-  size_t gu_rows = 0;
   float *att_o = nullptr, *att_ml = nullptr;
   // fused decode path: ring of three residual buffers (x_m lives in ring[m % 3]), arrival tickets, and
   // the launch list of one step
@@ -362,16 +361,18 @@ int finish_residual(ladder_ctx* c, const GemmArgs& a, int rows, int nc, const in
 // layers, us): 8B shape 200 rows 470 / 401 / 401 / 401, 1000 rows 1040 / 1040 / 1040 / 1018; 70B R = 8 shard 300 rows 465 /
 // 466 / 387 / 387, 1000 rows 892 / 892 / 891 / 818; 1.2B 400 rows 282 / 282 / 258 / 258, 1000 rows 404 / 404 / 404 / 420 (a
 // rule by module, fused where K is not worth a split, was no better: 70B R = 8 at 1000 rows 893).
-// FEW_ROWS_SLOTS slots per buffer up to 256 rows, as many as fit the same buffer beyond.
-constexpr int FEW_ROWS = 1024, FEW_ROWS_SLOTS = 8;
+// A call's number of slots depends on its rows alone, not on what the context was sized for (the same call gives the same bits
+// in every context): FEW_ROWS_SLOTS up to 256 rows, beyond them as many as fit the buffer that 256 rows need (more were no
+// faster: 700 rows with 2048 / rows slots and with up to 8, two layers, us: 8B shape 869 / 885, 70B R = 8 shard 557 / 559, 1.2B 315 / 317).
+constexpr int FEW_ROWS = 1024, FEW_ROWS_SLOTS = 8, FEW_ROWS_FULL = 256;
 constexpr float SPLIT_KERNEL_US = 4.0f;   // a kernel of its own that adds up partial products, where the epilogue would do
 
 size_t row_slots_of(const ladder_config& g) {
   const size_t rows = (size_t)g.max_batch * g.max_tokens;
-  return std::max(rows, FEW_ROWS_SLOTS * std::min<size_t>(rows, 256));
+  return std::max(rows, FEW_ROWS_SLOTS * std::min<size_t>(rows, FEW_ROWS_FULL));
 }
 
-int max_slots(const ladder_config& g, int rows) { return (int)std::min<size_t>(FEW_ROWS_SLOTS, row_slots_of(g) / (size_t)rows); }
+int max_slots(int rows) { return std::min(FEW_ROWS_SLOTS, FEW_ROWS_SLOTS * FEW_ROWS_FULL / rows); }
 
 // one projection of a call of at most FEW_ROWS rows: out[slot][rows][N], returns the number of slots written
 int run_few_rows(ladder_ctx* c, const char* x, int ldx, const char* wp, int rows, int K, int N, float* out, hipStream_t s,
@@ -387,7 +388,7 @@ int run_few_rows(ladder_ctx* c, const char* x, int ldx, const char* wp, int rows
   }
   GemmArgs a{};
   a.x = (const bf16_t*)x; a.ldx = ldx; a.wp = wp; a.M = rows; a.K = K; a.N = N; a.out = out; a.epilogue = 0; a.row_scale = row_scale;
-  a.ksplit = gemm_ksplit(rows, N, K, max_slots(c->cfg, rows), 0.f);
+  a.ksplit = gemm_ksplit(rows, N, K, max_slots(rows), 0.f);
   a.out_stride = (size_t)rows * N;
   *slots = a.ksplit;
   HIP_TRY(c, timed(c, LADDER_K_GEMM, s, [&] { return launch_gemm_mfma(a, s); }));
@@ -412,10 +413,21 @@ int run_last_projection(ladder_ctx* c, int m, const char* x, const char* wp, int
   return fuse ? finish_residual(c, a, rows, nc, cons, s) : LADDER_OK;
 }
 
-// splits of the gate/up projection: its partial products have a buffer of their own, of gu_rows rows (slots times rows)
-int gate_up_ksplit(const ladder_config& g, int rows, size_t gu_rows) {
+// splits of the gate/up projection, by the rows in sixteens; its partial products have a buffer of their own, in which the
+// largest number of slots times rows fits (gu_rows_of)
+int gate_up_ksplit(const ladder_config& g, int rows) {
   if (rows <= 16 || rows > FEW_ROWS) return 1;
-  return gemm_ksplit(rows, 2 * g.inter, g.hidden, (int)std::min<size_t>(4, gu_rows / (size_t)rows), SPLIT_KERNEL_US);
+  return gemm_ksplit((rows + 15) / 16 * 16, 2 * g.inter, g.hidden, 4, SPLIT_KERNEL_US);
+}
+
+size_t gu_rows_of(const ladder_config& g) {
+  const size_t rows = std::min<size_t>((size_t)g.max_batch * g.max_tokens, FEW_ROWS);
+  size_t most = 0;
+  for (size_t r = 32; r < rows + 16; r += 16) {
+    const int n = gate_up_ksplit(g, (int)std::min(r, rows));
+    if (n > 1) most = std::max(most, (size_t)n * std::min(r, rows));
+  }
+  return most;
 }
 
 // one module of the plain path: three launches (attention) or two (MLP) for all computed shards, which leave a partial
@@ -471,7 +483,7 @@ int run_module(ladder_ctx* c, int m, int B, int T, int pos0, bool decode, hipStr
     LayerStore& L = c->store[(size_t)layer * g.n_real_shards + r];
     if (is_attn) {
       int qkv_slots = 1;
-      if (few && (T == 1 || rows <= 16 || gemm_ksplit(rows, c->nqkv, H, max_slots(g, rows), SPLIT_KERNEL_US) > 1)) {
+      if (few && (T == 1 || rows <= 16 || gemm_ksplit(rows, c->nqkv, H, max_slots(rows), SPLIT_KERNEL_US) > 1)) {
         const int rc = run_few_rows(c, yin, H, L.pqkv, rows, H, c->nqkv, c->qkv, s, &qkv_slots, c->y_scale[par]);
         if (rc) return rc;
       } else {
@@ -519,7 +531,7 @@ int run_module(ladder_ctx* c, int m, int B, int T, int pos0, bool decode, hipStr
       } else {
         GemmArgs a{};
         a.x = (const bf16_t*)yin; a.ldx = H; a.wp = L.pgu; a.M = rows; a.K = H; a.N = 2 * I; a.row_scale = c->y_scale[par];
-        const int gu_slots = gate_up_ksplit(g, rows, c->gu_rows);
+        const int gu_slots = gate_up_ksplit(g, rows);
         if (gu_slots > 1) { a.out = c->gu; a.epilogue = 0; a.ksplit = gu_slots; a.out_stride = (size_t)rows * 2 * I; }
         else { a.act = (bf16_t*)c->act; a.epilogue = 1; }
         HIP_TRY(c, timed(c, LADDER_K_GEMM, s, [&] { return launch_gemm_mfma(a, s); }));
@@ -1570,13 +1582,8 @@ static int init_impl(const ladder_config* cfg, void* hip_stream, ladder_ctx** ou
   INIT_TRY(dev_alloc(c, (void**)&c->qbuf, shards * rows * nq * d * esz, false));
   INIT_TRY(dev_alloc(c, (void**)&c->obuf, shards * rows * nq * d * esz, false));
   INIT_TRY(dev_alloc(c, (void**)&c->act, shards * rows * I * esz, false));
-  // the slots of a split gate/up projection: what the largest wants (looked up every 16 rows; a call in between that would
-  // want more takes a split less)
-  for (size_t r = 32; c->fast && r <= (size_t)FEW_ROWS && r < rows + 16; r += 16) {
-    const int n = gate_up_ksplit(g, (int)std::min(r, rows), (size_t)4 * FEW_ROWS);
-    if (n > 1) c->gu_rows = std::max(c->gu_rows, (size_t)n * std::min(r, rows));
-  }
-  if (c->gu_rows) INIT_TRY(dev_alloc(c, (void**)&c->gu, c->gu_rows * 2 * I * 4, false));
+  const size_t gu_rows = c->fast ? gu_rows_of(g) : 0;
+  if (gu_rows) INIT_TRY(dev_alloc(c, (void**)&c->gu, gu_rows * 2 * I * 4, false));
   if (c->fast) {
     INIT_TRY(dev_alloc(c, (void**)&c->ssq_part, (size_t)((H + 31) / 32) * rows * 4, false));
     for (int i = 0; i < 2; ++i) INIT_TRY(dev_alloc(c, (void**)&c->y_rs[i], rows * 4, false));

@@ -104,3 +104,20 @@ def test_wide_decode_attention_ignores_what_an_earlier_sequence_left(harness, nq
         ctx.free()
     for a, b in zip(*outs):
         assert torch.isfinite(a).all() and torch.equal(a, b)
+
+
+@pytest.mark.parametrize("shape", [dict(hidden=1024, n_q_heads=8, n_kv_heads=2, head_dim=128, inter=8192),
+                                   dict(hidden=8192, n_q_heads=8, n_kv_heads=1, head_dim=128, inter=3584)])
+def test_same_bits_in_contexts_of_any_capacity(harness, shape):
+    """What a context was sized for does not change how a call's products are split (700 and 1000 rows: the number of partial
+    products that would pay is larger than what the buffers of a small context hold)."""
+    w = WIDE.with_(name="capacity", prefill=1024, **shape)
+    tensors = harness.make_tensors(w, "cuda:0")
+    big = harness.build_gpu(w, tensors, max_tokens=4096, max_batch=4, max_seq=4096)
+    x = inputs.embeddings(w, 1, 1024, inputs.SEED_PREFILL, "cuda:0")
+    for rows in (17, 100, 250, 300, 337, 700, 1000):
+        own = harness.build_gpu(w, tensors, max_tokens=rows, max_seq=rows)
+        want, got = big.prefill(x[:, :rows].contiguous()), own.prefill(x[:, :rows].contiguous())
+        own.free()
+        assert torch.equal(want, got), rows
+    big.free()
