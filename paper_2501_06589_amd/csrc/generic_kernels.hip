@@ -95,7 +95,7 @@ hipError_t launch_reduce_norm(const ReduceNormArgs& a, bool is_bf16, hipStream_t
 
 // ------------------------------------------------------------------------------------------------
 // Plain projections: any size, both storage types, weights [K][N] as they were given, fp32 arithmetic.  One launch is
-// one step of a module for ALL computed shards (grid y) and all the matrices that read the same rows (q | k | v, or gate
+// one step of a module for ALL computed shards (grid z) and all the matrices that read the same rows (q | k | v, or gate
 // and up), with what follows as its epilogue: a decode step of a small model is a chain of launches, and what counts is how
 // many there are and how many memory round trips each one is long.  A workgroup takes MR rows x 64 columns and
 // the whole K: 16 lanes side by side cover the columns, four at a time, and 16 groups of lanes deal out K in fours; every
@@ -108,6 +108,14 @@ hipError_t launch_reduce_norm(const ReduceNormArgs& a, bool is_bf16, hipStream_t
 // 1.7 / 6.5 / 30.4, bf16 4.5 / 6.9 / 36.5 -> 1.3 / 4.7 / 20.9 (8.5 at 512 rows with the weights converted as they are loaded).
 // ------------------------------------------------------------------------------------------------
 constexpr int PLAIN_KC = 256;   // k per pass
+
+// blocks beyond what one grid dimension takes (fewer than 2^32 threads) go on in the second one; the kernel leaves at once where
+// its index is past the end
+__device__ __forceinline__ unsigned flat_block() { return blockIdx.y * gridDim.x + blockIdx.x; }
+static dim3 flat_grid(long long blocks, int n_shards) {
+  const long long x = blocks < (1 << 20) ? blocks : (1 << 20);
+  return dim3((unsigned)x, (unsigned)((blocks + x - 1) / x), (unsigned)n_shards);
+}
 
 // four weights as they were loaded: converted where they are multiplied, because a conversion in front of the activations' loads
 // would wait for the weights first, one memory round trip after the other
@@ -191,9 +199,11 @@ __global__ __launch_bounds__(256) void plain_gemm_kernel(PlainGemmArgs a) {
   __shared__ __attribute__((aligned(16))) float xs[MR][PLAIN_KC];
   __shared__ float red[4][MR][64];
   __shared__ float sum[2][MR][64];
-  const int t = threadIdx.x, shard = blockIdx.y;
-  const int m0 = (int)(blockIdx.x / (unsigned)a.n_blocks) * MR;
-  int blk = (int)(blockIdx.x % (unsigned)a.n_blocks), mat = 0;   // the matrices' column blocks side by side (SwiGLU: the gate's; the up matrix goes along)
+  const int t = threadIdx.x, shard = blockIdx.z;
+  const unsigned m_blk = flat_block() / (unsigned)a.n_blocks;
+  if (m_blk >= ((unsigned)a.M + MR - 1) / MR) return;
+  const int m0 = (int)m_blk * MR;
+  int blk = (int)(flat_block() % (unsigned)a.n_blocks), mat = 0;   // the matrices' column blocks side by side (SwiGLU: the gate's; the up matrix goes along)
   while (a.epilogue != PLAIN_SWIGLU && mat + 1 < a.n_mat && blk >= (a.N[mat] + 63) / 64) { blk -= (a.N[mat] + 63) / 64; ++mat; }
   const int n0 = blk * 64, N = a.N[mat];
   const T* x = reinterpret_cast<const T*>(a.x) + shard * a.x_stride;
@@ -246,9 +256,9 @@ template <typename T, int MR>
 static hipError_t launch_plain_gemm_t(PlainGemmArgs a, bool vec, hipStream_t s) {
   a.n_blocks = 0;
   for (int i = 0; i < (a.epilogue == PLAIN_SWIGLU ? 1 : a.n_mat); ++i) a.n_blocks += (a.N[i] + 63) / 64;
-  const long long blocks = (long long)a.n_blocks * ((a.M + MR - 1) / MR);   // (rows and columns in one grid dimension: the others end at 65535)
+  const long long blocks = (long long)a.n_blocks * (((long long)a.M + MR - 1) / MR);
   if (blocks > 0x7fffffff || a.n_shards > 65535) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)blocks, a.n_shards);
+  const dim3 grid = flat_grid(blocks, a.n_shards);
   if (vec) hipLaunchKernelGGL((plain_gemm_kernel<T, MR, true>), grid, dim3(256), 0, s, a);
   else hipLaunchKernelGGL((plain_gemm_kernel<T, MR, false>), grid, dim3(256), 0, s, a);
   return hipGetLastError();
@@ -336,7 +346,9 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(AttnGenericArgs a) {
   __shared__ __attribute__((aligned(16))) float ps[4][64];
   __shared__ float om[4][256], ms[4], ls[4];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int row = blockIdx.x / a.nq, h = blockIdx.x % a.nq, shard = blockIdx.y;
+  const unsigned unit = flat_block();
+  if (unit >= (unsigned)a.B * (unsigned)a.T * (unsigned)a.nq) return;
+  const int row = (int)(unit / (unsigned)a.nq), h = (int)(unit % (unsigned)a.nq), shard = blockIdx.z;
   const int b = row / a.T, t = row % a.T;
   const int kvh = h / (a.nq / a.nkv);
   const int n_vis = a.pos0 + t + 1;
@@ -410,7 +422,7 @@ hipError_t launch_attn_generic(const AttnGenericArgs& a, bool is_bf16, hipStream
   const long long units = (long long)a.B * a.T * a.nq;
   if (units <= 0 || a.n_shards <= 0) return hipSuccess;
   if (units > 0x7fffffff || a.n_shards > 65535 || a.d > 256) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)units, a.n_shards);
+  const dim3 grid = flat_grid(units, a.n_shards);
   const bool vec = a.d % 4 == 0;   // (a K row then starts on a boundary of four elements)
   if (is_bf16) {
     if (vec) hipLaunchKernelGGL((attn_generic_kernel<bf16_t, true>), grid, dim3(256), 0, s, a);

@@ -85,3 +85,20 @@ def test_overlapped_schedules_of_the_plain_path(harness):
     for r in runs[1:]:
         for a, b in zip(runs[0].gpu, r.gpu):
             assert np.array_equal(a, b)
+
+
+def test_more_blocks_than_one_grid_dimension_takes(harness):
+    """4 million rows, the most that 64-row tiles in the second grid dimension took: projections and attention have more than
+    2^24 blocks of 256 threads each. The last sequences come out as in a call of their own."""
+    w = BASE.with_(name="many_blocks", dtype="bf16", tp_degree=1, n_real_shards=1, hidden=8, n_q_heads=5, n_kv_heads=1, head_dim=2,
+                   inter=4160, batch=32767, prefill=128, decode_steps=0)
+    assert w.batch * w.prefill * w.n_q_heads > 1 << 24 and w.batch * w.prefill // 16 * (w.inter // 64) > 1 << 24
+    tensors = harness.make_tensors(w)
+    x = inputs.embeddings(w, w.batch, w.prefill, inputs.SEED_PREFILL, "cuda:0")
+    ctx = harness.build_gpu(w, tensors, kernel_path=ladder.LADDER_PATH_GENERIC)
+    got = ctx.prefill(x)
+    ctx.free()
+    few = harness.build_gpu(w.with_(batch=64), tensors, kernel_path=ladder.LADDER_PATH_GENERIC)
+    for first in (0, 16384, w.batch - 64):
+        assert torch.equal(got[first:first + 64], few.prefill(x[first:first + 64].contiguous())), first
+    few.free()
