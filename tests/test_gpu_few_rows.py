@@ -3,6 +3,7 @@ the edges of their tiles, splits and row ranges, against the CPU oracle."""
 import pytest
 import torch
 
+import wide_attention
 from paper_2501_06589_amd import inputs
 
 pytestmark = pytest.mark.gpu
@@ -42,15 +43,17 @@ def test_two_computed_shards_and_peers(harness):
     assert max(res.errs) < TOL, res.errs
 
 
-@pytest.mark.parametrize("nq,nkv,d", [(2, 2, 64), (4, 2, 128), (4, 1, 64), (8, 1, 128)])
-@pytest.mark.parametrize("cached", [1, 31, 127, 128, 300, 1025])
+@pytest.mark.parametrize("nq,nkv,d", wide_attention.HEADS)
+@pytest.mark.parametrize("cached", wide_attention.CACHED)
 def test_wide_decode_attention(harness, nq, nkv, d, cached):
     """Batches above 16: one and several splits, at the edges of a 32-key block, of a wavefront round and of a split, while
-    the position moves over them; every number of q heads per kv head."""
-    w = WIDE.with_(name="wide_attn", hidden=256, n_q_heads=nq, n_kv_heads=nkv, head_dim=d, inter=352, batch=17, prefill=0,
-                   kv_preload=cached, decode_steps=3)
-    res = harness.run_case(w, kv_preload=cached, decode_steps=3, max_tokens=1)
+    the position moves over them; every number of q heads per kv head. What is compared is what attention adds to the stream
+    (the MLP adds nothing): a single lost key shows (test_wide_attention_sensitivity.py)."""
+    w, tensors = wide_attention.case(nq, nkv, d, cached)
+    res = harness.run_case(w, kv_preload=cached, max_tokens=1, tensors=tensors)
     assert max(res.errs) < TOL, res.errs
+    errs = [wide_attention.error(w, i, g, r) for i, (g, r) in enumerate(zip(res.gpu, res.ref))]
+    assert max(errs) < wide_attention.TOL, errs
 
 
 def test_residual_epilogue_of_the_wide_ring_tile(harness):
