@@ -109,12 +109,14 @@ hipError_t launch_reduce_norm(const ReduceNormArgs& a, bool is_bf16, hipStream_t
 // ------------------------------------------------------------------------------------------------
 constexpr int PLAIN_KC = 256;   // k per pass
 
-// blocks beyond what one grid dimension takes (fewer than 2^32 threads) go on in the second one; the kernel leaves at once where
-// its index is past the end
-__device__ __forceinline__ unsigned flat_block() { return blockIdx.y * gridDim.x + blockIdx.x; }
+// Blocks beyond what one grid dimension takes (fewer than 2^32 threads) go on in the second one, in rows of 2^20; the kernel leaves
+// at once where its index is past the end.  (The row's length is a constant: gridDim comes from an implicit argument in memory,
+// 557 -> 606 us on the tiny fp32 model's prompt of 32 and 8 steps.)
+constexpr int FLAT_SHIFT = 20;
+__device__ __forceinline__ unsigned flat_block() { return (blockIdx.y << FLAT_SHIFT) + blockIdx.x; }
 static dim3 flat_grid(long long blocks, int n_shards) {
-  const long long x = blocks < (1 << 20) ? blocks : (1 << 20);
-  return dim3((unsigned)x, (unsigned)((blocks + x - 1) / x), (unsigned)n_shards);
+  const long long row = 1ll << FLAT_SHIFT;
+  return dim3((unsigned)(blocks < row ? blocks : row), (unsigned)((blocks + row - 1) / row), (unsigned)n_shards);
 }
 
 // four weights as they were loaded: converted where they are multiplied, because a conversion in front of the activations' loads
