@@ -124,3 +124,22 @@ def test_same_bits_in_contexts_of_any_capacity(harness, shape):
         own.free()
         assert torch.equal(want, got), rows
     big.free()
+
+
+@pytest.mark.parametrize("nq,nkv,d", [(2, 2, 64), (8, 1, 128), (2, 1, 128)])
+@pytest.mark.parametrize("tokens", [3, 33, 64, 65, 100, 130])
+def test_prefill_attention_ignores_what_an_earlier_sequence_left(harness, nq, nkv, d, tokens):
+    """The same for a prompt (up to 64 tokens and more take different kernels) in a slot that held a longer sequence."""
+    w = WIDE.with_(name="stale_prompt", hidden=256, n_q_heads=nq, n_kv_heads=nkv, head_dim=d, inter=352, batch=2, prefill=tokens,
+                   kv_preload=200, decode_steps=1)
+    tensors = harness.make_tensors(w)
+    k, v = (torch.full((2, nkv, tokens + 60, d), float("nan"), dtype=torch.bfloat16, device="cuda:0") for _ in range(2))
+    x = inputs.embeddings(w, 2, tokens, inputs.SEED_PREFILL).cuda()
+    outs = []
+    for used in (False, True):
+        ctx = harness.build_gpu(w, tensors)
+        if used:
+            ctx.load_kv(0, 0, k, v)
+        outs.append(ctx.prefill(x).cpu())
+        ctx.free()
+    assert torch.isfinite(outs[0]).all() and torch.equal(*outs)
