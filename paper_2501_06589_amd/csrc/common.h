@@ -16,6 +16,21 @@ __device__ __forceinline__ uint32_t f32_to_bf16x2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, (bf16x2_t){(__bf16)lo, (__bf16)hi});
 }
 
+// The attention kernels of the bf16 path take the cache in blocks of 32 positions and give what lies behind the last one a
+// probability of 0, which does not cancel an infinity or NaN that an earlier, longer sequence may have left there in V.  So the
+// V row is kept clear behind the last position, to the end of the 64 positions (a whole cache line: half a line costs a read of the
+// other half, 29 -> 37 us on a handed-over cache of 16 x 8 x 1024) that the next one falls into: by whoever stores the last position
+// of a prefill or of a handed-over cache, and by a step's append to the last of 64 positions, for the 64 behind it.  (Wide batches'
+// steps mask V in their attention and clear nothing.)  next: the next position, at: its place in the row.
+#define CACHE_BLOCK 64
+template <typename T> __device__ __forceinline__ void clear_block(T* at, int next, int max_seq) {
+  if (next >= max_seq) return;   // (the row's length is a multiple of the block's)
+  int n = CACHE_BLOCK - next % CACHE_BLOCK;
+  constexpr int E = 16 / sizeof(T);
+  for (; n % E; --n) *at++ = T(0);
+  for (; n > 0; n -= E, at += E) *reinterpret_cast<uint4*>(at) = make_uint4(0u, 0u, 0u, 0u);
+}
+
 template <typename T> __device__ __forceinline__ float load_f(const T* p);
 template <> __device__ __forceinline__ float load_f<float>(const float* p) { return *p; }
 template <> __device__ __forceinline__ float load_f<bf16_t>(const bf16_t* p) { return bf16_to_f32(*p); }
@@ -242,6 +257,6 @@ struct AttnPrefillArgs {
 };
 hipError_t launch_attn_prefill(const AttnPrefillArgs& a, hipStream_t s);
 
-// transposes caller-made V content [B][nkv][S][d] into the cache layout [B_cap][nkv][d][max_seq] and copies K
+// transposes caller-made V content [B][nkv][S][d] into the cache layout [B_cap][nkv][d][max_seq] and copies K (clear: see clear_block)
 hipError_t launch_load_kv(const void* k, const void* v, void* cache_k, void* cache_v, int B, int nkv, int S, int d,
-                          int max_seq, bool is_bf16, hipStream_t s);
+                          int max_seq, bool is_bf16, bool clear, hipStream_t s);

@@ -593,6 +593,15 @@ __device__ __forceinline__ bool gemv_job(const GemvJob& j, const void* wp, const
     }
   }
   if (CHAIN) gemv_signal_done(j, lb);
+  // the last position of a block: the block behind it is cleared for the next step (see clear_block; nothing of this step reads it)
+  if (tid < 16 * TN * 8 && tid / (TN * 8) < j.M && pre_pos % CACHE_BLOCK == CACHE_BLOCK - 1) {
+    const int row = tid / (TN * 8), col = grp * (TN * 16) + 2 * (tid % (TN * 8)), kvh = col / j.d - j.nq - j.nkv;
+    if (kvh >= 0) {
+      bf16_t* const next = j.cache_v + (((size_t)row * j.nkv + kvh) * j.d + col % j.d) * j.max_seq + pre_pos + 1;
+      clear_block(next, pre_pos + 1, j.max_seq);
+      clear_block(next + j.max_seq, pre_pos + 1, j.max_seq);
+    }
+  }
   return true;
 }
 

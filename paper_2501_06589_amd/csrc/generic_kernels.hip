@@ -318,6 +318,10 @@ __global__ void rope_append_kernel(RopeAppendArgs a) {
       T* vt = reinterpret_cast<T*>(a.cache_v) + (((size_t)b * a.nkv + kvh) * a.d + 2 * j) * a.max_seq + pos;
       store_f<T>(vt, e);
       store_f<T>(vt + a.max_seq, o);
+      if (!a.pos_dev && t == a.T - 1) {   // (a prefill)
+        clear_block(vt + 1, pos + 1, a.max_seq);
+        clear_block(vt + a.max_seq + 1, pos + 1, a.max_seq);
+      }
       return;
     }
     const int kvh = head - a.nq;
@@ -470,7 +474,7 @@ hipError_t launch_swiglu_parts(const float* parts, int n_parts, size_t part_stri
 // ------------------------------------------------------------------------------------------------
 template <typename T>
 __global__ void load_kv_kernel(const T* __restrict__ k, const T* __restrict__ v, T* __restrict__ ck,
-                               T* __restrict__ cv, int B, int nkv, int S, int d, int max_seq) {
+                               T* __restrict__ cv, int B, int nkv, int S, int d, int max_seq, bool clear) {
   const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   const long long total = (long long)B * nkv * S * d;
   if (gid >= total) return;
@@ -478,7 +482,9 @@ __global__ void load_kv_kernel(const T* __restrict__ k, const T* __restrict__ v,
   const int p = (int)((gid / d) % S);
   const long long bh = gid / ((long long)d * S);
   ck[((size_t)bh * max_seq + p) * d + i] = k[gid];
-  cv[((size_t)bh * d + i) * max_seq + p] = v[gid];
+  T* const at = cv + ((size_t)bh * d + i) * max_seq + p;
+  *at = v[gid];
+  if (clear && p == S - 1) clear_block(at + 1, S, max_seq);
 }
 
 // The same, 16 bytes per lane on both sides: a workgroup takes P positions of one (sequence, kv head), copies its K rows
@@ -488,7 +494,7 @@ __global__ void load_kv_kernel(const T* __restrict__ k, const T* __restrict__ v,
 // 16 x 8 x 1024 115 -> 29; 4 x 1 x 32001 117 -> 28.
 template <typename T, int P>
 __global__ __launch_bounds__(256) void load_kv_tiles_kernel(const T* __restrict__ k, const T* __restrict__ v, T* __restrict__ ck,
-                                                            T* __restrict__ cv, int S, int d, int max_seq) {
+                                                            T* __restrict__ cv, int S, int d, int max_seq, bool clear) {
   constexpr int E = 16 / sizeof(T);            // elements per 16 bytes
   constexpr int ROW = P + 4 / (int)sizeof(T);  // a turned row: one word of padding
   extern __shared__ __attribute__((aligned(16))) unsigned char load_kv_lds[];
@@ -509,6 +515,13 @@ __global__ __launch_bounds__(256) void load_kv_tiles_kernel(const T* __restrict_
   }
   __syncthreads();
   const int pieces = P / E;
+  // the last tile is stored as whole cache lines, zeros behind the last position (16 x 8 x 1023 positions: 31 -> 24 us); one that
+  // ends with its lines clears the next ones where asked to
+  if (n < P || (clear && p0 + P == S && S < max_seq)) {
+    const int from = n < P ? (n + E - 1) / E * E : P, m = ((n < P ? P : 2 * P) - from) / E;   // (the rows are whole tiles long)
+    for (int i = threadIdx.x; i < d * m; i += 256)
+      *reinterpret_cast<uint4*>(cv + (bh * d + i / m) * max_seq + p0 + from + i % m * E) = make_uint4(0u, 0u, 0u, 0u);
+  }
   for (int i = threadIdx.x; i < d * pieces; i += 256) {
     const int dim = i / pieces, p = i % pieces * E;
     if (p >= n) continue;
@@ -520,34 +533,34 @@ __global__ __launch_bounds__(256) void load_kv_tiles_kernel(const T* __restrict_
     if (p + E <= n) {
       *reinterpret_cast<uint4*>(dst) = u;   // (max_seq is a multiple of 128, p0 and p of E)
     } else {
-      for (int j = 0; p + j < n; ++j) dst[j] = e[j];
+      for (int j = 0; j < E; ++j) dst[j] = p + j < n ? e[j] : T(0);
     }
   }
 }
 
 template <typename T, int P>
-static hipError_t launch_load_kv_tiles(const void* k, const void* v, void* ck, void* cv, int B, int nkv, int S, int d, int max_seq, hipStream_t s) {
+static hipError_t launch_load_kv_tiles(const void* k, const void* v, void* ck, void* cv, int B, int nkv, int S, int d, int max_seq, bool clear, hipStream_t s) {
   const size_t lds = (size_t)d * (P + 4 / sizeof(T)) * sizeof(T);   // at most 36 KiB (d <= 256)
-  hipLaunchKernelGGL((load_kv_tiles_kernel<T, P>), dim3((S + P - 1) / P, B * nkv), dim3(256), lds, s, (const T*)k, (const T*)v, (T*)ck, (T*)cv, S, d, max_seq);
+  hipLaunchKernelGGL((load_kv_tiles_kernel<T, P>), dim3((S + P - 1) / P, B * nkv), dim3(256), lds, s, (const T*)k, (const T*)v, (T*)ck, (T*)cv, S, d, max_seq, clear);
   return hipGetLastError();
 }
 
 hipError_t launch_load_kv(const void* k, const void* v, void* cache_k, void* cache_v, int B, int nkv, int S, int d,
-                          int max_seq, bool is_bf16, hipStream_t s) {
+                          int max_seq, bool is_bf16, bool clear, hipStream_t s) {
   const long long total = (long long)B * nkv * S * d;
   if (total <= 0) return hipSuccess;
   // 16-byte accesses: the caller's tensors have to be aligned and a row has to be whole pieces (d need only be even), and
-  // the cache rows too (max_seq, a multiple of 128, and the library's own allocation); B * nkv is a grid dimension
-  const bool aligned = (((uintptr_t)k | (uintptr_t)v) & 15) == 0 && d % (is_bf16 ? 8 : 4) == 0 && d <= 256 && max_seq % 8 == 0 && (long long)B * nkv <= 65535;
-  if (aligned) return is_bf16 ? launch_load_kv_tiles<bf16_t, 64>(k, v, cache_k, cache_v, B, nkv, S, d, max_seq, s)
-                              : launch_load_kv_tiles<float, 32>(k, v, cache_k, cache_v, B, nkv, S, d, max_seq, s);
+  // the cache rows whole tiles (max_seq, a multiple of 128, and the library's own allocation); B * nkv is a grid dimension
+  const bool aligned = (((uintptr_t)k | (uintptr_t)v) & 15) == 0 && d % (is_bf16 ? 8 : 4) == 0 && d <= 256 && max_seq % 64 == 0 && (long long)B * nkv <= 65535;
+  if (aligned) return is_bf16 ? launch_load_kv_tiles<bf16_t, 64>(k, v, cache_k, cache_v, B, nkv, S, d, max_seq, clear, s)
+                              : launch_load_kv_tiles<float, 32>(k, v, cache_k, cache_v, B, nkv, S, d, max_seq, clear, s);
   const unsigned blocks = (unsigned)((total + 255) / 256);
   if (is_bf16)
     hipLaunchKernelGGL(load_kv_kernel<bf16_t>, dim3(blocks), dim3(256), 0, s, (const bf16_t*)k, (const bf16_t*)v,
-                       (bf16_t*)cache_k, (bf16_t*)cache_v, B, nkv, S, d, max_seq);
+                       (bf16_t*)cache_k, (bf16_t*)cache_v, B, nkv, S, d, max_seq, clear);
   else
     hipLaunchKernelGGL(load_kv_kernel<float>, dim3(blocks), dim3(256), 0, s, (const float*)k, (const float*)v,
-                       (float*)cache_k, (float*)cache_v, B, nkv, S, d, max_seq);
+                       (float*)cache_k, (float*)cache_v, B, nkv, S, d, max_seq, clear);
   return hipGetLastError();
 }
 

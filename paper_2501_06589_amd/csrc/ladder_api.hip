@@ -1746,7 +1746,7 @@ int ladder_load_kv(ladder_ctx* c, int32_t layer, int32_t shard, const void* k, c
   if (B <= 0 || B > g.max_batch || S <= 0) return fail(c, LADDER_E_SHAPE, "B or S out of range");
   if (S > g.max_seq) return fail(c, LADDER_E_OVERFLOW, "S exceeds max_seq");
   LayerStore& L = c->store[(size_t)layer * g.n_real_shards + shard];
-  HIP_TRY(c, launch_load_kv(k, v, L.cache_k, L.cache_v, B, g.n_kv_heads, S, g.head_dim, c->s_cap, c->bf16, c->main));
+  HIP_TRY(c, launch_load_kv(k, v, L.cache_k, L.cache_v, B, g.n_kv_heads, S, g.head_dim, c->s_cap, c->bf16, c->fused, c->main));
   L.kv_B = B;
   L.kv_S = S;
   bool all = true;

@@ -149,6 +149,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x4_t (&acc)[
           bf16_t* vt = a.cache_v + (((size_t)seq * a.nkv + (head - a.nq - a.nkv)) * a.d + dim) * a.max_seq + pos;
 #pragma unroll
           for (int r = 0; r < 4; ++r) vt[(size_t)r * a.max_seq] = f32_to_bf16(v4[r]);
+          if (m % a.T == a.T - 1)
+            for (int r = 0; r < 4; ++r) clear_block(vt + (size_t)r * a.max_seq + 1, pos + 1, a.max_seq);
         }
       }
     }
@@ -822,14 +824,8 @@ hipError_t launch_gemm_mfma(const GemmArgs& given, hipStream_t s) {
 //                                 the same key order (two 8-byte loads per lane).
 // One wavefront owns QT tiles of 16 queries of one q head; a workgroup = 4 wavefronts.
 // ------------------------------------------------------------------------------------------------
-// two bf16 V entries of which the first `keep` are the sequence's (any number): the others, which an earlier, longer sequence may
-// have left as infinities or NaN, are cleared, because a probability of 0 does not cancel those
-__device__ __forceinline__ uint32_t keep_entries(uint32_t v, int keep) {
-  return v & ((keep > 0 ? 0x0000FFFFu : 0u) | (keep > 1 ? 0xFFFF0000u : 0u));
-}
-
 template <int D, int QT>
-__global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnPrefillArgs a) {
+__global__ __launch_bounds__(256) void attn_prefill_kernel(AttnPrefillArgs a) {
   constexpr int DS = D / 32;  // 32-dim slabs
   constexpr int DT = D / 16;  // 16-dim output tiles
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -881,13 +877,6 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(AttnPrefillArgs a)
       const uint2 lo = *reinterpret_cast<const uint2*>(vp);
       const uint2 hi = *reinterpret_cast<const uint2*>(vp + 16);
       vreg[dt] = make_uint4(lo.x, lo.y, hi.x, hi.y);
-    }
-    if (kb + 32 > a.pos0 + a.T) {   // (uniform) the block crosses the end of the sequence
-      const int keep = a.pos0 + a.T - kb - 4 * q;
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-        vreg[dt] = make_uint4(keep_entries(vreg[dt].x, keep), keep_entries(vreg[dt].y, keep - 2),
-                              keep_entries(vreg[dt].z, keep - 16), keep_entries(vreg[dt].w, keep - 18));
     }
 #pragma unroll
     for (int qt = 0; qt < QT; ++qt) {
@@ -1034,15 +1023,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_lds_kernel(AttnPrefillArg
       vst[i] = *reinterpret_cast<const u32x4_t*>(vc + (size_t)vrow * a.max_seq + kb + vcx * 8);
     }
   };
-  auto stash = [&](int buf, int blk) {   // registers -> LDS
-    if (blk * 32 + 32 > a.pos0 + a.T) {   // (uniform) the block crosses the end of the sequence
-#pragma unroll
-      for (int i = 0; i < SEGS; ++i) {
-        const int keep = a.pos0 + a.T - blk * 32 - 8 * ((tid + 256 * i) & 3);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) vst[i][e] = keep_entries(vst[i][e], keep - 2 * e);
-      }
-    }
+  auto stash = [&](int buf) {   // registers -> LDS
 #pragma unroll
     for (int i = 0; i < SEGS; ++i) {
       const int seg = tid + 256 * i;
@@ -1055,13 +1036,12 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_lds_kernel(AttnPrefillArg
   };
 
   fetch(0);
-  stash(0, 0);
+  stash(0);
   __syncthreads();
   for (int blk = 0; blk < n_blk; ++blk) {
     const int buf = blk & 1;
     const int kb = blk * 32;
-    const int next = min(blk + 1, n_blk - 1);
-    fetch(next);   // next block's tiles travel while this one is computed
+    fetch(min(blk + 1, n_blk - 1));   // next block's tiles travel while this one is computed
     if (kb <= my_last && t0 < a.T) {
       const unsigned char* kl = &lds[buf][0];
       const unsigned char* vl = &lds[buf][KBYTES];
@@ -1117,7 +1097,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_lds_kernel(AttnPrefillArg
         for (int qt = 0; qt < QT; ++qt) oacc[qt][dt] = mfma16(vf, pb[qt], oacc[qt][dt]);
       }
     }
-    stash(buf ^ 1, next);   // that buffer was last read before the previous barrier
+    stash(buf ^ 1);   // that buffer was last read before the previous barrier
     __syncthreads();
   }
   if (t0 >= a.T) return;

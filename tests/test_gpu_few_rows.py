@@ -84,31 +84,6 @@ def test_products_of_a_single_stage(harness, hidden, inter, rows):
     assert max(res.errs) < TOL, res.errs
 
 
-@pytest.mark.parametrize("nq,nkv,d", [(2, 2, 64), (8, 1, 128)])
-@pytest.mark.parametrize("cached", [1, 30, 129, 1025])
-def test_wide_decode_attention_ignores_what_an_earlier_sequence_left(harness, nq, nkv, d, cached):
-    """A cache slot that held a longer sequence with infinities and NaN behind the present position: same bits as a fresh
-    context, while the position moves through the block that holds them."""
-    w = WIDE.with_(name="stale", hidden=256, n_q_heads=nq, n_kv_heads=nkv, head_dim=d, inter=352, batch=17, prefill=0,
-                   kv_preload=cached + 40, decode_steps=3)
-    tensors = harness.make_tensors(w)
-    k, v = (t.cuda() for t in inputs.kv_cache(w, 0, 0, w.batch, cached))
-    bad_k, bad_v = (torch.cat([t, torch.empty_like(t[:, :, :1]).expand(-1, -1, 40, -1)], 2).contiguous() for t in (k, v))
-    for t in (bad_k, bad_v):
-        t[:, :, cached:] = torch.tensor([float("nan"), float("inf"), -float("inf"), 1.0]).repeat(10)[None, None, :, None].cuda()
-    xs = [inputs.embeddings(w, w.batch, 1, inputs.SEED_DECODE0 + i)[:, 0].contiguous().cuda() for i in range(3)]
-    outs = []
-    for used in (False, True):
-        ctx = harness.build_gpu(w, tensors, max_tokens=1)
-        if used:
-            ctx.load_kv(0, 0, bad_k, bad_v)
-        ctx.load_kv(0, 0, k, v)
-        outs.append([ctx.decode_step(x).cpu() for x in xs])
-        ctx.free()
-    for a, b in zip(*outs):
-        assert torch.isfinite(a).all() and torch.equal(a, b)
-
-
 @pytest.mark.parametrize("shape", [dict(hidden=1024, n_q_heads=8, n_kv_heads=2, head_dim=128, inter=8192),
                                    dict(hidden=8192, n_q_heads=8, n_kv_heads=1, head_dim=128, inter=3584)])
 def test_same_bits_in_contexts_of_any_capacity(harness, shape):
@@ -124,22 +99,3 @@ def test_same_bits_in_contexts_of_any_capacity(harness, shape):
         own.free()
         assert torch.equal(want, got), rows
     big.free()
-
-
-@pytest.mark.parametrize("nq,nkv,d", [(2, 2, 64), (8, 1, 128), (2, 1, 128)])
-@pytest.mark.parametrize("tokens", [3, 33, 64, 65, 100, 130])
-def test_prefill_attention_ignores_what_an_earlier_sequence_left(harness, nq, nkv, d, tokens):
-    """The same for a prompt (up to 64 tokens and more take different kernels) in a slot that held a longer sequence."""
-    w = WIDE.with_(name="stale_prompt", hidden=256, n_q_heads=nq, n_kv_heads=nkv, head_dim=d, inter=352, batch=2, prefill=tokens,
-                   kv_preload=200, decode_steps=1)
-    tensors = harness.make_tensors(w)
-    k, v = (torch.full((2, nkv, tokens + 60, d), float("nan"), dtype=torch.bfloat16, device="cuda:0") for _ in range(2))
-    x = inputs.embeddings(w, 2, tokens, inputs.SEED_PREFILL).cuda()
-    outs = []
-    for used in (False, True):
-        ctx = harness.build_gpu(w, tensors)
-        if used:
-            ctx.load_kv(0, 0, k, v)
-        outs.append(ctx.prefill(x).cpu())
-        ctx.free()
-    assert torch.isfinite(outs[0]).all() and torch.equal(*outs)
