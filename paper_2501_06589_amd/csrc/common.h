@@ -181,7 +181,7 @@ struct GemvArgs {
 // launch shape of the skinny GEMM for a problem: column tiles per workgroup, wavefronts per workgroup,
 // k tiles per register buffer, workgroups along K (1 unless allow_ksplit)
 struct GemvPlan { int tn, waves, u, ksplit; };
-GemvPlan gemv_plan(int M, int N, int K, bool allow_ksplit);
+GemvPlan gemv_plan(int N, int K, bool allow_ksplit);
 hipError_t launch_gemv(const GemvArgs& a, hipStream_t s);
 
 struct AttnDecodeArgs {

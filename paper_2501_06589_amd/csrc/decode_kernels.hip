@@ -60,7 +60,7 @@ hipError_t launch_repack_tiles(const bf16_t* src, void* dst, int K, int N, int N
 // ------------------------------------------------------------------------------------------------
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4_t;
 
-template <int MT, int WAVES, int U, int TN>
+template <int WAVES, int U, int TN>
 __global__ __launch_bounds__(WAVES * 64) void gemv_mfma_kernel(GemvArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int b = lane & 15, q = lane >> 4;
@@ -75,43 +75,32 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_mfma_kernel(GemvArgs a) {
   const int kt0 = wg0 + wave * U;
   const int kt1 = wg1;
 
-  f32x4_t acc[TN][MT];
+  f32x4_t acc[TN];
 #pragma unroll
-  for (int j = 0; j < TN; ++j)
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[j][mt] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+  for (int j = 0; j < TN; ++j) acc[j] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
 
   const u32x4_t* wptr = reinterpret_cast<const u32x4_t*>(a.wp) + ((size_t)nt0 * KT) * 64 + lane;
-  const bf16_t* xptr[MT];
-  bool rowok[MT];
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt) {
-    rowok[mt] = mt * 16 + b < a.M;
-    xptr[mt] = a.x + (size_t)min(mt * 16 + b, a.M - 1) * a.ldx + q * 8;
-  }
-  u32x4_t wa[TN][U], wb[TN][U], xa[MT][U], xb[MT][U];
-  auto load = [&](u32x4_t (&wv)[TN][U], u32x4_t (&xv)[MT][U], int kt) {
+  const bool rowok = b < a.M;
+  const bf16_t* xptr = a.x + (size_t)min(b, a.M - 1) * a.ldx + q * 8;
+  u32x4_t wa[TN][U], wb[TN][U], xa[U], xb[U];
+  auto load = [&](u32x4_t (&wv)[TN][U], u32x4_t (&xv)[U], int kt) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int ktc = min(kt + u, kt1 - 1);
 #pragma unroll
       for (int j = 0; j < TN; ++j) wv[j][u] = __builtin_nontemporal_load(wptr + ((size_t)j * KT + ktc) * 64);
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) xv[mt][u] = *reinterpret_cast<const u32x4_t*>(xptr[mt] + (size_t)ktc * 32);
+      xv[u] = *reinterpret_cast<const u32x4_t*>(xptr + (size_t)ktc * 32);
     }
   };
-  auto fma = [&](const u32x4_t (&wv)[TN][U], const u32x4_t (&xv)[MT][U], int kt) {
+  auto fma = [&](const u32x4_t (&wv)[TN][U], const u32x4_t (&xv)[U], int kt) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const bool kok = kt + u < kt1;
+      const u32x4_t xz = (kok && rowok) ? xv[u] : (u32x4_t){0u, 0u, 0u, 0u};
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        const u32x4_t xz = (kok && rowok[mt]) ? xv[mt][u] : (u32x4_t){0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[j][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wv[j][u]),
-                                                              __builtin_bit_cast(bf16x8_t, xz), acc[j][mt], 0, 0, 0);
-      }
+      for (int j = 0; j < TN; ++j)
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wv[j][u]),
+                                                        __builtin_bit_cast(bf16x8_t, xz), acc[j], 0, 0, 0);
     }
   };
   if (kt0 < kt1) {
@@ -128,54 +117,44 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_mfma_kernel(GemvArgs a) {
     }
   }
 
-  // acc[j][mt][r] = out[row = mt*16 + b][col = (nt0 + j)*16 + 4q + r]; reduce over the waves through LDS,
-  // 4 (tile, row-tile) slots per round
-  constexpr int SLOTS = TN * MT, PER_ROUND = SLOTS < 4 ? SLOTS : 4;
-  __shared__ float red[WAVES][PER_ROUND][16][17];  // [wave][slot][col in tile][row in tile]
+  // acc[j][r] = out[row = b][col = (nt0 + j)*16 + 4q + r]; reduce over the waves through LDS
+  __shared__ float red[WAVES][TN][16][17];  // [wave][tile][col in tile][row]
   const int I = a.N >> 1;
 #pragma unroll
-  for (int s0 = 0; s0 < SLOTS; s0 += PER_ROUND) {
-    if (s0 > 0) __syncthreads();
+  for (int j = 0; j < TN; ++j)
 #pragma unroll
-    for (int s = 0; s < PER_ROUND; ++s) {
-      const int j = (s0 + s) / MT, mt = (s0 + s) % MT;
+    for (int r = 0; r < 4; ++r) red[wave][j][4 * q + r][b] = acc[j][r];
+  __syncthreads();
+  if (a.epilogue == 0) {
+    for (int i = threadIdx.x; i < TN * 256; i += WAVES * 64) {
+      const int j = i >> 8, row = (i >> 4) & 15, col16 = i & 15;
+      const int col = (nt0 + j) * 16 + col16;
+      if (row < a.M && col < a.N) {
+        float v = 0.f;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) red[wave][s][4 * q + r][b] = acc[j][mt][r];
-    }
-    __syncthreads();
-    if (a.epilogue == 0) {
-      for (int i = threadIdx.x; i < PER_ROUND * 256; i += WAVES * 64) {
-        const int s = i >> 8, row16 = (i >> 4) & 15, col16 = i & 15;
-        const int j = (s0 + s) / MT, mt = (s0 + s) % MT;
-        const int row = mt * 16 + row16, col = (nt0 + j) * 16 + col16;
-        if (row < a.M && col < a.N) {
-          float v = 0.f;
-#pragma unroll
-          for (int w = 0; w < WAVES; ++w) v += red[w][s][col16][row16];
-          a.out[(size_t)(a.slot0 + ks) * a.out_stride + (size_t)row * a.N + col] = v;
-        }
+        for (int w = 0; w < WAVES; ++w) v += red[w][j][col16][row];
+        a.out[(size_t)(a.slot0 + ks) * a.out_stride + (size_t)row * a.N + col] = v;
       }
-    } else {
-      // SwiGLU: tile columns 0..7 are gate columns 8nt..8nt+7, columns 8..15 the matching up columns
-      for (int i = threadIdx.x; i < PER_ROUND * 128; i += WAVES * 64) {
-        const int s = i >> 7, row16 = (i >> 3) & 15, c8 = i & 7;
-        const int j = (s0 + s) / MT, mt = (s0 + s) % MT;
-        const int row = mt * 16 + row16, col = (nt0 + j) * 8 + c8;
-        if (row < a.M && col < I) {
-          float g = 0.f, u = 0.f;
+    }
+  } else {
+    // SwiGLU: tile columns 0..7 are gate columns 8nt..8nt+7, columns 8..15 the matching up columns
+    for (int i = threadIdx.x; i < TN * 128; i += WAVES * 64) {
+      const int j = i >> 7, row = (i >> 3) & 15, c8 = i & 7;
+      const int col = (nt0 + j) * 8 + c8;
+      if (row < a.M && col < I) {
+        float g = 0.f, u = 0.f;
 #pragma unroll
-          for (int w = 0; w < WAVES; ++w) {
-            g += red[w][s][c8][row16];
-            u += red[w][s][c8 + 8][row16];
-          }
-          a.act[(size_t)row * I + col] = f32_to_bf16(g / (1.0f + __expf(-g)) * u);
+        for (int w = 0; w < WAVES; ++w) {
+          g += red[w][j][c8][row];
+          u += red[w][j][c8 + 8][row];
         }
+        a.act[(size_t)row * I + col] = f32_to_bf16(g / (1.0f + __expf(-g)) * u);
       }
     }
   }
 }
 
-GemvPlan gemv_plan(int M, int N, int K, bool allow_ksplit) {
+GemvPlan gemv_plan(int N, int K, bool allow_ksplit) {
   GemvPlan p;
   const int NT = N / 16, KT = K / 32;
   p.tn = (NT <= 192 && NT % 4 == 0) ? 4 : 2;
@@ -184,26 +163,20 @@ GemvPlan gemv_plan(int M, int N, int K, bool allow_ksplit) {
   p.ksplit = 1;
   if (allow_ksplit)
     while (groups * p.ksplit * p.waves < 1536 && KT / (p.ksplit * 2 * p.waves) >= 8 && p.ksplit < 8) p.ksplit *= 2;
-  p.u = (M <= 16 && p.waves == 4 && p.tn == 2) ? 4 : 2;
+  p.u = p.waves == 4 && p.tn == 2 ? 4 : 2;
   return p;
-}
-
-template <int MT>
-static hipError_t launch_gemv_mt(const GemvArgs& a, const GemvPlan& p, hipStream_t s) {
-  const dim3 grid(a.N / 16 / p.tn, a.ksplit), block(p.waves * 64);
-  if (p.waves == 8 && p.tn == 2) hipLaunchKernelGGL((gemv_mfma_kernel<MT, 8, 2, 2>), grid, block, 0, s, a);
-  else if (p.waves == 8 && p.tn == 4) hipLaunchKernelGGL((gemv_mfma_kernel<MT, 8, 2, 4>), grid, block, 0, s, a);
-  else if (p.waves == 4 && p.tn == 4) hipLaunchKernelGGL((gemv_mfma_kernel<MT, 4, 2, 4>), grid, block, 0, s, a);
-  else if (p.u == 4) hipLaunchKernelGGL((gemv_mfma_kernel<MT, 4, 4, 2>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((gemv_mfma_kernel<MT, 4, 2, 2>), grid, block, 0, s, a);
-  return hipGetLastError();
 }
 
 hipError_t launch_gemv(const GemvArgs& a, hipStream_t s) {
   if (a.M <= 0 || a.M > 16 || (a.N & 31) || (a.K & 31)) return hipErrorInvalidValue;
-  GemvPlan p = gemv_plan(a.M, a.N, a.K, a.epilogue == 0);
+  const GemvPlan p = gemv_plan(a.N, a.K, a.epilogue == 0);
   if (a.ksplit != p.ksplit) return hipErrorInvalidValue;  // the caller sizes its slots from the same plan
-  return launch_gemv_mt<1>(a, p, s);
+  const dim3 grid(a.N / 16 / p.tn, a.ksplit), block(p.waves * 64);
+  if (p.waves == 8 && p.tn == 2) hipLaunchKernelGGL((gemv_mfma_kernel<8, 2, 2>), grid, block, 0, s, a);
+  else if (p.waves == 8) hipLaunchKernelGGL((gemv_mfma_kernel<8, 2, 4>), grid, block, 0, s, a);
+  else if (p.tn == 4) hipLaunchKernelGGL((gemv_mfma_kernel<4, 2, 4>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((gemv_mfma_kernel<4, 4, 2>), grid, block, 0, s, a);
+  return hipGetLastError();
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -400,7 +373,7 @@ __global__ void attn_combine_kernel(AttnDecodeArgs a) {
   a.o[(size_t)bi * a.nq * D + h * D + t] = f32_to_bf16(o / stat[0]);
 }
 
-// splits of a (sequence, kv head): as many as give the chip two workgroups per CU and no more (a few workgroups of a second
+// splits of a (sequence, kv head): as many as give the chip (256 CUs) two workgroups per CU and no more (a few workgroups of a second
 // round cost a round), of at least 128 positions each
 int attn_decode_splits(int B, int nkv, int max_seq) {
   const int want = 512 / (B * nkv), most = (max_seq + 127) / 128;

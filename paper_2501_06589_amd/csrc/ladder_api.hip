@@ -359,8 +359,9 @@ int finish_residual(ladder_ctx* c, const GemmArgs& a, int rows, int nc, const in
 // number of columns) and leave partial products, which the next kernel (rotary + append, SwiGLU, reduce + norm) adds up.
 // Beyond, the residual update is an epilogue (fuse_residual).  Measured with the line at 128 / 256 / 512 / 1024 rows (two
 // layers, us): 8B shape 200 rows 470 / 401 / 401 / 401, 1000 rows 1040 / 1040 / 1040 / 1018; 70B R = 8 shard 300 rows 465 /
-// 466 / 387 / 387, 1000 rows 892 / 892 / 891 / 818; 1.2B 400 rows 282 / 282 / 258 / 258, 1000 rows 404 / 404 / 404 / 420 (a
-// rule by module, fused where K is not worth a split, was no better: 70B R = 8 at 1000 rows 893).
+// 466 / 387 / 387, 1000 rows 892 / 892 / 891 / 818; 1.2B 400 rows 282 / 282 / 258 / 258, 1000 rows 404 / 404 / 404 / 420 (its K
+// is not worth a split at 1000 rows, so it would be 4 % better off with the epilogue, the wider shapes 2 - 8 % worse; a rule by
+// module, fused where K is not worth a split, was no better: 70B R = 8 at 1000 rows 893).
 // A call's number of slots depends on its rows alone, not on what the context was sized for (the same call gives the same bits
 // in every context): FEW_ROWS_SLOTS up to 256 rows, beyond them as many as fit the buffer that 256 rows need (more were no
 // faster: 700 rows with 2048 / rows slots and with up to 8, two layers, us: 8B shape 869 / 885, 70B R = 8 shard 557 / 559, 1.2B 315 / 317).
@@ -380,7 +381,7 @@ int run_few_rows(ladder_ctx* c, const char* x, int ldx, const char* wp, int rows
   if (rows <= 16) {
     GemvArgs a{};
     a.x = (const bf16_t*)x; a.ldx = ldx; a.wp = wp; a.M = rows; a.K = K; a.N = N;
-    a.ksplit = gemv_plan(rows, N, K, true).ksplit;
+    a.ksplit = gemv_plan(N, K, true).ksplit;
     a.out = out; a.out_stride = (size_t)rows * N; a.slot0 = 0; a.epilogue = 0;
     *slots = a.ksplit;
     HIP_TRY(c, timed(c, LADDER_K_GEMV, s, [&] { return launch_gemv(a, s); }));
@@ -398,7 +399,7 @@ int run_few_rows(ladder_ctx* c, const char* x, int ldx, const char* wp, int rows
 // the last projection of module m: (fuse) the residual update, or the partial products in out[slot][rows][hidden]
 int run_last_projection(ladder_ctx* c, int m, const char* x, const char* wp, int rows, int K, float* out, bool fuse, float* x_copy,
                         hipStream_t s, int* slots) {
-  if (rows <= FEW_ROWS && !fuse) {
+  if (rows <= FEW_ROWS) {   // (never with fuse)
     int n = 0;
     const int rc = run_few_rows(c, x, K, wp, rows, K, c->cfg.hidden, out, s, &n);
     *slots += n;
@@ -663,7 +664,9 @@ int forward_body(ladder_ctx* c, const void* x_in, int B, int T, int pos0, bool d
   const int rows = B * T;
   // calls with more than 64 rows (prefill) run in order on one stream: each of their kernels fills the
   // chip, and the same work measured 4 % (reduce on the side stream) to 16 % (two module streams) slower
-  // when spread over streams
+  // when spread over streams.  Up to 64 rows the caller's choice stands; two layers, us, two module streams / reduces on a side
+  // stream / in order: 8B shape 17 rows 204 / 259 / 212, 64 rows 242 / 313 / 264, decode of 64 sequences 354 / 420 / 374; 70B
+  // R = 8 shard 148 / 191 / 142, 166 / 219 / 173, 188 / 240 / 189; 1.2B 115 / 146 / 109, 126 / 159 / 125, 235 / 270 / 236
   // (and so does a pipeline stage's call: its hand-over reads the stream between the last modules)
   // (and so do calls whose kernels are shorter than the events between two streams: a layer of the plain path under
   // 32 MB of weights.  Measured, prompt of 32 and 8 steps, overlapped / in order, us: tiny model (2.8 MB) 1078 / 556, 10 MB
@@ -1980,7 +1983,7 @@ static int head_body(ladder_ctx* c, const float* x, int rows, char* y, float* lo
     PlainGemmArgs a{};
     a.x = y; a.M = rows; a.K = H; a.n_shards = 1; a.n_mat = 1; a.w[0] = c->head_w; a.N[0] = V; a.epilogue = PLAIN_OUT; a.out = logits;
     HIP_TRY(c, launch_plain_gemm(a, c->bf16, s));
-  } else if (rows <= 16 && (V & 31) == 0 && gemv_plan(rows, V, H, true).ksplit == 1) {   // (what the skinny GEMM takes: whole pairs of tiles, and so many that K is not split)
+  } else if (rows <= 16 && (V & 31) == 0 && gemv_plan(V, H, true).ksplit == 1) {   // (what the skinny GEMM takes: whole pairs of tiles, and so many that K is not split)
     GemvArgs a{};
     a.x = (const bf16_t*)y; a.ldx = H; a.wp = c->head_wp; a.M = rows; a.K = H; a.N = V; a.ksplit = 1;
     a.out = logits; a.out_stride = (size_t)rows * V; a.slot0 = 0; a.epilogue = 0;

@@ -50,7 +50,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x4_t (&acc)[
   } else if (a.epilogue == 3) {
     // residual update; the summation order per element is fixed: old value, product, peers 0, 1, ...
     // The operands (old values, the first three peers) of two column tiles are requested at once.
-    constexpr int PB = 3, JB = JT < 2 ? 1 : 2, JG = JT / JB, STEPS = WM * JG;
+    constexpr int PB = 3, JB = JT < 2 ? 1 : 2, JG = JT / JB, STEPS = WM * JG;   // (JT = 1, 64 x 64 tiles: compiled, never chosen)
     struct Operands { float4 xo[JB]; uint2 pk[JB][PB]; };
     Operands o;
     auto row_of = [&](int mt) { return (size_t)min(m0 + mt * 16 + b, a.M - 1) * a.N; };
@@ -551,7 +551,7 @@ static hipError_t launch_gemm_lds(const GemmArgs& a, hipStream_t s) {
 // Few or ragged rows: BM x BN workgroup tile, WR x WC wavefronts, K in stages of 64 through a ring of S stages in LDS,
 // optionally split over ksplit workgroups whose partial products the caller's next kernel adds up.  With up to a few
 // hundred rows the product is bound by the one pass over the weights, so what counts is how many bytes of them are in
-// flight on how many CUs: S - 1 stages of direct-to-LDS loads per workgroup (64 - 120 KiB, one workgroup per CU) and, by
+// flight on how many CUs: S - 1 stages of direct-to-LDS loads per workgroup (80 - 128 KiB, one workgroup per CU) and, by
 // the split of K, a workgroup for every CU whatever N is.  Both operands are staged as in gemm_lds_kernel (weights: packed
 // tiles as they stand; activations: 8 rows x 64 k per load, XOR-swizzled).  K is a multiple of 32; an odd last k tile
 // half-fills its stage.
@@ -734,10 +734,12 @@ enum { TILE_64x64, TILE_64x128, TILE_128x64, TILE_128x128, TILE_128x256, TILE_25
 static const struct { int bm, bn; float stage_us, alone; } gemm_tiles[TILE_COUNT] = {
     {64, 64, 0.24f, 1.0f}, {64, 128, 0.39f, 1.0f}, {128, 64, 0.35f, 0.87f}, {128, 128, 0.58f, 0.82f}, {128, 256, 0.99f, 0.85f}, {256, 256, 1.59f, 0.74f}};
 
-// Estimated time (us) of a tile shape and split: the larger of the rounds of one workgroup per CU (2.6 us for a workgroup's
+// Estimated time (us) of a tile shape and split on the whole chip (256 CUs, which the fit is made on): the larger of the rounds of one workgroup per CU (2.6 us for a workgroup's
 // start and end) and the weights once from memory (6.3 TB/s + 3.4 us), and the partial products of a split.  Fitted to
 // 3900 measured times (the projections of the 1.2B, 8B and 70B R = 8 / R = 4 shapes at 17 - 6000 rows, every tile, splits
 // 1 - 8; rms error 7 %): the tile and split it picks are on average 1.6 %, at worst 23 %, off the fastest measured ones.
+// The products alone were measured: the bytes of a residual epilogue (epilogue 3: 26 per element with seven peers and a copy,
+// 180 us at 4001 x 8192) are not in it, so there it chooses by the smaller part of the launch where K is short.
 static float gemm_cost(int tile, int M, int N, int K, int ksplit) {
   const auto& t = gemm_tiles[tile];
   const long wgs = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * ksplit;
@@ -1121,7 +1123,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_lds_kernel(AttnPrefillArg
   }
 }
 
-// 16-query tiles per wavefront: the fewest whose workgroups still fit the chip together (two per CU), because a call is
+// 16-query tiles per wavefront: the fewest whose workgroups still fit the chip together (two per CU of 256), because a call is
 // then as long as its longest workgroup; where even three tiles make more workgroups, three (the K / V^T reads from LDS
 // are shared by more queries; four leave one wavefront per SIMD and took 1.45 instead of 0.55 ms on 16 x 2048 tokens).
 // Whole layer, us, with 1 / 2 / 3: 70B R = 8 shard, 1 x 1000 374 / 388 / 395, 2 layers 1 x 4001 3223 / 3277 / 3315; 8B 2 layers

@@ -65,13 +65,13 @@ def test_small_bf16_generic_kernels(harness):
 
 
 def test_small_bf16_streaming_kernels(harness):
-    """rows = 80 > 64 at prefill: MFMA GEMM + flash attention; decode: skinny GEMM + split-KV attention."""
+    """80 rows at prefill: split-K GEMM + flash attention; decode: skinny GEMM + split-KV attention."""
     res = harness.run_case(SMALL_BF16)
     assert max(res.errs) < TOL_BF16, res.errs
 
 
 def test_small_bf16_skinny_prefill(harness):
-    """rows <= 64 at prefill: the skinny GEMM also serves short prefills; ragged T."""
+    """39 rows at prefill, ragged T: the ring GEMM's smallest tiles (the skinny GEMM serves up to 16)."""
     res = harness.run_case(SMALL_BF16.with_(name="small_bf16_skinny", batch=3, prefill=13), decode_steps=2)
     assert max(res.errs) < TOL_BF16, res.errs
 
@@ -94,7 +94,7 @@ def test_bf16_d128_prefill_ragged_rows(harness):
 
 @pytest.mark.parametrize("nq,nkv,d,T", [(8, 1, 128, 300), (4, 2, 64, 257), (2, 2, 128, 290)])
 def test_bf16_long_prefill_lds_attention(harness, nq, nkv, d, T):
-    """Prompts of 256 tokens and more take the LDS-shared flash-attention kernel: 4, 2 and 1 q heads per
+    """Prompts of more than 64 tokens take the LDS-shared flash-attention kernel: 4, 2 and 1 q heads per
     workgroup (8, 2 and 1 q heads per kv head), d = 128 and 64, ragged last query and key blocks, and a
     decode step over the cache it filled."""
     w = inputs.WORKLOADS["70b_r4_prefill"].with_(name=f"long_prefill_{nq}_{nkv}_{d}", n_layers=2, hidden=256, inter=256,
@@ -414,13 +414,14 @@ def test_bf16_large_tile_gemm_ragged_edges(harness, hidden, inter, batch):
 
 @pytest.mark.parametrize("wiring,nstd", [(ladder.LADDER_WIRING_LADDER, 0), (ladder.LADDER_WIRING_STANDARD, 0),
                                          (ladder.LADDER_WIRING_LADDER, 1), (ladder.LADDER_WIRING_PARALLEL, 0)])
-def test_bf16_wide_prefill_residual_epilogue_all_wirings(harness, wiring, nstd):
-    """Calls of more than 64 rows update the residual in the epilogue of each module's last GEMM (old rows +
+@pytest.mark.parametrize("prefill", [50, 347])
+def test_bf16_wide_prefill_residual_epilogue_all_wirings(harness, wiring, nstd, prefill):
+    """Calls of more than 1024 rows update the residual in the epilogue of each module's last GEMM (old rows +
     product + peers, bf16 rows for the consumers, whose products are scaled by the rows' 1/rms).  Seven peers
-    (more than the epilogue requests at once), 150 ragged rows on the small-tile GEMM, and every wiring: in
-    the hybrid stack the last standard module's output has two consumers."""
+    (more than the epilogue requests at once), 1041 ragged rows (and 150, whose residual the reduce kernel updates),
+    and every wiring: in the hybrid stack the last standard module's output has two consumers."""
     w = inputs.WORKLOADS["70b_r8_decode"].with_(name=f"wide_residual_{wiring}_{nstd}", n_layers=3, hidden=512, inter=448,
-                                                batch=3, prefill=50, decode_steps=1)
+                                                batch=3, prefill=prefill, decode_steps=1)
     res = harness.run_case(w, wiring=wiring, n_standard_layers=nstd)
     assert len(res.errs) == 2 and max(res.errs) < TOL_BF16, res.errs
     # the whole model on one rank: no peers to add
@@ -428,15 +429,16 @@ def test_bf16_wide_prefill_residual_epilogue_all_wirings(harness, wiring, nstd):
     assert len(res.errs) == 2 and max(res.errs) < TOL_BF16, res.errs
 
 
-def test_bf16_decode_of_more_than_64_sequences(harness):
-    """A decode step of 80 sequences is a wide call (80 rows): the projections take the GEMM kernels, the position
-    comes from device memory (rotary + append as a kernel of its own), attention the split-KV decode kernels,
-    and the residual update is the GEMM epilogue; after a synthetic cache and after a prefill."""
-    w = inputs.WORKLOADS["70b_r8_decode"].with_(name="decode_b80", n_layers=2, hidden=256, inter=352, n_q_heads=4,
-                                                n_kv_heads=2, head_dim=64, batch=80, decode_steps=2)
+@pytest.mark.parametrize("batch", [80, 1030])
+def test_bf16_decode_of_more_than_64_sequences(harness, batch):
+    """A decode step of 80 or 1030 sequences: the projections take the GEMM kernels, the position comes from device
+    memory (rotary + append as a kernel of its own), attention the split-KV decode kernels, and the residual update is
+    the reduce kernel's, or the GEMM epilogue's beyond 1024 rows; after a synthetic cache and after a prefill."""
+    w = inputs.WORKLOADS["70b_r8_decode"].with_(name="decode_wide", n_layers=2, hidden=256, inter=352, n_q_heads=4,
+                                                n_kv_heads=2, head_dim=64, batch=batch, decode_steps=2)
     res = harness.run_case(w, kv_preload=40)
     assert len(res.errs) == 2 and max(res.errs) < TOL_BF16, res.errs
-    res = harness.run_case(w.with_(name="decode_b80_prefill", prefill=3), wiring=ladder.LADDER_WIRING_STANDARD)
+    res = harness.run_case(w.with_(name="decode_wide_prefill", prefill=3), wiring=ladder.LADDER_WIRING_STANDARD)
     assert len(res.errs) == 3 and max(res.errs) < TOL_BF16, res.errs
 
 

@@ -134,9 +134,11 @@ def test_decode_stages_full_width_70b_r8(harness):
     check(harness, out, TOL_BF16, "70B R = 8 width")
 
 
-def test_prefill_then_decode_stages_bf16(harness):
-    """A prefill wide enough for the GEMM path with the residual epilogue (more than 64 rows), then decode steps."""
-    w = R8_STAGED.with_(name="r8_staged_prefill", n_layers=4, batch=2, prefill=160, kv_preload=0, decode_steps=2)
+@pytest.mark.parametrize("prefill", [160, 520])
+def test_prefill_then_decode_stages_bf16(harness, prefill):
+    """A prefill on the GEMM path, without and with the residual update as its epilogue (more than 1024 rows), then decode
+    steps."""
+    w = R8_STAGED.with_(name="r8_staged_prefill", n_layers=4, batch=2, prefill=prefill, kv_preload=0, decode_steps=2)
     out = run_stages(harness, w, [(0, 2), (2, 4)], steps=2)
     check(harness, out, TOL_BF16, "bf16 prefill + decode")
 
