@@ -104,11 +104,9 @@ hipError_t launch_reduce_norm(const ReduceNormArgs& a, bool is_bf16, hipStream_t
 // tiny fp32 model (hidden 256, 2 shards), one row: 22 us per matrix and shard (64 x 64 tiles, one k step of 16 in flight)
 // -> 5 us for all
 // of them; fp32 model of hidden 2048 (50 M weights a layer), 8 steps behind a prompt of 32: 23.9 -> 2.2 ms for 2 layers.
-// Many rows, a layer of hidden 4096 and SwiGLU 11008, 64 x 64 tiles -> this, ms: fp32 128 / 512 / 2048 rows 4.6 / 7.5 / 39.8 ->
-// 1.7 / 6.5 / 30.4, bf16 4.5 / 6.9 / 36.5 -> 1.3 / 4.7 / 20.9 (8.5 at 512 rows with the weights converted as they are loaded).
+// Many rows, a layer of hidden 4096 and SwiGLU 11008, 64 x 64 tiles -> this, ms: fp32 128 / 512 / 2048 rows 4.6 / 7.4 / 40 ->
+// 1.3 / 5.1 / 24.6, bf16 4.5 / 6.9 / 37 -> 1.3 / 4.8 / 19.8 (8.5 at 512 rows with the weights converted as they are loaded).
 // ------------------------------------------------------------------------------------------------
-constexpr int PLAIN_KC = 256;   // k per pass
-
 // Blocks beyond what one grid dimension takes (fewer than 2^32 threads) go on in the second one, in rows of 2^20; the kernel leaves
 // at once where its index is past the end.  (The row's length is a constant: gridDim comes from an implicit argument in memory,
 // 557 -> 606 us on the tiny fp32 model's prompt of 32 and 8 steps.)
@@ -151,25 +149,29 @@ __device__ __forceinline__ PlainW4<T, VEC> plain_w4(const T* w, int k, int K, in
 }
 
 // rows m0 .. m0 + MR - 1 of x times columns n .. n + 3 (per lane) of w; the sums over all K end up in `sum` [MR][64]
-template <typename T, int MR, bool VEC>
-__device__ __forceinline__ void plain_product(const T* x, int M, int K, int m0, const T* w, int N, int n0, float (*xs)[PLAIN_KC],
+template <typename T, int MR, bool VEC, int KC>
+__device__ __forceinline__ void plain_product(const T* x, int M, int K, int m0, const T* w, int N, int n0, float (*xs)[KC],
                                               float (*red)[MR][64], float (*sum)[64]) {
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
   const int c4 = (lane & 15) * 4, kg = t >> 4;
+  constexpr int PASSES = KC / 64, ROWS = 256 / KC;   // (rows of x that the workgroup's threads take side by side)
   float acc[MR][4] = {};
-  for (int k0 = 0; k0 < K; k0 += PLAIN_KC) {
-    PlainW4<T, VEC> wr[4][4];   // [pass][k]
+  for (int k0 = 0; k0 < K; k0 += KC) {
+    PlainW4<T, VEC> wr[PASSES][4];   // [pass][k]
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < PASSES; ++i)
 #pragma unroll
       for (int e = 0; e < 4; ++e) wr[i][e] = plain_w4<T, VEC>(w, k0 + i * 64 + kg * 4 + e, K, n0 + c4, N);
     if (k0 > 0) __syncthreads();   // the previous pass has been read
 #pragma unroll
-    for (int m = 0; m < MR; ++m) xs[m][t] = m0 + m < M && k0 + t < K ? load_f<T>(x + (size_t)(m0 + m) * K + k0 + t) : 0.f;
+    for (int i = 0; i < MR; i += ROWS) {
+      const int m = ROWS == 1 ? i : i + t / KC, k = ROWS == 1 ? t : t % KC;
+      xs[m][k] = m0 + m < M && k0 + k < K ? load_f<T>(x + (size_t)(m0 + m) * K + k0 + k) : 0.f;
+    }
     __syncthreads();
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < PASSES; ++i) {
       float wv[4][4];   // [k][column]
 #pragma unroll
       for (int e = 0; e < 4; ++e) wr[i][e].value(wv[e]);
@@ -196,22 +198,51 @@ __device__ __forceinline__ void plain_product(const T* x, int M, int K, int m0, 
   __syncthreads();
 }
 
-template <typename T, int MR, bool VEC>
+// Which tile a block takes.  Where the blocks are more than the chip holds at once, PLAIN_GROUP row blocks share a column block
+// back to back and each of the 8 XCDs, to which blocks go round robin, works through one stretch of that order, so that a column
+// block's weights come from memory once per group and not once per row block, which the caches cannot hide where a matrix is larger
+// than they are (hidden 8192, SwiGLU 28672, one layer, 512 / 1024 / 2048 rows, ms: 64 x 64 tiles before fp32 23.8 / 43.2 / 98.0, bf16
+// 21.2 / 39.0 / 89.0; columns first 31.3 / 64.1 / 135.1, 44.5 / 89.7 / 181.2; this 21.0 / 42.5 / 92.5, 20.2 / 39.2 / 80.1).  Else columns
+// first (all blocks run side by side; hidden 1024, 32 rows: 176 against 181 us).
+constexpr unsigned PLAIN_GROUP = 64;
+__device__ __forceinline__ bool plain_tile(unsigned row_blocks, unsigned col_blocks, unsigned& m_blk, unsigned& col_blk) {
+  const unsigned total = row_blocks * col_blocks, total8 = total & ~7u, id = flat_block();
+  if (id >= total) return false;
+  if (total <= 512) {
+    m_blk = id / col_blocks;
+    col_blk = id % col_blocks;
+    return true;
+  }
+  const unsigned at = id < total8 ? (id & 7) * (total8 >> 3) + (id >> 3) : id;
+  const unsigned group = at / (PLAIN_GROUP * col_blocks), in_group = at % (PLAIN_GROUP * col_blocks);
+  const unsigned gm = min(PLAIN_GROUP, row_blocks - group * PLAIN_GROUP);
+  m_blk = group * PLAIN_GROUP + in_group % gm;
+  col_blk = in_group / gm;
+  return true;
+}
+
+template <typename T, int MR, bool VEC, int KC>
 __global__ __launch_bounds__(256) void plain_gemm_kernel(PlainGemmArgs a) {
-  __shared__ __attribute__((aligned(16))) float xs[MR][PLAIN_KC];
+  __shared__ __attribute__((aligned(16))) float xs[MR][KC];
   __shared__ float red[4][MR][64];
   __shared__ float sum[2][MR][64];
   const int t = threadIdx.x, shard = blockIdx.z;
-  const unsigned m_blk = flat_block() / (unsigned)a.n_blocks;
-  if (m_blk >= ((unsigned)a.M + MR - 1) / MR) return;
+  unsigned m_blk, col_blk;
+  if (MR == 1) {   // (a single row: m_blk is 0 inside the grid; written this way the tiny fp32 model's steps take 558 us, as one comparison 568)
+    m_blk = flat_block() / (unsigned)a.n_blocks;
+    col_blk = flat_block() % (unsigned)a.n_blocks;
+    if (m_blk >= (unsigned)a.M) return;
+  } else if (!plain_tile(((unsigned)a.M + MR - 1) / MR, (unsigned)a.n_blocks, m_blk, col_blk)) {
+    return;
+  }
   const int m0 = (int)m_blk * MR;
-  int blk = (int)(flat_block() % (unsigned)a.n_blocks), mat = 0;   // the matrices' column blocks side by side (SwiGLU: the gate's; the up matrix goes along)
+  int blk = (int)col_blk, mat = 0;   // the matrices' column blocks side by side (SwiGLU: the gate's; the up matrix goes along)
   while (a.epilogue != PLAIN_SWIGLU && mat + 1 < a.n_mat && blk >= (a.N[mat] + 63) / 64) { blk -= (a.N[mat] + 63) / 64; ++mat; }
   const int n0 = blk * 64, N = a.N[mat];
   const T* x = reinterpret_cast<const T*>(a.x) + shard * a.x_stride;
   auto weights = [&](int i) { return reinterpret_cast<const T*>(reinterpret_cast<const char*>(a.w[i]) + shard * a.w_stride); };
-  plain_product<T, MR, VEC>(x, a.M, a.K, m0, weights(mat), N, n0, xs, red, sum[0]);
-  if (a.epilogue == PLAIN_SWIGLU) plain_product<T, MR, VEC>(x, a.M, a.K, m0, weights(1), N, n0, xs, red, sum[1]);
+  plain_product<T, MR, VEC, KC>(x, a.M, a.K, m0, weights(mat), N, n0, xs, red, sum[0]);
+  if (a.epilogue == PLAIN_SWIGLU) plain_product<T, MR, VEC, KC>(x, a.M, a.K, m0, weights(1), N, n0, xs, red, sum[1]);
   if (a.epilogue == PLAIN_OUT) {
     for (int i = t; i < MR * 64; i += 256) {
       const int m = m0 + (i >> 6), n = n0 + (i & 63);
@@ -261,8 +292,17 @@ static hipError_t launch_plain_gemm_t(PlainGemmArgs a, bool vec, hipStream_t s) 
   const long long blocks = (long long)a.n_blocks * (((long long)a.M + MR - 1) / MR);
   if (blocks > 0x7fffffff || a.n_shards > 65535) return hipErrorInvalidValue;
   const dim3 grid = flat_grid(blocks, a.n_shards);
-  if (vec) hipLaunchKernelGGL((plain_gemm_kernel<T, MR, true>), grid, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((plain_gemm_kernel<T, MR, false>), grid, dim3(256), 0, s, a);
+  // k per pass: 256, or 128 where fp32 tiles of 16 rows are more than two workgroups per CU: their registers then allow three
+  // (hidden 8192, 1024 rows 50.4 -> 42.5 ms; but hidden 1024, 128 rows, which do not fill two, 477 -> 583 us).  Same order of sums.
+  if constexpr (sizeof(T) == 4 && MR == 16) {
+    if (blocks * a.n_shards > 512) {
+      if (vec) hipLaunchKernelGGL((plain_gemm_kernel<T, MR, true, 128>), grid, dim3(256), 0, s, a);
+      else hipLaunchKernelGGL((plain_gemm_kernel<T, MR, false, 128>), grid, dim3(256), 0, s, a);
+      return hipGetLastError();
+    }
+  }
+  if (vec) hipLaunchKernelGGL((plain_gemm_kernel<T, MR, true, 256>), grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((plain_gemm_kernel<T, MR, false, 256>), grid, dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

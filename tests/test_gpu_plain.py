@@ -72,6 +72,16 @@ def test_stretches_of_scores_of_minus_infinity(harness, dtype, batch, nq, nkv, c
     assert torch.isfinite(outs[0]).all() and torch.equal(*outs)
 
 
+@pytest.mark.parametrize("rows", [30, 100, 1100])
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_more_tiles_than_the_chip_holds(harness, dtype, rows):
+    """The order in which blocks take the tiles of a large grid: one ragged group of row blocks and several (of 64 x 16 rows), tile
+    counts that are no multiple of 8; fp32 tiles with the shorter pass over K, K no multiple of it."""
+    w = BASE.with_(tp_degree=1, n_real_shards=1, hidden=264, n_q_heads=4, n_kv_heads=2, head_dim=66, inter=6500, prefill=rows, dtype=dtype)
+    res = harness.run_case(w, kernel_path=ladder.LADDER_PATH_GENERIC, gen_device="cuda:0")
+    assert max(res.errs) < (1e-4 if dtype == "fp32" else 0.0029 * 2 ** 0.5 * 5.8), res.errs
+
+
 def test_overlapped_schedules_of_the_plain_path(harness):
     """Layers of 32 MB and more run their modules on two streams, or the reduces on a side stream, smaller ones in order: the
     schedules give the same bits, and the right ones."""
