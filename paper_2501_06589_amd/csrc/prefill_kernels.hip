@@ -1,7 +1,7 @@
 // Prefill-shape kernels of the bf16 path (gfx950): MFMA GEMM on the packed weight tiles and causal
 // GQA flash attention over the cache, both on v_mfma_f32_16x16x32_bf16.
 #include "common.h"
-#include <type_traits>
+#include <math.h>
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
@@ -20,9 +20,10 @@ __device__ __forceinline__ f32x4_t mfma16(const uint4 a, const uint4 b, const f3
 }
 
 // ------------------------------------------------------------------------------------------------
-// C[M][N] = X[M][K] W[K][N] on the packed weight tiles: two kernels, gemm_lds_kernel (256 x 256 tiles) for calls whose
-// tiles fill the chip and gemm_ring_kernel (smaller tiles, optional split of K) for the others; gemm_plan chooses.
-// In both the weights are the MFMA A operand and the activations the B operand, so output element (m, n) sits in
+// C[M][N] = X[M][K] W[K][N] on the packed weight tiles: three kernels, gemm_duo_kernel (128 rows, two workgroups per CU) for many
+// rows, gemm_lds_kernel (256 x 256 tiles, one per CU) for the shapes where it stays ahead of that, and gemm_ring_kernel (smaller
+// tiles, a deep queue of weights) for few rows and odd K; gemm_best_tile chooses.
+// In all of them the weights are the MFMA A operand and the activations the B operand, so output element (m, n) sits in
 // lane (n%16)/4*16 + m%16, register n%4: a lane stores 4 consecutive columns.
 // Rows >= M and weight tiles >= N/16 are clamped on load: they only reach outputs that are not stored.
 // ------------------------------------------------------------------------------------------------
@@ -211,6 +212,150 @@ hipError_t launch_row_rms(const float* ssq_part, int n_part, int M, int H, float
   return hipGetLastError();
 }
 
+#define GEMM_GROUP_M 8   // row blocks that share one column block back to back
+#define GEMM_EPI_STRIDE(bn) ((bn) + 4)   // floats per staged row of the residual epilogue
+#define GEMM2_LDSP(p) ((__attribute__((address_space(3))) void*)(p))
+#define GEMM2_GLBP(p) ((const __attribute__((address_space(1))) void*)(p))
+
+// s_waitcnt vmcnt(N) lgkmcnt(0): this wave's LDS reads are complete and at most N of its vector-memory operations in flight (gfx9
+// encoding: vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8); then a bare workgroup barrier, without the fence of
+// __syncthreads(), which would wait for ALL outstanding loads.  Builtins, not inline assembly: after an asm statement the compiler
+// no longer knows which LDS reads are pending and waits for all of them at the next use.
+template <int N>
+__device__ __forceinline__ void ring_meet() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_waitcnt(0x0070 | (N & 15) | ((N >> 4) << 14));
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// 16 bytes that no cache should keep
+__device__ __forceinline__ uint4 load_once(const void* p) {
+  return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p)));
+}
+
+// Epilogue 3 of a workgroup's tile of WR x 16 MT rows and WC x 16 JT columns (see GemmArgs), with whole rows per memory
+// instruction.  In the accumulator layout a wavefront's load or store touches 16 rows, 64 (fp32) or 32 (bf16) bytes of each, and
+// in that shape the 16 - 26 bytes per element that the update moves cost as much as a reduce kernel of its own.  So the tile
+// passes through LDS (free once the workgroup is past its last k tile), 64 rows at a time: the wavefronts write their accumulator
+// blocks, meet, and read back one row of the tile per half-wavefront (quarter, for 128 columns), eight columns per lane: 16 bytes
+// per lane and instruction, row segments of 512 bytes and more.  The rows' sums of squares are left per column block of the tile:
+// ssq_part[n_blk][m].  The summation order per element is fixed: old value, product, peers 0, 1, ...
+// The peers are read once per call and bypass the caches (non-temporal): they would push out the operands that the workgroups
+// beside are multiplying and the rows that the next kernels read (4001 x 8192, seven peers, K 1024 / 3584: 224 / 300 -> 188 / 277 us).
+// (The rows themselves non-temporal too: 1 - 4 % faster measured alone where they exceed the last-level cache, no different in a call.)
+template <int MT, int JT, int WR, int WC, int PB>   // PB: peers requested at once
+__device__ __forceinline__ void gemm_residual_epilogue(const GemmArgs& a, f32x4_t (&acc)[JT][MT], unsigned char* lds, int m0,
+                                                       int n_blk, int wave, int lane) {
+  constexpr int BN = 16 * JT * WC, STRIDE = GEMM_EPI_STRIDE(BN);   // floats per staged row: + 4, so that the 16 rows of a write spread over the banks
+  constexpr int LPR = BN > 128 ? 32 : 16, RPI = 64 / LPR;          // lanes per row, rows per instruction
+  constexpr int ROWS = 64 / WR, H = ROWS / 16;                     // staged rows and row tiles per wavefront row and pass
+  constexpr int STEPS = 64 / (WR * WC * RPI);                      // rows that a lane group takes per pass
+  constexpr int RB = 2;                                            // rows requested at once
+  static_assert(STEPS % RB == 0 && MT % H == 0, "whole passes");
+  float* stage = reinterpret_cast<float*>(lds);
+  const int b = lane & 15, q = lane >> 4, wr = wave / WC, wc = wave % WC;
+  const int sub = lane / LPR, l = lane % LPR;
+  const int n = n_blk * BN + 8 * l;
+  const bool col_ok = 8 * l < BN && n < a.N;   // (N is a multiple of 16)
+  const int nc = col_ok ? n : 0;
+  // the gains of the modules that read the new rows, for this lane's eight columns (the same for every row)
+  float ga8[8], gb8[8];
+  unpack8(a.xh_a ? *reinterpret_cast<const uint4*>(a.gain_a + nc) : make_uint4(0, 0, 0, 0), ga8);
+  unpack8(a.xh_b ? *reinterpret_cast<const uint4*>(a.gain_b + nc) : make_uint4(0, 0, 0, 0), gb8);
+#pragma unroll
+  for (int pass = 0; pass < MT / H; ++pass) {
+    if (pass > 0) __syncthreads();           // the previous pass has been read
+#pragma unroll
+    for (int h = 0; h < H; ++h)
+#pragma unroll
+      for (int j = 0; j < JT; ++j)
+        *reinterpret_cast<f32x4_t*>(stage + (wr * ROWS + h * 16 + b) * STRIDE + (wc * JT + j) * 16 + 4 * q) = acc[j][H * pass + h];
+    __syncthreads();
+#pragma unroll
+    for (int g = 0; g < STEPS / RB; ++g) {
+      float4 xo[RB][2];
+      uint4 pk[RB][PB];
+      size_t off[RB];
+      bool ok[RB];
+      int mrow[RB];
+#pragma unroll
+      for (int r = 0; r < RB; ++r) {
+        const int lr = ((g * RB + r) * (WR * WC) + wave) * RPI + sub;   // staged row
+        mrow[r] = m0 + lr / ROWS * (MT * 16) + pass * ROWS + lr % ROWS;
+        ok[r] = col_ok && mrow[r] < a.M;
+        off[r] = (size_t)min(mrow[r], a.M - 1) * a.N + nc;
+        xo[r][0] = *reinterpret_cast<const float4*>(a.x_res + off[r]);
+        xo[r][1] = *reinterpret_cast<const float4*>(a.x_res + off[r] + 4);
+#pragma unroll
+        for (int p = 0; p < PB; ++p)
+          if (p < a.n_peers) pk[r][p] = load_once(a.peers + p * a.peer_stride + off[r]);
+      }
+#pragma unroll
+      for (int r = 0; r < RB; ++r) {
+        const int lr = ((g * RB + r) * (WR * WC) + wave) * RPI + sub;
+        const float4 p0 = *reinterpret_cast<const float4*>(stage + lr * STRIDE + 8 * l);
+        const float4 p1 = *reinterpret_cast<const float4*>(stage + lr * STRIDE + 8 * l + 4);
+        float v8[8] = {xo[r][0].x + p0.x, xo[r][0].y + p0.y, xo[r][0].z + p0.z, xo[r][0].w + p0.w,
+                       xo[r][1].x + p1.x, xo[r][1].y + p1.y, xo[r][1].z + p1.z, xo[r][1].w + p1.w};
+        auto add_peer = [&](const uint4 u) {
+          float f[8];
+          unpack8(u, f);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v8[e] += f[e];
+        };
+#pragma unroll
+        for (int p = 0; p < PB; ++p)
+          if (p < a.n_peers) add_peer(pk[r][p]);
+        for (int p = PB; p < a.n_peers; ++p) add_peer(load_once(a.peers + p * a.peer_stride + off[r]));
+        if (ok[r]) {
+          *reinterpret_cast<float4*>(a.x_res + off[r]) = make_float4(v8[0], v8[1], v8[2], v8[3]);
+          *reinterpret_cast<float4*>(a.x_res + off[r] + 4) = make_float4(v8[4], v8[5], v8[6], v8[7]);
+          if (a.x_copy) {
+            *reinterpret_cast<float4*>(a.x_copy + off[r]) = make_float4(v8[0], v8[1], v8[2], v8[3]);
+            *reinterpret_cast<float4*>(a.x_copy + off[r] + 4) = make_float4(v8[4], v8[5], v8[6], v8[7]);
+          }
+          // the rows as the modules that read them want them: times their norm's gain (fp32 product, one rounding)
+          auto store_gained = [&](bf16_t* dst, const float (&g8)[8]) {
+            uint4 u;
+            u.x = f32_to_bf16x2(v8[0] * g8[0], v8[1] * g8[1]);
+            u.y = f32_to_bf16x2(v8[2] * g8[2], v8[3] * g8[3]);
+            u.z = f32_to_bf16x2(v8[4] * g8[4], v8[5] * g8[5]);
+            u.w = f32_to_bf16x2(v8[6] * g8[6], v8[7] * g8[7]);
+            *reinterpret_cast<uint4*>(dst + off[r]) = u;
+          };
+          if (a.xh_a) store_gained(a.xh_a, ga8);
+          if (a.xh_b) store_gained(a.xh_b, gb8);
+        }
+        if (a.ssq_part) {   // (uniform)
+          float ss = 0.f;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) ss += v8[e] * v8[e];
+          if (!ok[r]) ss = 0.f;
+#pragma unroll
+          for (int o = LPR / 2; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);   // over the lanes of the row
+          if (l == 0 && mrow[r] < a.M) a.ssq_part[(size_t)n_blk * a.M + mrow[r]] = ss;
+        }
+      }
+    }
+  }
+}
+
+// dynamic LDS above the default 64 KiB has to be allowed per kernel and device, once
+static hipError_t allow_lds(const void* kernel, int bytes, bool (&prepared)[64]) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+  if (!prepared[dev]) {
+    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e != hipSuccess) return e;
+    prepared[dev] = true;
+  }
+  return hipSuccess;
+}
+
 // ------------------------------------------------------------------------------------------------
 // Large-M GEMM: 256 x 256 workgroup tile, 8 wavefronts (2 along M x 4 along N, 128 x 64 each), one
 // workgroup per CU.  Both operands travel global memory -> LDS without passing through registers
@@ -240,15 +385,7 @@ hipError_t launch_row_rms(const float* ssq_part, int n_part, int M, int H, float
 // 1129 / 993 / 1271 / 1338 TFLOP/s on the QKV / O / down / gate-up shapes of the 70B R = 4 shard at 32768 rows.
 // ------------------------------------------------------------------------------------------------
 #define GEMM2_GROUP_M 4
-#define RING_GROUP_M 8
-#define GEMM2_LDSP(p) ((__attribute__((address_space(3))) void*)(p))
-#define GEMM2_GLBP(p) ((const __attribute__((address_space(1))) void*)(p))
-
-// s_waitcnt vmcnt(N) (at most N of this wave's vector-memory operations still in flight; the other counters
-// are left alone: gfx9 encoding, vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8) and a bare
-// workgroup barrier, without the fence of __syncthreads(), which would wait for ALL outstanding loads.
-// Written with builtins, not inline assembly: after an asm statement the compiler no longer knows which
-// LDS reads are pending and waits for all of them at the next use.
+// as ring_meet, but the LDS reads in flight are left alone
 template <int N>
 __device__ __forceinline__ void gemm2_wait_and_meet() {
   static_assert(N >= 0 && N < 64, "vmcnt range");
@@ -263,117 +400,6 @@ __device__ __forceinline__ void gemm2_wait_and_meet() {
 #define GEMM2_XBLOCKS 3
 #define GEMM2_WSTAGES 4
 #define GEMM2_LDS_BYTES (GEMM2_XBLOCKS * GEMM2_XBLOCK_BYTES + GEMM2_WSTAGES * GEMM2_WSTAGE_BYTES)
-
-// Epilogue 3 of a tile of 32 MT rows x 256 columns whose wavefronts lie 2 x 4 (see GemmArgs), with whole rows per memory
-// instruction.  In the accumulator
-// layout a wavefront's load or store touches 16 rows, 64 (fp32) or 32 (bf16) bytes of each; this epilogue
-// moves 16 bytes per element through memory (the old row, three peers, the new row twice), and in that shape it
-// cost as much as the separate reduce kernel it replaces.  So the tile passes through LDS (free once the
-// workgroup is past its last k tile), 64 rows at a time: the wavefronts write their accumulator blocks, meet,
-// and read back one row of 256 columns per half-wavefront, eight columns per lane, so that every access to
-// memory is a whole row segment of 1 KiB (fp32) or 512 bytes (bf16), 16 bytes per lane and instruction.  The rows' sums of squares are left per 256-column
-// block: ssq_part[n_blk][m].  The summation order per element is fixed: old value, product, peers 0, 1, ...
-#define GEMM2_EPI_STRIDE 260   // floats per staged row: 256 + 4, so that the 16 rows of a write spread over the banks
-static_assert(64 * GEMM2_EPI_STRIDE * 4 <= GEMM2_LDS_BYTES, "staging area");
-template <int MT>
-__device__ __forceinline__ void gemm2_residual_epilogue(const GemmArgs& a, f32x4_t (&acc)[4][MT], unsigned char* lds, int m0,
-                                                        int n_blk, int wave, int lane) {
-  float* stage = reinterpret_cast<float*>(lds);
-  const int b = lane & 15, q = lane >> 4;
-  const int wm = wave >> 2, wn = wave & 3;
-  const int half = lane >> 5, l32 = lane & 31;
-  const int n = n_blk * 256 + 8 * l32;       // on the way back: a half-wavefront per row, eight columns per lane
-  const bool col_ok = n < a.N;               // (N is a multiple of 16)
-  const int nc = col_ok ? n : 0;
-  constexpr int PB = 3, RB = 2;              // peers and row pairs requested at once
-  // the gains of the modules that read the new rows, for this lane's eight columns (the same for every row)
-  float ga8[8], gb8[8];
-  {
-    const uint4 za = a.xh_a ? *reinterpret_cast<const uint4*>(a.gain_a + nc) : make_uint4(0, 0, 0, 0);
-    const uint4 zb = a.xh_b ? *reinterpret_cast<const uint4*>(a.gain_b + nc) : make_uint4(0, 0, 0, 0);
-    unpack8(za, ga8);
-    unpack8(zb, gb8);
-  }
-#pragma unroll
-  for (int pass = 0; pass < MT / 2; ++pass) {   // row blocks mt = 2 pass, 2 pass + 1 of both halves of the tile
-    if (pass > 0) __syncthreads();           // the previous pass has been read
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        *reinterpret_cast<f32x4_t*>(stage + (wm * 32 + h * 16 + b) * GEMM2_EPI_STRIDE + wn * 64 + j * 16 + 4 * q) = acc[j][2 * pass + h];
-    __syncthreads();
-    // wavefront w takes the staged row pairs (2 w, 2 w + 1), (2 w + 16, 2 w + 17), ..., RB of them at a time
-#pragma unroll
-    for (int g = 0; g < 4 / RB; ++g) {
-      float4 xo[RB][2];
-      uint4 pk[RB][PB];
-      size_t off[RB];
-      bool ok[RB];
-      int mrow[RB];
-#pragma unroll
-      for (int r = 0; r < RB; ++r) {
-        const int lr = 2 * wave + 16 * (g * RB + r) + half;              // staged row: half lr / 32, row lr % 32 of the pass
-        mrow[r] = m0 + (lr >> 5) * (MT * 16) + pass * 32 + (lr & 31);
-        ok[r] = col_ok && mrow[r] < a.M;
-        off[r] = (size_t)min(mrow[r], a.M - 1) * a.N + nc;
-        xo[r][0] = *reinterpret_cast<const float4*>(a.x_res + off[r]);
-        xo[r][1] = *reinterpret_cast<const float4*>(a.x_res + off[r] + 4);
-#pragma unroll
-        for (int p = 0; p < PB; ++p)
-          if (p < a.n_peers) pk[r][p] = *reinterpret_cast<const uint4*>(a.peers + p * a.peer_stride + off[r]);
-      }
-#pragma unroll
-      for (int r = 0; r < RB; ++r) {
-        const int lr = 2 * wave + 16 * (g * RB + r) + half;
-        const float4 p0 = *reinterpret_cast<const float4*>(stage + lr * GEMM2_EPI_STRIDE + 8 * l32);
-        const float4 p1 = *reinterpret_cast<const float4*>(stage + lr * GEMM2_EPI_STRIDE + 8 * l32 + 4);
-        float v8[8] = {xo[r][0].x + p0.x, xo[r][0].y + p0.y, xo[r][0].z + p0.z, xo[r][0].w + p0.w,
-                       xo[r][1].x + p1.x, xo[r][1].y + p1.y, xo[r][1].z + p1.z, xo[r][1].w + p1.w};
-        auto add_peer = [&](const uint4 u) {
-          const uint32_t w4[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            v8[2 * e] += __uint_as_float(w4[e] << 16);
-            v8[2 * e + 1] += __uint_as_float(w4[e] & 0xFFFF0000u);
-          }
-        };
-#pragma unroll
-        for (int p = 0; p < PB; ++p)
-          if (p < a.n_peers) add_peer(pk[r][p]);
-        for (int p = PB; p < a.n_peers; ++p) add_peer(*reinterpret_cast<const uint4*>(a.peers + p * a.peer_stride + off[r]));
-        if (ok[r]) {
-          *reinterpret_cast<float4*>(a.x_res + off[r]) = make_float4(v8[0], v8[1], v8[2], v8[3]);
-          *reinterpret_cast<float4*>(a.x_res + off[r] + 4) = make_float4(v8[4], v8[5], v8[6], v8[7]);
-          if (a.x_copy) {
-            *reinterpret_cast<float4*>(a.x_copy + off[r]) = make_float4(v8[0], v8[1], v8[2], v8[3]);
-            *reinterpret_cast<float4*>(a.x_copy + off[r] + 4) = make_float4(v8[4], v8[5], v8[6], v8[7]);
-          }
-          // the rows as the modules that read them want them: times their norm's gain (fp32 product, one rounding)
-          auto store_gained = [&](bf16_t* dst, const float (&g8)[8]) {
-            uint4 u;
-            u.x = f32_to_bf16x2(v8[0] * g8[0], v8[1] * g8[1]);
-            u.y = f32_to_bf16x2(v8[2] * g8[2], v8[3] * g8[3]);
-            u.z = f32_to_bf16x2(v8[4] * g8[4], v8[5] * g8[5]);
-            u.w = f32_to_bf16x2(v8[6] * g8[6], v8[7] * g8[7]);
-            *reinterpret_cast<uint4*>(dst + off[r]) = u;
-          };
-          if (a.xh_a) store_gained(a.xh_a, ga8);
-          if (a.xh_b) store_gained(a.xh_b, gb8);
-        }
-        if (a.ssq_part) {   // (uniform)
-          float ss = 0.f;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) ss += v8[e] * v8[e];
-          if (!ok[r]) ss = 0.f;
-#pragma unroll
-          for (int o = 16; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);   // over the half-wavefront of the row
-          if (l32 == 0 && mrow[r] < a.M) a.ssq_part[(size_t)n_blk * a.M + mrow[r]] = ss;
-        }
-      }
-    }
-  }
-}
 
 __global__ __launch_bounds__(512, 2) void gemm_lds_kernel(GemmArgs a) {
   constexpr int WM = 8;
@@ -527,23 +553,188 @@ __global__ __launch_bounds__(512, 2) void gemm_lds_kernel(GemmArgs a) {
   }
   // the clamped loads past the last k tile are still in flight into LDS: they must land before the workgroup ends
   gemm2_wait_and_meet<0>();
-  if (a.epilogue == 3) gemm2_residual_epilogue<WM>(a, acc, g2_lds, m0, n_blk, wave, lane);
+  if (a.epilogue == 3) gemm_residual_epilogue<WM, 4, 2, 4, 3>(a, acc, g2_lds, m0, n_blk, wave, lane);
   else gemm_epilogue<WM, 4>(a, acc, m0 + wm * 128, nt0 + wn * 4, NT, lane);
 }
 
 static hipError_t launch_gemm_lds(const GemmArgs& a, hipStream_t s) {
   static bool prepared[64] = {};
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
+  const hipError_t e = allow_lds(reinterpret_cast<const void*>(gemm_lds_kernel), (int)GEMM2_LDS_BYTES, prepared);
   if (e != hipSuccess) return e;
-  if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-  if (!prepared[dev]) {   // more than the default 64 KiB of dynamic LDS: asked for once per device
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_lds_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)GEMM2_LDS_BYTES);
-    if (e != hipSuccess) return e;
-    prepared[dev] = true;
-  }
   const int tiles_m = (a.M + 255) / 256, tiles_n = (a.N + 255) / 256;
   hipLaunchKernelGGL(gemm_lds_kernel, dim3(tiles_m * tiles_n), dim3(512), GEMM2_LDS_BYTES, s, a);
+  return hipGetLastError();
+}
+
+// ------------------------------------------------------------------------------------------------
+// Many rows: 128 x 64 JT workgroup tile, 4 wavefronts side by side along N (128 rows x 16 JT columns each), two workgroups per CU.
+// A wavefront shares its weight tiles with nobody, so they go from memory straight to registers, as packed (two stages of 64 k
+// in flight, 64 registers at JT = 4); only the activations pass through LDS, a ring of DUO_STAGES stages of 64 k filled by
+// direct-to-LDS loads.  A load covers 8 rows x 64 k = whole 128-byte lines; the 16-byte segments of fragment row b lie
+// XOR-swizzled by b / 2 (the lane that fetches segment s of row b sits at position s ^ (b / 2) of the row's eight lanes), so
+// that the 16 lanes of a fragment read that hold the same k segment hit 16 different bank groups.  One barrier per stage, behind the
+// first two rows of its second half: the wavefronts have read the stage by then, the next one has landed.
+// What bounds it at thousands of rows is power: 1280 - 1430 TFLOP/s at a shader clock of 1.8 - 1.9 GHz, where MFMAs alone reach
+// 1670 and a large library product 1350.  Two workgroups per CU because a workgroup's start and end (first loads; SwiGLU,
+// residual update: 26 bytes per element with seven peers) then run beside the other's MFMAs, and because 128-row tiles leave less of
+// the chip idle in the last round.  Against one workgroup of 256 x 256 per CU with both operands through LDS, us:
+//   32768 x 14336 x 8192 SwiGLU 5609 -> 5396; 32768 x 8192, residual with 3 peers, K 2048 / 7168 1454 / 3339 -> 1369 / 3249;
+//   4001 x 8192, residual with 7 peers, K 1024 / 3584 260 / 345 -> 188 / 277; 2048 x 28672 x 4096 SwiGLU 419 -> 375.
+// Whole calls: 8B shape, 2 layers, 2048 rows 1798 -> 1701; 70B R = 8 stage, 4001 rows 3087 -> 2858; R = 4, 32768 rows 12547 -> 12226.
+// Columns per wavefront (JT 2, 3, 4) are the cost model's choice: 192 columns where 256 leave half a round idle
+// (2048 x 6144 x 4096 106 -> 95 us), 128 for short products.
+// Tile order: workgroups are handed to the 8 XCDs round robin by block index and every XCD has its own L2, so block index i is
+// mapped to position (i % 8) * (n / 8) + i / 8 of the tile order: each XCD works through one contiguous eighth of it and
+// neighbours in the order (which share operands) meet in one L2.  GEMM_GROUP_M row blocks share one column block back to back
+// (4 / 6 / 8 / 16: gate/up above 5608 / 5619 / 5396 / 5828 us).
+// Rows >= M and weight tiles >= N/16 are clamped on load.  K is a multiple of 64.  Epilogue 0 may split K over workgroups.
+// ------------------------------------------------------------------------------------------------
+#define DUO_STAGES 3
+template <int JT>
+__global__ __launch_bounds__(256, 2) void gemm_duo_kernel(GemmArgs a) {
+#if defined(__HIP_DEVICE_COMPILE__)   // (buffer descriptors are a device type)
+  constexpr int MT = 8, BM = 16 * MT, BN = 64 * JT, S = DUO_STAGES;
+  constexpr int XB = BM * 128, XL = BM / 32;   // bytes of a stage, 1 KiB loads per wavefront and stage
+  extern __shared__ __attribute__((aligned(16))) unsigned char duo_lds[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int b = lane & 15, q = lane >> 4;
+  const int KT = a.K >> 5, ST = a.K >> 6, NT = a.N >> 4;
+  const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
+  const int nblk = gridDim.x, nblk8 = nblk & ~7;   // XCD-aware order
+  int bid = (int)blockIdx.x < nblk8 ? ((int)blockIdx.x & 7) * (nblk8 >> 3) + ((int)blockIdx.x >> 3) : (int)blockIdx.x;
+  const int ks = bid / (tiles_m * tiles_n);
+  bid -= ks * (tiles_m * tiles_n);
+  const int per_split = (ST + a.ksplit - 1) / a.ksplit;
+  const int s0 = ks * per_split, n = min(ST, s0 + per_split) - s0;   // (the host's plan leaves no split empty)
+  const int per_group = GEMM_GROUP_M * tiles_n;
+  const int group = bid / per_group, in_group = bid % per_group;
+  const int gm = min(GEMM_GROUP_M, tiles_m - group * GEMM_GROUP_M);
+  const int m0 = (group * GEMM_GROUP_M + in_group % gm) * BM;
+  const int n_blk = in_group / gm;
+  const int nt0 = n_blk * (BN / 16) + wave * JT;   // (may lie past the last tile)
+
+  // both operands through buffer descriptors: a uniform base and offset, and 32 bits per lane instead of a 64-bit address per load
+  const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(a.x + (size_t)m0 * a.ldx), 0, -1, 0x00020000);
+  const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<char*>(static_cast<const char*>(a.wp) + (size_t)min(nt0, NT - 1) * KT * 1024), 0, -1, 0x00020000);
+  int xsrc[XL], wtile[JT];
+#pragma unroll
+  for (int i = 0; i < XL; ++i) {   // row group (8 rows) XL wave + i
+    const int g = XL * wave + i, r = lane >> 3;
+    const int seg = (lane & 7) ^ (((8 * (g & 1) + r) >> 1) & 7);
+    xsrc[i] = (min(8 * g + r, a.M - 1 - m0) * a.ldx + seg * 8) * 2;
+  }
+#pragma unroll
+  for (int j = 0; j < JT; ++j) wtile[j] = min(j, max(NT - 1 - nt0, 0)) * KT * 1024;
+  // (requests beyond the last stage repeat it: the counts that the waits rely on stay the same to the end)
+  auto issue_x = [&](int st, int buf) {
+    const int k = (s0 + min(st, n - 1)) * 128;
+#pragma unroll
+    for (int i = 0; i < XL; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, GEMM2_LDSP(duo_lds + buf * XB + (XL * wave + i) * 1024), 16, xsrc[i], k, 0, 0);
+  };
+  auto load_w = [&](u32x4_t (&w)[JT], int kt) {
+    const int k = (2 * s0 + min(kt, 2 * n - 1)) * 1024;
+#pragma unroll
+    for (int j = 0; j < JT; ++j) w[j] = __builtin_amdgcn_raw_buffer_load_b128(wr, lane * 16, wtile[j] + k, 0);
+  };
+  f32x4_t acc[JT][MT];
+#pragma unroll
+  for (int j = 0; j < JT; ++j)
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) acc[j][mt] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+  // read offsets inside a stage, first and second k tile
+  const int xoff0 = (b >> 3) * 1024 + (b & 7) * 128 + ((q) ^ ((b >> 1) & 7)) * 16;
+  const int xoff1 = (b >> 3) * 1024 + (b & 7) * 128 + ((4 + q) ^ ((b >> 1) & 7)) * 16;
+  u32x4_t w[2][2][JT], f[MT];   // weights [stage parity][k tile], activation fragments of the k tile at hand
+  auto row = [&](const u32x4_t (&wk)[JT], int mt) {
+#pragma unroll
+    for (int j = 0; j < JT; ++j)
+      acc[j][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wk[j]), __builtin_bit_cast(bf16x8_t, f[mt]), acc[j][mt], 0, 0, 0);
+  };
+  // Order of a wavefront's requests, stage s: W(s+2, k tile 0) | barrier | X(s+3) | W(s+2, k tile 1); the prologue is what the
+  // three stages before the first would have requested.
+  static_assert(S == 3, "the counts below");
+  issue_x(0, 0);
+  load_w(w[0][0], 0);
+  issue_x(1, 1);
+  load_w(w[0][1], 1);
+  load_w(w[1][0], 2);
+  issue_x(2, 2);
+  load_w(w[1][1], 3);
+  ring_meet<2 * XL + 4 * JT>();   // X(0) has landed
+  int buf = 0;
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) f[mt] = *reinterpret_cast<const u32x4_t*>(duo_lds + xoff0 + mt * 2048);
+  auto first_half = [&](const u32x4_t (&wk)[JT]) {   // ... and the fragments of the second
+    const unsigned char* const xb = duo_lds + buf * XB + xoff1;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      row(wk, mt);
+      f[mt] = *reinterpret_cast<const u32x4_t*>(xb + mt * 2048);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  auto stage = [&](u32x4_t (&wc)[2][JT], int s) {
+    first_half(wc[0]);
+    load_w(wc[0], 2 * s + 4);
+    __builtin_amdgcn_sched_barrier(0);
+    row(wc[1], 0);
+    row(wc[1], 1);
+    // every wavefront has read the stage (its buffer may be filled again), and X(s+1) has landed: behind it in the queue are
+    // W(s, 1), W(s+1, 0), X(s+2), W(s+1, 1), W(s+2, 0)
+    ring_meet<XL + 4 * JT>();
+    const int next = buf + 1 == S ? 0 : buf + 1;
+    const unsigned char* const nx = duo_lds + next * XB + xoff0;
+    f[0] = *reinterpret_cast<const u32x4_t*>(nx);
+    f[1] = *reinterpret_cast<const u32x4_t*>(nx + 2048);
+    issue_x(s + 3, buf);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int mt = 2; mt < MT; ++mt) {
+      row(wc[1], mt);
+      f[mt] = *reinterpret_cast<const u32x4_t*>(nx + mt * 2048);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    load_w(wc[1], 2 * s + 5);
+    __builtin_amdgcn_sched_barrier(0);
+    buf = next;
+  };
+  int s = 0;
+  for (; s + 1 < n; s += 2) {
+    stage(w[0], s);
+    stage(w[1], s + 1);
+  }
+  if (s < n) {   // (an odd number of stages)
+    first_half(w[0][0]);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) row(w[0][1], mt);
+  }
+  ring_meet<0>();   // the repeated requests land before the LDS is used again or the workgroup ends
+  // (the lane is taken afresh from the hardware, so that nothing made from it stays in registers across the loop: three spills less)
+  unsigned zero = 0u;
+  asm volatile("" : "+v"(zero));
+  const int lane_e = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
+  if (a.epilogue == 3) {
+    gemm_residual_epilogue<MT, JT, 1, 4, 8>(a, acc, duo_lds, m0, n_blk, wave, lane_e);
+    return;
+  }
+  GemmArgs e = a;
+  if (a.ksplit > 1) e.out = a.out + (size_t)ks * a.out_stride;
+  gemm_epilogue<MT, JT>(e, acc, m0, nt0, NT, lane_e);
+#endif
+}
+
+template <int JT>
+static hipError_t launch_gemm_duo(const GemmArgs& a, hipStream_t s) {
+  constexpr int RING = DUO_STAGES * 128 * 128, EPI = 64 * GEMM_EPI_STRIDE(64 * JT) * 4;
+  static bool prepared[64] = {};
+  if ((a.K & 63) || (long long)a.ldx * 256 + (long long)a.K * 2 > 0x7fffffffll || (long long)a.K * 32 * JT > 0x7fffffffll) return hipErrorInvalidValue;   // (32-bit offsets)
+  const hipError_t e = allow_lds(reinterpret_cast<const void*>(gemm_duo_kernel<JT>), EPI > RING ? EPI : RING, prepared);
+  if (e != hipSuccess) return e;
+  const int tiles = (a.M + 127) / 128 * ((a.N + 64 * JT - 1) / (64 * JT));
+  hipLaunchKernelGGL((gemm_duo_kernel<JT>), dim3(tiles * a.ksplit), dim3(256), a.epilogue == 3 && EPI > RING ? EPI : RING, s, a);
   return hipGetLastError();
 }
 
@@ -552,7 +743,7 @@ static hipError_t launch_gemm_lds(const GemmArgs& a, hipStream_t s) {
 // optionally split over ksplit workgroups whose partial products the caller's next kernel adds up.  With up to a few
 // hundred rows the product is bound by the one pass over the weights, so what counts is how many bytes of them are in
 // flight on how many CUs: S - 1 stages of direct-to-LDS loads per workgroup (80 - 128 KiB, one workgroup per CU) and, by
-// the split of K, a workgroup for every CU whatever N is.  Both operands are staged as in gemm_lds_kernel (weights: packed
+// the split of K, a workgroup for every CU whatever N is.  Both operands are staged as in gemm_duo_kernel (weights: packed
 // tiles as they stand; activations: 8 rows x 64 k per load, XOR-swizzled).  K is a multiple of 32; an odd last k tile
 // half-fills its stage.
 // Measured (8B shape, us, weights from memory; against 64- or 128-row tiles with register-staged operands and no split):
@@ -561,16 +752,6 @@ static hipError_t launch_gemm_lds(const GemmArgs& a, hipStream_t s) {
 // Non-temporal weight loads where one row block covers all rows: gate/up 46.6 -> 41.5 at 64 rows; with several row
 // blocks they are 5 - 13 % slower.  A rotated start of the K sweep: no change.
 // ------------------------------------------------------------------------------------------------
-// this wave's LDS reads are complete and at most N of its vector-memory operations in flight; then the workgroup meets
-template <int N>
-__device__ __forceinline__ void ring_meet() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_waitcnt(0x0070 | (N & 15) | ((N >> 4) << 14));
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_sched_barrier(0);
-}
-
 template <int BM, int BN, int WR, int WC, int S>
 __global__ __launch_bounds__(WR * WC * 64) void gemm_ring_kernel(GemmArgs a) {
   constexpr int WAVES = WR * WC, MT = BM / WR / 16, JT = BN / WC / 16;
@@ -587,14 +768,14 @@ __global__ __launch_bounds__(WR * WC * 64) void gemm_ring_kernel(GemmArgs a) {
   const int wr = wave / WC, wc = wave % WC;
   const int KT = a.K >> 5, ST = (KT + 1) >> 1, NT = a.N >> 4;
   const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
-  const int nblk = gridDim.x, nblk8 = nblk & ~7;   // XCD-aware order, as in gemm_lds_kernel
+  const int nblk = gridDim.x, nblk8 = nblk & ~7;   // XCD-aware order, as in gemm_duo_kernel
   int bid = (int)blockIdx.x < nblk8 ? ((int)blockIdx.x & 7) * (nblk8 >> 3) + ((int)blockIdx.x >> 3) : (int)blockIdx.x;
   const int ks = bid / (tiles_m * tiles_n);
   bid -= ks * (tiles_m * tiles_n);
-  const int per_group = RING_GROUP_M * tiles_n;
+  const int per_group = GEMM_GROUP_M * tiles_n;
   const int group = bid / per_group, in_group = bid % per_group;
-  const int gm = min(RING_GROUP_M, tiles_m - group * RING_GROUP_M);
-  const int m0 = (group * RING_GROUP_M + in_group % gm) * BM;
+  const int gm = min(GEMM_GROUP_M, tiles_m - group * GEMM_GROUP_M);
+  const int m0 = (group * GEMM_GROUP_M + in_group % gm) * BM;
   const int nt0 = in_group / gm * (BN / 16);
   const int per_split = (ST + a.ksplit - 1) / a.ksplit;
   const int s0 = ks * per_split, n = min(ST, s0 + per_split) - s0;   // (the host's plan leaves no split empty)
@@ -702,7 +883,7 @@ __global__ __launch_bounds__(WR * WC * 64) void gemm_ring_kernel(GemmArgs a) {
   if constexpr (BN == 256 && WR == 2) {   // (whole rows per memory instruction: 8B shape, 2 layers, 1100 rows 1265 -> 1251 us, 2048 1795 -> 1784)
     if (a.epilogue == 3) {
       ring_meet<0>();   // every wavefront is past its last read of the ring, whose memory stages the tile
-      gemm2_residual_epilogue<MT>(a, acc, ring_lds, m0, nt0 >> 4, wave, lane);
+      gemm_residual_epilogue<MT, JT, WR, WC, 3>(a, acc, ring_lds, m0, nt0 >> 4, wave, lane);
       return;
     }
   }
@@ -715,50 +896,70 @@ template <int BM, int BN, int WR, int WC, int S>
 static hipError_t launch_gemm_ring_t(const GemmArgs& a, hipStream_t s) {
   constexpr int LDS = S * (BM + BN) * 128;
   static bool prepared[64] = {};
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
+  const hipError_t e = allow_lds(reinterpret_cast<const void*>(gemm_ring_kernel<BM, BN, WR, WC, S>), LDS, prepared);
   if (e != hipSuccess) return e;
-  if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-  if (!prepared[dev]) {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_ring_kernel<BM, BN, WR, WC, S>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-    if (e != hipSuccess) return e;
-    prepared[dev] = true;
-  }
   const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
   hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, WR, WC, S>), dim3(tiles_m * tiles_n * a.ksplit), dim3(WR * WC * 64), LDS, s, a);
   return hipGetLastError();
 }
 
-// Tile shapes of the two kernels: what a stage of 64 k takes on a full chip, and the share of that on a nearly empty one.
-enum { TILE_64x64, TILE_64x128, TILE_128x64, TILE_128x128, TILE_128x256, TILE_256x256, TILE_COUNT };
-static const struct { int bm, bn; float stage_us, alone; } gemm_tiles[TILE_COUNT] = {
-    {64, 64, 0.24f, 1.0f}, {64, 128, 0.39f, 1.0f}, {128, 64, 0.35f, 0.87f}, {128, 128, 0.58f, 0.82f}, {128, 256, 0.99f, 0.85f}, {256, 256, 1.59f, 0.74f}};
+// Tile shapes of the two kernels and what a stage of 64 k takes of a workgroup (us).  Ring tiles (one workgroup per CU): on a full
+// chip, and the share of that on a nearly empty one.  Duo tiles (two per CU): with every CU holding two; the share of that where
+// few CUs hold two (two); where every CU holds one (one), or few do (alone).
+enum { TILE_64x64, TILE_64x128, TILE_128x64, TILE_128x128, TILE_128x256, TILE_256x256, TILE_DUO_128, TILE_DUO_192, TILE_DUO_256, TILE_COUNT };
+static const struct { int bm, bn; float stage_us, alone, one, two; } gemm_tiles[TILE_COUNT] = {
+    {64, 64, 0.24f, 1.0f, 0, 0},    {64, 128, 0.39f, 1.0f, 0, 0},   {128, 64, 0.35f, 0.87f, 0, 0},
+    {128, 128, 0.58f, 0.82f, 0, 0}, {128, 256, 0.99f, 0.85f, 0, 0}, {256, 256, 1.59f, 0.74f, 0, 0},
+    {128, 128, 0.888f, 0.435f, 0.52f, 0.964f}, {128, 192, 1.316f, 0.418f, 0.50f, 0.814f}, {128, 256, 1.659f, 0.419f, 0.501f, 0.808f}};
 
-// Estimated time (us) of a tile shape and split on the whole chip (256 CUs, which the fit is made on): the larger of the rounds of one workgroup per CU (2.6 us for a workgroup's
-// start and end) and the weights once from memory (6.3 TB/s + 3.4 us), and the partial products of a split.  Fitted to
-// 3900 measured times (the projections of the 1.2B, 8B and 70B R = 8 / R = 4 shapes at 17 - 6000 rows, every tile, splits
-// 1 - 8; rms error 7 %): the tile and split it picks are on average 1.6 %, at worst 23 %, off the fastest measured ones.
+// Estimated time (us) of a tile shape and split on the whole chip (256 CUs, which the fit is made on): the rounds of workgroups
+// (start: a workgroup's start and end) against one pass over the weights, and the partial products of a split.  Ring tiles: the larger
+// of the two, fitted to 3900 measured times (the projections of the 1.2B, 8B and 70B R = 8 / R = 4 shapes at 17 - 6000 rows, every
+// tile, splits 1 - 8; rms error 7 %).  Duo tiles: the root of the sum of their squares, fitted to 1900 measured times (the same
+// shapes at 80 - 8192 rows; rms error 8 %).  What it picks is on average 1.2 % off the fastest measured tile and split at 257 - 1024 rows and 0.6 % above, at worst
+// 18 %.  (Sums of squares with refitted constants for the ring tiles too: 0.6 instead of 5.7 % off at up to 64 rows measured alone, but
+// their larger tiles and splits leave less to the kernels beside: 8B shape, decode of 64 sequences 2981 -> 3277 us.)
 // The products alone were measured: the bytes of a residual epilogue (epilogue 3: 26 per element with seven peers and a copy,
 // 180 us at 4001 x 8192) are not in it, so there it chooses by the smaller part of the launch where K is short.
 static float gemm_cost(int tile, int M, int N, int K, int ksplit) {
   const auto& t = gemm_tiles[tile];
+  const bool duo = tile >= TILE_DUO_128;
+  const int slots = duo ? 512 : 256;
   const long wgs = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * ksplit;
   const int stages = (K + 63) / 64, per = (stages + ksplit - 1) / ksplit;
-  const float last = (float)(wgs % 256) / 256.f;
-  float tiles_us = (float)(wgs / 256) * (2.6f + (float)per * t.stage_us);
-  if (last > 0.f) tiles_us += 2.6f + (float)per * t.stage_us * (t.alone + (1.f - t.alone) * last);
-  const float mem_us = 3.4f + (float)N * (float)K * 2.0f / 6.3e6f;
-  const float split_us = ksplit > 1 ? (float)ksplit * (float)M * (float)N * 8.0f / 6.0e6f : 0.f;
-  return (tiles_us > mem_us ? tiles_us : mem_us) + split_us;
+  const float last = (float)(wgs % slots) / (float)slots;
+  const float start = duo ? 6.4f : 2.6f;
+  float tiles_us = (float)(wgs / slots) * (start + (float)per * t.stage_us);
+  if (last > 0.f) {
+    const float share = !duo ? t.alone + (1.f - t.alone) * last
+                        : last <= 0.5f ? t.alone + (t.one - t.alone) * 2.f * last : t.two + (1.f - t.two) * (2.f * last - 1.f);
+    tiles_us += start + (float)per * t.stage_us * share;
+  }
+  const float weights = (float)N * (float)K * 2.0f, parts = ksplit > 1 ? (float)ksplit * (float)M * (float)N * 8.0f : 0.f;
+  if (duo) {
+    const float mem_us = 1.6f + weights / 6.07e6f;
+    return sqrtf(tiles_us * tiles_us + mem_us * mem_us) + parts / 7.1e6f;
+  }
+  const float mem_us = 3.4f + weights / 6.3e6f;
+  return (tiles_us > mem_us ? tiles_us : mem_us) + parts / 6.0e6f;
 }
 
-static int gemm_best_tile(int M, int N, int K, int epilogue, int ksplit, float* cost) {
+// Which of the 256 x 256 and the duo tiles: where both epilogues are cheap the model's; a SwiGLU epilogue costs a 256 x 256 round, which
+// nothing hides, 7 us (8192 x 28672 x 4096 in place 1561 us, duo 1469; but 400 rows, one round, 111 against 125), and peers rule it out
+// (O of the 70B R = 4 shard, 32768 rows: 1450 against 1330).  Without peers its residual update is the faster one where it fills the
+// chip (8B shape, 8192 rows, O + down: 962 against 1030 us in place).
+static int gemm_best_tile(const GemmArgs& a, int ksplit, float* cost) {
+  const int M = a.M, N = a.N, K = a.K;
   int best = -1;
   float best_us = 0.f;
   for (int t = 0; t < TILE_COUNT; ++t) {
-    if (t == TILE_256x256 && (ksplit > 1 || (K & 63) || K < 256)) continue;   // (what gemm_lds_kernel takes)
-    if (t == TILE_64x64 && epilogue == 3) continue;                           // (16 columns per wavefront: more sums of squares per row than the buffer holds)
-    const float us = gemm_cost(t, M, N, K, ksplit);
+    if (t == TILE_256x256 && (ksplit > 1 || (K & 63) || K < 256)) continue;                   // (what gemm_lds_kernel takes)
+    if (t == TILE_256x256 && (a.epilogue == 3 ? a.n_peers > 0 : a.epilogue == 1 && M > 1024)) continue;
+    // duo tiles: from 257 rows on (below, the ring's deeper queue of weights is faster: 200 x 7168 x 8192 38 against 45 us)
+    if (t >= TILE_DUO_128 && (M <= 256 || (K & 63))) continue;
+    if (t == TILE_64x64 && a.epilogue == 3) continue;   // (16 columns per wavefront: more sums of squares per row than the buffer holds)
+    float us = gemm_cost(t, M, N, K, ksplit);
+    if (t == TILE_256x256 && a.epilogue == 1) us += 7.0f * (float)(((long)((M + 255) / 256) * ((N + 255) / 256) + 255) / 256);
     if (best < 0 || us < best_us) { best = t; best_us = us; }
   }
   if (cost) *cost = best_us;
@@ -767,14 +968,16 @@ static int gemm_best_tile(int M, int N, int K, int epilogue, int ksplit, float* 
 
 int gemm_ksplit(int M, int N, int K, int max_split, float extra_us) {
   const int stages = (K + 63) / 64;
+  GemmArgs a{};
+  a.M = M; a.N = N; a.K = K;
   int best = 1;
   float best_us = 0.f;
-  gemm_best_tile(M, N, K, 0, 1, &best_us);
+  gemm_best_tile(a, 1, &best_us);
   for (int ks = 2; ks <= max_split && ks <= 16; ++ks) {
     const int per = (stages + ks - 1) / ks;
     if ((stages + per - 1) / per != ks) continue;   // (a split would be left without work)
     float us;
-    gemm_best_tile(M, N, K, 0, ks, &us);
+    gemm_best_tile(a, ks, &us);
     us += extra_us;
     if (us < best_us) { best = ks; best_us = us; }
   }
@@ -783,8 +986,8 @@ int gemm_ksplit(int M, int N, int K, int max_split, float extra_us) {
 
 int gemm_ssq_parts(const GemmArgs& a) {
   // columns per workgroup (256-column tiles) or per wavefront
-  static const int cols[TILE_COUNT] = {16, 32, 32, 32, 256, 256};
-  const int c = cols[gemm_best_tile(a.M, a.N, a.K, a.epilogue, 1, nullptr)];
+  static const int cols[TILE_COUNT] = {16, 32, 32, 32, 256, 256, 128, 192, 256};
+  const int c = cols[gemm_best_tile(a, 1, nullptr)];
   return (a.N + c - 1) / c;
 }
 
@@ -804,13 +1007,16 @@ hipError_t launch_gemm_mfma(const GemmArgs& given, hipStream_t s) {
   if (a.epilogue == 3 && (!a.x_res || a.n_peers < 0 || (a.n_peers > 0 && !a.peers) || (a.xh_b && !a.xh_a) || (a.ssq_part && !a.xh_a) ||
                           (a.xh_a && !a.gain_a) || (a.xh_b && !a.gain_b)))
     return hipErrorInvalidValue;
-  switch (gemm_best_tile(a.M, a.N, a.K, a.epilogue, a.ksplit, nullptr)) {
+  switch (gemm_best_tile(a, a.ksplit, nullptr)) {
     case TILE_64x64: return launch_gemm_ring_t<64, 64, 2, 4, 6>(a, s);
     case TILE_64x128: return launch_gemm_ring_t<64, 128, 2, 4, 6>(a, s);
     case TILE_128x64: return launch_gemm_ring_t<128, 64, 4, 2, 5>(a, s);
     case TILE_128x128: return launch_gemm_ring_t<128, 128, 2, 4, 5>(a, s);
     case TILE_128x256: return launch_gemm_ring_t<128, 256, 2, 4, 3>(a, s);
-    default: return launch_gemm_lds(a, s);
+    case TILE_256x256: return launch_gemm_lds(a, s);
+    case TILE_DUO_128: return launch_gemm_duo<2>(a, s);
+    case TILE_DUO_192: return launch_gemm_duo<3>(a, s);
+    default: return launch_gemm_duo<4>(a, s);
   }
 }
 

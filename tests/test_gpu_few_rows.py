@@ -64,6 +64,22 @@ def test_residual_epilogue_of_the_wide_ring_tile(harness):
     assert max(res.errs) < TOL * 2 ** 0.5, res.errs
 
 
+@pytest.mark.parametrize("batch,prefill,hidden,inter,n_q,peers", [
+    (1, 257, 4160, 4160, 8, 0),     # the first row count that takes them: 128 columns, SwiGLU (32.5 row blocks of 8, 65 column blocks)
+    (1, 513, 2112, 8256, 8, 0),     # 128 columns, K of 129 stages in 3 splits: the rows' partial products
+    (1, 700, 576, 8256, 8, 2),      # 256 columns, SwiGLU, K of 9 stages (an odd number)
+    (1, 1025, 4160, 1088, 8, 9),    # 192 columns, residual update with more peers than are requested at once; 17 stages
+    (3, 700, 1088, 416, 16, 0),     # 192 columns, rotary + append over three sequences; 4.25 column blocks elsewhere
+    (3, 1000, 2112, 2112, 16, 2)])  # 256 columns in every projection, the last column block a quarter full
+def test_two_workgroups_per_cu(harness, batch, prefill, hidden, inter, n_q, peers):
+    """The tiles of 128 rows x 128 / 192 / 256 columns that share a CU in pairs, ragged in both directions, with every epilogue; the
+    second layer reads what the residual update left."""
+    w = WIDE.with_(name="pairs", n_layers=2, hidden=hidden, inter=inter, n_q_heads=n_q, batch=batch, prefill=prefill,
+                   tp_degree=1 + peers, peer_pool=2 if peers else 0)
+    res = harness.run_case(w, decode_steps=0, gen_device="cuda:0")
+    assert max(res.errs) < TOL * 2 ** 0.5, res.errs
+
+
 def test_wide_decode_replayed_from_a_graph(harness):
     """Every replay of a captured wide step against the eager steps, with eager work and a synchronisation between them."""
     import numpy as np
