@@ -9,6 +9,12 @@ typedef uint16_t bf16_t;  // bfloat16 bit pattern
 
 __device__ __forceinline__ float bf16_to_f32(bf16_t v) { return __uint_as_float(((uint32_t)v) << 16); }
 
+// 16 bytes on an 8-byte boundary (a caller's bf16 tensor: what the kernels ask of it)
+__device__ __forceinline__ uint4 load_16_at_8(const void* p) {
+  typedef uint32_t u32x4_at_8_t __attribute__((vector_size(16), aligned(8)));
+  return __builtin_bit_cast(uint4, *reinterpret_cast<const u32x4_at_8_t*>(p));
+}
+
 // round to nearest even (one v_cvt_pk_bf16_f32, which two values can share, instead of four integer operations each)
 __device__ __forceinline__ bf16_t f32_to_bf16(float f) { return __builtin_bit_cast(bf16_t, (__bf16)f); }
 __device__ __forceinline__ uint32_t f32_to_bf16x2(float lo, float hi) {
@@ -72,10 +78,33 @@ struct ReduceNormArgs {
   void* out_b;
   const void* gain_b;
   float* x_out;            // f32 or null
+  int x_step;              // x_out takes the step from the old rows to the new ones, not the new rows
   int rows, H;
   float eps;
 };
 hipError_t launch_reduce_norm(const ReduceNormArgs& a, bool is_bf16, hipStream_t s);
+
+// out_a[r][:] = rmsnorm(emb[r][:]) * gain_a, out_b likewise (or null), all bf16 [rows][H], on 16-byte boundaries except emb (8); H <= 16384, a multiple of 8
+#define EMBED_NORM_MAX_H 16384
+hipError_t launch_embed_norm(const bf16_t* emb, bf16_t* out_a, const bf16_t* gain_a, bf16_t* out_b, const bf16_t* gain_b, int rows, int H,
+                             float eps, hipStream_t s);
+
+// The start of a pipeline stage (three tensors handed over, f32 [rows][H]; att, mlp null: zeros) in one pass: x_{-1} = res + att,
+// whose normed rows are out_a, and x = x_{-1} + mlp, whose normed rows are out_b (T); x_out: an optional copy of x.  Any output of
+// the stage may be one of the inputs (a thread reads its elements of all of them first).  H <= 16384.
+struct StageInArgs {
+  const float *res, *att, *mlp;
+  float* x;
+  float* x_out;            // or null
+  void* out_a;
+  const void* gain_a;
+  void* out_b;
+  const void* gain_b;
+  int rows, H;
+  float eps;
+};
+#define STAGE_IN_MAX_H 16384
+hipError_t launch_stage_in(const StageInArgs& a, bool is_bf16, hipStream_t s);
 
 // Plain projections of the rows x (T [shard][M][K]) for all computed shards at once; w: T [K][N], a shard's matrices
 // w_stride BYTES behind the previous shard's, as are its caches (cache_stride); the other strides are elements per shard.
@@ -224,7 +253,10 @@ struct GemmArgs {
   // copy of them times the gain of that module's RMSNorm (the product in fp32, one rounding), and the rows' sums
   // of squares per column block: ssq_part[block][m], gemm_ssq_parts() blocks
   float* x_res;
+  const bf16_t* x_emb;     // if non-null the old rows are these (the embeddings, bf16 [M][N]) and not what x_res holds
+  int last;                // the new rows are not left in x_res: nothing reads the stream after this module
   float* x_copy;           // or null
+  int copy_step;           // the copy is the step from the old rows to the new ones (a module output that a stage hands over), not the new rows
   bf16_t* xh_a;            // bf16 [M][N], or null
   const bf16_t* gain_a;    // bf16 [N] (with xh_a)
   bf16_t* xh_b;            // or null (only with xh_a)

@@ -42,6 +42,7 @@ __global__ void reduce_norm_kernel(ReduceNormArgs a) {
     float v[4], t[4];
     if (emb) load4<T>(emb + (size_t)row * H + i, v);
     else load4<float>(a.x_src ? a.x_src + (size_t)row * H + i : xr + i, v);
+    const float old[4] = {v[0], v[1], v[2], v[3]};
     for (int s = 0; s < a.n_parts; ++s) {
       load4<float>(a.parts + s * a.part_stride + (size_t)row * H + i, t);
       v[0] += t[0]; v[1] += t[1]; v[2] += t[2]; v[3] += t[3];
@@ -51,7 +52,11 @@ __global__ void reduce_norm_kernel(ReduceNormArgs a) {
       v[0] += t[0]; v[1] += t[1]; v[2] += t[2]; v[3] += t[3];
     }
     store4<float>(xr + i, v);
-    if (a.x_out) store4<float>(a.x_out + (size_t)row * H + i, v);
+    if (a.x_out) {
+      if (a.x_step)
+        for (int e = 0; e < 4; ++e) t[e] = v[e] - old[e];
+      store4<float>(a.x_out + (size_t)row * H + i, a.x_step ? t : v);
+    }
     ss += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
   }
   if (!a.out_a && !a.out_b) return;
@@ -90,6 +95,136 @@ hipError_t launch_reduce_norm(const ReduceNormArgs& a, bool is_bf16, hipStream_t
   const int threads = a.H >= 4096 ? 1024 : 256;
   if (is_bf16) hipLaunchKernelGGL(reduce_norm_kernel<bf16_t>, dim3(a.rows), dim3(threads), 0, s, a);
   else hipLaunchKernelGGL(reduce_norm_kernel<float>, dim3(a.rows), dim3(threads), 0, s, a);
+  return hipGetLastError();
+}
+
+// ------------------------------------------------------------------------------------------------
+// Normed copies of the embeddings (bf16, see launch_embed_norm): 256 threads per row, eight columns per load and thread, the row in
+// registers (C pieces).  Memory traffic alone: 2 bytes read and 2 per copy written (the reduce kernel, a thread's columns four at a time
+// and 1024 threads per row: 32768 x 8192, two copies BEFORE -> AFTER us; with the rows left as fp32 beside them 598).
+// ------------------------------------------------------------------------------------------------
+template <int C>
+__global__ __launch_bounds__(256) void embed_norm_kernel(const bf16_t* __restrict__ emb, bf16_t* __restrict__ out_a, const bf16_t* __restrict__ gain_a,
+                                                         bf16_t* __restrict__ out_b, const bf16_t* __restrict__ gain_b, int H, float eps) {
+  const size_t base = (size_t)blockIdx.x * H;
+  uint4 x[C];
+  float ss = 0.f;
+  auto unpack = [](const uint4 u, float (&f)[8]) {
+    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { f[2 * e] = __uint_as_float(w[e] << 16); f[2 * e + 1] = __uint_as_float(w[e] & 0xFFFF0000u); }
+  };
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const int i = ((int)threadIdx.x + c * 256) * 8;
+    x[c] = i < H ? load_16_at_8(emb + base + i) : make_uint4(0, 0, 0, 0);
+  }
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    float f[8];
+    unpack(x[c], f);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ss += f[e] * f[e];
+  }
+  __shared__ float red[4];
+  ss = wave_sum(ss);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  const float rs = 1.0f / sqrtf((red[0] + red[1] + red[2] + red[3]) / (float)H + eps);
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const int i = ((int)threadIdx.x + c * 256) * 8;
+    if (i >= H) break;
+    float f[8];
+    unpack(x[c], f);
+    auto store = [&](bf16_t* out, const bf16_t* gain) {
+      float g[8];
+      unpack(*reinterpret_cast<const uint4*>(gain + i), g);
+      uint4 u;
+      u.x = f32_to_bf16x2(f[0] * rs * g[0], f[1] * rs * g[1]);
+      u.y = f32_to_bf16x2(f[2] * rs * g[2], f[3] * rs * g[3]);
+      u.z = f32_to_bf16x2(f[4] * rs * g[4], f[5] * rs * g[5]);
+      u.w = f32_to_bf16x2(f[6] * rs * g[6], f[7] * rs * g[7]);
+      *reinterpret_cast<uint4*>(out + base + i) = u;
+    };
+    store(out_a, gain_a);
+    if (out_b) store(out_b, gain_b);
+  }
+}
+
+hipError_t launch_embed_norm(const bf16_t* emb, bf16_t* out_a, const bf16_t* gain_a, bf16_t* out_b, const bf16_t* gain_b, int rows, int H,
+                             float eps, hipStream_t s) {
+  if (rows <= 0) return hipSuccess;
+  if (H > EMBED_NORM_MAX_H || (H & 7) || !emb || !out_a || !gain_a || (out_b && !gain_b)) return hipErrorInvalidValue;
+  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(rows), dim3(256), 0, s, emb, out_a, gain_a, out_b, gain_b, H, eps); };
+  if (H <= 4096) launch(embed_norm_kernel<2>);
+  else if (H <= 8192) launch(embed_norm_kernel<4>);
+  else launch(embed_norm_kernel<8>);
+  return hipGetLastError();
+}
+
+// ------------------------------------------------------------------------------------------------
+// The start of a pipeline stage (see StageInArgs), one workgroup per row, its C x 4 columns per thread in registers: memory traffic
+// alone, 20 bytes per element where two passes of the reduce kernel moved 28 (4001 x 8192, bf16: 95 + 78 -> 112 us, 5.8 TB/s).
+// ------------------------------------------------------------------------------------------------
+template <typename T, int C>
+__global__ __launch_bounds__(1024) void stage_in_kernel(StageInArgs a) {
+  const int row = blockIdx.x, H = a.H, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const size_t base = (size_t)row * H;
+  float p[C][4], v[C][4], sp = 0.f, sv = 0.f;   // x_{-1}, x_0 and their sums of squares
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const int i = ((int)threadIdx.x + c * (int)blockDim.x) * 4;
+    if (i >= H) break;
+    float t[4], u[4];
+    load4<float>(a.res + base + i, p[c]);
+    if (a.att) load4<float>(a.att + base + i, t);
+    if (a.mlp) load4<float>(a.mlp + base + i, u);
+    for (int e = 0; e < 4; ++e) {
+      if (a.att) p[c][e] += t[e];
+      v[c][e] = a.mlp ? p[c][e] + u[e] : p[c][e];
+    }
+    store4<float>(a.x + base + i, v[c]);
+    if (a.x_out) store4<float>(a.x_out + base + i, v[c]);
+    sp += p[c][0] * p[c][0] + p[c][1] * p[c][1] + p[c][2] * p[c][2] + p[c][3] * p[c][3];
+    sv += v[c][0] * v[c][0] + v[c][1] * v[c][1] + v[c][2] * v[c][2] + v[c][3] * v[c][3];
+  }
+  __shared__ float red[2][16];
+  sp = wave_sum(sp);
+  sv = wave_sum(sv);
+  if ((threadIdx.x & 63) == 0) { red[0][wave] = sp; red[1][wave] = sv; }
+  __syncthreads();
+  sp = sv = 0.f;
+  for (int w = 0; w < nw; ++w) { sp += red[0][w]; sv += red[1][w]; }
+  const float rp = 1.0f / sqrtf(sp / (float)H + a.eps), rv = 1.0f / sqrtf(sv / (float)H + a.eps);
+  auto normed = [&](void* out, const void* gain, int i, const float (&x)[4], float rs) {
+    float g[4], y[4];
+    load4<T>(reinterpret_cast<const T*>(gain) + i, g);
+    for (int e = 0; e < 4; ++e) y[e] = x[e] * rs * g[e];
+    store4<T>(reinterpret_cast<T*>(out) + base + i, y);
+  };
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const int i = ((int)threadIdx.x + c * (int)blockDim.x) * 4;
+    if (i >= H) break;
+    normed(a.out_a, a.gain_a, i, p[c], rp);
+    normed(a.out_b, a.gain_b, i, v[c], rv);
+  }
+}
+
+hipError_t launch_stage_in(const StageInArgs& a, bool is_bf16, hipStream_t s) {
+  if (a.rows <= 0) return hipSuccess;
+  if (a.H > STAGE_IN_MAX_H || !a.res || !a.x || !a.out_a || !a.gain_a || !a.out_b || !a.gain_b) return hipErrorInvalidValue;
+  const int threads = a.H >= 4096 ? 1024 : 256;
+  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(a.rows), dim3(threads), 0, s, a); };
+  if (a.H <= threads * 8) {   // (the registers of four are one workgroup per CU less)
+    if (is_bf16) launch(stage_in_kernel<bf16_t, 2>);
+    else launch(stage_in_kernel<float, 2>);
+  } else if (is_bf16) {
+    launch(stage_in_kernel<bf16_t, 4>);
+  } else {
+    launch(stage_in_kernel<float, 4>);
+  }
   return hipGetLastError();
 }
 

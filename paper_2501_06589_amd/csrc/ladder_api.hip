@@ -329,9 +329,13 @@ int consumers_of(const ladder_ctx* c, int m, int out[2]) {
 // product through memory.  The epilogue leaves the new rows, times the reading module's gain, as bf16 for the
 // modules that read x_m; their 1/rms (from the sums of squares the epilogue also leaves) scales the consumer's
 // product instead (the factor commutes with the product).
-int fuse_residual(ladder_ctx* c, GemmArgs& a, int m, float* x_copy, int cons[2]) {
+// emb: if non-null x_0, which is then read where it is instead of from a copy in the stream's buffer (module 1); the last module
+// leaves its rows in the copy alone.
+struct StreamCopy { float* at; bool step; };   // a copy of x_m (or, step, of x_m - x_{m-1}) that the residual update of module m leaves
+int fuse_residual(ladder_ctx* c, GemmArgs& a, int m, const void* emb, StreamCopy copy, int cons[2]) {
   const ladder_config& g = c->cfg;
-  a.epilogue = 3; a.x_res = c->x; a.x_copy = x_copy;
+  a.epilogue = 3; a.x_res = c->x; a.x_emb = (const bf16_t*)emb; a.x_copy = copy.at; a.copy_step = copy.step;
+  a.last = m == c->n_mod && copy.at;
   if (c->peers && c->n_peers > 0) {
     const size_t set = (size_t)(m % g.peer_pool);
     a.peers = (const bf16_t*)(c->peers + set * c->n_peers * (size_t)g.peer_rows * g.hidden * c->esz);
@@ -397,7 +401,7 @@ int run_few_rows(ladder_ctx* c, const char* x, int ldx, const char* wp, int rows
 }
 
 // the last projection of module m: (fuse) the residual update, or the partial products in out[slot][rows][hidden]
-int run_last_projection(ladder_ctx* c, int m, const char* x, const char* wp, int rows, int K, float* out, bool fuse, float* x_copy,
+int run_last_projection(ladder_ctx* c, int m, const char* x, const char* wp, int rows, int K, float* out, bool fuse, const void* emb, StreamCopy copy,
                         hipStream_t s, int* slots) {
   if (rows <= FEW_ROWS) {   // (never with fuse)
     int n = 0;
@@ -408,7 +412,7 @@ int run_last_projection(ladder_ctx* c, int m, const char* x, const char* wp, int
   GemmArgs a{};
   a.x = (const bf16_t*)x; a.ldx = K; a.wp = wp; a.M = rows; a.K = K; a.N = c->cfg.hidden; a.out = out; a.epilogue = 0;
   int cons[2], nc = 0;
-  if (fuse) nc = fuse_residual(c, a, m, x_copy, cons);
+  if (fuse) nc = fuse_residual(c, a, m, emb, copy, cons);
   HIP_TRY(c, timed(c, LADDER_K_GEMM, s, [&] { return launch_gemm_mfma(a, s); }));
   *slots += 1;
   return fuse ? finish_residual(c, a, rows, nc, cons, s) : LADDER_OK;
@@ -463,7 +467,7 @@ int run_module_plain(ladder_ctx* c, int m, int B, int T, int pos0, float* out, h
 // one module's compute on the main stream; writes parts[m%2] and returns the number of slots written, or (fuse)
 // updates the residual itself and returns -1 slots: then no reduce follows
 // ---------------------------------------------------------------------------------------------
-int run_module(ladder_ctx* c, int m, int B, int T, int pos0, bool decode, hipStream_t s, int* n_slots, bool fuse, float* x_copy) {
+int run_module(ladder_ctx* c, int m, int B, int T, int pos0, bool decode, hipStream_t s, int* n_slots, bool fuse, const void* emb, StreamCopy copy) {
   const ladder_config& g = c->cfg;
   const int rows = B * T, H = g.hidden, d = g.head_dim, nq = g.n_q_heads, nkv = g.n_kv_heads, I = g.inter;
   const int layer = (m - 1) / 2, par = m & 1;
@@ -521,7 +525,7 @@ int run_module(ladder_ctx* c, int m, int B, int T, int pos0, bool decode, hipStr
         HIP_TRY(c, timed(c, LADDER_K_ATTN_PREFILL, s, [&] { return launch_attn_prefill(aa, s); }));
       }
       const int nqd = nq * d;
-      const int rc = run_last_projection(c, m, c->obuf, L.po, rows, nqd, pout + slots * pstride, fuse, x_copy, s, &slots);
+      const int rc = run_last_projection(c, m, c->obuf, L.po, rows, nqd, pout + slots * pstride, fuse, emb, copy, s, &slots);
       if (rc) return rc;
     } else {
       if (rows <= 16) {
@@ -538,7 +542,7 @@ int run_module(ladder_ctx* c, int m, int B, int T, int pos0, bool decode, hipStr
         HIP_TRY(c, timed(c, LADDER_K_GEMM, s, [&] { return launch_gemm_mfma(a, s); }));
         if (gu_slots > 1) HIP_TRY(c, timed(c, LADDER_K_OTHER, s, [&] { return launch_swiglu_parts(c->gu, gu_slots, (size_t)rows * 2 * I, (bf16_t*)c->act, rows, I, s); }));
       }
-      const int rc = run_last_projection(c, m, c->act, L.pd, rows, I, pout + slots * pstride, fuse, x_copy, s, &slots);
+      const int rc = run_last_projection(c, m, c->act, L.pd, rows, I, pout + slots * pstride, fuse, emb, copy, s, &slots);
       if (rc) return rc;
     }
   }
@@ -582,7 +586,7 @@ __global__ __launch_bounds__(256) void stage_out_kernel(const float4* x2, const 
                                                         float4* r, float4* a, float4* m, size_t n4) {
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (size_t)gridDim.x * 256) {
     const float4 v2 = x2[i], v1 = x1[i], v0 = x0[i];
-    if (r != x2) r[i] = v2;   // (uniform; the stream may have been left there already)
+    r[i] = v2;
     a[i] = make_float4(v1.x - v2.x, v1.y - v2.y, v1.z - v2.z, v1.w - v2.w);
     m[i] = make_float4(v0.x - v1.x, v0.y - v1.y, v0.z - v1.z, v0.w - v1.w);
   }
@@ -602,6 +606,15 @@ int launch_stage_out(ladder_ctx* c, const float* x2, const float* x1, const floa
 // stream; module 2 reads it); ladder wiring in both modules
 int run_stage_in(ladder_ctx* c, const StageIo& st, int rows, hipStream_t s) {
   const ladder_config& g = c->cfg;
+  if (g.hidden <= STAGE_IN_MAX_H) {
+    StageInArgs a{};
+    a.res = st.res; a.att = st.att; a.mlp = st.mlp; a.x = c->x; a.rows = rows; a.H = g.hidden; a.eps = g.rms_eps;
+    if (c->n_mod == 2) a.x_out = st.r_out;   // (a stage of one layer: x_0 is the stream it hands over)
+    a.out_a = c->y[1]; a.gain_a = c->gain_attn[0]; a.out_b = c->y[0]; a.gain_b = c->gain_mlp[0];
+    c->y_scale[0] = c->y_scale[1] = nullptr;   // normed rows
+    HIP_TRY(c, timed(c, LADDER_K_REDUCE_NORM, s, [&] { return launch_stage_in(a, c->bf16, s); }));
+    return LADDER_OK;
+  }
   for (int cm = 1; cm <= 2; ++cm) {
     ReduceNormArgs a{};
     a.x = c->x; a.x_src = cm == 1 ? st.res : nullptr; a.rows = rows; a.H = g.hidden; a.eps = g.rms_eps;
@@ -615,7 +628,7 @@ int run_stage_in(ladder_ctx* c, const StageIo& st, int rows, hipStream_t s) {
   return LADDER_OK;
 }
 
-int run_reduce(ladder_ctx* c, int m, int rows, int n_slots, const void* emb, float* x_out, hipStream_t s) {
+int run_reduce(ladder_ctx* c, int m, int rows, int n_slots, const void* emb, StreamCopy copy, hipStream_t s) {
   const ladder_config& g = c->cfg;
   ReduceNormArgs a{};
   a.x = c->x; a.emb = emb; a.rows = rows; a.H = g.hidden; a.eps = g.rms_eps;
@@ -637,7 +650,7 @@ int run_reduce(ladder_ctx* c, int m, int rows, int n_slots, const void* emb, flo
     if (i == 0) { a.out_a = out; a.gain_a = gain; }
     else { a.out_b = out; a.gain_b = gain; }
   }
-  a.x_out = x_out;
+  a.x_out = copy.at; a.x_step = copy.step;
   // (the parallel block sums the partial sums of both modules of a layer before its one collective: the
   // attention module's reduce stands for the local addition, the MLP module's for the collective)
   const bool local_only = g.wiring == LADDER_WIRING_PARALLEL && (m & 1);
@@ -649,6 +662,24 @@ int run_reduce(ladder_ctx* c, int m, int rows, int n_slots, const void* emb, flo
     }));
   }
   HIP_TRY(c, timed(c, LADDER_K_REDUCE_NORM, s, [&] { return launch_reduce_norm(a, c->bf16, s); }));
+  return LADDER_OK;
+}
+
+// the start of a call whose module 1 reads the embeddings themselves in its residual update: the normed rows of the modules that read x_0
+int run_embed_norm(ladder_ctx* c, const void* emb, int rows, hipStream_t s) {
+  const ladder_config& g = c->cfg;
+  int cons[2];
+  const int nc = consumers_of(c, 0, cons);
+  bf16_t* out[2] = {nullptr, nullptr};
+  const bf16_t* gain[2] = {nullptr, nullptr};
+  for (int i = 0; i < nc; ++i) {
+    out[i] = (bf16_t*)c->y[cons[i] & 1];
+    gain[i] = (const bf16_t*)((cons[i] & 1) ? c->gain_attn[0] : c->gain_mlp[0]);
+    c->y_scale[cons[i] & 1] = nullptr;   // normed rows
+  }
+  HIP_TRY(c, timed(c, LADDER_K_REDUCE_NORM, s, [&] {
+    return launch_embed_norm((const bf16_t*)emb, out[0], gain[0], out[1], gain[1], rows, g.hidden, g.rms_eps, s);
+  }));
   return LADDER_OK;
 }
 
@@ -680,7 +711,9 @@ int forward_body(ladder_ctx* c, const void* x_in, int B, int T, int pos0, bool d
   // (calls of few rows split K over workgroups, whose partial products the reduce adds up; several real shards would each add to the residual, and the
   // emulated collective latency wants the reduce as a step of its own)
   const bool fuse = c->fast && rows > FEW_ROWS && c->cfg.n_real_shards == 1 && c->cfg.reduce_delay_us == 0;
-  int rc = st ? run_stage_in(c, *st, rows, s0) : run_reduce(c, 0, rows, 0, x_in, c->n_mod == 0 ? (float*)x_out : nullptr, s0);
+  // module 1's residual update reads the embeddings themselves: a copy of them in the stream's buffer is 10 bytes per element more
+  const bool emb_in_place = fuse && !st && c->cfg.hidden <= EMBED_NORM_MAX_H;
+  int rc = emb_in_place ? run_embed_norm(c, x_in, rows, s0) : st ? run_stage_in(c, *st, rows, s0) : run_reduce(c, 0, rows, 0, x_in, {c->n_mod == 0 ? (float*)x_out : nullptr, false}, s0);
   if (rc) return rc;
   if (overlap && c->n_mod >= 2) {  // fork: the MLP stream starts once x_0 and its normed copies exist
     HIP_TRY(c, hipEventRecord(c->ev_fork, s0));
@@ -692,11 +725,13 @@ int forward_body(ladder_ctx* c, const void* x_in, int B, int T, int pos0, bool d
     const int src = m - lag_of(c, m);
     if (src >= 1 && reduce_stream(src) != sm) HIP_TRY(c, hipStreamWaitEvent(sm, c->ev_red[src & 1], 0));
     int n_slots = 0;
-    // a copy of the stream x_m: the call's result, or of a stage's hand-over the stream before and after the last attention
-    // module's output joins it (the residual update writes the copy itself; the two outputs are the differences of
-    // consecutive streams)
-    float* copy = m == c->n_mod ? (float*)x_out : !st ? nullptr : m == c->n_mod - 2 ? st->r_out : m == c->n_mod - 1 ? st->a_out : nullptr;
-    rc = run_module(c, m, B, T, pos0, decode, sm, &n_slots, fuse, copy);
+    // a copy of the stream x_m: the call's result, or of a stage's hand-over the stream before the last two modules; and of the
+    // hand-over's two module outputs, the steps x_m - x_{m-1} (the residual update writes them itself: 34 bytes per element and a
+    // kernel less than differences of copies, 109 us at 4001 x 8192)
+    StreamCopy copy{m == c->n_mod ? (float*)x_out : nullptr, false};
+    if (st) copy = m == c->n_mod ? StreamCopy{st->m_out, true} : m == c->n_mod - 1 ? StreamCopy{st->a_out, true}
+                                 : StreamCopy{m == c->n_mod - 2 ? st->r_out : nullptr, false};
+    rc = run_module(c, m, B, T, pos0, decode, sm, &n_slots, fuse, m == 1 && emb_in_place ? x_in : nullptr, copy);
     if (rc) return rc;
     if (n_slots >= 0) {   // (else the module has updated the residual itself: wide calls run on one stream)
       if (rs != sm) {
@@ -707,10 +742,6 @@ int forward_body(ladder_ctx* c, const void* x_in, int B, int T, int pos0, bool d
       rc = run_reduce(c, m, rows, n_slots, nullptr, copy, rs);
       if (rc) return rc;
       if (overlap || side) HIP_TRY(c, hipEventRecord(c->ev_red[m & 1], rs));
-    }
-    if (st && m == c->n_mod) {
-      rc = launch_stage_out(c, st->r_out, st->a_out, c->x, *st, rows, s0);
-      if (rc) return rc;
     }
   }
   // join: the last reduce is after every module and every earlier reduce

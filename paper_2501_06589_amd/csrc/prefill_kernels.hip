@@ -60,7 +60,12 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x4_t (&acc)[
 #pragma unroll
       for (int jj = 0; jj < JB; ++jj) {
         const size_t off = row + min(nt0 + (st % JG) * JB + jj, NT - 1) * 16 + 4 * q;
-        o.xo[jj] = *reinterpret_cast<const float4*>(a.x_res + off);
+        if (a.x_emb) {
+          const uint2 e = *reinterpret_cast<const uint2*>(a.x_emb + off);
+          o.xo[jj] = __builtin_bit_cast(float4, make_uint4(e.x << 16, e.x & 0xFFFF0000u, e.y << 16, e.y & 0xFFFF0000u));
+        } else {
+          o.xo[jj] = *reinterpret_cast<const float4*>(a.x_res + off);
+        }
 #pragma unroll
         for (int p = 0; p < PB; ++p)
           if (p < a.n_peers) o.pk[jj][p] = *reinterpret_cast<const uint2*>(a.peers + p * a.peer_stride + off);
@@ -91,8 +96,10 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x4_t (&acc)[
           if (p < a.n_peers) add_peer(v4, o.pk[jj][p]);
         for (int p = PB; p < a.n_peers; ++p) add_peer(v4, *reinterpret_cast<const uint2*>(a.peers + p * a.peer_stride + off));
         if (ok) {
-          *reinterpret_cast<float4*>(a.x_res + off) = make_float4(v4[0], v4[1], v4[2], v4[3]);
-          if (a.x_copy) *reinterpret_cast<float4*>(a.x_copy + off) = make_float4(v4[0], v4[1], v4[2], v4[3]);
+          if (!a.last) *reinterpret_cast<float4*>(a.x_res + off) = make_float4(v4[0], v4[1], v4[2], v4[3]);
+          if (a.x_copy)
+            *reinterpret_cast<float4*>(a.x_copy + off) = a.copy_step ? make_float4(v4[0] - o.xo[jj].x, v4[1] - o.xo[jj].y, v4[2] - o.xo[jj].z, v4[3] - o.xo[jj].w)
+                                                                     : make_float4(v4[0], v4[1], v4[2], v4[3]);
           // the rows as the modules that read them want them: times their norm's gain (fp32 product, one rounding)
           auto store_gained = [&](bf16_t* dst, const bf16_t* gain) {
             const uint2 gk = *reinterpret_cast<const uint2*>(gain + (nt0 + j) * 16 + 4 * q);
@@ -286,8 +293,12 @@ __device__ __forceinline__ void gemm_residual_epilogue(const GemmArgs& a, f32x4_
         mrow[r] = m0 + lr / ROWS * (MT * 16) + pass * ROWS + lr % ROWS;
         ok[r] = col_ok && mrow[r] < a.M;
         off[r] = (size_t)min(mrow[r], a.M - 1) * a.N + nc;
-        xo[r][0] = *reinterpret_cast<const float4*>(a.x_res + off[r]);
-        xo[r][1] = *reinterpret_cast<const float4*>(a.x_res + off[r] + 4);
+        if (a.x_emb) {
+          xo[r][0] = __builtin_bit_cast(float4, load_16_at_8(a.x_emb + off[r]));
+        } else {
+          xo[r][0] = *reinterpret_cast<const float4*>(a.x_res + off[r]);
+          xo[r][1] = *reinterpret_cast<const float4*>(a.x_res + off[r] + 4);
+        }
 #pragma unroll
         for (int p = 0; p < PB; ++p)
           if (p < a.n_peers) pk[r][p] = load_once(a.peers + p * a.peer_stride + off[r]);
@@ -297,8 +308,9 @@ __device__ __forceinline__ void gemm_residual_epilogue(const GemmArgs& a, f32x4_
         const int lr = ((g * RB + r) * (WR * WC) + wave) * RPI + sub;
         const float4 p0 = *reinterpret_cast<const float4*>(stage + lr * STRIDE + 8 * l);
         const float4 p1 = *reinterpret_cast<const float4*>(stage + lr * STRIDE + 8 * l + 4);
-        float v8[8] = {xo[r][0].x + p0.x, xo[r][0].y + p0.y, xo[r][0].z + p0.z, xo[r][0].w + p0.w,
-                       xo[r][1].x + p1.x, xo[r][1].y + p1.y, xo[r][1].z + p1.z, xo[r][1].w + p1.w};
+        float old8[8] = {xo[r][0].x, xo[r][0].y, xo[r][0].z, xo[r][0].w, xo[r][1].x, xo[r][1].y, xo[r][1].z, xo[r][1].w};
+        if (a.x_emb) unpack8(__builtin_bit_cast(uint4, xo[r][0]), old8);
+        float v8[8] = {old8[0] + p0.x, old8[1] + p0.y, old8[2] + p0.z, old8[3] + p0.w, old8[4] + p1.x, old8[5] + p1.y, old8[6] + p1.z, old8[7] + p1.w};
         auto add_peer = [&](const uint4 u) {
           float f[8];
           unpack8(u, f);
@@ -310,11 +322,17 @@ __device__ __forceinline__ void gemm_residual_epilogue(const GemmArgs& a, f32x4_
           if (p < a.n_peers) add_peer(pk[r][p]);
         for (int p = PB; p < a.n_peers; ++p) add_peer(load_once(a.peers + p * a.peer_stride + off[r]));
         if (ok[r]) {
-          *reinterpret_cast<float4*>(a.x_res + off[r]) = make_float4(v8[0], v8[1], v8[2], v8[3]);
-          *reinterpret_cast<float4*>(a.x_res + off[r] + 4) = make_float4(v8[4], v8[5], v8[6], v8[7]);
+          if (!a.last) {
+            *reinterpret_cast<float4*>(a.x_res + off[r]) = make_float4(v8[0], v8[1], v8[2], v8[3]);
+            *reinterpret_cast<float4*>(a.x_res + off[r] + 4) = make_float4(v8[4], v8[5], v8[6], v8[7]);
+          }
           if (a.x_copy) {
-            *reinterpret_cast<float4*>(a.x_copy + off[r]) = make_float4(v8[0], v8[1], v8[2], v8[3]);
-            *reinterpret_cast<float4*>(a.x_copy + off[r] + 4) = make_float4(v8[4], v8[5], v8[6], v8[7]);
+            if (!a.copy_step) {
+#pragma unroll
+              for (int e = 0; e < 8; ++e) old8[e] = 0.f;
+            }
+            *reinterpret_cast<float4*>(a.x_copy + off[r]) = make_float4(v8[0] - old8[0], v8[1] - old8[1], v8[2] - old8[2], v8[3] - old8[3]);
+            *reinterpret_cast<float4*>(a.x_copy + off[r] + 4) = make_float4(v8[4] - old8[4], v8[5] - old8[5], v8[6] - old8[6], v8[7] - old8[7]);
           }
           // the rows as the modules that read them want them: times their norm's gain (fp32 product, one rounding)
           auto store_gained = [&](bf16_t* dst, const float (&g8)[8]) {

@@ -80,6 +80,21 @@ def test_two_workgroups_per_cu(harness, batch, prefill, hidden, inter, n_q, peer
     assert max(res.errs) < TOL * 2 ** 0.5, res.errs
 
 
+@pytest.mark.parametrize("rows", [100, 1100])
+def test_embeddings_off_a_16_byte_boundary(harness, rows):
+    """The same bits wherever the call's input lies (the residual update of module 1 reads it 16 bytes at a time beyond 1024 rows)."""
+    w = WIDE.with_(name="offset_input", hidden=512, inter=416, n_q_heads=4, prefill=rows)
+    ctx = harness.build_gpu(w, harness.make_tensors(w))
+    x = inputs.embeddings(w, 1, rows, inputs.SEED_PREFILL, "cuda:0")
+    want = ctx.prefill(x)
+    held = torch.empty(x.numel() + 8, dtype=x.dtype, device=x.device)
+    for shift in (4, 8):     # elements: 8 and 16 bytes
+        at = held[shift:shift + x.numel()].view(x.shape)
+        at.copy_(x)
+        assert torch.equal(want, ctx.prefill(at)), shift
+    ctx.free()
+
+
 def test_wide_decode_replayed_from_a_graph(harness):
     """Every replay of a captured wide step against the eager steps, with eager work and a synchronisation between them."""
     import numpy as np

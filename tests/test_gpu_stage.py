@@ -143,6 +143,16 @@ def test_prefill_then_decode_stages_bf16(harness, prefill):
     check(harness, out, TOL_BF16, "bf16 prefill + decode")
 
 
+@pytest.mark.parametrize("dtype,hidden,rows", [("bf16", 2048, 3), ("bf16", 2080, 3), ("fp32", 4088, 2), ("bf16", 8224, 2), ("fp32", 16400, 2)])
+def test_stage_start_at_the_edges_of_its_widths(harness, dtype, hidden, rows):
+    """The start of a stage in one pass: eight and sixteen columns per thread, 256 and 1024 threads, a last piece that is not
+    full, and a stream wider than it takes (two passes)."""
+    w = inputs.WORKLOADS["tiny"].with_(name="stage_start", dtype=dtype, hidden=hidden, n_q_heads=2, n_kv_heads=1, head_dim=64, inter=64,
+                                       tp_degree=1, n_real_shards=1, n_layers=2, batch=1, prefill=rows, decode_steps=1)
+    out = run_stages(harness, w, [(0, 1), (1, 2)], steps=1)
+    check(harness, out, TOL_BF16 if dtype == "bf16" else TOL_FP32, f"hidden {hidden}")
+
+
 def test_stages_fp32_two_real_shards(harness):
     """The fp32 storage path with both shards computed: the hand-over itself (sums and differences of fp32 streams)
     to the fp32 bar."""
