@@ -80,19 +80,20 @@ typedef struct {
   int32_t n_standard_layers; /* hybrid: with wiring LADDER, the first n_standard_layers layers still use
                                 the standard wiring (the paper's hybrid keeps ladder for the upper layers) */
   int32_t reduce_on_side_stream; /* 1: reduce + residual add overlap the next module on a side stream;
-                                    0: everything in order on one stream (same results).  Like
-                                    overlap_modules it applies to calls of at most 64 rows that do not take
-                                    the fused decode schedule; larger calls (prefill) always run in order:
-                                    their kernels fill the chip and measured slower when spread over streams;
-                                    so do calls of the plain kernels on layers of less than 32 MB, whose
-                                    kernels are shorter than the events between streams */
+                                    0: everything in order on one stream (same results).  It applies (where
+                                    overlap_modules is off) to calls of at most 64 rows that do not take the
+                                    fused decode schedule */
   int32_t peer_pool;      /* number of distinct synthetic peer sets; module m uses set m % peer_pool */
   int32_t peer_rows;      /* rows of each synthetic peer tensor (>= rows of any call), 0 if no peers */
   int32_t kernel_path;    /* LADDER_PATH_AUTO: MFMA/streaming kernels when dtype and sizes allow;
                              LADDER_PATH_GENERIC: the plain kernels (any size, both dtypes) */
   int32_t overlap_modules; /* 1: attention modules and MLP modules run on two internal streams, so that
                               module m+1 (which under the ladder wiring needs only x_{m-1}) can execute
-                              while module m still runs; 0: one compute stream.  Same results. */
+                              while module m still runs; 0: one compute stream.  Same results.  It applies
+                              to calls that do not take the fused decode schedule and gain by it: of at most
+                              1024 rows (64 where the wiring is not all ladder) and not from 257 to 512, on layers long
+                              enough for the events between the streams (plain kernels: of 32 MB and more);
+                              the others run in order */
   int32_t decode_graph;   /* 1: a decode step of the bf16 streaming path is captured once into a HIP graph
                              and replayed (the position lives in device memory and is advanced by the
                              graph itself); 0: eager launches.  Same results. */

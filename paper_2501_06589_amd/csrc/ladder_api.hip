@@ -10,9 +10,9 @@
 // into the fp32 residual x in place (x_m = x_{m-1} + sum), and emits the RMS-normed input of the
 // module(s) that read x_m: module m+2 with the ladder wiring, module m+1 with the standard wiring (the
 // parallel attention / MLP block: both modules of a layer read the layer's input, lag_of()).
-// The event recorded after it is the handle; module m+lag waits on it.  For calls of at most 64 rows
-// the two module kinds may run on two streams (or the reduces on a side stream), so that with the
-// ladder wiring reduce(m) overlaps module m+1; larger calls run in order on one stream, and with the
+// The event recorded after it is the handle; module m+lag waits on it.  For calls of at most 1024 rows
+// the two module kinds may run on two streams (or, to 64 rows, the reduces on a side stream), so that with the
+// ladder wiring reduce(m) overlaps module m+1 (forward_body says which); larger calls run in order on one stream, and with the
 // packed weights and one computed shard their reduce is the epilogue of the module's last GEMM
 // (fuse_residual).
 //
@@ -690,22 +690,29 @@ int run_embed_norm(ladder_ctx* c, const void* emb, int rows, hipStream_t s) {
 //     module m and reduce(m) still run on the other stream; reduce(m) waits for reduce(m-1) (the
 //     residual is updated in place, in module order) through an event.
 //   else reduce_on_side_stream: all modules on s0, all reduces on the side stream.
-//   else (and for every call with more than 64 rows): everything in order on s0.
+//   else: everything in order on s0.
 int forward_body(ladder_ctx* c, const void* x_in, int B, int T, int pos0, bool decode, void* x_out, hipStream_t s0, const StageIo* st = nullptr) {
   const int rows = B * T;
-  // calls with more than 64 rows (prefill) run in order on one stream: each of their kernels fills the
-  // chip, and the same work measured 4 % (reduce on the side stream) to 16 % (two module streams) slower
-  // when spread over streams.  Up to 64 rows the caller's choice stands; two layers, us, two module streams / reduces on a side
-  // stream / in order: 8B shape 17 rows 204 / 259 / 212, 64 rows 242 / 313 / 264, decode of 64 sequences 354 / 420 / 374; 70B
-  // R = 8 shard 148 / 191 / 142, 166 / 219 / 173, 188 / 240 / 189; 1.2B 115 / 146 / 109, 126 / 159 / 125, 235 / 270 / 236
-  // (and so does a pipeline stage's call: its hand-over reads the stream between the last modules)
+  // Which calls run on two module streams, where the caller has not switched them off.  Two modules side by side fill what each leaves
+  // idle: short kernels beside long ones, the last round of a product's tiles.  Too short for the events between the streams: layers
+  // whose weights and products take less than some 32 us (bytes at 5 TB/s, 1000 TFLOP/s).  From 257 to 512 rows in order: gate/up is
+  // then about one workgroup per CU, and kernels beside it only get in its way.  Beyond 1024 rows every kernel fills the chip (4 - 16 %
+  // slower side by side).  In order / side by side, us, 2 or 4 layers: 8B shape 80 rows 226 / 212, 100 (4) 478 / 420, 200 349 / 322, 400 517 /
+  // 500, 500 546 / 560, 600 660 / 625, 800 861 / 818, 1000 935 / 910; 70B R = 4 250 401 / 373, 350 509 / 527, 500 600 / 652, 560 748 / 691, 800
+  // 914 / 845; R = 8 (4) 17 rows 292 / 286, 64 356 / 323, 150 513 / 467, (2) 300 336 / 338, 500 440 / 453, 700 577 / 553, 1000 717 / 635; 1.2B
+  // (4) 17 rows 217 / 251, 64 248 / 256, 100 237 / 251, 200 299 / 262, 300 372 / 338, (2) 160 139 / 140, 700 268 / 241.  Decode steps of
+  // up to 64 sequences, whose attention reads a cache beside: side by side whatever the layer (1.2B, 40 sequences 1242 / 1146).
+  // (a pipeline stage's call is in order too: its hand-over reads the stream between the last modules)
   // (and so do calls whose kernels are shorter than the events between two streams: a layer of the plain path under
   // 32 MB of weights.  Measured, prompt of 32 and 8 steps, overlapped / in order, us: tiny model (2.8 MB) 1078 / 556, 10 MB
   // 970 / 725, 41 MB 1246 / 1077 and at batch 4 1498 / 1688, 100 MB 1288 / 1534, 200 MB 2221 / 2732)
   const bool brief = !c->fast && c->shard_bytes * (size_t)c->cfg.n_real_shards < (32u << 20);
+  const double layer_bytes = (double)c->shard_bytes * c->cfg.n_real_shards;
+  const bool independent = c->cfg.wiring == LADDER_WIRING_LADDER && c->cfg.n_standard_layers == 0;   // (the wiring that was measured beyond 64 rows)
+  const bool pays = !c->fast || (rows <= 64 && (T == 1 || c->cfg.reduce_delay_us > 0)) ? rows <= 64 : rows <= (independent ? FEW_ROWS : 64) && (rows <= 256 || rows > 512) && layer_bytes * (200.0 + rows) >= 32e9;
   const bool small = rows <= 64 && !st && !brief;
-  const bool overlap = small && c->cfg.overlap_modules != 0;
-  const bool side = small && !overlap && c->cfg.reduce_on_side_stream != 0;
+  const bool overlap = pays && !st && !brief && c->cfg.overlap_modules != 0;
+  const bool side = small && c->cfg.overlap_modules == 0 && c->cfg.reduce_on_side_stream != 0;
   auto module_stream = [&](int m) { return (overlap && (m & 1) == 0) ? c->s_mlp : s0; };
   auto reduce_stream = [&](int m) { return m == 0 ? s0 : (overlap ? module_stream(m) : (side ? c->side : s0)); };
   // (calls of few rows split K over workgroups, whose partial products the reduce adds up; several real shards would each add to the residual, and the

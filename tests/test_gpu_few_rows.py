@@ -95,6 +95,25 @@ def test_embeddings_off_a_16_byte_boundary(harness, rows):
     ctx.free()
 
 
+def test_module_streams_leave_the_same_bits(harness):
+    """Calls that run attention and MLP modules on two streams (65 - 256 and 513 - 1024 rows of a layer of 240 MB) against the same
+    calls in order, with calls of other row counts in between and decode steps behind them."""
+    w = WIDE.with_(name="streams", n_layers=3, hidden=4096, inter=6144, prefill=1024)
+    tensors = harness.make_tensors(w, "cuda:0")
+    side, order = (harness.build_gpu(w, tensors, overlap_modules=v) for v in (1, 0))
+    x = inputs.embeddings(w, 1, 1024, inputs.SEED_PREFILL, "cuda:0")
+    for rows in (100, 256, 257, 513, 1024, 65, 100):
+        calls = []
+        for ctx in (side, order):
+            out = [ctx.prefill(x[:, :rows].contiguous())]
+            out += [ctx.decode_step(x[:, i].contiguous()) for i in range(2)]
+            calls.append(out)
+        for a, b in zip(*calls):
+            assert torch.equal(a, b), rows
+    side.free()
+    order.free()
+
+
 def test_wide_decode_replayed_from_a_graph(harness):
     """Every replay of a captured wide step against the eager steps, with eager work and a synchronisation between them."""
     import numpy as np
