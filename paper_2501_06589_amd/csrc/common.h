@@ -106,6 +106,22 @@ struct StageInArgs {
 #define STAGE_IN_MAX_H 16384
 hipError_t launch_stage_in(const StageInArgs& a, bool is_bf16, hipStream_t s);
 
+// Rows of the stream as a sum that nobody has stored yet: a stored stream (emb: T, the embeddings x_0; else base: f32) and the outputs of
+// the one or two modules behind it, each the partial sums of the computed shards and then the peers (order: base, parts 0.., peers 0.., ...)
+struct StreamSum {
+  const void* emb;
+  const float* base;
+  int n_adds;              // 0 .. 2
+  const float* parts[2];   // f32 [n_parts][rows][H]
+  int n_parts;
+  size_t part_stride;      // elements
+  const void* peers[2];    // T or null
+  int n_peers;
+  size_t peer_stride;      // elements
+};
+// x_out[r][:] = the sum, f32
+hipError_t launch_stream_sum(const StreamSum& a, float* x_out, int rows, int H, bool is_bf16, hipStream_t s);
+
 // Plain projections of the rows x (T [shard][M][K]) for all computed shards at once; w: T [K][N], a shard's matrices
 // w_stride BYTES behind the previous shard's, as are its caches (cache_stride); the other strides are elements per shard.
 enum { PLAIN_OUT = 0, PLAIN_SWIGLU = 1, PLAIN_QKV = 2 };
@@ -132,8 +148,15 @@ struct PlainGemmArgs {
   const float* cos_tab;    // [max_seq][d/2]
   const float* sin_tab;
   int T, pos0, nkv, d, max_seq;
+  // gain non-null (QKV and SWIGLU, M <= PLAIN_NORM_ROWS): instead of x the rows are rmsnorm(in) * gain, made where they are multiplied, and
+  // the new rows of the stream are left in x_store (f32 [M][K], or null; not what `in` reads)
+  const void* gain;
+  StreamSum in;
+  float eps;
+  float* x_store;
   int n_blocks;            // set by the launcher: column blocks of all matrices
 };
+#define PLAIN_NORM_ROWS 64
 hipError_t launch_plain_gemm(const PlainGemmArgs& a, bool is_bf16, hipStream_t s);
 
 // qkv: f32 [n_parts][rows][(nq+2nkv)*d] (slots summed).  rows = B*T, row = b*T + t, position = pos0 + t.

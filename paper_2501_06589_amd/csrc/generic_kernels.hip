@@ -101,7 +101,7 @@ hipError_t launch_reduce_norm(const ReduceNormArgs& a, bool is_bf16, hipStream_t
 // ------------------------------------------------------------------------------------------------
 // Normed copies of the embeddings (bf16, see launch_embed_norm): 256 threads per row, eight columns per load and thread, the row in
 // registers (C pieces).  Memory traffic alone: 2 bytes read and 2 per copy written (the reduce kernel, a thread's columns four at a time
-// and 1024 threads per row: 32768 x 8192, two copies BEFORE -> AFTER us; with the rows left as fp32 beside them 598).
+// and 1024 threads per row: 32768 x 8192, two copies 461 -> 289 us; with the rows left as fp32 beside them 598).
 // ------------------------------------------------------------------------------------------------
 template <int C>
 __global__ __launch_bounds__(256) void embed_norm_kernel(const bf16_t* __restrict__ emb, bf16_t* __restrict__ out_a, const bf16_t* __restrict__ gain_a,
@@ -283,53 +283,120 @@ __device__ __forceinline__ PlainW4<T, VEC> plain_w4(const T* w, int k, int K, in
   return r;
 }
 
-// rows m0 .. m0 + MR - 1 of x times columns n .. n + 3 (per lane) of w; the sums over all K end up in `sum` [MR][64]
-template <typename T, int MR, bool VEC, int KC>
-__device__ __forceinline__ void plain_product(const T* x, int M, int K, int m0, const T* w, int N, int n0, float (*xs)[KC],
-                                              float (*red)[MR][64], float (*sum)[64]) {
+// element (row, k) of MR rows of a StreamSum; every load of a group of four pieces is requested before the first is needed
+template <typename T, int MR>
+__device__ __forceinline__ void stream_rows(const StreamSum& a, int H, int m0, int M, int k, float (&v)[MR]) {
+  size_t at[MR];
+#pragma unroll
+  for (int m = 0; m < MR; ++m) {
+    at[m] = (size_t)min(m0 + m, M - 1) * H + k;
+    v[m] = a.emb ? load_f<T>(reinterpret_cast<const T*>(a.emb) + at[m]) : a.base[at[m]];
+  }
+  auto add = [&](int n, auto piece) {
+    for (int s0 = 0; s0 < n; s0 += 4) {
+      float t[4][MR];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int m = 0; m < MR; ++m) t[j][m] = s0 + j < n ? piece(s0 + j, at[m]) : 0.f;   // (uniform)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int m = 0; m < MR; ++m) v[m] = s0 + j < n ? v[m] + t[j][m] : v[m];
+    }
+  };
+  for (int i = 0; i < a.n_adds; ++i) {
+    const float* const parts = a.parts[i];
+    const T* const peers = reinterpret_cast<const T*>(a.peers[i]);
+    add(a.n_parts, [&](int s, size_t o) { return parts[s * a.part_stride + o]; });
+    add(peers ? a.n_peers : 0, [&](int s, size_t o) { return load_f<T>(peers + s * a.peer_stride + o); });
+  }
+}
+
+// rows m0 .. m0 + MR - 1 of x times columns n .. n + 3 (per lane) of the NM matrices w; the sums over all K end up in `sum` [NM][MR][64].
+// NORM: the rows are those of a.in times the gain; the factor 1/rms commutes with the product and is applied to the sums; store: this
+// workgroup leaves the rows in a.x_store.
+template <typename T, int MR, bool VEC, int KC, int NM, bool NORM>
+__device__ __forceinline__ void plain_product(const PlainGemmArgs& a, const T* x, int m0, const T* const (&w)[NM], int N, int n0, bool store, float (*xs)[KC],
+                                              float (*red)[MR][64], float (*sum)[MR][64], float (*red_ss)[4]) {
+  const int M = a.M, K = a.K;
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
   const int c4 = (lane & 15) * 4, kg = t >> 4;
   constexpr int PASSES = KC / 64, ROWS = 256 / KC;   // (rows of x that the workgroup's threads take side by side)
-  float acc[MR][4] = {};
+  static_assert(!NORM || ROWS == 1, "a thread per k");
+  float acc[NM][MR][4] = {}, ss[MR] = {};
   for (int k0 = 0; k0 < K; k0 += KC) {
-    PlainW4<T, VEC> wr[PASSES][4];   // [pass][k]
+    PlainW4<T, VEC> wr[NM][PASSES][4];   // [matrix][pass][k]
 #pragma unroll
-    for (int i = 0; i < PASSES; ++i)
+    for (int j = 0; j < NM; ++j)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) wr[i][e] = plain_w4<T, VEC>(w, k0 + i * 64 + kg * 4 + e, K, n0 + c4, N);
-    if (k0 > 0) __syncthreads();   // the previous pass has been read
+      for (int i = 0; i < PASSES; ++i)
 #pragma unroll
-    for (int i = 0; i < MR; i += ROWS) {
-      const int m = ROWS == 1 ? i : i + t / KC, k = ROWS == 1 ? t : t % KC;
-      xs[m][k] = m0 + m < M && k0 + k < K ? load_f<T>(x + (size_t)(m0 + m) * K + k0 + k) : 0.f;
+        for (int e = 0; e < 4; ++e) wr[j][i][e] = plain_w4<T, VEC>(w[j], k0 + i * 64 + kg * 4 + e, K, n0 + c4, N);
+    if constexpr (NORM) {
+      const int k = k0 + t, kc = min(k, K - 1);
+      float v[MR];
+      const float gain = load_f<T>(reinterpret_cast<const T*>(a.gain) + kc);
+      stream_rows<T, MR>(a.in, K, m0, M, kc, v);
+      if (k0 > 0) __syncthreads();   // the previous pass has been read
+#pragma unroll
+      for (int m = 0; m < MR; ++m) {
+        const bool ok = m0 + m < M && k < K;
+        if (ok && store) a.x_store[(size_t)(m0 + m) * K + k] = v[m];
+        xs[m][t] = ok ? v[m] * gain : 0.f;
+        ss[m] += ok ? v[m] * v[m] : 0.f;
+      }
+    } else {
+      if (k0 > 0) __syncthreads();   // the previous pass has been read
+#pragma unroll
+      for (int i = 0; i < MR; i += ROWS) {
+        const int m = ROWS == 1 ? i : i + t / KC, k = ROWS == 1 ? t : t % KC;
+        xs[m][k] = m0 + m < M && k0 + k < K ? load_f<T>(x + (size_t)(m0 + m) * K + k0 + k) : 0.f;
+      }
     }
     __syncthreads();
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int i = 0; i < PASSES; ++i) {
-      float wv[4][4];   // [k][column]
+    for (int i = 0; i < PASSES; ++i)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) wr[i][e].value(wv[e]);
+      for (int j = 0; j < NM; ++j) {
+        float wv[4][4];   // [k][column]
 #pragma unroll
-      for (int m = 0; m < MR; ++m) {
-        const float4 xv = *reinterpret_cast<const float4*>(&xs[m][i * 64 + kg * 4]);
+        for (int e = 0; e < 4; ++e) wr[j][i][e].value(wv[e]);
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-          acc[m][c] = fmaf(xv.w, wv[3][c], fmaf(xv.z, wv[2][c], fmaf(xv.y, wv[1][c], fmaf(xv.x, wv[0][c], acc[m][c]))));
+        for (int m = 0; m < MR; ++m) {
+          const float4 xv = *reinterpret_cast<const float4*>(&xs[m][i * 64 + kg * 4]);
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            acc[j][m][c] = fmaf(xv.w, wv[3][c], fmaf(xv.z, wv[2][c], fmaf(xv.y, wv[1][c], fmaf(xv.x, wv[0][c], acc[j][m][c]))));
+        }
       }
-    }
   }
 #pragma unroll
-  for (int m = 0; m < MR; ++m)
+  for (int j = 0; j < NM; ++j)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      float v = acc[m][c];
-      v += __shfl_xor(v, 16, 64);
-      v += __shfl_xor(v, 32, 64);
-      if (lane < 16) red[wave][m][c4 + c] = v;
+    for (int m = 0; m < MR; ++m)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        float v = acc[j][m][c];
+        v += __shfl_xor(v, 16, 64);
+        v += __shfl_xor(v, 32, 64);
+        if (lane < 16) red[j * 4 + wave][m][c4 + c] = v;
+      }
+  if constexpr (NORM) {
+#pragma unroll
+    for (int m = 0; m < MR; ++m) {
+      const float v = wave_sum(ss[m]);
+      if (lane == 0) red_ss[m][wave] = v;
     }
+  }
   __syncthreads();
-  for (int i = t; i < MR * 64; i += 256) sum[i >> 6][i & 63] = red[0][i >> 6][i & 63] + red[1][i >> 6][i & 63] + red[2][i >> 6][i & 63] + red[3][i >> 6][i & 63];
+  for (int i = t; i < NM * MR * 64; i += 256) {
+    const int j = i / (MR * 64), m = i / 64 % MR, c = i & 63;
+    float v = red[j * 4][m][c] + red[j * 4 + 1][m][c] + red[j * 4 + 2][m][c] + red[j * 4 + 3][m][c];
+    if constexpr (NORM) v *= 1.0f / sqrtf((red_ss[m][0] + red_ss[m][1] + red_ss[m][2] + red_ss[m][3]) / (float)K + a.eps);
+    sum[j][m][c] = v;
+  }
   __syncthreads();
 }
 
@@ -356,11 +423,13 @@ __device__ __forceinline__ bool plain_tile(unsigned row_blocks, unsigned col_blo
   return true;
 }
 
-template <typename T, int MR, bool VEC, int KC>
+template <typename T, int MR, bool VEC, int KC, bool NORM>
 __global__ __launch_bounds__(256) void plain_gemm_kernel(PlainGemmArgs a) {
+  constexpr int NM = MR <= 4 ? 2 : 1;   // gate and up in one sweep over K where the registers allow it
   __shared__ __attribute__((aligned(16))) float xs[MR][KC];
-  __shared__ float red[4][MR][64];
+  __shared__ float red[4 * NM][MR][64];
   __shared__ float sum[2][MR][64];
+  __shared__ float red_ss[MR][4];
   const int t = threadIdx.x, shard = blockIdx.z;
   unsigned m_blk, col_blk;
   if (MR == 1) {   // (a single row: m_blk is 0 inside the grid; written this way the tiny fp32 model's steps take 558 us, as one comparison 568)
@@ -376,8 +445,18 @@ __global__ __launch_bounds__(256) void plain_gemm_kernel(PlainGemmArgs a) {
   const int n0 = blk * 64, N = a.N[mat];
   const T* x = reinterpret_cast<const T*>(a.x) + shard * a.x_stride;
   auto weights = [&](int i) { return reinterpret_cast<const T*>(reinterpret_cast<const char*>(a.w[i]) + shard * a.w_stride); };
-  plain_product<T, MR, VEC, KC>(x, a.M, a.K, m0, weights(mat), N, n0, xs, red, sum[0]);
-  if (a.epilogue == PLAIN_SWIGLU) plain_product<T, MR, VEC, KC>(x, a.M, a.K, m0, weights(1), N, n0, xs, red, sum[1]);
+  const bool store = NORM && a.x_store && col_blk == 0 && shard == 0;
+  if (NM == 2 && a.epilogue == PLAIN_SWIGLU) {
+    const T* const w[2] = {weights(0), weights(1)};
+    plain_product<T, MR, VEC, KC, 2, NORM>(a, x, m0, w, N, n0, store, xs, red, sum, red_ss);
+  } else {
+    const T* const w[1] = {weights(mat)};
+    plain_product<T, MR, VEC, KC, 1, NORM>(a, x, m0, w, N, n0, store, xs, red, sum, red_ss);
+    if (a.epilogue == PLAIN_SWIGLU) {
+      const T* const up[1] = {weights(1)};
+      plain_product<T, MR, VEC, KC, 1, NORM>(a, x, m0, up, N, n0, false, xs, red, sum + 1, red_ss);
+    }
+  }
   if (a.epilogue == PLAIN_OUT) {
     for (int i = t; i < MR * 64; i += 256) {
       const int m = m0 + (i >> 6), n = n0 + (i & 63);
@@ -431,23 +510,49 @@ static hipError_t launch_plain_gemm_t(PlainGemmArgs a, bool vec, hipStream_t s) 
   // (hidden 8192, 1024 rows 50.4 -> 42.5 ms; but hidden 1024, 128 rows, which do not fill two, 477 -> 583 us).  Same order of sums.
   if constexpr (sizeof(T) == 4 && MR == 16) {
     if (blocks * a.n_shards > 512) {
-      if (vec) hipLaunchKernelGGL((plain_gemm_kernel<T, MR, true, 128>), grid, dim3(256), 0, s, a);
-      else hipLaunchKernelGGL((plain_gemm_kernel<T, MR, false, 128>), grid, dim3(256), 0, s, a);
+      if (vec) hipLaunchKernelGGL((plain_gemm_kernel<T, MR, true, 128, false>), grid, dim3(256), 0, s, a);
+      else hipLaunchKernelGGL((plain_gemm_kernel<T, MR, false, 128, false>), grid, dim3(256), 0, s, a);
       return hipGetLastError();
     }
   }
-  if (vec) hipLaunchKernelGGL((plain_gemm_kernel<T, MR, true, 256>), grid, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((plain_gemm_kernel<T, MR, false, 256>), grid, dim3(256), 0, s, a);
+  if constexpr (MR <= 4) {
+    if (a.gain) {
+      if (vec) hipLaunchKernelGGL((plain_gemm_kernel<T, MR, true, 256, true>), grid, dim3(256), 0, s, a);
+      else hipLaunchKernelGGL((plain_gemm_kernel<T, MR, false, 256, true>), grid, dim3(256), 0, s, a);
+      return hipGetLastError();
+    }
+  }
+  if (vec) hipLaunchKernelGGL((plain_gemm_kernel<T, MR, true, 256, false>), grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((plain_gemm_kernel<T, MR, false, 256, false>), grid, dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void stream_sum_kernel(StreamSum a, float* x_out, int rows, int H) {
+  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (i >= (long long)rows * H) return;
+  float v[1];
+  stream_rows<T, 1>(a, H, (int)(i / H), rows, (int)(i % H), v);
+  x_out[i] = v[0];
+}
+
+hipError_t launch_stream_sum(const StreamSum& a, float* x_out, int rows, int H, bool is_bf16, hipStream_t s) {
+  const long long blocks = ((long long)rows * H + 255) / 256;
+  if (blocks <= 0) return hipSuccess;
+  if ((!a.emb && !a.base) || !x_out || blocks > 0x7fffff || a.n_adds < 0 || a.n_adds > 2) return hipErrorInvalidValue;
+  if (is_bf16) hipLaunchKernelGGL(stream_sum_kernel<bf16_t>, dim3((unsigned)blocks), dim3(256), 0, s, a, x_out, rows, H);
+  else hipLaunchKernelGGL(stream_sum_kernel<float>, dim3((unsigned)blocks), dim3(256), 0, s, a, x_out, rows, H);
   return hipGetLastError();
 }
 
 hipError_t launch_plain_gemm(const PlainGemmArgs& a, bool is_bf16, hipStream_t s) {
   if (a.M <= 0 || a.n_shards <= 0) return hipSuccess;
+  if (a.gain && (a.M > PLAIN_NORM_ROWS || a.epilogue == PLAIN_OUT || (!a.in.emb && !a.in.base) || a.in.n_adds < 0 || a.in.n_adds > 2)) return hipErrorInvalidValue;
   // four weights per load where every row of every matrix starts on such a boundary
   bool vec = (a.w_stride & 15) == 0;
   for (int i = 0; i < a.n_mat; ++i) vec = vec && a.N[i] % 4 == 0 && ((uintptr_t)a.w[i] & 15) == 0;
   // rows per workgroup: one for a single row; four for a few; more re-use of the weights beyond
-  const int mr = a.M == 1 ? 1 : a.M <= 64 ? 4 : 16;
+  const int mr = a.M == 1 ? 1 : a.M <= PLAIN_NORM_ROWS ? 4 : 16;
   if (is_bf16) return mr == 1 ? launch_plain_gemm_t<bf16_t, 1>(a, vec, s) : mr == 4 ? launch_plain_gemm_t<bf16_t, 4>(a, vec, s) : launch_plain_gemm_t<bf16_t, 16>(a, vec, s);
   return mr == 1 ? launch_plain_gemm_t<float, 1>(a, vec, s) : mr == 4 ? launch_plain_gemm_t<float, 4>(a, vec, s) : launch_plain_gemm_t<float, 16>(a, vec, s);
 }

@@ -106,6 +106,7 @@ struct ladder_ctx {
   const char* peers = nullptr;
   // workspaces
   float* x = nullptr;
+  float* x_other = nullptr;     // plain path, calls of few rows: the stream before or after the one in x
   char* y[2] = {nullptr, nullptr};
   // wide calls of the packed-weight path: the residual update is the epilogue of a module's last GEMM, which
   // leaves un-normed bf16 rows in y[] and the rows' 1/rms in y_rs[]; y_scale[i] is y_rs[i] while y[i] holds
@@ -436,13 +437,17 @@ size_t gu_rows_of(const ladder_config& g) {
 }
 
 // one module of the plain path: three launches (attention) or two (MLP) for all computed shards, which leave a partial
-// sum each in out[shard][rows][hidden]
-int run_module_plain(ladder_ctx* c, int m, int B, int T, int pos0, float* out, hipStream_t s) {
+// sum each in out[shard][rows][hidden]; in: if non-null the rows the module reads are made from this sum (not read from y) and left in x_store
+int run_module_plain(ladder_ctx* c, int m, int B, int T, int pos0, float* out, hipStream_t s, const StreamSum* in = nullptr, float* x_store = nullptr) {
   const ladder_config& g = c->cfg;
   const int rows = B * T, H = g.hidden, d = g.head_dim, nqd = g.n_q_heads * d, nkd = g.n_kv_heads * d, I = g.inter;
   const LayerStore& L = c->store[(size_t)((m - 1) / 2) * g.n_real_shards];   // shard 0; the others lie at fixed strides behind it
   PlainGemmArgs a{};
   a.x = c->y[m & 1]; a.M = rows; a.K = H; a.n_shards = g.n_real_shards; a.w_stride = c->shard_bytes;
+  if (in) {
+    a.in = *in; a.x_store = x_store; a.eps = g.rms_eps;
+    a.gain = (m & 1) ? (const void*)c->gain_attn[(size_t)(m - 1) / 2] : (const void*)c->gain_mlp[(size_t)(m - 1) / 2];
+  }
   PlainGemmArgs last{};
   last.M = rows; last.n_shards = g.n_real_shards; last.w_stride = c->shard_bytes; last.n_mat = 1; last.N[0] = H;
   last.epilogue = PLAIN_OUT; last.out = out; last.out_stride = (size_t)rows * H;
@@ -683,6 +688,42 @@ int run_embed_norm(ladder_ctx* c, const void* emb, int rows, hipStream_t s) {
   return LADDER_OK;
 }
 
+// A call of few rows of the plain path, in order: five launches per layer instead of seven.  Reduce and norm are no kernels of their own:
+// the first projection of a module makes the rows it reads (the last stored stream and the module outputs behind it), and one of
+// its workgroups per row block stores them for the modules that come.  What is read is there when it is read: module m's first projection
+// adds the outputs up to module m - lag, so the output of module m - 2, whose buffer module m's last projection overwrites, has been added.
+// tiny fp32 model, one row: 16 launches -> 11 (prompt of 32 and 8 steps 565 -> 484 us; hidden 512 726 -> 634, hidden 1024, two sequences 1383 -> 1287).
+int forward_plain(ladder_ctx* c, const void* x_in, int B, int T, int pos0, float* x_out, hipStream_t s) {
+  const ladder_config& g = c->cfg;
+  const int rows = B * T;
+  StreamSum in{};
+  in.emb = x_in; in.n_parts = g.n_real_shards; in.part_stride = (size_t)rows * g.hidden;
+  if (c->peers && c->n_peers > 0) { in.n_peers = c->n_peers; in.peer_stride = (size_t)g.peer_rows * g.hidden; }
+  int stored = 0;   // in.emb / in.base hold the stream x_stored
+  auto add_up_to = [&](int m) {
+    in.n_adds = 0;
+    for (int h = stored + 1; h <= m; ++h, ++in.n_adds) {
+      in.parts[in.n_adds] = c->parts[h & 1];
+      in.peers[in.n_adds] = in.n_peers ? c->peers + (size_t)(h % g.peer_pool) * c->n_peers * (size_t)g.peer_rows * g.hidden * c->esz : nullptr;
+    }
+  };
+  float* buf[2] = {c->x, c->x_other};
+  for (int m = 1; m <= c->n_mod; ++m) {
+    const int src = std::max(0, m - lag_of(c, m));
+    add_up_to(src);
+    float* const store = in.n_adds ? buf[0] : nullptr;
+    const int rc = run_module_plain(c, m, B, T, pos0, c->parts[m & 1], s, &in, store);
+    if (rc) return rc;
+    if (store) {
+      in.emb = nullptr; in.base = store; stored = src;
+      std::swap(buf[0], buf[1]);
+    }
+  }
+  add_up_to(c->n_mod);
+  HIP_TRY(c, timed(c, LADDER_K_REDUCE_NORM, s, [&] { return launch_stream_sum(in, x_out, rows, g.hidden, c->bf16, s); }));
+  return LADDER_OK;
+}
+
 // the 2N modules and their reduces, from stream s0 and back to it.
 // Stream plan:
 //   overlap_modules: odd (attention) modules and their reduces on the call's stream s0, even (MLP) modules and their
@@ -713,6 +754,11 @@ int forward_body(ladder_ctx* c, const void* x_in, int B, int T, int pos0, bool d
   const bool small = rows <= 64 && !st && !brief;
   const bool overlap = pays && !st && !brief && c->cfg.overlap_modules != 0;
   const bool side = small && c->cfg.overlap_modules == 0 && c->cfg.reduce_on_side_stream != 0;
+  // the plain path in order, up to PLAIN_NORM_ROWS rows: module inputs made where they are multiplied, by every column block anew, which
+  // pays while that is little beside a block's 64 columns of weights (four rows per block beyond one)
+  if (!c->fast && !st && !overlap && !side && rows <= PLAIN_NORM_ROWS && c->cfg.reduce_delay_us == 0 &&
+      (rows == 1 ? 1 : 4) * (1 + c->cfg.n_real_shards + (c->peers ? c->n_peers : 0)) <= 16)
+    return forward_plain(c, x_in, B, T, pos0, (float*)x_out, s0);
   auto module_stream = [&](int m) { return (overlap && (m & 1) == 0) ? c->s_mlp : s0; };
   auto reduce_stream = [&](int m) { return m == 0 ? s0 : (overlap ? module_stream(m) : (side ? c->side : s0)); };
   // (calls of few rows split K over workgroups, whose partial products the reduce adds up; several real shards would each add to the residual, and the
@@ -763,6 +809,14 @@ __global__ __launch_bounds__(256) void calibration_copy_kernel(const uint4* __re
 
 __global__ void set_pos_kernel(int* p, int v) { *p = v; }
 __global__ void inc_pos_kernel(int* p) { *p += 1; }
+
+// the device's copy of the position, which the kernels of the packed path read (the plain ones take it as an argument)
+int set_pos_dev(ladder_ctx* c, int pos) {
+  if (!c->fast) return LADDER_OK;
+  hipLaunchKernelGGL(set_pos_kernel, dim3(1), dim3(1), 0, c->main, c->pos_dev, pos);
+  HIP_TRY(c, hipGetLastError());
+  return LADDER_OK;
+}
 
 // ---------------------------------------------------------------------------------------------
 // fused decode path: the launch list of one step (see decode_fused.hip)
@@ -1612,6 +1666,7 @@ static int init_impl(const ladder_config* cfg, void* hip_stream, ladder_ctx** ou
   const size_t rows = (size_t)c->rows_cap;
   const size_t row_slots = row_slots_of(g);
   INIT_TRY(dev_alloc(c, (void**)&c->x, rows * H * 4, false));
+  if (!c->fast) INIT_TRY(dev_alloc(c, (void**)&c->x_other, std::min<size_t>(rows, PLAIN_NORM_ROWS) * H * 4, false));
   INIT_TRY(dev_alloc(c, (void**)&c->pos_dev, 256, true));
   INIT_TRY(dev_alloc(c, (void**)&c->emb_stage, (size_t)g.max_batch * H * esz, false));
   for (int i = 0; i < 2; ++i) INIT_TRY(dev_alloc(c, (void**)&c->y[i], rows * H * esz, false));
@@ -1795,8 +1850,7 @@ int ladder_load_kv(ladder_ctx* c, int32_t layer, int32_t shard, const void* k, c
   if (all) {
     c->pos = S;
     c->batch = B;
-    hipLaunchKernelGGL(set_pos_kernel, dim3(1), dim3(1), 0, c->main, c->pos_dev, S);
-    HIP_TRY(c, hipGetLastError());
+    return set_pos_dev(c, S);
   }
   return LADDER_OK;
 }
@@ -1819,9 +1873,7 @@ int ladder_prefill(ladder_ctx* c, const void* x_in, int32_t B, int32_t T, void* 
   for (auto& X : c->store) { X.kv_B = 0; X.kv_S = 0; }
   c->pos = T;
   c->batch = B;
-  hipLaunchKernelGGL(set_pos_kernel, dim3(1), dim3(1), 0, c->main, c->pos_dev, T);
-  HIP_TRY(c, hipGetLastError());
-  return LADDER_OK;
+  return set_pos_dev(c, T);
 }
 
 int ladder_decode_step(ladder_ctx* c, const void* x_in, void* x_out) {
@@ -1843,8 +1895,10 @@ int ladder_decode_step(ladder_ctx* c, const void* x_in, void* x_out) {
   } else {
     rc = forward_body(c, x_in, c->batch, 1, c->pos, true, x_out, c->main);
     if (rc) return rc;
-    hipLaunchKernelGGL(inc_pos_kernel, dim3(1), dim3(1), 0, c->main, c->pos_dev);
-    HIP_TRY(c, hipGetLastError());
+    if (c->fast) {   // (see set_pos_dev)
+      hipLaunchKernelGGL(inc_pos_kernel, dim3(1), dim3(1), 0, c->main, c->pos_dev);
+      HIP_TRY(c, hipGetLastError());
+    }
   }
   c->pos += 1;
   return LADDER_OK;
@@ -1882,9 +1936,7 @@ int ladder_prefill_stage(ladder_ctx* c, const float* residual_in, const float* a
   for (auto& X : c->store) { X.kv_B = 0; X.kv_S = 0; }
   c->pos = T;
   c->batch = B;
-  hipLaunchKernelGGL(set_pos_kernel, dim3(1), dim3(1), 0, c->main, c->pos_dev, T);
-  HIP_TRY(c, hipGetLastError());
-  return LADDER_OK;
+  return set_pos_dev(c, T);
 }
 
 int ladder_decode_step_stage(ladder_ctx* c, const float* residual_in, const float* attn_in, const float* mlp_in,
@@ -1907,8 +1959,10 @@ int ladder_decode_step_stage(ladder_ctx* c, const float* residual_in, const floa
   } else {
     rc = forward_body(c, nullptr, c->batch, 1, c->pos, true, nullptr, c->main, &st);
     if (rc) return rc;
-    hipLaunchKernelGGL(inc_pos_kernel, dim3(1), dim3(1), 0, c->main, c->pos_dev);
-    HIP_TRY(c, hipGetLastError());
+    if (c->fast) {   // (see set_pos_dev)
+      hipLaunchKernelGGL(inc_pos_kernel, dim3(1), dim3(1), 0, c->main, c->pos_dev);
+      HIP_TRY(c, hipGetLastError());
+    }
   }
   c->pos += 1;
   return LADDER_OK;

@@ -30,6 +30,19 @@ def test_sizes(harness, hidden, nq, nkv, d, inter, rows, dtype):
     assert max(res.errs) < (1e-4 if dtype == "fp32" else 0.0029 * 2 ** 0.5 * 5.8), res.errs
 
 
+@pytest.mark.parametrize("wiring,n_std", [(ladder.LADDER_WIRING_LADDER, 0), (ladder.LADDER_WIRING_LADDER, 1), (ladder.LADDER_WIRING_LADDER, 2),
+                                          (ladder.LADDER_WIRING_STANDARD, 0), (ladder.LADDER_WIRING_PARALLEL, 0)])
+@pytest.mark.parametrize("n_layers,rows,shards", [(1, 5, 2), (3, 1, 2), (3, 64, 2), (3, 65, 2), (3, 1, 9), (3, 3, 9)])
+def test_rows_made_where_they_are_multiplied(harness, wiring, n_std, n_layers, rows, shards):
+    """Up to 64 rows the stream is summed and normed by the projections that read it: one or two module outputs behind a stored
+    stream, peers among them, more partial sums than are requested at once; 65 rows and too many pieces take the reduce kernel."""
+    if n_std > n_layers:
+        pytest.skip("more standard layers than layers")
+    w = BASE.with_(name="made", n_layers=n_layers, prefill=rows, hidden=264, inter=96, tp_degree=shards + 1, n_real_shards=shards, peer_pool=2)
+    res = harness.run_case(w, wiring=wiring, n_standard_layers=n_std)
+    assert max(res.errs) < 1e-4, res.errs
+
+
 @pytest.mark.parametrize("cached", [63, 64, 255, 256, 700])
 def test_attention_chunks(harness, cached):
     """One step behind a handed-over cache: part of a chunk, whole chunks, more chunks than wavefronts."""
