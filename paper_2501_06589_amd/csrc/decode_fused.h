@@ -64,7 +64,8 @@ struct GemvJob {
   unsigned* err_word;
   // Chained step (one launch for the whole decode step): every job waits for the jobs that produce what it reads.
   // wait_on (above) then is the flag (or, for the attention job's output, the arrival counter) of the producer
-  // of the x operand, wait_on2 that of the producer of x_old where that is another job; operands whose producer
+  // of the x operand, wait_on2 that of the producer of x_old where that is another job (needed for the epilogue only: the
+  // kernel may wait for it behind the product); operands whose producer
   // is a projection are read with ordinary loads after the wait (each such buffer is written once per launch and
   // read by nobody before, so no cache of the chip holds an older copy of it).
   // done_ctr != null: this job is a producer.  Its workgroups write their results with device-coherent stores,

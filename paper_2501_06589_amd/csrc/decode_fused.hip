@@ -207,16 +207,18 @@ __device__ __forceinline__ bool sync_poll(const unsigned* words, unsigned n_flag
   }
   return ok;
 }
-// waits (bounded) for one or two producers (w2 null: one); all 64 lanes of the wavefront must call
-__device__ __forceinline__ bool sync_wait(const unsigned* w1, unsigned n1, const unsigned* w2, unsigned n2, unsigned bias,
-                                          int spins, int lane) {
+// Waits (bounded) for one or two producers (w2 null: one); first_only: for the first, and says whether the second has arrived as well.
+// 0 = the wait gave up, 1 = both are there, 2 = the second is not; all 64 lanes of the wavefront must call
+__device__ __forceinline__ unsigned sync_wait(const unsigned* w1, unsigned n1, const unsigned* w2, unsigned n2, unsigned bias,
+                                              int spins, int lane, bool first_only) {
   for (int spin = 0; spin < spins; ++spin) {
-    bool ok = sync_poll(w1, n1, bias, lane);
-    if (w2) ok = sync_poll(w2, n2, bias, lane) && ok;   // (both polls' loads are in flight together)
-    if (__all(ok)) return true;
+    bool ok = sync_poll(w1, n1, bias, lane), ok2 = true;
+    if (w2) ok2 = sync_poll(w2, n2, bias, lane);   // (both polls' loads are in flight together)
+    if (!first_only) ok = ok && ok2;
+    if (__all(ok)) return __all(ok2) ? 1u : 2u;
     __builtin_amdgcn_s_sleep(FUSED_POLL_SLEEP);
   }
-  return false;
+  return 0u;
 }
 // A producer job of a chained step: the workgroup's coherent stores have completed, count it.
 __device__ __forceinline__ void gemv_signal_done(const GemvJob& j, int lb) {
@@ -251,6 +253,12 @@ template <int U, int TN, bool COH, bool WIDE, bool CHAIN>
 __device__ __forceinline__ bool gemv_job(const GemvJob& j, const void* wp, const bf16_t* xop, int KT, int group0, int M, int lb,
                                          float* smem, unsigned* s_flag, float* x_out, unsigned long long* t_ready) {
   constexpr bool EARLY_X = !COH && !CHAIN;
+  // A residual job of a chained step needs two producers: its operand's at the start, the old rows' only for its epilogue.  Where the second
+  // has not finished when the first has, the product goes ahead and the wait follows it.  One row, or up to 4 of a stream of 4096 columns
+  // and more; us, 4 - 8 steps, before / after: headline (8 layers) 2662 / 2641, 8B shape, batch 1 2494 / 2460, R = 8, batch 1 677 / 669, 1.2B, batch 1
+  // 538 / 526, parallel block 1111 / 1086.  With more rows, or on short layers, a down projection beside the attention side slows that:
+  // 1.2B, batch 3 1137 / 1164, batch 4 behind 4000 positions 1674 / 1780, batch 8 1417 / 1513, batch 16 5210 / 5753, R = 4, batch 12 1631 / 1724.
+  constexpr bool LATE = CHAIN && !WIDE;
   constexpr int WAVES = FUSED_WAVES;
   constexpr int XP = WIDE ? 2 : 1;   // operand registers per k tile
   const int grp = group0 + lb;
@@ -324,15 +332,17 @@ __device__ __forceinline__ bool gemv_job(const GemvJob& j, const void* wp, const
   if (EARLY_X && kt0 + KB < kt1) loadx(xb, kt0 + KB);
   __builtin_amdgcn_sched_barrier(0);
 
+  bool late = false;   // (uniform) the old rows' producer had not finished when the operand's had: they are waited for behind the product
   if (j.wait_on) {
     // What the job reads comes from other jobs of this launch.  A workgroup only waits for workgroups that come
     // before it in the launch's order and that wait, in turn, only for earlier ones: the words always arrive.  The
     // wait is bounded all the same, so that the kernel ends whatever happens; a workgroup whose wait gives up stores
     // nothing and raises the error word, which the host reads at the library's next call.
     if (wave == 0) {
-      const bool arrived = sync_wait(j.wait_on, j.wait_flags, j.wait_on2, j.wait_flags2, j.wait_bias, j.wait_spins, lane);
+      const unsigned arrived = sync_wait(j.wait_on, j.wait_flags, j.wait_on2, j.wait_flags2, j.wait_bias, j.wait_spins, lane,
+                                         LATE && (M == 1 || (M <= 4 && j.N >= 4096)));
       if (lane == 0) {
-        *s_flag = arrived ? 1u : 0u;
+        *s_flag = arrived;
         if (!arrived && j.err_word) __hip_atomic_store(j.err_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
       }
     }
@@ -340,7 +350,9 @@ __device__ __forceinline__ bool gemv_job(const GemvJob& j, const void* wp, const
                        // device-coherent loads, and what a projection of the same launch has written is in no cache
                        // of this XCD yet, having been read by nobody before; an agent-scope acquire per workgroup
                        // would flush the L2 under the weight streams that run beside)
-    if (*s_flag == 0u) return false;
+    const unsigned arrived = (unsigned)__builtin_amdgcn_readfirstlane((int)*s_flag);
+    if (arrived == 0u) return false;
+    late = LATE && arrived == 2u;
   }
 
   if (j.t_ready) {
@@ -423,7 +435,7 @@ __device__ __forceinline__ bool gemv_job(const GemvJob& j, const void* wp, const
       pre_ga[e] = pre_gb[e] = 0x3F80;   // 1.0
       if (idx < TN * 256) {
         const int t = idx >> 8, row = min((idx >> 4) & 15, j.M - 1), col = (nt0 + t) * 16 + (idx & 15);
-        pre_old[e] = j.x_old[(size_t)row * j.N + col];
+        if (!late) pre_old[e] = j.x_old[(size_t)row * j.N + col];
         if (j.xop_a) pre_ga[e] = j.gain_a[col];
         if (j.xop_b) pre_gb[e] = j.gain_b[col];
         if (j.n_peers > 0) {
@@ -489,7 +501,23 @@ __device__ __forceinline__ bool gemv_job(const GemvJob& j, const void* wp, const
       }
     }
   }
+  if (LATE && late && wave == 0) {
+    const unsigned arrived = sync_wait(j.wait_on2, j.wait_flags2, nullptr, 0u, j.wait_bias, j.wait_spins, lane, false);
+    if (lane == 0) {
+      *s_flag = arrived;
+      if (!arrived && j.err_word) __hip_atomic_store(j.err_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+  }
   __syncthreads();
+  if (LATE && late) {
+    if (*s_flag == 0u) return false;
+    if (t_ready && tid == 0) *t_ready = wall_clock64();   // (now all of its inputs are complete)
+#pragma unroll
+    for (int e = 0; e < E_RES; ++e) {
+      const int idx = tid + e * FUSED_THREADS;
+      if (idx < TN * 256) pre_old[e] = j.x_old[(size_t)min((idx >> 4) & 15, j.M - 1) * j.N + (nt0 + (idx >> 8)) * 16 + (idx & 15)];
+    }
+  }
   auto out_of = [&](int t, int col16, int row) {  // finished output element: wave sums (high + low half), then 1/rms of the row
     float v = 0.f;
 #pragma unroll
@@ -639,9 +667,9 @@ __device__ __forceinline__ bool attn_job(const AttnJob& a, int lb, float* smem, 
   if (a.wait_on) {
     // chained step: q and the new cache rows come from the QKV projection of the same launch (see gemv_job)
     if (wave == 0) {
-      const bool arrived = sync_wait(a.wait_on, a.wait_flags, nullptr, 0u, a.wait_bias, a.wait_spins, tid0 & 63);
+      const unsigned arrived = sync_wait(a.wait_on, a.wait_flags, nullptr, 0u, a.wait_bias, a.wait_spins, tid0 & 63, false);
       if (tid0 == 0) {
-        *s_flag = arrived ? 1u : 0u;
+        *s_flag = arrived;
         if (!arrived && a.err_word) __hip_atomic_store(a.err_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
       }
     }
