@@ -844,6 +844,7 @@ void build_fused_plan(ladder_ctx* c, int B) {
   auto R = [&](int m) { return (size_t)(m % c->ring_n); };            // ring slot of stream x_m
   auto F = [&](int l) { return (size_t)((l - 1) % c->n_fbuf); };      // q / SwiGLU buffer of layer l
 
+  const bool many = B >= 13 && g.wiring != LADDER_WIRING_PARALLEL;
   auto job_qkv = [&](int l, int src) {
     GemvJob j{};
     j.xb = c->xop_ring[R(src)][1]; j.ldx = H; j.normed = 1; j.eps = g.rms_eps; j.ssq = c->ssq_ring[R(src)];
@@ -857,7 +858,9 @@ void build_fused_plan(ladder_ctx* c, int B) {
     j.nq = nq; j.nkv = nkv; j.d = d; j.max_seq = c->s_cap;
     // short K range: two tiles per workgroup (8B shape, batch 4: 2.90 -> 2.81 ms per step; 1.2B: 0.86 -> 0.83);
     // over hidden 8192 one tile is already 256 KiB and two were slower
-    if (H <= 4096 && j.n_groups % 2 == 0) { j.tn = 2; j.n_groups /= 2; }
+    // (13 rows and more of a stream so narrow that single tiles are one per CU: singles; 1.2B shape at batch 16, 12 layers, 8 steps 5156 -> 4893
+    // us; batch 1 - 12 are 1 - 5 % faster with pairs, and so is the parallel block, whose QKV runs beside gate/up: batch 14 1330 / 1399)
+    if (H <= 4096 && j.n_groups % 2 == 0 && !(many && j.n_groups <= c->n_cu)) { j.tn = 2; j.n_groups /= 2; }
     return j;
   };
   // the job adds the output (and peers) of module m to ring slot at - 1 and leaves the sum in slot at (at = m
@@ -887,8 +890,10 @@ void build_fused_plan(ladder_ctx* c, int B) {
     GemvJob j{};
     j.xb = c->f_o[F(l)]; j.ldx = nqd; j.wp = layer(l).po; j.M = B; j.K = nqd; j.after_attention = 1;
     residual(j, m, at < 0 ? m : at);
-    // its K range is short: two tiles per workgroup halve the number of (latency-bound) workgroups
-    if (j.n_groups % 2 == 0) { j.tn = 2; j.n_groups /= 2; }
+    // its K range is short: two tiles per workgroup halve the number of (latency-bound) workgroups, unless those are few as it is (half the
+    // CUs and fewer, 1.2B shape, six layers, 4 steps, batch 1 / 2 / 4 / 6 / 8 / 12: 742 / 801 / 869 / 959 / 1274 / 1078 -> 729 / 762 / 830 / 920
+    // / 1239 / 1037; with 13 rows and more the QKV projection gains more, see there, and the two together are no better)
+    if (j.n_groups % 2 == 0 && (j.n_groups > c->n_cu / 2 || many)) { j.tn = 2; j.n_groups /= 2; }
     return j;
   };
   auto job_gu = [&](int l, int src) {
@@ -1056,8 +1061,10 @@ void build_fused_plan(ladder_ctx* c, int B) {
       // make more than that (large batches: attention has a workgroup per sequence and split), o_l takes four
       // tiles per workgroup, if its K range is long enough for that to pay (measured: 8B shape at batch 16
       // 4.06 -> 3.86 ms per step, 70B R = 4 shard at batch 16 8.89 -> 8.61; with the R = 8 shard's K range of
-      // 1024, batch 8 and 16, it cost 1 - 2 %).
-      if (n_splits * nkv * B + blocks_of(gu_a) + blocks_of(o) > 2 * c->n_cu && nqd >= 2048 && o.tn == 2 && o.n_groups % 2 == 0) { o.tn = 4; o.n_groups /= 2; }
+      // 1024, batch 8 and 16, it cost 1 - 2 %; and not where fewer than a quarter of the CUs would be left with work: 1.2B shape,
+      // batch 16 1420 -> 1388 us).
+      if (n_splits * nkv * B + blocks_of(gu_a) + blocks_of(o) > 2 * c->n_cu && nqd >= 2048 && o.tn == 2 && o.n_groups % 2 == 0 &&
+          o.n_groups / 2 >= c->n_cu / 4) { o.tn = 4; o.n_groups /= 2; }
       // Chained step: a slot ends every block with its stores' round trip and its count before it asks for the next
       // one, so where single gate/up tiles make more blocks than there are slots, pairs (same sums in the same order:
       // same bits).  8B shape at batch 1 / 4 / 8: 2.52 / 2.75 / 3.22 -> 2.46 / 2.64 / 3.02 ms per step; R = 8 shard at
