@@ -749,7 +749,9 @@ int forward_body(ladder_ctx* c, const void* x_in, int B, int T, int pos0, bool d
   // 970 / 725, 41 MB 1246 / 1077 and at batch 4 1498 / 1688, 100 MB 1288 / 1534, 200 MB 2221 / 2732)
   const bool brief = !c->fast && c->shard_bytes * (size_t)c->cfg.n_real_shards < (32u << 20);
   const double layer_bytes = (double)c->shard_bytes * c->cfg.n_real_shards;
-  const bool independent = c->cfg.wiring == LADDER_WIRING_LADDER && c->cfg.n_standard_layers == 0;   // (the wiring that was measured beyond 64 rows)
+  // beyond 64 rows: the wiring that was measured, and more than one layer (of one, the fork and the join are the larger part: 70B R = 8, 600
+  // rows 302 / 327, 1.2B 122 / 131)
+  const bool independent = c->cfg.wiring == LADDER_WIRING_LADDER && c->cfg.n_standard_layers == 0 && c->cfg.n_layers > 1;
   const bool pays = !c->fast || (rows <= 64 && (T == 1 || c->cfg.reduce_delay_us > 0)) ? rows <= 64 : rows <= (independent ? FEW_ROWS : 64) && (rows <= 256 || rows > 512) && layer_bytes * (200.0 + rows) >= 32e9;
   const bool small = rows <= 64 && !st && !brief;
   const bool overlap = pays && !st && !brief && c->cfg.overlap_modules != 0;
