@@ -80,6 +80,14 @@ def test_two_workgroups_per_cu(harness, batch, prefill, hidden, inter, n_q, peer
     assert max(res.errs) < TOL * 2 ** 0.5, res.errs
 
 
+def test_residual_epilogue_of_the_largest_tile(harness):
+    """256 x 256 tiles with the residual update as epilogue (taken without peers only), ragged in both directions: 4 rows and 64 columns
+    in the last tiles; the second layer reads what the epilogue left."""
+    w = WIDE.with_(name="large_tile", n_layers=2, hidden=2112, inter=512, n_q_heads=4, batch=2, prefill=2050, tp_degree=1, peer_pool=0)
+    res = harness.run_case(w, decode_steps=0, gen_device="cuda:0")
+    assert max(res.errs) < TOL * 2 ** 0.5, res.errs
+
+
 @pytest.mark.parametrize("rows", [100, 1100])
 def test_embeddings_off_a_16_byte_boundary(harness, rows):
     """The same bits wherever the call's input lies (the residual update of module 1 reads it 16 bytes at a time beyond 1024 rows)."""
