@@ -302,7 +302,9 @@ size_t ladder_weight_bytes(const ladder_config* cfg);
  * of 2^20, and target_bias added to the value a wait polls for.  With a bias no producer can reach, the waits give
  * up: the waiting workgroups store nothing, every kernel still ends normally, and the NEXT ladder_decode_step /
  * ladder_prefill returns LADDER_E_HIP (and puts the device's copy of the position back in step with the host's).
- * (1 << 20, 0) restores normal operation.  Errors: LADDER_E_ARG. */
+ * (1 << 20, 0) restores normal operation.  A job of a chained step may wait for two producers, for the second one (the old rows of
+ * a residual update) also behind its product; target_bias = LADDER_WAIT_SECOND_ONLY makes those waits alone give up.  Errors: LADDER_E_ARG. */
+enum { LADDER_WAIT_SECOND_ONLY = 1 << 30 };
 int ladder_set_wait_limit(ladder_ctx* ctx, int32_t max_polls, int32_t target_bias);
 
 /* Timeline of a chained decode step (decode_fused = 3), for measurement.  A chained step is one launch of

@@ -71,10 +71,11 @@ struct GemvJob {
   // done_ctr != null: this job is a producer.  Its workgroups write their results with device-coherent stores,
   // wait for them and count themselves at done_ctr (FUSED_SYNC_WORDS words); done_target = the workgroups of the
   // whole projection (its jobs share done_ctr), done_ord0 = the ordinal of this job's first workgroup among them.
-  // wait_on / wait_on2 point at such words of a producer (the job polls their flag); wait_bias is added to the
-  // value the flag must reach (0; a test makes the wait fail with it).
+  // wait_on / wait_on2 point at such words of a producer (the job polls their flag); wait_bias / wait_bias2 is added to
+  // the value the flag must reach (0; a test makes the wait fail with it).
   const unsigned* wait_on2;
   unsigned wait_flags2;
+  unsigned wait_bias2;
   int coherent_x;          // chained step: the x operand is read with device-coherent loads (a buffer that is written more than once per launch)
   unsigned* done_ctr;
   unsigned done_target;

@@ -209,11 +209,11 @@ __device__ __forceinline__ bool sync_poll(const unsigned* words, unsigned n_flag
 }
 // Waits (bounded) for one or two producers (w2 null: one); first_only: for the first, and says whether the second has arrived as well.
 // 0 = the wait gave up, 1 = both are there, 2 = the second is not; all 64 lanes of the wavefront must call
-__device__ __forceinline__ unsigned sync_wait(const unsigned* w1, unsigned n1, const unsigned* w2, unsigned n2, unsigned bias,
+__device__ __forceinline__ unsigned sync_wait(const unsigned* w1, unsigned n1, unsigned bias1, const unsigned* w2, unsigned n2, unsigned bias2,
                                               int spins, int lane, bool first_only) {
   for (int spin = 0; spin < spins; ++spin) {
-    bool ok = sync_poll(w1, n1, bias, lane), ok2 = true;
-    if (w2) ok2 = sync_poll(w2, n2, bias, lane);   // (both polls' loads are in flight together)
+    bool ok = sync_poll(w1, n1, bias1, lane), ok2 = true;
+    if (w2) ok2 = sync_poll(w2, n2, bias2, lane);   // (both polls' loads are in flight together)
     if (!first_only) ok = ok && ok2;
     if (__all(ok)) return __all(ok2) ? 1u : 2u;
     __builtin_amdgcn_s_sleep(FUSED_POLL_SLEEP);
@@ -339,7 +339,7 @@ __device__ __forceinline__ bool gemv_job(const GemvJob& j, const void* wp, const
     // wait is bounded all the same, so that the kernel ends whatever happens; a workgroup whose wait gives up stores
     // nothing and raises the error word, which the host reads at the library's next call.
     if (wave == 0) {
-      const unsigned arrived = sync_wait(j.wait_on, j.wait_flags, j.wait_on2, j.wait_flags2, j.wait_bias, j.wait_spins, lane,
+      const unsigned arrived = sync_wait(j.wait_on, j.wait_flags, j.wait_bias, j.wait_on2, j.wait_flags2, j.wait_bias2, j.wait_spins, lane,
                                          LATE && (M == 1 || (M <= 4 && j.N >= 4096)));
       if (lane == 0) {
         *s_flag = arrived;
@@ -502,15 +502,16 @@ __device__ __forceinline__ bool gemv_job(const GemvJob& j, const void* wp, const
     }
   }
   if (LATE && late && wave == 0) {
-    const unsigned arrived = sync_wait(j.wait_on2, j.wait_flags2, nullptr, 0u, j.wait_bias, j.wait_spins, lane, false);
+    // (its result has a word of its own: a wavefront that lags may still have to read the first wait's)
+    const unsigned arrived = sync_wait(j.wait_on2, j.wait_flags2, j.wait_bias2, nullptr, 0u, 0u, j.wait_spins, lane, false);
     if (lane == 0) {
-      *s_flag = arrived;
+      s_flag[1] = arrived;
       if (!arrived && j.err_word) __hip_atomic_store(j.err_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
   }
   __syncthreads();
   if (LATE && late) {
-    if (*s_flag == 0u) return false;
+    if (s_flag[1] == 0u) return false;
     if (t_ready && tid == 0) *t_ready = wall_clock64();   // (now all of its inputs are complete)
 #pragma unroll
     for (int e = 0; e < E_RES; ++e) {
@@ -667,7 +668,7 @@ __device__ __forceinline__ bool attn_job(const AttnJob& a, int lb, float* smem, 
   if (a.wait_on) {
     // chained step: q and the new cache rows come from the QKV projection of the same launch (see gemv_job)
     if (wave == 0) {
-      const unsigned arrived = sync_wait(a.wait_on, a.wait_flags, nullptr, 0u, a.wait_bias, a.wait_spins, tid0 & 63, false);
+      const unsigned arrived = sync_wait(a.wait_on, a.wait_flags, a.wait_bias, nullptr, 0u, 0u, a.wait_spins, tid0 & 63, false);
       if (tid0 == 0) {
         *s_flag = arrived;
         if (!arrived && a.err_word) __hip_atomic_store(a.err_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -924,7 +925,7 @@ __global__ __launch_bounds__(FUSED_THREADS, 4) void fused_decode_kernel(const vo
                                                                        unsigned kinds, unsigned geo0, unsigned geo1,
                                                                        unsigned geo2, FusedArgs fa) {
   extern __shared__ float smem[];   // fa.lds_bytes: the largest need of the launch's jobs
-  __shared__ unsigned s_flag;
+  __shared__ unsigned s_flag[1];   // (no job of these launches waits a second time)
   const int end0 = (int)(ends01 & 0xFFFFu), end1 = (int)(ends01 >> 16), end2 = (int)(end2_m & 0xFFFFu);
   int lb = blockIdx.x, job = 0;
   if ((int)blockIdx.x >= end0) { lb = blockIdx.x - end0; job = 1; }
@@ -939,7 +940,7 @@ __global__ __launch_bounds__(FUSED_THREADS, 4) void fused_decode_kernel(const vo
   const kernarg_ptr_t ka = (kernarg_ptr_t)__builtin_amdgcn_kernarg_segment_ptr();
   if ((kb & FUSED_KIND_MASK) == (unsigned)JOB_ATTN) {
     const AttnJob& aj = *(const AttnJob*)(ka + offsetof(FusedKernelParams, fa) + offsetof(FusedArgs, a));
-    (void)attn_job<D, G>(aj, lb, smem, &s_flag, nullptr);
+    (void)attn_job<D, G>(aj, lb, smem, s_flag, nullptr);
   } else {
     const GemvJob& j = *(const GemvJob*)(ka + offsetof(FusedKernelParams, fa) + offsetof(FusedArgs, g) + (size_t)job * sizeof(GemvJob));
     const unsigned slot = kb >> FUSED_KIND_SLOT_SHIFT;   // which preloaded pointer pair: 0, 1, or 3 = none
@@ -955,8 +956,8 @@ __global__ __launch_bounds__(FUSED_THREADS, 4) void fused_decode_kernel(const vo
     // was complete before the launch: requested at once)
 #define FUSED_GEMV(U_, TN_, COH_)                                                                                  \
   do {                                                                                                             \
-    if (M > 8) (void)gemv_job<U_, TN_, COH_, true, false>(j, wp, xop, KT, group0, M, lb, smem, &s_flag, nullptr, nullptr);  \
-    else (void)gemv_job<U_, TN_, COH_, false, false>(j, wp, xop, KT, group0, M, lb, smem, &s_flag, nullptr, nullptr);       \
+    if (M > 8) (void)gemv_job<U_, TN_, COH_, true, false>(j, wp, xop, KT, group0, M, lb, smem, s_flag, nullptr, nullptr);  \
+    else (void)gemv_job<U_, TN_, COH_, false, false>(j, wp, xop, KT, group0, M, lb, smem, s_flag, nullptr, nullptr);       \
   } while (0)
     if (kb & FUSED_KIND_WAITS) {
       if (tn == 4) FUSED_GEMV(1, 4, true);
@@ -999,7 +1000,7 @@ __global__ __launch_bounds__(FUSED_THREADS, 4) void fused_chain_kernel(const Ste
                                                                       const AttnJob* __restrict__ attn_jobs, float* x_out,
                                                                       unsigned long long* timeline) {
   extern __shared__ float smem[];
-  __shared__ unsigned s_flag;
+  __shared__ unsigned s_flag[2];   // results of a job's first and second wait
   __shared__ unsigned s_claim, s_claim_n;
   __shared__ uint4 s_items[2 * FUSED_CHAIN_CHUNK];
   __shared__ uint4 s_surplus[2 * FUSED_CLAIM_MAX];
@@ -1058,7 +1059,7 @@ __global__ __launch_bounds__(FUSED_THREADS, 4) void fused_chain_kernel(const Ste
     if (tl && threadIdx.x == 0) tl[0] = wall_clock64();
     bool ok;
     if ((kb & FUSED_KIND_MASK) == (unsigned)JOB_ATTN) {
-      ok = attn_job<D, G>(*(const AttnJob*)(aj + (size_t)job * sizeof(AttnJob)), lb, smem, &s_flag, tl ? tl + 1 : nullptr);
+      ok = attn_job<D, G>(*(const AttnJob*)(aj + (size_t)job * sizeof(AttnJob)), lb, smem, s_flag, tl ? tl + 1 : nullptr);
     } else {
       const GemvJob& j = *(const GemvJob*)(gj + (size_t)job * sizeof(GemvJob));
       const unsigned long long wpu = (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)i0.x) |
@@ -1075,8 +1076,8 @@ __global__ __launch_bounds__(FUSED_THREADS, 4) void fused_chain_kernel(const Ste
       const unsigned tn = ((kb >> FUSED_KIND_TN_SHIFT) & 3u) + 1u;
 #define CHAIN_GEMV(U_, TN_, COH_)                                                                                   \
   do {                                                                                                              \
-    if (M > 8) ok = gemv_job<U_, TN_, COH_, true, true>(j, wp, xop, KT, group0, M, lb, smem, &s_flag, x_out, tl ? tl + 1 : nullptr);   \
-    else ok = gemv_job<U_, TN_, COH_, false, true>(j, wp, xop, KT, group0, M, lb, smem, &s_flag, x_out, tl ? tl + 1 : nullptr);        \
+    if (M > 8) ok = gemv_job<U_, TN_, COH_, true, true>(j, wp, xop, KT, group0, M, lb, smem, s_flag, x_out, tl ? tl + 1 : nullptr);   \
+    else ok = gemv_job<U_, TN_, COH_, false, true>(j, wp, xop, KT, group0, M, lb, smem, s_flag, x_out, tl ? tl + 1 : nullptr);        \
   } while (0)
       if (kb & FUSED_KIND_COH) {
         if (tn == 4) CHAIN_GEMV(1, 4, true);

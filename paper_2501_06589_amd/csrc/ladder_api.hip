@@ -159,7 +159,7 @@ struct ladder_ctx {
   unsigned* err_word = nullptr;   // host-visible word that a kernel raises when its bounded in-launch wait gives up
   unsigned* err_word_dev = nullptr;   // its device address
   int wait_spins = 1 << 20;       // polls of that wait (about a second); a test shortens it
-  unsigned wait_bias = 0;         // added to the wait's target (0 in normal operation; a test makes it unreachable)
+  unsigned wait_bias = 0, wait_bias2 = 0;   // added to the targets of the wait for the first and the second producer (0 in normal operation; a test makes them unreachable)
   unsigned* tk_att = nullptr;     // arrival tickets of split attention, [max_batch][nkv]
   std::vector<FusedArgs> fused_plan;
   // emulated collectives (reduce_delay_us) of the fused schedule: t_done[m] = wall-clock time at which the last
@@ -1239,7 +1239,7 @@ int build_chain(ladder_ctx* c, int B) {
         j.wait_on = nullptr; j.wait_on2 = nullptr; j.coherent_x = 0;
         if (d1 >= 0) { j.wait_on = prod[(size_t)d1].words; j.wait_flags = prod[(size_t)d1].flagged ? prod[(size_t)d1].blocks : 0u; }
         if (d2 >= 0) { j.wait_on2 = prod[(size_t)d2].words; j.wait_flags2 = prod[(size_t)d2].flagged ? prod[(size_t)d2].blocks : 0u; }
-        j.wait_bias = c->wait_bias; j.wait_spins = c->wait_spins; j.err_word = c->err_word_dev;
+        j.wait_bias = c->wait_bias; j.wait_bias2 = c->wait_bias2; j.wait_spins = c->wait_spins; j.err_word = c->err_word_dev;
         j.done_ctr = me.words;
         j.done_target = me.blocks;
         j.done_ord0 = me.seen;
@@ -1787,7 +1787,8 @@ int ladder_set_wait_limit(ladder_ctx* c, int32_t max_polls, int32_t target_bias)
   if (!c) return LADDER_E_ARG;
   if (max_polls < 1 || max_polls > (1 << 24) || target_bias < 0) return fail(c, LADDER_E_ARG, "max_polls must be in 1 .. 2^24, target_bias >= 0");
   c->wait_spins = max_polls;
-  c->wait_bias = (unsigned)target_bias;
+  c->wait_bias2 = (unsigned)target_bias;
+  c->wait_bias = (target_bias & LADDER_WAIT_SECOND_ONLY) ? 0u : c->wait_bias2;
   c->fused_plan.clear();     // the launch list carries both: it is built again at the next step
   c->graph_stale = true;
   return LADDER_OK;

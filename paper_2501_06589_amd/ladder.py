@@ -19,6 +19,7 @@ LADDER_FP32, LADDER_BF16 = 0, 1
 LADDER_WIRING_LADDER, LADDER_WIRING_STANDARD, LADDER_WIRING_PARALLEL = 0, 1, 2
 LADDER_PATH_AUTO, LADDER_PATH_GENERIC = 0, 1
 LADDER_OK, LADDER_E_ARG, LADDER_E_SHAPE, LADDER_E_STATE, LADDER_E_OVERFLOW, LADDER_E_HIP = 0, -1, -2, -3, -4, -5
+LADDER_WAIT_SECOND_ONLY = 1 << 30     # set_wait_limit: the bias of the waits for a second producer alone
 (LADDER_K_REDUCE_NORM, LADDER_K_GEMV, LADDER_K_GEMM, LADDER_K_ROPE_APPEND, LADDER_K_ATTN_DECODE,
  LADDER_K_ATTN_PREFILL, LADDER_K_GENERIC, LADDER_K_OTHER, LADDER_K_FUSED_DECODE, LADDER_K_COUNT) = range(10)
 KERNEL_CLASS_NAMES = ["reduce_norm", "gemv", "gemm", "rope_append", "attn_decode", "attn_prefill", "generic", "other", "fused_decode"]

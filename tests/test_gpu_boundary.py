@@ -79,6 +79,37 @@ def test_in_launch_wait_that_gives_up_is_reported_by_the_next_call(harness, fuse
     ctx.free()
 
 
+@pytest.mark.parametrize("batch,hidden", [(1, 512), (3, 4096), (3, 512)])
+def test_wait_for_the_old_rows_that_gives_up_is_reported_by_the_next_call(harness, batch, hidden):
+    """A chained step whose residual updates never see their old rows' producer: they give up behind the product (one row, or up to four of
+    4096 columns and more), or before it (the last case).  Every kernel ends normally, the next call reports it, and the
+    context works again: the same bits as before."""
+    w = R8_SMALL.with_(batch=batch, hidden=hidden)
+    ctx = harness.build_gpu(w, harness.make_tensors(w), inputs.peer_partials(w, w.batch), max_seq=200, decode_fused=3)
+    x = inputs.embeddings(w, w.batch, 1, inputs.SEED_DECODE0)[:, 0].contiguous().to(DEV)
+
+    def step():
+        for i in range(w.n_layers):
+            k, v = inputs.kv_cache(w, i, 0, w.batch, 50)
+            ctx.load_kv(i, 0, k.to(DEV), v.to(DEV))
+        out = ctx.decode_step(x)
+        torch.cuda.synchronize()
+        return out
+
+    good = step()
+    for _ in range(2):
+        ctx.set_wait_limit(4096, ladder.LADDER_WAIT_SECOND_ONLY)
+        step()
+        pos = ctx.position()
+        with pytest.raises(ladder.LadderError) as e:
+            ctx.decode_step(x)
+        assert e.value.code == ladder.LADDER_E_HIP and "wait" in str(e.value)
+        assert ctx.position() == pos
+        ctx.set_wait_limit(1 << 20, 0)
+        assert torch.equal(step(), good)
+    ctx.free()
+
+
 @pytest.mark.parametrize("fused", [1, 0, 3])
 def test_peers_changed_under_a_captured_decode_step(harness, fused):
     """decode_graph = 1: a step replayed from the captured graph, then another set of peer partial sums, then
