@@ -673,13 +673,20 @@ __global__ __launch_bounds__(256, 2) void gemm_duo_kernel(GemmArgs a) {
   };
   // Order of a wavefront's requests, stage s: W(s+2, k tile 0) | barrier | X(s+3) | W(s+2, k tile 1); the prologue is what the
   // three stages before the first would have requested.
+  // (held in this order: the waits count what was requested behind a stage, and weight loads may otherwise move over the others)
   static_assert(S == 3, "the counts below");
   issue_x(0, 0);
+  __builtin_amdgcn_sched_barrier(0);
   load_w(w[0][0], 0);
+  __builtin_amdgcn_sched_barrier(0);
   issue_x(1, 1);
+  __builtin_amdgcn_sched_barrier(0);
   load_w(w[0][1], 1);
+  __builtin_amdgcn_sched_barrier(0);
   load_w(w[1][0], 2);
+  __builtin_amdgcn_sched_barrier(0);
   issue_x(2, 2);
+  __builtin_amdgcn_sched_barrier(0);
   load_w(w[1][1], 3);
   ring_meet<2 * XL + 4 * JT>();   // X(0) has landed
   int buf = 0;
