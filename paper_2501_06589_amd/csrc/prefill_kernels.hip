@@ -242,6 +242,10 @@ __device__ __forceinline__ uint4 load_once(const void* p) {
   return __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p)));
 }
 
+// the staged column that lane l of a row reads (192 columns: 24 of the 32 lanes have eight each, the others repeat the first)
+template <int BN>
+__device__ __forceinline__ constexpr int gemm_staged_column(int l) { return 8 * l < BN ? 8 * l : 0; }
+
 // Epilogue 3 of a workgroup's tile of WR x 16 MT rows and WC x 16 JT columns (see GemmArgs), with whole rows per memory
 // instruction.  In the accumulator layout a wavefront's load or store touches 16 rows, 64 (fp32) or 32 (bf16) bytes of each, and
 // in that shape the 16 - 26 bytes per element that the update moves cost as much as a reduce kernel of its own.  So the tile
@@ -261,12 +265,14 @@ __device__ __forceinline__ void gemm_residual_epilogue(const GemmArgs& a, f32x4_
   constexpr int STEPS = 64 / (WR * WC * RPI);                      // rows that a lane group takes per pass
   constexpr int RB = 2;                                            // rows requested at once
   static_assert(STEPS % RB == 0 && MT % H == 0, "whole passes");
+  static_assert(gemm_staged_column<BN>(LPR - 1) + 8 <= STRIDE, "the lanes of a row read inside it");
   float* stage = reinterpret_cast<float*>(lds);
   const int b = lane & 15, q = lane >> 4, wr = wave / WC, wc = wave % WC;
   const int sub = lane / LPR, l = lane % LPR;
   const int n = n_blk * BN + 8 * l;
   const bool col_ok = 8 * l < BN && n < a.N;   // (N is a multiple of 16)
   const int nc = col_ok ? n : 0;
+  const int lc = gemm_staged_column<BN>(l);
   // the gains of the modules that read the new rows, for this lane's eight columns (the same for every row)
   float ga8[8], gb8[8];
   unpack8(a.xh_a ? *reinterpret_cast<const uint4*>(a.gain_a + nc) : make_uint4(0, 0, 0, 0), ga8);
@@ -306,8 +312,8 @@ __device__ __forceinline__ void gemm_residual_epilogue(const GemmArgs& a, f32x4_
 #pragma unroll
       for (int r = 0; r < RB; ++r) {
         const int lr = ((g * RB + r) * (WR * WC) + wave) * RPI + sub;
-        const float4 p0 = *reinterpret_cast<const float4*>(stage + lr * STRIDE + 8 * l);
-        const float4 p1 = *reinterpret_cast<const float4*>(stage + lr * STRIDE + 8 * l + 4);
+        const float4 p0 = *reinterpret_cast<const float4*>(stage + lr * STRIDE + lc);
+        const float4 p1 = *reinterpret_cast<const float4*>(stage + lr * STRIDE + lc + 4);
         float old8[8] = {xo[r][0].x, xo[r][0].y, xo[r][0].z, xo[r][0].w, xo[r][1].x, xo[r][1].y, xo[r][1].z, xo[r][1].w};
         if (a.x_emb) unpack8(__builtin_bit_cast(uint4, xo[r][0]), old8);
         float v8[8] = {old8[0] + p0.x, old8[1] + p0.y, old8[2] + p0.z, old8[3] + p0.w, old8[4] + p1.x, old8[5] + p1.y, old8[6] + p1.z, old8[7] + p1.w};
