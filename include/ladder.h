@@ -178,7 +178,8 @@ int ladder_load_kv(ladder_ctx* ctx, int32_t layer, int32_t shard, const void* k,
  * wiring) on T tokens of each of B sequences with causal attention, filling the KV cache; position
  * becomes T.
  *   x_in   device T   [B][T][H]  input embeddings x_0.
- *   x_out  device f32 [B][T][H]  x_2N = residual + last attention output + last MLP output.
+ *   x_out  device f32 [B][T][H]  x_2N = residual + last attention output + last MLP output; may overlap x_in
+ *                                (x_in is read before any of x_out is written).
  * Errors: LADDER_E_ARG, LADDER_E_SHAPE (B > max_batch, T > max_tokens, B*T > peer_rows),
  * LADDER_E_OVERFLOW (T > max_seq), LADDER_E_STATE (a layer is not loaded), LADDER_E_HIP. */
 int ladder_prefill(ladder_ctx* ctx, const void* x_in, int32_t B, int32_t T, void* x_out);
@@ -188,7 +189,7 @@ int ladder_prefill(ladder_ctx* ctx, const void* x_in, int32_t B, int32_t T, void
  * embedding per sequence at the current position (the batch size is the one of the preceding prefill /
  * load_kv); appends to the cache; position += 1.
  *   x_in   device T   [B][H]
- *   x_out  device f32 [B][H]
+ *   x_out  device f32 [B][H]; may overlap x_in, as in ladder_prefill
  * Errors: LADDER_E_STATE (no prefill / load_kv yet), LADDER_E_OVERFLOW (cache full), others as above;
  * LADDER_E_HIP also when a kernel of an EARLIER step gave up its bounded in-launch wait (that step's output
  * is then invalid; the failing call itself does nothing and clears the condition). */

@@ -711,7 +711,9 @@ int forward_plain(ladder_ctx* c, const void* x_in, int B, int T, int pos0, float
   for (int m = 1; m <= c->n_mod; ++m) {
     const int src = std::max(0, m - lag_of(c, m));
     add_up_to(src);
-    float* const store = in.n_adds ? buf[0] : nullptr;
+    // (a call whose modules all read the embeddings, of one layer: the last one leaves them too, so that what writes x_out reads nothing of
+    // x_in, which may lie in the same memory)
+    float* const store = in.n_adds || (m == c->n_mod && in.emb) ? buf[0] : nullptr;
     const int rc = run_module_plain(c, m, B, T, pos0, c->parts[m & 1], s, &in, store);
     if (rc) return rc;
     if (store) {

@@ -125,3 +125,31 @@ def test_more_blocks_than_one_grid_dimension_takes(harness):
     for first in (0, 16384, w.batch - 64):
         assert torch.equal(got[first:first + 64], few.prefill(x[first:first + 64].contiguous())), first
     few.free()
+
+
+@pytest.mark.parametrize("wiring", [ladder.LADDER_WIRING_LADDER, ladder.LADDER_WIRING_STANDARD, ladder.LADDER_WIRING_PARALLEL])
+@pytest.mark.parametrize("dtype,n_layers,rows,path", [("fp32", 1, 64, ladder.LADDER_PATH_GENERIC), ("bf16", 1, 1, ladder.LADDER_PATH_GENERIC),
+                                                      ("bf16", 1, 64, ladder.LADDER_PATH_GENERIC), ("bf16", 2, 64, ladder.LADDER_PATH_GENERIC),
+                                                      ("bf16", 1, 10, ladder.LADDER_PATH_AUTO), ("bf16", 1, 1100, ladder.LADDER_PATH_AUTO)])
+def test_input_and_output_in_the_same_memory(harness, wiring, dtype, n_layers, rows, path):
+    """A prefill and a decode step whose input lies at the start, in the middle and at the end of their output's memory (fp32: a quarter
+    before it, in it, a quarter behind): the same bits as with buffers of their own (what writes the output must not read the input)."""
+    w = BASE.with_(name="same_memory", dtype=dtype, tp_degree=1, n_real_shards=1, n_layers=n_layers, hidden=1024, n_q_heads=4, n_kv_heads=2,
+                   head_dim=64, inter=352, prefill=rows)
+    ctx = harness.build_gpu(w, harness.make_tensors(w), wiring=wiring, kernel_path=path)
+    x = inputs.embeddings(w, 1, rows, inputs.SEED_PREFILL, "cuda:0")
+    e = inputs.embeddings(w, 1, 1, inputs.SEED_DECODE0, "cuda:0")[:, 0].contiguous()
+    want = ctx.prefill(x), ctx.decode_step(e)
+    for place in (0, 1, 2):
+        got = []
+        for call, given in ((ctx.prefill, x), (ctx.decode_step, e)):
+            n = given.numel()
+            held = torch.empty(2 * n, dtype=torch.float32, device=given.device)
+            out = held[n // 2:n // 2 + n].view(given.shape)
+            first = (n // 4, n // 2, 3 * n // 4) if dtype == "fp32" else (n, 3 * n // 2, 2 * n)     # in elements of the input
+            at = held.view(x.dtype)[first[place]:first[place] + n].view(given.shape)
+            at.copy_(given)
+            got.append(call(at, out))
+        for a, b in zip(want, got):
+            assert torch.equal(a, b), place
+    ctx.free()
