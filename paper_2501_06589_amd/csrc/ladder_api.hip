@@ -633,6 +633,21 @@ int run_stage_in(ladder_ctx* c, const StageIo& st, int rows, hipStream_t s) {
   return LADDER_OK;
 }
 
+// the emulated collective behind module m takes reduce_delay_us before its result is there
+// (the parallel block sums the partial sums of both modules of a layer before its one collective: the
+// attention module's reduce stands for the local addition, the MLP module's for the collective)
+int emulate_collective(ladder_ctx* c, int m, hipStream_t s) {
+  const ladder_config& g = c->cfg;
+  const bool local_only = g.wiring == LADDER_WIRING_PARALLEL && (m & 1);
+  if (m == 0 || g.reduce_delay_us == 0 || local_only) return LADDER_OK;
+  const unsigned long long ticks = (unsigned long long)g.reduce_delay_us * (unsigned long long)c->wall_khz / 1000ull;
+  HIP_TRY(c, timed(c, LADDER_K_OTHER, s, [&] {
+    hipLaunchKernelGGL(delay_kernel, dim3(1), dim3(64), 0, s, ticks);
+    return hipGetLastError();
+  }));
+  return LADDER_OK;
+}
+
 int run_reduce(ladder_ctx* c, int m, int rows, int n_slots, const void* emb, StreamCopy copy, hipStream_t s) {
   const ladder_config& g = c->cfg;
   ReduceNormArgs a{};
@@ -656,16 +671,8 @@ int run_reduce(ladder_ctx* c, int m, int rows, int n_slots, const void* emb, Str
     else { a.out_b = out; a.gain_b = gain; }
   }
   a.x_out = copy.at; a.x_step = copy.step;
-  // (the parallel block sums the partial sums of both modules of a layer before its one collective: the
-  // attention module's reduce stands for the local addition, the MLP module's for the collective)
-  const bool local_only = g.wiring == LADDER_WIRING_PARALLEL && (m & 1);
-  if (m > 0 && g.reduce_delay_us > 0 && !local_only) {   // the emulated collective takes this long before its result is there
-    const unsigned long long ticks = (unsigned long long)g.reduce_delay_us * (unsigned long long)c->wall_khz / 1000ull;
-    HIP_TRY(c, timed(c, LADDER_K_OTHER, s, [&] {
-      hipLaunchKernelGGL(delay_kernel, dim3(1), dim3(64), 0, s, ticks);
-      return hipGetLastError();
-    }));
-  }
+  const int rc = emulate_collective(c, m, s);
+  if (rc) return rc;
   HIP_TRY(c, timed(c, LADDER_K_REDUCE_NORM, s, [&] { return launch_reduce_norm(a, c->bf16, s); }));
   return LADDER_OK;
 }
@@ -688,7 +695,7 @@ int run_embed_norm(ladder_ctx* c, const void* emb, int rows, hipStream_t s) {
   return LADDER_OK;
 }
 
-// A call of few rows of the plain path, in order: five launches per layer instead of seven.  Reduce and norm are no kernels of their own:
+// A call of few rows of the plain path on layers that run in order: five launches per layer instead of seven.  Reduce and norm are no kernels of their own:
 // the first projection of a module makes the rows it reads (the last stored stream and the module outputs behind it), and one of
 // its workgroups per row block stores them for the modules that come.  What is read is there when it is read: module m's first projection
 // adds the outputs up to module m - lag, so the output of module m - 2, whose buffer module m's last projection overwrites, has been added.
@@ -714,7 +721,8 @@ int forward_plain(ladder_ctx* c, const void* x_in, int B, int T, int pos0, float
     // (a call whose modules all read the embeddings, of one layer: the last one leaves them too, so that what writes x_out reads nothing of
     // x_in, which may lie in the same memory)
     float* const store = in.n_adds || (m == c->n_mod && in.emb) ? buf[0] : nullptr;
-    const int rc = run_module_plain(c, m, B, T, pos0, c->parts[m & 1], s, &in, store);
+    int rc = run_module_plain(c, m, B, T, pos0, c->parts[m & 1], s, &in, store);
+    if (rc == LADDER_OK) rc = emulate_collective(c, m, s);
     if (rc) return rc;
     if (store) {
       in.emb = nullptr; in.base = store; stored = src;
@@ -758,10 +766,11 @@ int forward_body(ladder_ctx* c, const void* x_in, int B, int T, int pos0, bool d
   const bool small = rows <= 64 && !st && !brief;
   const bool overlap = pays && !st && !brief && c->cfg.overlap_modules != 0;
   const bool side = small && c->cfg.overlap_modules == 0 && c->cfg.reduce_on_side_stream != 0;
-  // the plain path in order, up to PLAIN_NORM_ROWS rows: module inputs made where they are multiplied, by every column block anew, which
-  // pays while that is little beside a block's 64 columns of weights (four rows per block beyond one)
-  if (!c->fast && !st && !overlap && !side && rows <= PLAIN_NORM_ROWS && c->cfg.reduce_delay_us == 0 &&
-      (rows == 1 ? 1 : 4) * (1 + c->cfg.n_real_shards + (c->peers ? c->n_peers : 0)) <= 16)
+  // the plain path, up to PLAIN_NORM_ROWS rows: module inputs made where they are multiplied, by every column block anew, which
+  // pays while that is little beside a block's 64 columns of weights (four rows per block beyond one).  It rounds otherwise than a reduce and
+  // a norm of their own (1/rms is applied to the products), so no switch that only moves work between streams may choose it: the
+  // layers that always run in order take it, the others never.
+  if (brief && !st && rows <= PLAIN_NORM_ROWS && (rows == 1 ? 1 : 4) * (1 + c->cfg.n_real_shards + (c->peers ? c->n_peers : 0)) <= 16)
     return forward_plain(c, x_in, B, T, pos0, (float*)x_out, s0);
   auto module_stream = [&](int m) { return (overlap && (m & 1) == 0) ? c->s_mlp : s0; };
   auto reduce_stream = [&](int m) { return m == 0 ? s0 : (overlap ? module_stream(m) : (side ? c->side : s0)); };

@@ -110,6 +110,25 @@ def test_overlapped_schedules_of_the_plain_path(harness):
             assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("dtype,inter", [("fp32", 96), ("bf16", 96), ("fp32", 2800), ("bf16", 5600)])
+@pytest.mark.parametrize("wiring", [ladder.LADDER_WIRING_LADDER, ladder.LADDER_WIRING_STANDARD, ladder.LADDER_WIRING_PARALLEL])
+def test_schedule_switches_leave_the_bits(harness, wiring, dtype, inter):
+    """One computed shard, a row and a few: layers below 32 MB, whose projections sum and norm the rows themselves, and beyond, which run on
+    two streams, with a side stream or in order as they are told, with and without an emulated latency: the same bits from all of them."""
+    w = BASE.with_(name="switches", dtype=dtype, n_layers=3, hidden=1024, n_q_heads=4, n_kv_heads=2, head_dim=64, inter=inter, tp_degree=2,
+                   n_real_shards=1, prefill=5, peer_pool=2)
+    assert (w.params_per_layer() * (4 if dtype == "fp32" else 2) >= 32 << 20) == (inter > 96)
+    tensors = harness.make_tensors(w, "cuda:0")
+    runs = [harness.run_case(w, tensors=tensors, gen_device="cuda:0", gpu_only=i > 0, wiring=wiring, kernel_path=ladder.LADDER_PATH_GENERIC,
+                             overlap_modules=overlap, reduce_on_side_stream=side, reduce_delay_us=delay)
+            for i, (overlap, side, delay) in enumerate(((0, 0, 0), (1, 0, 0), (0, 1, 0), (0, 0, 20), (1, 1, 20)))]
+    # (three layers of bf16 roundings between the modules)
+    assert max(runs[0].errs) < (1e-4 if dtype == "fp32" else 0.0029 * 6 ** 0.5 * 5.8), runs[0].errs
+    for r in runs[1:]:
+        for a, b in zip(runs[0].gpu, r.gpu):
+            assert np.array_equal(a, b)
+
+
 def test_more_blocks_than_one_grid_dimension_takes(harness):
     """4 million rows, the most that 64-row tiles in the second grid dimension took: projections and attention have more than
     2^24 blocks of 256 threads each. The last sequences come out as in a call of their own."""
