@@ -154,9 +154,15 @@ struct PlainGemmArgs {
   StreamSum in;
   float eps;
   float* x_store;
+  int held;                // workgroups that may count on a place of two per CU: PLAIN_HELD_WORKGROUPS, or 0
   int n_blocks;            // set by the launcher: column blocks of all matrices
 };
 #define PLAIN_NORM_ROWS 64
+#define PLAIN_HELD_WORKGROUPS 512   // two on each of 256 CUs
+// a plain matrix of N columns is read four weights at a time
+inline bool plain_four_at_once(const void* w, int N) { return N % 4 == 0 && ((uintptr_t)w & 15) == 0; }
+// workgroups of a plain projection of at most PLAIN_NORM_ROWS rows: 64 columns, and four rows where there is more than one
+inline long long plain_workgroups(int rows, int col_blocks, int n_shards) { return (long long)(rows == 1 ? 1 : (rows + 3) / 4) * col_blocks * n_shards; }
 hipError_t launch_plain_gemm(const PlainGemmArgs& a, bool is_bf16, hipStream_t s);
 
 // qkv: f32 [n_parts][rows][(nq+2nkv)*d] (slots summed).  rows = B*T, row = b*T + t, position = pos0 + t.

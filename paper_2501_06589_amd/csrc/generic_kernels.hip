@@ -428,9 +428,10 @@ __device__ __forceinline__ bool plain_tile(unsigned row_blocks, unsigned col_blo
   return true;
 }
 
-template <typename T, int MR, bool VEC, int KC, bool NORM>
-__global__ __launch_bounds__(256) void plain_gemm_kernel(PlainGemmArgs a) {
-  constexpr int NM = MR <= 4 ? 2 : 1;   // gate and up in one sweep over K where the registers allow it
+// NM = 2: gate and up in one sweep over K, and more loads in flight in the other projections too.  (Two workgroups per CU: without the bound the rows that fp32 sums and norms itself cost two registers too many
+// for that; three layers of 264 - 512 workgroups of four rows, hidden 512 and 1024, 2 - 7 % slower than it was as separate kernels, with it 14 - 20 % faster.)
+template <typename T, int MR, bool VEC, int KC, bool NORM, int NM>
+__global__ __launch_bounds__(256, 2) void plain_gemm_kernel(PlainGemmArgs a) {
   __shared__ __attribute__((aligned(16))) float xs[MR][KC];
   __shared__ float red[4 * NM][MR][64];
   __shared__ float sum[2][MR][64];
@@ -513,23 +514,24 @@ static hipError_t launch_plain_gemm_t(PlainGemmArgs a, bool vec, hipStream_t s) 
   const dim3 grid = flat_grid(blocks, a.n_shards);
   // k per pass: 256, or 128 where fp32 tiles of 16 rows are more than two workgroups per CU: their registers then allow three
   // (hidden 8192, 1024 rows 50.4 -> 42.5 ms; but hidden 1024, 128 rows, which do not fill two, 477 -> 583 us).  Same order of sums.
-  if constexpr (sizeof(T) == 4 && MR == 16) {
-    if (blocks * a.n_shards > 512) {
-      if (vec) hipLaunchKernelGGL((plain_gemm_kernel<T, MR, true, 128, false>), grid, dim3(256), 0, s, a);
-      else hipLaunchKernelGGL((plain_gemm_kernel<T, MR, false, 128, false>), grid, dim3(256), 0, s, a);
-      return hipGetLastError();
-    }
+  auto launch = [&](auto kernel_vec, auto kernel) {
+    if (vec) hipLaunchKernelGGL(kernel_vec, grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, a);
+    return hipGetLastError();
+  };
+  if constexpr (MR == 16) {
+    if constexpr (sizeof(T) == 4)
+      if (blocks * a.n_shards > PLAIN_HELD_WORKGROUPS) return launch(plain_gemm_kernel<T, MR, true, 128, false, 1>, plain_gemm_kernel<T, MR, false, 128, false, 1>);
+    return launch(plain_gemm_kernel<T, MR, true, 256, false, 1>, plain_gemm_kernel<T, MR, false, 256, false, 1>);
+  } else {
+    if (a.gain) return launch(plain_gemm_kernel<T, MR, true, 256, true, 2>, plain_gemm_kernel<T, MR, false, 256, true, 2>);
+    // Gate and up in one sweep take the registers of two workgroups per CU, one after the other those of four, which is what counts where
+    // there are more, beside the other module's on a second stream too (hidden 1024, 2 layers of 2 shards, 64 rows, one sweep / two: inter 1408
+    // fp32 191 / 165 us, bf16 189 / 171; inter 2816 259 / 240, 249 / 217), and bf16 weights that come one by one are requested faster than they
+    // can be waited for (inter 1409, 8 rows 329 / 310).
+    if (blocks * a.n_shards <= a.held && (vec || sizeof(T) == 4)) return launch(plain_gemm_kernel<T, MR, true, 256, false, 2>, plain_gemm_kernel<T, MR, false, 256, false, 2>);
+    return launch(plain_gemm_kernel<T, MR, true, 256, false, 1>, plain_gemm_kernel<T, MR, false, 256, false, 1>);
   }
-  if constexpr (MR <= 4) {
-    if (a.gain) {
-      if (vec) hipLaunchKernelGGL((plain_gemm_kernel<T, MR, true, 256, true>), grid, dim3(256), 0, s, a);
-      else hipLaunchKernelGGL((plain_gemm_kernel<T, MR, false, 256, true>), grid, dim3(256), 0, s, a);
-      return hipGetLastError();
-    }
-  }
-  if (vec) hipLaunchKernelGGL((plain_gemm_kernel<T, MR, true, 256, false>), grid, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((plain_gemm_kernel<T, MR, false, 256, false>), grid, dim3(256), 0, s, a);
-  return hipGetLastError();
 }
 
 template <typename T>
@@ -555,7 +557,7 @@ hipError_t launch_plain_gemm(const PlainGemmArgs& a, bool is_bf16, hipStream_t s
   if (a.gain && (a.M > PLAIN_NORM_ROWS || a.epilogue == PLAIN_OUT || (!a.in.emb && !a.in.base) || a.in.n_adds < 0 || a.in.n_adds > 2)) return hipErrorInvalidValue;
   // four weights per load where every row of every matrix starts on such a boundary
   bool vec = (a.w_stride & 15) == 0;
-  for (int i = 0; i < a.n_mat; ++i) vec = vec && a.N[i] % 4 == 0 && ((uintptr_t)a.w[i] & 15) == 0;
+  for (int i = 0; i < a.n_mat; ++i) vec = vec && plain_four_at_once(a.w[i], a.N[i]);
   // rows per workgroup: one for a single row; four for a few; more re-use of the weights beyond
   const int mr = a.M == 1 ? 1 : a.M <= PLAIN_NORM_ROWS ? 4 : 16;
   if (is_bf16) return mr == 1 ? launch_plain_gemm_t<bf16_t, 1>(a, vec, s) : mr == 4 ? launch_plain_gemm_t<bf16_t, 4>(a, vec, s) : launch_plain_gemm_t<bf16_t, 16>(a, vec, s);

@@ -106,6 +106,7 @@ struct ladder_ctx {
   const char* peers = nullptr;
   // workspaces
   float* x = nullptr;
+  int plain_held = 0;           // plain path: PlainGemmArgs::held of the call's projections
   float* x_other = nullptr;     // plain path, calls of few rows: the stream before or after the one in x
   char* y[2] = {nullptr, nullptr};
   // wide calls of the packed-weight path: the residual update is the epilogue of a module's last GEMM, which
@@ -443,13 +444,13 @@ int run_module_plain(ladder_ctx* c, int m, int B, int T, int pos0, float* out, h
   const int rows = B * T, H = g.hidden, d = g.head_dim, nqd = g.n_q_heads * d, nkd = g.n_kv_heads * d, I = g.inter;
   const LayerStore& L = c->store[(size_t)((m - 1) / 2) * g.n_real_shards];   // shard 0; the others lie at fixed strides behind it
   PlainGemmArgs a{};
-  a.x = c->y[m & 1]; a.M = rows; a.K = H; a.n_shards = g.n_real_shards; a.w_stride = c->shard_bytes;
+  a.x = c->y[m & 1]; a.M = rows; a.K = H; a.n_shards = g.n_real_shards; a.w_stride = c->shard_bytes; a.held = c->plain_held;
   if (in) {
     a.in = *in; a.x_store = x_store; a.eps = g.rms_eps;
     a.gain = (m & 1) ? (const void*)c->gain_attn[(size_t)(m - 1) / 2] : (const void*)c->gain_mlp[(size_t)(m - 1) / 2];
   }
   PlainGemmArgs last{};
-  last.M = rows; last.n_shards = g.n_real_shards; last.w_stride = c->shard_bytes; last.n_mat = 1; last.N[0] = H;
+  last.M = rows; last.n_shards = g.n_real_shards; last.w_stride = c->shard_bytes; last.held = c->plain_held; last.n_mat = 1; last.N[0] = H;
   last.epilogue = PLAIN_OUT; last.out = out; last.out_stride = (size_t)rows * H;
   if (m & 1) {
     a.n_mat = 3; a.w[0] = L.wq; a.w[1] = L.wk; a.w[2] = L.wv; a.N[0] = nqd; a.N[1] = a.N[2] = nkd; a.epilogue = PLAIN_QKV;
@@ -769,8 +770,23 @@ int forward_body(ladder_ctx* c, const void* x_in, int B, int T, int pos0, bool d
   // the plain path, up to PLAIN_NORM_ROWS rows: module inputs made where they are multiplied, by every column block anew, which
   // pays while that is little beside a block's 64 columns of weights (four rows per block beyond one).  It rounds otherwise than a reduce and
   // a norm of their own (1/rms is applied to the products), so no switch that only moves work between streams may choose it: the
-  // layers that always run in order take it, the others never.
-  if (brief && !st && rows <= PLAIN_NORM_ROWS && (rows == 1 ? 1 : 4) * (1 + c->cfg.n_real_shards + (c->peers ? c->n_peers : 0)) <= 16)
+  // layers that always run in order take it, the others never.  bf16, whose other kernels are four to a CU, only while two per CU hold the
+  // whole projection, and not where its weights come one by one: 2 layers, other kernels / rows made, us, 512 workgroups and fewer 1.02 - 1.16 times as fast
+  // (fp32 1.02 - 1.28), 40 rows of hidden 128, inter 4096 (640 workgroups) 148 / 151, fp32 155 / 149; 64 rows of hidden 64, inter 8192 (2048) 237 / 254,
+  // fp32 259 / 251; inter 1409 of hidden 1024, 8 rows, bf16 310 / 329.
+  const int nqd = c->cfg.n_q_heads * c->cfg.head_dim, nkd = c->cfg.n_kv_heads * c->cfg.head_dim, I = c->cfg.inter;
+  const long long wg_qkv = plain_workgroups(rows, (nqd + 63) / 64 + 2 * ((nkd + 63) / 64), c->cfg.n_real_shards);
+  const long long wg_gu = plain_workgroups(rows, (I + 63) / 64, c->cfg.n_real_shards), wg_out = plain_workgroups(rows, (c->cfg.hidden + 63) / 64, c->cfg.n_real_shards);
+  // (side by side the two modules' largest have to find a place together)
+  c->plain_held = !overlap || std::max(wg_qkv, wg_out) + std::max(wg_gu, wg_out) <= PLAIN_HELD_WORKGROUPS ? PLAIN_HELD_WORKGROUPS : 0;
+  auto made_where_multiplied = [&] {
+    if (!c->bf16) return true;
+    const LayerStore& L = c->store[0];
+    if (!plain_four_at_once(L.wq, nqd) || !plain_four_at_once(L.wk, nkd) || !plain_four_at_once(L.wv, nkd) ||
+        !plain_four_at_once(L.wg, I) || !plain_four_at_once(L.wu, I)) return false;
+    return rows == 1 || std::max(wg_qkv, wg_gu) <= PLAIN_HELD_WORKGROUPS;
+  };
+  if (brief && !st && rows <= PLAIN_NORM_ROWS && made_where_multiplied() && (rows == 1 ? 1 : 4) * (1 + c->cfg.n_real_shards + (c->peers ? c->n_peers : 0)) <= 16)
     return forward_plain(c, x_in, B, T, pos0, (float*)x_out, s0);
   auto module_stream = [&](int m) { return (overlap && (m & 1) == 0) ? c->s_mlp : s0; };
   auto reduce_stream = [&](int m) { return m == 0 ? s0 : (overlap ? module_stream(m) : (side ? c->side : s0)); };
@@ -2094,7 +2110,7 @@ static int head_body(ladder_ctx* c, const float* x, int rows, char* y, float* lo
   HIP_TRY(c, launch_head_norm(x, c->head_gain, y, rows, H, g.rms_eps, c->bf16, s));
   if (!c->head_fast) {
     PlainGemmArgs a{};
-    a.x = y; a.M = rows; a.K = H; a.n_shards = 1; a.n_mat = 1; a.w[0] = c->head_w; a.N[0] = V; a.epilogue = PLAIN_OUT; a.out = logits;
+    a.x = y; a.M = rows; a.K = H; a.n_shards = 1; a.held = PLAIN_HELD_WORKGROUPS; a.n_mat = 1; a.w[0] = c->head_w; a.N[0] = V; a.epilogue = PLAIN_OUT; a.out = logits;
     HIP_TRY(c, launch_plain_gemm(a, c->bf16, s));
   } else if (rows <= 16 && (V & 31) == 0 && gemv_plan(V, H, true).ksplit == 1) {   // (what the skinny GEMM takes: whole pairs of tiles, and so many that K is not split)
     GemvArgs a{};

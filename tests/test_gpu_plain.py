@@ -43,6 +43,16 @@ def test_rows_made_where_they_are_multiplied(harness, wiring, n_std, n_layers, r
     assert max(res.errs) < 1e-4, res.errs
 
 
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("rows,shards", [(32, 1), (36, 1), (8, 4), (12, 4)])
+def test_as_many_workgroups_as_the_chip_holds_and_more(harness, dtype, rows, shards):
+    """512 workgroups of four rows in the gate/up projection, and 576 and 768: one sweep over gate and up or two, rows made by the projections or not
+    (bf16), with a row block that is not full behind them (the steps)."""
+    w = BASE.with_(name="held", n_layers=2, prefill=rows, hidden=136, inter=4096, tp_degree=shards, n_real_shards=shards, dtype=dtype)
+    res = harness.run_case(w, kernel_path=ladder.LADDER_PATH_GENERIC)
+    assert max(res.errs) < (1e-4 if dtype == "fp32" else 0.0029 * 4 ** 0.5 * 5.8), res.errs
+
+
 @pytest.mark.parametrize("cached", [63, 64, 255, 256, 700])
 def test_attention_chunks(harness, cached):
     """One step behind a handed-over cache: part of a chunk, whole chunks, more chunks than wavefronts."""
