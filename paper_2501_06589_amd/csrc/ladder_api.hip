@@ -748,12 +748,15 @@ int forward_body(ladder_ctx* c, const void* x_in, int B, int T, int pos0, bool d
   // Which calls run on two module streams, where the caller has not switched them off.  Two modules side by side fill what each leaves
   // idle: short kernels beside long ones, the last round of a product's tiles.  Too short for the events between the streams: layers
   // whose weights and products take less than some 32 us (bytes at 5 TB/s, 1000 TFLOP/s).  From 257 to 512 rows in order: gate/up is
-  // then about one workgroup per CU, and kernels beside it only get in its way.  Beyond 1024 rows every kernel fills the chip (4 - 16 %
-  // slower side by side).  In order / side by side, us, 2 or 4 layers: 8B shape 80 rows 226 / 212, 100 (4) 478 / 420, 200 349 / 322, 400 517 /
+  // then about one workgroup per CU for the wider shapes, and kernels beside it only get in its way (not for all: 1.2B 300 rows and 8B 400 below would
+  // gain; the rule asks for the rows alone).  Beyond 1024 rows in order (4 - 16 % slower side by side, with tiles of 256 x 256 that have a CU to
+  // themselves; not measured with the smaller ones).  In order / side by side, us, 2 or 4 layers: 8B shape 80 rows 226 / 212, 100 (4) 478 / 420, 200 349 / 322, 400 517 /
   // 500, 500 546 / 560, 600 660 / 625, 800 861 / 818, 1000 935 / 910; 70B R = 4 250 401 / 373, 350 509 / 527, 500 600 / 652, 560 748 / 691, 800
   // 914 / 845; R = 8 (4) 17 rows 292 / 286, 64 356 / 323, 150 513 / 467, (2) 300 336 / 338, 500 440 / 453, 700 577 / 553, 1000 717 / 635; 1.2B
   // (4) 17 rows 217 / 251, 64 248 / 256, 100 237 / 251, 200 299 / 262, 300 372 / 338, (2) 160 139 / 140, 700 268 / 241.  Decode steps of
-  // up to 64 sequences, whose attention reads a cache beside: side by side whatever the layer (1.2B, 40 sequences 1242 / 1146).
+  // up to 64 sequences, whose attention reads a cache beside: side by side whatever the layer (1.2B, 40 sequences 1242 / 1146).  Of more sequences in
+  // order: what it gives depends on the cache as well (2 layers, behind 64 positions 8B 65 sequences 253 / 273, 160 391 / 360, 1.2B 256 212 / 227, 70B R = 8 160
+  // 274 / 242, behind 1024 8B 160 655 / 683, 1.2B 256 654 / 682, 70B R = 4 256 514 / 539, R = 8 160 310 / 286).
   // (a pipeline stage's call is in order too: its hand-over reads the stream between the last modules)
   // (and so do calls whose kernels are shorter than the events between two streams: a layer of the plain path under
   // 32 MB of weights.  Measured, prompt of 32 and 8 steps, overlapped / in order, us: tiny model (2.8 MB) 1078 / 556, 10 MB
@@ -763,7 +766,7 @@ int forward_body(ladder_ctx* c, const void* x_in, int B, int T, int pos0, bool d
   // beyond 64 rows: the wiring that was measured, and more than one layer (of one, the fork and the join are the larger part: 70B R = 8, 600
   // rows 302 / 327, 1.2B 122 / 131)
   const bool independent = c->cfg.wiring == LADDER_WIRING_LADDER && c->cfg.n_standard_layers == 0 && c->cfg.n_layers > 1;
-  const bool pays = !c->fast || (rows <= 64 && (T == 1 || c->cfg.reduce_delay_us > 0)) ? rows <= 64 : rows <= (independent ? FEW_ROWS : 64) && (rows <= 256 || rows > 512) && layer_bytes * (200.0 + rows) >= 32e9;
+  const bool pays = !c->fast || T == 1 || (rows <= 64 && c->cfg.reduce_delay_us > 0) ? rows <= 64 : rows <= (independent ? FEW_ROWS : 64) && (rows <= 256 || rows > 512) && layer_bytes * (200.0 + rows) >= 32e9;
   const bool small = rows <= 64 && !st && !brief;
   const bool overlap = pays && !st && !brief && c->cfg.overlap_modules != 0;
   const bool side = small && c->cfg.overlap_modules == 0 && c->cfg.reduce_on_side_stream != 0;

@@ -132,6 +132,21 @@ def test_wide_decode_replayed_from_a_graph(harness):
         assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("batch", [64, 65, 100, 257])
+def test_decode_of_many_sequences_under_every_schedule(harness, batch):
+    """Steps of a layer that prompts of as many rows run on two streams: with module streams and in order, launched eagerly and replayed from a
+    captured graph, the same bits; and the right ones (one layer's bound for each of the two)."""
+    import numpy as np
+    w = WIDE.with_(name="many_sequences", n_layers=2, hidden=2112, inter=8256, n_q_heads=8, batch=batch, prefill=0, kv_preload=70, decode_steps=3)
+    tensors = harness.make_tensors(w, "cuda:0")
+    runs = [harness.run_case(w, kv_preload=70, decode_steps=3, tensors=tensors, gen_device="cuda:0", gpu_only=i > 0, max_tokens=1, overlap_modules=overlap,
+                             decode_graph=graph) for i, (overlap, graph) in enumerate(((1, 0), (1, 1), (0, 0), (0, 1)))]
+    assert max(runs[0].errs) < TOL * 2 ** 0.5, runs[0].errs
+    for r in runs[1:]:
+        for a, b in zip(runs[0].gpu, r.gpu):
+            assert np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("rows", [17, 100, 300])
 @pytest.mark.parametrize("hidden,inter", [(448, 32), (448, 416), (32, 64)])
 def test_products_of_a_single_stage(harness, hidden, inter, rows):
