@@ -45,6 +45,28 @@ extern "C" int reaches(int ldx, int K, int jt) {{ return gemm_duo_reaches(ldx, K
     return Rule(C.CDLL(str(at / "rule.so")))
 
 
+def test_the_gpu_tests_run_the_tiles_that_they_name(rule):
+    # test_gpu_few_rows.py
+    assert rule.tile(257, 2 * 4160, 4160, SWIGLU) == "duo 128"
+    assert rule.few(513, 2112, 8256) == ("duo 128", 3)
+    assert rule.tile(700, 2 * 8256, 576, SWIGLU) == "duo 256"
+    assert rule.tile(1025, 4160, 1088, RESIDUAL, 9) == "duo 192"
+    assert rule.tile(2100, (16 + 2 * 2) * 128, 1088, QKV) == "duo 192"
+    for n, k, epilogue in (((16 + 2 * 2) * 128, 2112, QKV), (2112, 2048, RESIDUAL), (2 * 2112, 2112, SWIGLU), (2112, 2112, RESIDUAL)):
+        assert rule.tile(3000, n, k, epilogue, 2) == "duo 256"
+    assert rule.tile(1101, 4128, 2080, RESIDUAL, 4) == "128x256"
+    assert rule.tile(4100, 2112, 512, RESIDUAL) == "256x256"
+    for rows in (385, 400, 500):
+        assert rule.tile(rows, 2 * 14304, 2112, SWIGLU) == "256x256"
+    # test_gpu_parity.py, 13200 rows
+    assert [rule.tile(13200, *a) for a in ((768, 1056, QKV), (1056, 512, RESIDUAL, 3), (2048, 1056, SWIGLU), (1056, 1024, RESIDUAL, 3))] == [
+        "128x128", "duo 128", "128x256", "duo 128"]
+    assert [rule.tile(13200, *a) for a in ((768, 1024, QKV), (1024, 512, RESIDUAL, 3), (2368, 1024, SWIGLU), (1024, 1184, RESIDUAL, 3))] == [
+        "256x256", "duo 256", "duo 192", "128x256"]
+    for peers in (2, 7):
+        assert rule.tile(13200, 1056, 512, RESIDUAL, peers) == rule.tile(13200, 1056, 1024, RESIDUAL, peers) == "duo 128"
+
+
 def test_no_tile_takes_a_shape_that_its_kernel_refuses(rule):
     """Offsets of the 128-row tiles' requests are 32 bits: K or a row stride of 2^23 and more, K x columns beyond 2^31 bytes; 256 x 256 and
     those tiles want whole stages of 64 k, and no split or no few rows."""

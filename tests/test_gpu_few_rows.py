@@ -88,6 +88,15 @@ def test_residual_epilogue_of_the_largest_tile(harness):
     assert max(res.errs) < TOL * 2 ** 0.5, res.errs
 
 
+@pytest.mark.parametrize("rows", [385, 400, 500])
+def test_swiglu_epilogue_of_the_largest_tile(harness, rows):
+    """256 x 256 tiles with SwiGLU as epilogue (taken up to 1024 rows), ragged in both directions: 129, 144 and 244 rows and three
+    quarters of the columns in the last tiles."""
+    w = WIDE.with_(name="large_tile_swiglu", hidden=2112, inter=14304, n_q_heads=4, prefill=rows)
+    res = harness.run_case(w, decode_steps=0, gen_device="cuda:0")
+    assert max(res.errs) < TOL, res.errs
+
+
 @pytest.mark.parametrize("rows", [100, 1100])
 def test_embeddings_off_a_16_byte_boundary(harness, rows):
     """The same bits wherever the call's input lies (the residual update of module 1 reads it 16 bytes at a time beyond 1024 rows)."""

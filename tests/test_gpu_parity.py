@@ -401,10 +401,9 @@ def test_full_width_70b_r4_prefill_against_oracle(harness):
 
 @pytest.mark.parametrize("hidden,inter,batch", [(1056, 1024, 12), (1024, 1184, 12)])
 def test_bf16_large_tile_gemm_ragged_edges(harness, hidden, inter, batch):
-    """The 256 x 256-tile GEMM serves the calls whose tiles fill the chip; here it gets a ragged last row
-    block (13200 rows) and a ragged last column block: hidden 1056 = 4.1 column blocks for the O projection
-    (residual epilogue), 2 x 1184 = 9.3 column blocks for gate/up (SwiGLU epilogue).  The projections whose K is
-    not a multiple of 64 or whose tiles leave the chip part idle take the ring GEMM in the same call."""
+    """13200 rows (a ragged last row block of every tile) and ragged last column blocks: hidden 1056 for the projections that update the residual
+    (three peers: tiles of 128 x 128, two workgroups per CU), 2 x 1184 for gate/up (128 x 192 tiles), 2 x 1024 and hidden 1056, and K of
+    1184, which are no multiple of 64 (ring tiles); QKV of the second shape takes 256 x 256 tiles."""
     w = inputs.WORKLOADS["70b_r4_prefill"].with_(name=f"ragged_tiles_{hidden}_{inter}", n_layers=1, hidden=hidden, inter=inter,
                                                  n_q_heads=8, n_kv_heads=2, head_dim=64, batch=batch, prefill=1100,
                                                  decode_steps=1)
@@ -443,15 +442,15 @@ def test_bf16_decode_of_more_than_64_sequences(harness, batch):
 
 
 def test_bf16_large_tile_residual_epilogue_hybrid(harness):
-    """The 256 x 256-tile GEMM's residual epilogue (staged through LDS, whole rows per memory instruction) with a
-    ragged last row block and a ragged last column block (hidden 1056), in a hybrid stack (one standard layer, two
+    """The residual epilogue (staged through LDS, whole rows per memory instruction) of 128 x 128 tiles, two workgroups per CU, which calls with
+    peers take, with a ragged last row block and a ragged last column block (hidden 1056), in a hybrid stack (one standard layer, two
     ladder layers: two consumers at the boundary) with seven peers."""
     w = inputs.WORKLOADS["70b_r8_decode"].with_(name="large_tile_residual_hybrid", n_layers=3, hidden=1056, inter=1024,
                                                 n_q_heads=8, n_kv_heads=2, head_dim=64, batch=12, prefill=1100,
                                                 decode_steps=1)
     res = harness.run_case(w, gen_device="cuda:0", wiring=ladder.LADDER_WIRING_LADDER, n_standard_layers=1)
     assert len(res.errs) == 2 and max(res.errs) < TOL_BF16, res.errs
-    # two peers (fewer than the epilogue requests at once), ladder wiring
+    # two peers, ladder wiring
     res = harness.run_case(w.with_(name="large_tile_residual_r3", tp_degree=3, n_layers=2), gen_device="cuda:0")
     assert len(res.errs) == 2 and max(res.errs) < TOL_BF16, res.errs
 
