@@ -29,11 +29,91 @@ __device__ __forceinline__ f32x4_t mfma16(const uint4 a, const uint4 b, const f3
 // ------------------------------------------------------------------------------------------------
 // Epilogue of a wavefront's (16 JT)-column x (16 WM)-row accumulator block: row base m0, first weight tile nt0.
 // Output element (m, n) sits in lane (n%16)/4*16 + m%16, register n%4: a lane stores 4 consecutive columns.
-template <int WM, int JT>
+// RESIDUAL: epilogue 3 is among those the kernel takes (the tiles of 192 columns and more update the residual through LDS, 64 x 64 ones never do).
+template <int WM, int JT, bool RESIDUAL>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x4_t (&acc)[JT][WM], int m0, int nt0, int NT, int lane) {
   const int b = lane & 15, q = lane >> 4;
   // row scale (1.0 where there is none: the multiplication is exact then), applied where an accumulator is read
   auto scale_of = [&](int mt) { return a.row_scale ? a.row_scale[min(m0 + mt * 16 + b, a.M - 1)] : 1.0f; };
+  if constexpr (RESIDUAL) {
+    static_assert(JT % 2 == 0, "two column tiles at a time");
+    if (a.epilogue == 3) {
+      // residual update; the summation order per element is fixed: old value, product, peers 0, 1, ...
+      // The operands (old values, the first three peers) of two column tiles are requested at once.
+      constexpr int PB = 3, JB = 2, JG = JT / JB, STEPS = WM * JG;
+      struct Operands { float4 xo[JB]; uint2 pk[JB][PB]; };
+      Operands o;
+      auto row_of = [&](int mt) { return (size_t)min(m0 + mt * 16 + b, a.M - 1) * a.N; };
+      auto request = [&](Operands& o, int st) {
+        const size_t row = row_of(st / JG);
+#pragma unroll
+        for (int jj = 0; jj < JB; ++jj) {
+          const size_t off = row + min(nt0 + (st % JG) * JB + jj, NT - 1) * 16 + 4 * q;
+          if (a.x_emb) {
+            const uint2 e = *reinterpret_cast<const uint2*>(a.x_emb + off);
+            o.xo[jj] = __builtin_bit_cast(float4, make_uint4(e.x << 16, e.x & 0xFFFF0000u, e.y << 16, e.y & 0xFFFF0000u));
+          } else {
+            o.xo[jj] = *reinterpret_cast<const float4*>(a.x_res + off);
+          }
+#pragma unroll
+          for (int p = 0; p < PB; ++p)
+            if (p < a.n_peers) o.pk[jj][p] = *reinterpret_cast<const uint2*>(a.peers + p * a.peer_stride + off);
+        }
+      };
+      auto add_peer = [&](float (&v4)[4], const uint2 pk) {
+        v4[0] += __uint_as_float(pk.x << 16);
+        v4[1] += __uint_as_float(pk.x & 0xFFFF0000u);
+        v4[2] += __uint_as_float(pk.y << 16);
+        v4[3] += __uint_as_float(pk.y & 0xFFFF0000u);
+      };
+      float ss = 0.f;
+#pragma unroll
+      for (int st = 0; st < STEPS; ++st) {
+        request(o, st);
+        const int mt = st / JG;
+        const int m = m0 + mt * 16 + b;
+        const bool ok = m < a.M;
+        const size_t row = row_of(mt);
+#pragma unroll
+        for (int jj = 0; jj < JB; ++jj) {
+          const int j = (st % JG) * JB + jj;
+          if (nt0 + j >= NT) continue;   // (uniform over the wavefront)
+          const size_t off = row + (nt0 + j) * 16 + 4 * q;
+          float v4[4] = {o.xo[jj].x + acc[j][mt][0], o.xo[jj].y + acc[j][mt][1], o.xo[jj].z + acc[j][mt][2], o.xo[jj].w + acc[j][mt][3]};
+#pragma unroll
+          for (int p = 0; p < PB; ++p)
+            if (p < a.n_peers) add_peer(v4, o.pk[jj][p]);
+          for (int p = PB; p < a.n_peers; ++p) add_peer(v4, *reinterpret_cast<const uint2*>(a.peers + p * a.peer_stride + off));
+          if (ok) {
+            if (!a.last) *reinterpret_cast<float4*>(a.x_res + off) = make_float4(v4[0], v4[1], v4[2], v4[3]);
+            if (a.x_copy)
+              *reinterpret_cast<float4*>(a.x_copy + off) = a.copy_step ? make_float4(v4[0] - o.xo[jj].x, v4[1] - o.xo[jj].y, v4[2] - o.xo[jj].z, v4[3] - o.xo[jj].w)
+                                                                       : make_float4(v4[0], v4[1], v4[2], v4[3]);
+            // the rows as the modules that read them want them: times their norm's gain (fp32 product, one rounding)
+            auto store_gained = [&](bf16_t* dst, const bf16_t* gain) {
+              const uint2 gk = *reinterpret_cast<const uint2*>(gain + (nt0 + j) * 16 + 4 * q);
+              const float g4[4] = {__uint_as_float(gk.x << 16), __uint_as_float(gk.x & 0xFFFF0000u),
+                                   __uint_as_float(gk.y << 16), __uint_as_float(gk.y & 0xFFFF0000u)};
+              uint2 pk;
+              pk.x = f32_to_bf16x2(v4[0] * g4[0], v4[1] * g4[1]);
+              pk.y = f32_to_bf16x2(v4[2] * g4[2], v4[3] * g4[3]);
+              *reinterpret_cast<uint2*>(dst + off) = pk;
+            };
+            if (a.xh_a) store_gained(a.xh_a, a.gain_a);
+            if (a.xh_b) store_gained(a.xh_b, a.gain_b);
+          }
+          ss += v4[0] * v4[0] + v4[1] * v4[1] + v4[2] * v4[2] + v4[3] * v4[3];
+        }
+        if (st % JG == JG - 1) {   // the row block is complete: its rows' sums of squares over this wavefront's columns
+          ss += __shfl_xor(ss, 16, 64);
+          ss += __shfl_xor(ss, 32, 64);
+          if (a.ssq_part && q == 0 && ok && nt0 < NT) a.ssq_part[(size_t)(nt0 / JT) * a.M + m] = ss;
+          ss = 0.f;
+        }
+      }
+      return;
+    }
+  }
   if (a.epilogue == 0) {
 #pragma unroll
     for (int mt = 0; mt < WM; ++mt) {
@@ -46,80 +126,6 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, f32x4_t (&acc)[
         const int n = (nt0 + j) * 16 + 4 * q;
         *reinterpret_cast<float4*>(a.out + (size_t)m * a.N + n) =
             make_float4(acc[j][mt][0] * rs, acc[j][mt][1] * rs, acc[j][mt][2] * rs, acc[j][mt][3] * rs);
-      }
-    }
-  } else if (a.epilogue == 3) {
-    // residual update; the summation order per element is fixed: old value, product, peers 0, 1, ...
-    // The operands (old values, the first three peers) of two column tiles are requested at once.
-    constexpr int PB = 3, JB = JT < 2 ? 1 : 2, JG = JT / JB, STEPS = WM * JG;   // (JT = 1, 64 x 64 tiles: compiled, never chosen)
-    struct Operands { float4 xo[JB]; uint2 pk[JB][PB]; };
-    Operands o;
-    auto row_of = [&](int mt) { return (size_t)min(m0 + mt * 16 + b, a.M - 1) * a.N; };
-    auto request = [&](Operands& o, int st) {
-      const size_t row = row_of(st / JG);
-#pragma unroll
-      for (int jj = 0; jj < JB; ++jj) {
-        const size_t off = row + min(nt0 + (st % JG) * JB + jj, NT - 1) * 16 + 4 * q;
-        if (a.x_emb) {
-          const uint2 e = *reinterpret_cast<const uint2*>(a.x_emb + off);
-          o.xo[jj] = __builtin_bit_cast(float4, make_uint4(e.x << 16, e.x & 0xFFFF0000u, e.y << 16, e.y & 0xFFFF0000u));
-        } else {
-          o.xo[jj] = *reinterpret_cast<const float4*>(a.x_res + off);
-        }
-#pragma unroll
-        for (int p = 0; p < PB; ++p)
-          if (p < a.n_peers) o.pk[jj][p] = *reinterpret_cast<const uint2*>(a.peers + p * a.peer_stride + off);
-      }
-    };
-    auto add_peer = [&](float (&v4)[4], const uint2 pk) {
-      v4[0] += __uint_as_float(pk.x << 16);
-      v4[1] += __uint_as_float(pk.x & 0xFFFF0000u);
-      v4[2] += __uint_as_float(pk.y << 16);
-      v4[3] += __uint_as_float(pk.y & 0xFFFF0000u);
-    };
-    float ss = 0.f;
-#pragma unroll
-    for (int st = 0; st < STEPS; ++st) {
-      request(o, st);
-      const int mt = st / JG;
-      const int m = m0 + mt * 16 + b;
-      const bool ok = m < a.M;
-      const size_t row = row_of(mt);
-#pragma unroll
-      for (int jj = 0; jj < JB; ++jj) {
-        const int j = (st % JG) * JB + jj;
-        if (nt0 + j >= NT) continue;   // (uniform over the wavefront)
-        const size_t off = row + (nt0 + j) * 16 + 4 * q;
-        float v4[4] = {o.xo[jj].x + acc[j][mt][0], o.xo[jj].y + acc[j][mt][1], o.xo[jj].z + acc[j][mt][2], o.xo[jj].w + acc[j][mt][3]};
-#pragma unroll
-        for (int p = 0; p < PB; ++p)
-          if (p < a.n_peers) add_peer(v4, o.pk[jj][p]);
-        for (int p = PB; p < a.n_peers; ++p) add_peer(v4, *reinterpret_cast<const uint2*>(a.peers + p * a.peer_stride + off));
-        if (ok) {
-          if (!a.last) *reinterpret_cast<float4*>(a.x_res + off) = make_float4(v4[0], v4[1], v4[2], v4[3]);
-          if (a.x_copy)
-            *reinterpret_cast<float4*>(a.x_copy + off) = a.copy_step ? make_float4(v4[0] - o.xo[jj].x, v4[1] - o.xo[jj].y, v4[2] - o.xo[jj].z, v4[3] - o.xo[jj].w)
-                                                                     : make_float4(v4[0], v4[1], v4[2], v4[3]);
-          // the rows as the modules that read them want them: times their norm's gain (fp32 product, one rounding)
-          auto store_gained = [&](bf16_t* dst, const bf16_t* gain) {
-            const uint2 gk = *reinterpret_cast<const uint2*>(gain + (nt0 + j) * 16 + 4 * q);
-            const float g4[4] = {__uint_as_float(gk.x << 16), __uint_as_float(gk.x & 0xFFFF0000u),
-                                 __uint_as_float(gk.y << 16), __uint_as_float(gk.y & 0xFFFF0000u)};
-            uint2 pk;
-            pk.x = f32_to_bf16x2(v4[0] * g4[0], v4[1] * g4[1]);
-            pk.y = f32_to_bf16x2(v4[2] * g4[2], v4[3] * g4[3]);
-            *reinterpret_cast<uint2*>(dst + off) = pk;
-          };
-          if (a.xh_a) store_gained(a.xh_a, a.gain_a);
-          if (a.xh_b) store_gained(a.xh_b, a.gain_b);
-        }
-        ss += v4[0] * v4[0] + v4[1] * v4[1] + v4[2] * v4[2] + v4[3] * v4[3];
-      }
-      if (st % JG == JG - 1) {   // the row block is complete: its rows' sums of squares over this wavefront's columns
-        ss += __shfl_xor(ss, 16, 64);
-        ss += __shfl_xor(ss, 32, 64);
-        if (a.ssq_part && q == 0 && ok && nt0 < NT) a.ssq_part[(size_t)(nt0 / JT) * a.M + m] = ss;
-        ss = 0.f;
       }
     }
   } else if (a.epilogue == 2) {
@@ -256,7 +262,7 @@ __device__ __forceinline__ constexpr int gemm_staged_column(int l) { return 8 * 
 // The peers are read once per call and bypass the caches (non-temporal): they would push out the operands that the workgroups
 // beside are multiplying and the rows that the next kernels read (4001 x 8192, seven peers, K 1024 / 3584: 224 / 300 -> 188 / 277 us).
 // (The rows themselves non-temporal too: 1 - 4 % faster measured alone where they exceed the last-level cache, no different in a call.)
-template <int MT, int JT, int WR, int WC, int PB>   // PB: peers requested at once
+template <int MT, int JT, int WR, int WC, int PB>   // PB: peers requested at once (0: there are none)
 __device__ __forceinline__ void gemm_residual_epilogue(const GemmArgs& a, f32x4_t (&acc)[JT][MT], unsigned char* lds, int m0,
                                                        int n_blk, int wave, int lane) {
   constexpr int BN = 16 * JT * WC, STRIDE = GEMM_EPI_STRIDE(BN);   // floats per staged row: + 4, so that the 16 rows of a write spread over the banks
@@ -289,7 +295,7 @@ __device__ __forceinline__ void gemm_residual_epilogue(const GemmArgs& a, f32x4_
 #pragma unroll
     for (int g = 0; g < STEPS / RB; ++g) {
       float4 xo[RB][2];
-      uint4 pk[RB][PB];
+      uint4 pk[RB][PB > 0 ? PB : 1];
       size_t off[RB];
       bool ok[RB];
       int mrow[RB];
@@ -326,7 +332,8 @@ __device__ __forceinline__ void gemm_residual_epilogue(const GemmArgs& a, f32x4_
 #pragma unroll
         for (int p = 0; p < PB; ++p)
           if (p < a.n_peers) add_peer(pk[r][p]);
-        for (int p = PB; p < a.n_peers; ++p) add_peer(load_once(a.peers + p * a.peer_stride + off[r]));
+        if constexpr (PB > 0)
+          for (int p = PB; p < a.n_peers; ++p) add_peer(load_once(a.peers + p * a.peer_stride + off[r]));
         if (ok[r]) {
           if (!a.last) {
             *reinterpret_cast<float4*>(a.x_res + off[r]) = make_float4(v8[0], v8[1], v8[2], v8[3]);
@@ -405,8 +412,10 @@ static hipError_t allow_lds(const void* kernel, int bytes, bool (&prepared)[64])
 // index i is mapped to position (i % 8) * (n / 8) + i / 8 of the tile order: each XCD works through one contiguous
 // eighth of it and neighbours in the order (which share operands) meet in one L2.  GEMM2_GROUP_M row blocks share one
 // column block back to back; the 32 CUs of an XCD then work on 4 row blocks x 8 column blocks at a time (groups of 2 / 4 / 8 row blocks:
-// 1309 / 1335 / 1297 TFLOP/s on 32768 x 8192 x 14336).
-// 1129 / 993 / 1271 / 1338 TFLOP/s on the QKV / O / down / gate-up shapes of the 70B R = 4 shard at 32768 rows.
+// 1309 / 1335 / 1297 TFLOP/s on 32768 x 8192 x 14336 with SwiGLU, which gemm_duo_kernel now takes at 1414).
+// What it takes (gemm_choice.h; of the configured shapes): QKV of thousands of rows (32768 x 2560 x 8192: 1177 - 1222 TFLOP/s), residual updates without
+// peers of 4000 rows and more (8B shape, 8192 rows, O + down 962 us in place, gemm_duo_kernel 1030) and SwiGLU of some calls of 385 - 1024 rows
+// (400 x 28672 x 4096 111 us, 125).
 // ------------------------------------------------------------------------------------------------
 #define GEMM2_GROUP_M 4
 // as ring_meet, but the LDS reads in flight are left alone
@@ -577,8 +586,8 @@ __global__ __launch_bounds__(512, 2) void gemm_lds_kernel(GemmArgs a) {
   }
   // the clamped loads past the last k tile are still in flight into LDS: they must land before the workgroup ends
   gemm2_wait_and_meet<0>();
-  if (a.epilogue == 3) gemm_residual_epilogue<WM, 4, 2, 4, 3>(a, acc, g2_lds, m0, n_blk, wave, lane);
-  else gemm_epilogue<WM, 4>(a, acc, m0 + wm * 128, nt0 + wn * 4, NT, lane);
+  if (a.epilogue == 3) gemm_residual_epilogue<WM, 4, 2, 4, 0>(a, acc, g2_lds, m0, n_blk, wave, lane);   // (calls with peers take other tiles)
+  else gemm_epilogue<WM, 4, false>(a, acc, m0 + wm * 128, nt0 + wn * 4, NT, lane);
 }
 
 static hipError_t launch_gemm_lds(const GemmArgs& a, hipStream_t s) {
@@ -753,7 +762,7 @@ __global__ __launch_bounds__(256, 2) void gemm_duo_kernel(GemmArgs a) {
   }
   GemmArgs e = a;
   if (a.ksplit > 1) e.out = a.out + (size_t)ks * a.out_stride;
-  gemm_epilogue<MT, JT>(e, acc, m0, nt0, NT, lane_e);
+  gemm_epilogue<MT, JT, false>(e, acc, m0, nt0, NT, lane_e);
 #endif
 }
 
@@ -920,7 +929,7 @@ __global__ __launch_bounds__(WR * WC * 64) void gemm_ring_kernel(GemmArgs a) {
   }
   GemmArgs e = a;
   if (a.ksplit > 1) e.out = a.out + (size_t)ks * a.out_stride;
-  gemm_epilogue<MT, JT>(e, acc, m0 + wr * (BM / WR), nt0 + wc * JT, NT, lane);
+  gemm_epilogue<MT, JT, JT == 2>(e, acc, m0 + wr * (BM / WR), nt0 + wc * JT, NT, lane);
 }
 
 template <int BM, int BN, int WR, int WC, int S>
@@ -961,7 +970,9 @@ hipError_t launch_gemm_mfma(const GemmArgs& given, hipStream_t s) {
   if (a.epilogue == 3 && (!a.x_res || a.n_peers < 0 || (a.n_peers > 0 && !a.peers) || (a.xh_b && !a.xh_a) || (a.ssq_part && !a.xh_a) ||
                           (a.xh_a && !a.gain_a) || (a.xh_b && !a.gain_b)))
     return hipErrorInvalidValue;
-  switch (gemm_best_tile(shape_of(a), a.ksplit, nullptr)) {
+  const int tile = gemm_best_tile(shape_of(a), a.ksplit, nullptr);
+  if (a.epilogue == 3 && (tile == TILE_64x64 || (tile == TILE_256x256 && a.n_peers > 0))) return hipErrorInvalidValue;   // (their kernels do not have it)
+  switch (tile) {
     case TILE_64x64: return launch_gemm_ring_t<64, 64, 2, 4, 6>(a, s);
     case TILE_64x128: return launch_gemm_ring_t<64, 128, 2, 4, 6>(a, s);
     case TILE_128x64: return launch_gemm_ring_t<128, 64, 4, 2, 5>(a, s);
