@@ -92,9 +92,9 @@ typedef struct {
                               while module m still runs; 0: one compute stream.  Same results.  It applies
                               to calls that do not take the fused decode schedule and gain by it: of at most
                               1024 rows (64 where there is one token per sequence, the wiring is not all
-                              ladder, or the layer is the only one) and not from 257 to 512, on layers long
-                              enough for the events between the streams (plain kernels: of 32 MB and more);
-                              the others run in order */
+                              ladder, or the layers are few and short) and not from 257 to 512, on layers
+                              long enough for the events between the streams (plain kernels: of 32 MB and
+                              more); the others run in order */
   int32_t decode_graph;   /* 1: a decode step of the bf16 streaming path is captured once into a HIP graph
                              and replayed (the position lives in device memory and is advanced by the
                              graph itself); 0: eager launches.  Same results. */

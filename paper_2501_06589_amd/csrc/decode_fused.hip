@@ -255,8 +255,10 @@ __device__ __forceinline__ bool gemv_job(const GemvJob& j, const void* wp, const
   constexpr bool EARLY_X = !COH && !CHAIN;
   // A residual job of a chained step needs two producers: its operand's at the start, the old rows' only for its epilogue.  Where the second
   // has not finished when the first has, the product goes ahead and the wait follows it.  One row, or up to 4 of a stream of 4096 columns
-  // and more; us, 4 - 8 steps, before / after: headline (8 layers) 2662 / 2641, 8B shape, batch 1 2494 / 2460, R = 8, batch 1 677 / 669, 1.2B, batch 1
-  // 538 / 526, parallel block 1111 / 1086.  With more rows, or on short layers, a down projection beside the attention side slows that:
+  // and more; us per step, before / after: 70B R = 8 (8 layers, batch 2 / 4) 333.3 / 328.6, 337.3 / 334.2, 8B shape (4) 319.5 / 315.0, 333.0 / 330.5, R = 4
+  // (4), batch 4 331.0 / 327.4; us of 4 - 8 steps, one row: 8B shape 2494 / 2460, R = 8 677 / 669, 1.2B 538 / 526, parallel block 1111 / 1086.  5 - 8 rows of 4096
+  // columns and more: no difference beyond 0.5 % (R = 8, batch 5 / 8 349.1 / 347.8, 402.3 / 402.4; 8B 356.0 / 354.8, 366.2 / 364.9).  With more, or on short
+  // layers, a down projection beside the attention side slows that:
   // 1.2B, batch 3 1137 / 1164, batch 4 behind 4000 positions 1674 / 1780, batch 8 1417 / 1513, batch 16 5210 / 5753, R = 4, batch 12 1631 / 1724.
   constexpr bool LATE = CHAIN && !WIDE;
   constexpr int WAVES = FUSED_WAVES;

@@ -749,8 +749,9 @@ int forward_body(ladder_ctx* c, const void* x_in, int B, int T, int pos0, bool d
   // idle: short kernels beside long ones, the last round of a product's tiles.  Too short for the events between the streams: layers
   // whose weights and products take less than some 32 us (bytes at 5 TB/s, 1000 TFLOP/s).  From 257 to 512 rows in order: gate/up is
   // then about one workgroup per CU for the wider shapes, and kernels beside it only get in its way (not for all: 1.2B 300 rows and 8B 400 below would
-  // gain; the rule asks for the rows alone).  Beyond 1024 rows in order (4 - 16 % slower side by side, with tiles of 256 x 256 that have a CU to
-  // themselves; not measured with the smaller ones).  In order / side by side, us, 2 or 4 layers: 8B shape 80 rows 226 / 212, 100 (4) 478 / 420, 200 349 / 322, 400 517 /
+  // gain; the rule asks for the rows alone).  Beyond 1024 rows in order: side by side the residual update would have to be a reduce of its own (2
+  // layers, in order / side by side with that: 8B 2048 rows 1687 / 1743, 4001 3298 / 3382, 70B R = 8 1100 767 / 768, 4001 2184 / 2318, R = 4 4001 3290 / 3742;
+  // short layers and few rows gain all the same: 1.2B 1100 391 / 352, 4001 1100 / 1005, 8B 1100 1159 / 1058).  In order / side by side, us, 2 or 4 layers: 8B shape 80 rows 226 / 212, 100 (4) 478 / 420, 200 349 / 322, 400 517 /
   // 500, 500 546 / 560, 600 660 / 625, 800 861 / 818, 1000 935 / 910; 70B R = 4 250 401 / 373, 350 509 / 527, 500 600 / 652, 560 748 / 691, 800
   // 914 / 845; R = 8 (4) 17 rows 292 / 286, 64 356 / 323, 150 513 / 467, (2) 300 336 / 338, 500 440 / 453, 700 577 / 553, 1000 717 / 635; 1.2B
   // (4) 17 rows 217 / 251, 64 248 / 256, 100 237 / 251, 200 299 / 262, 300 372 / 338, (2) 160 139 / 140, 700 268 / 241.  Decode steps of
@@ -763,9 +764,14 @@ int forward_body(ladder_ctx* c, const void* x_in, int B, int T, int pos0, bool d
   // 970 / 725, 41 MB 1246 / 1077 and at batch 4 1498 / 1688, 100 MB 1288 / 1534, 200 MB 2221 / 2732)
   const bool brief = !c->fast && c->shard_bytes * (size_t)c->cfg.n_real_shards < (32u << 20);
   const double layer_bytes = (double)c->shard_bytes * c->cfg.n_real_shards;
-  // beyond 64 rows: the wiring that was measured, and more than one layer (of one, the fork and the join are the larger part: 70B R = 8, 600
-  // rows 302 / 327, 1.2B 122 / 131)
-  const bool independent = c->cfg.wiring == LADDER_WIRING_LADDER && c->cfg.n_standard_layers == 0 && c->cfg.n_layers > 1;
+  // Beyond 64 rows: the wiring that was measured, and four layers or two or three long ones: the fork and the join cost some 15 us where the host is not
+  // ahead of the GPU, and calls behind them about 2 us each while the second stream waits for the next fork (of one layer more than it gives: 70B
+  // R = 8, 600 rows 302 / 327).  Two layers, in order / side by side, a call by itself, and a prompt with eight steps behind it, back to back: 1.2B 200 rows 155 /
+  // 162, 648 / 662, 1000 rows 348 / 356, 845 / 868; 70B R = 8 93 rows 200 / 211, 857 / 869, 600 567 / 553, 1228 / 1218; 8B 66 rows 264 / 251, 1495 / 1493, 160 363 /
+  // 344, 1560 / 1539.  Four: 1.2B 160 303 / 293, 1234 / 1208, 1000 692 / 675, 1635 / 1620; R = 8 66 376 / 345, 1632 / 1611, 128 415 / 393, 1678 / 1667.
+  const double all_bytes = layer_bytes * c->cfg.n_layers;
+  const bool independent = c->cfg.wiring == LADDER_WIRING_LADDER && c->cfg.n_standard_layers == 0 && c->cfg.n_layers > 1 &&
+                           (c->cfg.n_layers >= 4 || all_bytes * (200.0 + rows) >= 230e9);
   const bool pays = !c->fast || T == 1 || (rows <= 64 && c->cfg.reduce_delay_us > 0) ? rows <= 64 : rows <= (independent ? FEW_ROWS : 64) && (rows <= 256 || rows > 512) && layer_bytes * (200.0 + rows) >= 32e9;
   const bool small = rows <= 64 && !st && !brief;
   const bool overlap = pays && !st && !brief && c->cfg.overlap_modules != 0;

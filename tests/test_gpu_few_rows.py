@@ -112,10 +112,11 @@ def test_embeddings_off_a_16_byte_boundary(harness, rows):
     ctx.free()
 
 
-def test_module_streams_leave_the_same_bits(harness):
-    """Calls that run attention and MLP modules on two streams (65 - 256 and 513 - 1024 rows of a layer of 240 MB) against the same
-    calls in order, with calls of other row counts in between and decode steps behind them."""
-    w = WIDE.with_(name="streams", n_layers=3, hidden=4096, inter=6144, prefill=1024)
+@pytest.mark.parametrize("n_layers", [3, 4])
+def test_module_streams_leave_the_same_bits(harness, n_layers):
+    """Calls that run attention and MLP modules on two streams (65 - 256 and 513 - 1024 rows of four layers of 190 MB, 256 and 513 - 1024 of three) against the
+    same calls in order, with calls of other row counts in between and decode steps behind them."""
+    w = WIDE.with_(name="streams", n_layers=n_layers, hidden=4096, inter=6144, prefill=1024)
     tensors = harness.make_tensors(w, "cuda:0")
     side, order = (harness.build_gpu(w, tensors, overlap_modules=v) for v in (1, 0))
     x = inputs.embeddings(w, 1, 1024, inputs.SEED_PREFILL, "cuda:0")
@@ -144,13 +145,13 @@ def test_wide_decode_replayed_from_a_graph(harness):
 @pytest.mark.parametrize("batch", [64, 65, 100, 257])
 def test_decode_of_many_sequences_under_every_schedule(harness, batch):
     """Steps of a layer that prompts of as many rows run on two streams: with module streams and in order, launched eagerly and replayed from a
-    captured graph, the same bits; and the right ones (one layer's bound for each of the two)."""
+    captured graph, the same bits; and the right ones (one layer's bound for each of the four)."""
     import numpy as np
-    w = WIDE.with_(name="many_sequences", n_layers=2, hidden=2112, inter=8256, n_q_heads=8, batch=batch, prefill=0, kv_preload=70, decode_steps=3)
+    w = WIDE.with_(name="many_sequences", n_layers=4, hidden=2112, inter=9152, n_q_heads=8, batch=batch, prefill=0, kv_preload=70, decode_steps=3)
     tensors = harness.make_tensors(w, "cuda:0")
     runs = [harness.run_case(w, kv_preload=70, decode_steps=3, tensors=tensors, gen_device="cuda:0", gpu_only=i > 0, max_tokens=1, overlap_modules=overlap,
                              decode_graph=graph) for i, (overlap, graph) in enumerate(((1, 0), (1, 1), (0, 0), (0, 1)))]
-    assert max(runs[0].errs) < TOL * 2 ** 0.5, runs[0].errs
+    assert max(runs[0].errs) < TOL * 4 ** 0.5, runs[0].errs
     for r in runs[1:]:
         for a, b in zip(runs[0].gpu, r.gpu):
             assert np.array_equal(a, b)
