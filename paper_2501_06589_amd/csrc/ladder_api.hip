@@ -363,11 +363,10 @@ int finish_residual(ladder_ctx* c, const GemmArgs& a, int rows, int nc, const in
 
 // Calls of at most this many rows: the projections may be split along K over workgroups (every CU gets some, whatever the
 // number of columns) and leave partial products, which the next kernel (rotary + append, SwiGLU, reduce + norm) adds up.
-// Beyond, the residual update is an epilogue (fuse_residual).  Measured with the line at 128 / 256 / 512 / 1024 rows (two
-// layers, us): 8B shape 200 rows 470 / 401 / 401 / 401, 1000 rows 1040 / 1040 / 1040 / 1018; 70B R = 8 shard 300 rows 465 /
-// 466 / 387 / 387, 1000 rows 892 / 892 / 891 / 818; 1.2B 400 rows 282 / 282 / 258 / 258, 1000 rows 404 / 404 / 404 / 420 (its K
-// is not worth a split at 1000 rows, so it would be 4 % better off with the epilogue, the wider shapes 2 - 8 % worse; a rule by
-// module, fused where K is not worth a split, was no better: 70B R = 8 at 1000 rows 893).
+// Beyond, the residual update is an epilogue (fuse_residual).  Measured with the line at 256 / 512 / 1024 rows (two layers, us; below the line
+// with the module streams that forward_body gives such a call): 8B shape 300 rows 494 / 450 / 450, 500 579 / 542 / 540, 700 791 / 792 / 706, 1000 944 /
+// 945 / 901; 70B R = 8 300 rows 379 / 342 / 340, 700 551 / 549 / 553, 1000 656 / 655 / 634; R = 4 700 rows 772 / 773 / 732, 1000 912 / 916 / 925; 1.2B 400 rows
+// 210 / 192 / 192, 700 275 / 276 / 243, 1000 313 / 314 / 314.  (A rule by module, fused where K is not worth a split, was no better.)
 // A call's number of slots depends on its rows alone, not on what the context was sized for (the same call gives the same bits
 // in every context): FEW_ROWS_SLOTS up to 256 rows, beyond them as many as fit the buffer that 256 rows need (more were no
 // faster: 700 rows with 2048 / rows slots and with up to 8, two layers, us: 8B shape 869 / 885, 70B R = 8 shard 557 / 559, 1.2B 315 / 317).
