@@ -76,7 +76,6 @@ struct GemvJob {
   const unsigned* wait_on2;
   unsigned wait_flags2;
   unsigned wait_bias2;
-  int coherent_x;          // chained step: the x operand is read with device-coherent loads (a buffer that is written more than once per launch)
   unsigned* done_ctr;
   unsigned done_target;
   unsigned done_ord0;
@@ -181,7 +180,7 @@ struct StepItem {
   uint16_t group0;
   uint16_t lb;             // block index within the job
   uint16_t job;            // index into the GEMV or the attention job table
-  uint8_t kind;            // descriptor byte: JOB_* | (tiles per workgroup - 1) << 2 | coherent operand loads << 5; 0 ends the list
+  uint8_t kind;            // descriptor byte: JOB_* | (tiles per workgroup - 1) << 2; 0 ends the list
   uint8_t M;
   uint16_t pad0;
   uint32_t pad1;
@@ -205,7 +204,7 @@ int fused_chain_slots(int d, int g, int n_cu);
 // timeline (null in normal operation): u64 [n_slots][n_items][3], the wall-clock times at which a slot took an item,
 // had waited for its inputs, and had finished it
 hipError_t launch_fused_chain(const StepItem* items, int n_items, const GemvJob* gemv_jobs, const AttnJob* attn_jobs,
-                              float* x_out, unsigned long long* timeline, int n_slots, int lds_bytes, int d, int g,
+                              const int* pos_dev, float* x_out, unsigned long long* timeline, int n_slots, int lds_bytes, int d, int g,
                               hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
 hipError_t fused_decode_prepare(int d, int g);   // once per context, before the first launch
 size_t fused_attn_lds_bytes(int d, int g);

@@ -51,15 +51,6 @@ typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4_t;
 #define FUSED_KIND_WAITS 32u        // the job waits for another job of the launch
 #define FUSED_KIND_SLOT_SHIFT 6     // two bits: index of the job's preloaded (weights, operand) pointer pair, 3 = none
 
-// k tiles per register buffer (two buffers) of a one-tile / a two-tile workgroup: 4 KiB of weights in flight
-// per wavefront.  With the round-robin assignment of k tiles below, 2 beat 4 (3.57 against 3.65 ms per step;
-// 1 gave 4.04, 3 gave 3.74: its turns do not divide the k range).  Two-tile workgroups take two k tiles per
-// buffer as well: in a chained step 3.26 -> 3.23 ms per step (the output projection's whole weight share, 64 KiB,
-// is then requested before its wait); as separate launches that costs 1.4 %, accepted so that both schedules sum
-// in the same order and give the same bits (the k tiles a wavefront takes follow from this number).  Three- and
-// four-tile workgroups: one (two: 2.6 % slower).
-#define FUSED_U 2
-#define FUSED_U2 2
 #define FUSED_POLL_SLEEP 8      // s_sleep units (64 clocks) between two polls of a wait (2 measured the same)
 #define FUSED_LDS_FLOATS 9216   // attention job: per-wave statistics and outputs
 
@@ -229,30 +220,166 @@ __device__ __forceinline__ void gemv_signal_done(const GemvJob& j, int lb) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// skinny GEMM job: see gemv_mfma_kernel for the streaming scheme (same tiles, same pipeline).
-// A workgroup owns TN adjacent 16-column tiles and the whole K range; U k-tiles per register buffer.
-// A wavefront's streaming rate is its bytes in flight over the memory latency, so the launch time is
-// set by the workgroup with the most bytes: one tile per workgroup keeps the jobs of a launch even
-// and the number of streaming workgroups high.
-// ------------------------------------------------------------------------------------------------
-// wp, xop, KT, group0 and M repeat j.wp, j.xb, j.K / 32, j.group0 and j.M (the x rows are K elements apart): the
-// kernel hands them over from preloaded kernel arguments where it can, so that the first weight tiles and
-// operand slices are requested before the job's descriptor (j) has arrived from memory.
+// skinny GEMM job: a workgroup owns tn adjacent 16-column tiles and the whole K range; every weight tile goes global -> register ->
+// MFMA operand.  A wavefront's streaming rate is its bytes in flight over the memory latency, and a chain of short jobs is as long as the
+// round trips that each still has to make when its inputs arrive.  So the weights of the first R k tiles are requested before the job waits
+// for anything, and so are the epilogue's operands that no job of the launch writes; what is left behind the wait is the
+// operand's round trip, the old rows and the sums of squares.  Only the product is compiled per number of tiles (and its wait, which the
+// registers of the requested tiles have to live through); everything around it takes tn as it comes, which halves the kernel's code
+// (230 -> 140 KB; a compute unit's instruction cache holds 64 KB for two).  Chained step with this and the attention job's early requests,
+// hand-over and 8 steps, before / after, us: 70B R = 8, batch 4 (8 layers) 2647 / 2569, behind 32001 positions (4) 2261 / 2177; 1.2B (4), batch 1
+// 943 / 890, batch 8 1548 / 1498, (12) batch 16 4849 / 4749; 8B, batch 1 (4) 2470 / 2461, batch 4 and 12 (3) 2148 / 2125, 2513 / 2474; R = 4, batch 2 (3)
+// 1941 / 1888.
+// Tried: the same ring in LDS, filled by direct-to-LDS loads (64 KiB per workgroup, no registers): 4 - 6 % slower, gate/up pairs of short
+// layers 5.6 -> 9 us.
+// wp, xop, KT, group0, M and tn repeat j.wp, j.xb, j.K / 32, j.group0, j.M and j.tn (the x rows are K elements apart): the
+// kernel hands them over from preloaded kernel arguments or from its list, so that the first weight tiles
+// are requested before the job's descriptor (j) has arrived from memory.
 // WIDE = more than 8 rows: the high and the low parts of the operand are two MFMA operands (rows 0..15 each);
 // else one: lanes 0..7 of a row of 16 carry the high parts of rows 0..7, lanes 8..15 their low parts.
 // Operand columns beyond the rows in use hold whatever their slots hold (finite): a column of the operand only
 // reaches its own column of the result, which nobody reads.
+// COH: the operand is read with device-coherent loads.
 // CHAIN: the job is part of a chained step: other jobs of the same launch read what it writes, so the results go
 // out with device-coherent stores (else: ordinary stores, the launch's end publishes them), and it may be waiting for
-// any of its inputs, so the operand is requested behind the waits (else, unless COH: at once, with the weights).
+// any of its inputs.
 // x_out: where a job with x_copy set leaves its second copy of the new rows, if not null (the chained step hands the
 // caller's buffer over as a kernel argument; else x_copy itself is the place).  t_ready: if not null, thread 0
 // leaves the wall-clock time there at which the job's waits were over.
 // Returns false if a wait gave up (nothing stored, error word raised).
-template <int U, int TN, bool COH, bool WIDE, bool CHAIN>
-__device__ __forceinline__ bool gemv_job(const GemvJob& j, const void* wp, const bf16_t* xop, int KT, int group0, int M, int lb,
-                                         float* smem, unsigned* s_flag, float* x_out, unsigned long long* t_ready) {
-  constexpr bool EARLY_X = !COH && !CHAIN;
+// ------------------------------------------------------------------------------------------------
+#define FUSED_AUX_NT 2   // buffer loads: non-temporal
+
+// the k tiles of a wavefront, in the order it takes them: groups of U tiles, round robin over the wavefronts.  So the workgroup as a
+// whole sweeps its weight range once: measured 3 % faster over a decode step than a contiguous eighth of the
+// range per wavefront (DRAM page locality); tile-wise round robin for one and two tiles per workgroup was slower.
+__device__ __forceinline__ int gemv_steps(int KT, int U, int wave) {
+  return U == 2 ? 2 * (KT / (2 * FUSED_WAVES)) + min(max(KT % (2 * FUSED_WAVES) - 2 * wave, 0), 2)
+                : KT / FUSED_WAVES + (wave < KT % FUSED_WAVES ? 1 : 0);
+}
+__device__ __forceinline__ int gemv_step_tile(int i, int U, int wave) {
+  return U == 2 ? (i >> 1) * (2 * FUSED_WAVES) + 2 * wave + (i & 1) : i * FUSED_WAVES + wave;
+}
+
+#if defined(__HIP_DEVICE_COMPILE__)   // (buffer descriptors are a device type)
+// The product of TN tiles.  wait: what is to happen between the requests for the first weights and those for the operand (false: it gave
+// up); before_x, behind_x: what is to be requested before and behind the operand's first k tiles.  Leaves the wavefront's sums in red.
+// R k tiles (weights and operand) are in flight per wavefront: 8 KiB of weights (single tiles of separate launches, which do not wait, 4
+// KiB: 8 are 1 % slower; single tiles of more than 8 rows, whose operand is twice the weights, 4 KiB as well: 6 make no difference).  Slots are used
+// and requested again by U neighbouring k tiles at a time (one by one: up to 1 % slower).
+// EARLY_X: the operand was complete before the launch and does not wait.
+template <int TN, bool COH, bool WIDE, bool EARLY_X, typename W, typename P, typename F>
+__device__ __forceinline__ bool gemv_product(const __amdgpu_buffer_rsrc_t wr, const __amdgpu_buffer_rsrc_t xr, const char* xbase, unsigned xlane,
+                                             int tile_bytes, int KT, int rot, int wave, int lane, float* red, W&& wait, P&& before_x, F&& behind_x) {
+  constexpr int U = TN <= 2 ? 2 : 1, XP = WIDE ? 2 : 1, R = TN == 1 ? (WIDE || EARLY_X ? 4 : 8) : TN == 2 ? 4 : 2;
+  const int n = gemv_steps(KT, U, wave);
+  auto tile = [&](int i) {
+    const int kt = gemv_step_tile(i, U, wave) + rot;
+    return kt >= KT ? kt - KT : kt;
+  };
+  u32x4_t w[R][TN], x[R][XP];
+  f32x4_t acc[TN];
+#pragma unroll
+  for (int t = 0; t < TN; ++t) acc[t] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+  auto loadx = [&](u32x4_t (&xv)[XP], int kt) {
+#pragma unroll
+    for (int h = 0; h < XP; ++h) {
+      if (COH) {   // operand written by another workgroup of this launch: device-coherent loads, past L1 and the XCD's L2
+        const unsigned long long* p8 = reinterpret_cast<const unsigned long long*>(xbase + (size_t)kt * tile_bytes + (h ? 256 : 0) + xlane);
+        const unsigned long long lo = __hip_atomic_load(p8, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned long long hi = __hip_atomic_load(p8 + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        xv[h] = (u32x4_t){(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+      } else {
+        xv[h] = __builtin_amdgcn_raw_buffer_load_b128(xr, (int)xlane + (h ? 256 : 0), kt * tile_bytes, 0);
+      }
+    }
+  };
+  auto loadw = [&](u32x4_t (&wv)[TN], int kt) {
+#pragma unroll
+    for (int t = 0; t < TN; ++t) wv[t] = __builtin_amdgcn_raw_buffer_load_b128(wr, lane * 16, (t * KT + kt) * 1024, FUSED_AUX_NT);
+  };
+  auto issue = [&](int s, int i, int m) {   // steps i .. i + m - 1 (at most U: neighbouring k tiles) into slots s ..
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (u < m) loadw(w[s + u], tile(i + u));
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (u < m) loadx(x[s + u], tile(i + u));
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto step = [&](int s) {
+#pragma unroll
+    for (int h = 0; h < XP; ++h)
+#pragma unroll
+      for (int t = 0; t < TN; ++t)
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w[s][t]), __builtin_bit_cast(bf16x8_t, x[s][h]), acc[t], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // the first tiles depend on nothing but what the kernel handed over: requested before anything else (without a branch, so that the
+  // compiler's count of what is in flight stays exact: past the last step, or without any, a tile again)
+#pragma unroll
+  for (int s = 0; s < R; ++s) loadw(w[s], n > 0 ? tile(min(s, n - 1)) : 0);
+  __builtin_amdgcn_sched_barrier(0);
+  if (!EARLY_X) {
+    if (!wait()) return false;
+    before_x();
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int s = 0; s < R; ++s) loadx(x[s], n > 0 ? tile(min(s, n - 1)) : 0);
+  __builtin_amdgcn_sched_barrier(0);
+  if (EARLY_X) {
+    if (!wait()) return false;
+    before_x();
+  }
+  behind_x();
+  __builtin_amdgcn_sched_barrier(0);
+  int i = 0;
+  auto round = [&] {
+#pragma unroll
+    for (int s = 0; s < R; s += U) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) step(s + u);
+      issue(s, i + R + s, U);
+    }
+    i += R;
+  };
+  // (the first round by itself: its operands were requested one behind the other, and the compiler's count of what is in flight at the
+  // head of a loop is that of the way in with fewer)
+  if (n >= 2 * R) {
+    round();
+    while (i + 2 * R <= n) round();
+  }
+  const int r = n - i;   // what is left: the ring and less than another ring full
+#pragma unroll
+  for (int s = 0; s < R; s += U)
+    if (s < r) {
+      step(s);
+#pragma unroll
+      for (int u = 1; u < U; ++u)
+        if (s + u < r) step(s + u);
+      if (s + R < r) {
+        if (s + R + U <= r) issue(s, i + R + s, U);
+        else issue(s, i + R + s, 1);
+      }
+    }
+#pragma unroll
+  for (int s = 0; s < R; ++s)
+    if (s + R < r) step(s);
+  // cross-wave sums through LDS: [wave][tile][col in tile][operand column]
+  const int b = lane & 15, q = lane >> 4;
+#pragma unroll
+  for (int t = 0; t < TN; ++t)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) red[((wave * TN + t) * 16 + 4 * q + e) * 17 + b] = acc[t][e];
+  return true;
+}
+#endif
+
+template <int D, bool COH, bool WIDE, bool CHAIN>
+__device__ __forceinline__ bool gemv_job(const GemvJob& j, const void* wp, const bf16_t* xop, int KT, int group0, int M, int tn, int lb,
+                                         int pos, float* smem, unsigned* s_flag, float* x_out, unsigned long long* t_ready) {
+#if defined(__HIP_DEVICE_COMPILE__)
   // A residual job of a chained step needs two producers: its operand's at the start, the old rows' only for its epilogue.  Where the second
   // has not finished when the first has, the product goes ahead and the wait follows it.  One row, or up to 4 of a stream of 4096 columns
   // and more; us per step, before / after: 70B R = 8 (8 layers, batch 2 / 4) 333.3 / 328.6, 337.3 / 334.2, 8B shape (4) 319.5 / 315.0, 333.0 / 330.5, R = 4
@@ -261,118 +388,102 @@ __device__ __forceinline__ bool gemv_job(const GemvJob& j, const void* wp, const
   // layers, a down projection beside the attention side slows that:
   // 1.2B, batch 3 1137 / 1164, batch 4 behind 4000 positions 1674 / 1780, batch 8 1417 / 1513, batch 16 5210 / 5753, R = 4, batch 12 1631 / 1724.
   constexpr bool LATE = CHAIN && !WIDE;
-  constexpr int WAVES = FUSED_WAVES;
-  constexpr int XP = WIDE ? 2 : 1;   // operand registers per k tile
   const int grp = group0 + lb;
   const int tid = opaque_tid();
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int b = lane & 15, q = lane >> 4;
-  const int nt0 = grp * TN;
-  // The wavefronts take groups of U k tiles round robin, so that the workgroup as a whole sweeps its weight range
-  // once, 8 U tiles (16 KiB) at a time: measured 3 % faster over a decode step than a contiguous eighth of the
-  // range per wavefront (DRAM page locality); tile-wise round robin and 2 U tiles per turn were slower.
-  constexpr int KB = WAVES * U, KA = 2 * WAVES * U;   // tile distance to the second register buffer / to the next turn
-  const int kt0 = wave * U;
-  const int kt1 = KT;
-
-  f32x4_t acc[TN];
-#pragma unroll
-  for (int t = 0; t < TN; ++t) acc[t] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
-  const u32x4_t* wptr = reinterpret_cast<const u32x4_t*>(wp) + ((size_t)nt0 * KT) * 64 + lane;
-  // operand slot of this lane (decode_fused.h): WIDE: slot b = row b of the high parts, the low parts 16 slots
-  // further; else the k tile has S = 2, 4, 8 or 16 slots, the first half high parts, the second half low parts:
-  // lanes 0..7 of a row of 16 take the high slots (repeating them when there are fewer than 8), lanes 8..15 the low ones
-  const int S = WIDE ? 32 : fused_slots(M);
-  const int slot = WIDE ? b : ((b & ((S >> 1) - 1)) + ((b & 8) ? (S >> 1) : 0));
-  const int tile_stride = S * 32;                      // elements per k tile
-  const bf16_t* xbp = xop + (q * S + slot) * 8;
-  constexpr int low_off = 16 * 8;                      // WIDE: the low parts' slots
-  u32x4_t wa[TN][U], wb[TN][U], xa[U][XP], xb[U][XP];
+  const int nt0 = grp * tn;
+  float* const ssq = smem + FUSED_WAVES * tn * 16 * 17;   // WAVES * 16 floats
   // Where in its K range a workgroup starts: rotated by a number of k tiles that depends on its tile group, so that
   // the workgroups that stream side by side are not all at the same offset of their tiles, which lie a power of two
   // apart, at the same time (memory channels; headline shape: 3.22 -> 3.19 ms per step chained, 3.43 -> 3.38 as separate
   // launches).  A group of four tiles shares a rotation: a tile's sum has the same order whether its workgroup takes
   // one tile or two (four-tile workgroups split the k tiles over their wavefronts differently anyway).
   const int rot = ((nt0 >> 2) * FUSED_K_ROTATE) % KT;
-  auto rotated = [&](int k) { return k + rot >= KT ? k + rot - KT : k + rot; };
-  auto loadw = [&](u32x4_t (&wv)[TN][U], int kt) {
+  // operands through buffer descriptors: scalar bases and offsets, and 32 bits per lane that serve every load
+  const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<char*>(reinterpret_cast<const char*>(wp)) + (size_t)nt0 * KT * 1024, 0, -1, 0x00020000);
+  const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(xop), 0, -1, 0x00020000);
+  // operand slot of this lane (decode_fused.h): WIDE: slot b = row b of the high parts, the low parts 16 slots
+  // further; else the k tile has S = 2, 4, 8 or 16 slots, the first half high parts, the second half low parts:
+  // lanes 0..7 of a row of 16 take the high slots (repeating them when there are fewer than 8), lanes 8..15 the low ones
+  const int S = WIDE ? 32 : fused_slots(M);
+  const int slot = WIDE ? b : ((b & ((S >> 1) - 1)) + ((b & 8) ? (S >> 1) : 0));
+  const unsigned xlane = (unsigned)(q * S + slot) * 16u;
+  // The epilogue's own operands do not depend on the product: they are requested before the weight stream, so their memory latency is
+  // hidden behind it instead of trailing the last tile; those that no other job of the launch writes (peers, gains, rotary factors)
+  // before the wait.  (a thread owns output elements tid, tid + 512: one for one or two tiles per workgroup, two for three and four)
+  constexpr int PRE_PEERS = 8, E_RES = 2;
+  float pre_old[E_RES], pre_cos = 0.f, pre_sin = 0.f;
+  uint16_t pre_peer[E_RES][PRE_PEERS], pre_ga[E_RES], pre_gb[E_RES];
+  const int pair_shift = tn == 1 ? 3 : tn == 2 ? 4 : 5;   // rotary epilogue: 8 tn column pairs per row (tn is 1, 2 or 4)
+  const int qkv_row = tid >> pair_shift, qkv_pair = tid & ((1 << pair_shift) - 1);
+  auto outside = [&] {
+    if (j.epi == EPI_RESIDUAL) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int ktc = rotated(min(kt + u, kt1 - 1));
+      for (int e = 0; e < E_RES; ++e) {
+        const int idx = tid + e * FUSED_THREADS;
+        pre_ga[e] = pre_gb[e] = 0x3F80;   // 1.0
+        if (e * 2 < tn && idx < tn * 256) {
+          const int t = idx >> 8, row = min((idx >> 4) & 15, M - 1), col = (nt0 + t) * 16 + (idx & 15);
+          if (j.xop_a) pre_ga[e] = j.gain_a[col];
+          if (j.xop_b) pre_gb[e] = j.gain_b[col];
+          if (j.n_peers > 0) {
 #pragma unroll
-      for (int t = 0; t < TN; ++t) wv[t][u] = __builtin_nontemporal_load(wptr + ((size_t)t * KT + ktc) * 64);
-    }
-  };
-  auto loadx = [&](u32x4_t (&xv)[U][XP], int kt) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int ktc = rotated(min(kt + u, kt1 - 1));
-#pragma unroll
-      for (int h = 0; h < XP; ++h) {
-        const bf16_t* src = xbp + (size_t)ktc * tile_stride + (h ? low_off : 0);
-        if (COH) {   // operand written by another workgroup of this launch: device-coherent loads, past L1 and the XCD's L2
-          const unsigned long long* p8 = reinterpret_cast<const unsigned long long*>(src);
-          const unsigned long long lo = __hip_atomic_load(p8, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          const unsigned long long hi = __hip_atomic_load(p8 + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          xv[u][h] = (u32x4_t){(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
-        } else {
-          xv[u][h] = *reinterpret_cast<const u32x4_t*>(src);
+            for (int p = 0; p < PRE_PEERS; ++p)
+              pre_peer[e][p] = j.peers[min(p, j.n_peers - 1) * j.peer_stride + (size_t)row * j.N + col];
+          }
         }
       }
+    } else if (j.epi == EPI_QKV_ROPE) {
+      if (qkv_row < 16) {
+        const int jj = ((nt0 * 16 + 2 * qkv_pair) % D) >> 1;
+        pre_cos = j.cos_tab[(size_t)pos * (D >> 1) + jj];
+        pre_sin = j.sin_tab[(size_t)pos * (D >> 1) + jj];
+      }
     }
   };
-  auto load = [&](u32x4_t (&wv)[TN][U], u32x4_t (&xv)[U][XP], int kt) {
-    loadw(wv, kt);
-    loadx(xv, kt);
-  };
-  // the first tiles depend on nothing but the (preloaded) arguments: requested before anything else; the operand
-  // of a job that waits for its producer only behind the wait
-  // both register buffers
-  if (kt0 < kt1) loadw(wa, kt0);
-  if (kt0 + KB < kt1) loadw(wb, kt0 + KB);
-  if (EARLY_X && kt0 < kt1) loadx(xa, kt0);
-  if (EARLY_X && kt0 + KB < kt1) loadx(xb, kt0 + KB);
-  __builtin_amdgcn_sched_barrier(0);
-
   bool late = false;   // (uniform) the old rows' producer had not finished when the operand's had: they are waited for behind the product
-  if (j.wait_on) {
-    // What the job reads comes from other jobs of this launch.  A workgroup only waits for workgroups that come
-    // before it in the launch's order and that wait, in turn, only for earlier ones: the words always arrive.  The
-    // wait is bounded all the same, so that the kernel ends whatever happens; a workgroup whose wait gives up stores
-    // nothing and raises the error word, which the host reads at the library's next call.
-    if (wave == 0) {
-      const unsigned arrived = sync_wait(j.wait_on, j.wait_flags, j.wait_bias, j.wait_on2, j.wait_flags2, j.wait_bias2, j.wait_spins, lane,
-                                         LATE && (M == 1 || (M <= 4 && j.N >= 4096)));
-      if (lane == 0) {
-        *s_flag = arrived;
-        if (!arrived && j.err_word) __hip_atomic_store(j.err_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  auto wait = [&]() -> bool {
+    if (CHAIN) outside();
+    if (j.wait_on) {
+      // What the job reads comes from other jobs of this launch.  A workgroup only waits for workgroups that come
+      // before it in the launch's order and that wait, in turn, only for earlier ones: the words always arrive.  The
+      // wait is bounded all the same, so that the kernel ends whatever happens; a workgroup whose wait gives up stores
+      // nothing and raises the error word, which the host reads at the library's next call.
+      if (wave == 0) {
+        const unsigned arrived = sync_wait(j.wait_on, j.wait_flags, j.wait_bias, j.wait_on2, j.wait_flags2, j.wait_bias2, j.wait_spins, lane,
+                                           LATE && (M == 1 || (M <= 4 && j.N >= 4096)));
+        if (lane == 0) {
+          *s_flag = arrived;
+          if (!arrived && j.err_word) __hip_atomic_store(j.err_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
       }
+      __syncthreads();   // (workgroup-scope ordering.  No cache invalidation: the attention output is read with
+                         // device-coherent loads, and what a projection of the same launch has written is in no cache
+                         // of this XCD yet, having been read by nobody before; an agent-scope acquire per workgroup
+                         // would flush the L2 under the weight streams that run beside)
+      const unsigned arrived = (unsigned)__builtin_amdgcn_readfirstlane((int)*s_flag);
+      if (arrived == 0u) return false;
+      late = LATE && arrived == 2u;
     }
-    __syncthreads();   // (workgroup-scope ordering.  No cache invalidation: the attention output is read with
-                       // device-coherent loads, and what a projection of the same launch has written is in no cache
-                       // of this XCD yet, having been read by nobody before; an agent-scope acquire per workgroup
-                       // would flush the L2 under the weight streams that run beside)
-    const unsigned arrived = (unsigned)__builtin_amdgcn_readfirstlane((int)*s_flag);
-    if (arrived == 0u) return false;
-    late = LATE && arrived == 2u;
-  }
 
-  if (j.t_ready) {
-    // emulated collective: the stream this job reads counts as reduced delay_ticks after the time its producer
-    // left; a wait on the clock alone (it ends whatever other workgroups do), bounded all the same
-    if (tid == 0) {
-      const unsigned long long t1 = __hip_atomic_load(j.t_ready, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + j.delay_ticks;
-      for (int spin = 0; spin < (1 << 20); ++spin) {
-        if (wall_clock64() >= t1) break;
-        __builtin_amdgcn_s_sleep(FUSED_POLL_SLEEP);
+    if (j.t_ready) {
+      // emulated collective: the stream this job reads counts as reduced delay_ticks after the time its producer
+      // left; a wait on the clock alone (it ends whatever other workgroups do), bounded all the same
+      if (tid == 0) {
+        const unsigned long long t1 = __hip_atomic_load(j.t_ready, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + j.delay_ticks;
+        for (int spin = 0; spin < (1 << 20); ++spin) {
+          if (wall_clock64() >= t1) break;
+          __builtin_amdgcn_s_sleep(FUSED_POLL_SLEEP);
+        }
       }
+      __syncthreads();
     }
-    __syncthreads();
-  }
 
-  if (t_ready && tid == 0) *t_ready = wall_clock64();
-  if (!EARLY_X && kt0 < kt1) loadx(xa, kt0);
-  if (!EARLY_X && kt0 + KB < kt1) loadx(xb, kt0 + KB);
+    if (t_ready && tid == 0) *t_ready = wall_clock64();
+    return true;
+  };
   // results: coherent stores in a chained step (a split value's two halves as 32-bit stores of a column pair, all
   // lanes of the wavefront taking part), ordinary stores else
   auto store_f32 = [&](float* p, float v) {
@@ -397,112 +508,59 @@ __device__ __forceinline__ bool gemv_job(const GemvJob& j, const void* wp, const
       *lo_at = (bf16_t)lo;
     }
   };
-  auto fma = [&](const u32x4_t (&wv)[TN][U], const u32x4_t (&xv)[U][XP], int kt) {
+  // normed: this thread's share of the rows' sums of squares, tile tid of the stream, four rows per register quad; requested before the
+  // operand and added up while that is on its way, so that they hold no registers during the product
+  constexpr int QUADS = WIDE ? 4 : 2;
+  float4 pre_ss[QUADS];
+  const int n_st = KT * 2;   // 16-column tiles of the stream the operand was made from
+  auto before_x = [&] {
+    if (j.normed) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const bool ok = kt + u < kt1;
-#pragma unroll
-      for (int h = 0; h < XP; ++h) {
-        const u32x4_t xz = ok ? xv[u][h] : (u32x4_t){0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int t = 0; t < TN; ++t)
-          acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wv[t][u]),
-                                                          __builtin_bit_cast(bf16x8_t, xz), acc[t], 0, 0, 0);
+      for (int rq = 0; rq < QUADS; ++rq) {
+        pre_ss[rq] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (rq * 4 < M) pre_ss[rq] = *reinterpret_cast<const float4*>(j.ssq + (size_t)min(tid, n_st - 1) * 16 + rq * 4);
       }
     }
   };
-  // The epilogue's own operands do not depend on the product: they are requested now, before the
-  // weight stream, so their memory latency is hidden behind it instead of trailing the last tile.
-  // (a thread owns output elements tid, tid + 512, ...: one for one or two tiles per workgroup, two for three)
-  constexpr int PRE_PEERS = 8;
-  constexpr int E_RES = (TN * 256 + FUSED_THREADS - 1) / FUSED_THREADS;   // residual epilogue: elements per thread
-  float pre_old[E_RES], pre_cos = 0.f, pre_sin = 0.f;
-  uint16_t pre_peer[E_RES][PRE_PEERS], pre_ga[E_RES], pre_gb[E_RES];
-  int pre_pos = 0;
-  // normed: this thread's share of the rows' sums of squares, tile tid of the stream, four rows per register quad
-  float4 pre_ss[4];
-  const int n_st = KT * 2;   // 16-column tiles of the stream the operand was made from
-  if (j.normed) {
+  auto behind_x = [&] {
+    if (!CHAIN) outside();
+    if (j.epi == EPI_RESIDUAL) {
 #pragma unroll
-    for (int rq = 0; rq < 4; ++rq) {
-      pre_ss[rq] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (rq * 4 < M) pre_ss[rq] = *reinterpret_cast<const float4*>(j.ssq + (size_t)min(tid, n_st - 1) * 16 + rq * 4);
+      for (int e = 0; e < E_RES; ++e) {
+        const int idx = tid + e * FUSED_THREADS;
+        pre_old[e] = 0.f;
+        if (e * 2 < tn && idx < tn * 256 && !late)
+          pre_old[e] = j.x_old[(size_t)min((idx >> 4) & 15, M - 1) * j.N + (nt0 + (idx >> 8)) * 16 + (idx & 15)];
+      }
     }
-  }
-  if (j.epi == EPI_RESIDUAL) {
+    if (j.normed) {
+      // the rows' sums of squares: this thread's tile (and, for streams of more than 512 tiles, the tiles beyond),
+      // then the wavefront, then (below) the eight wavefronts, always in this order
 #pragma unroll
-    for (int e = 0; e < E_RES; ++e) {
-      const int idx = tid + e * FUSED_THREADS;
-      pre_old[e] = 0.f;
-      pre_ga[e] = pre_gb[e] = 0x3F80;   // 1.0
-      if (idx < TN * 256) {
-        const int t = idx >> 8, row = min((idx >> 4) & 15, j.M - 1), col = (nt0 + t) * 16 + (idx & 15);
-        if (!late) pre_old[e] = j.x_old[(size_t)row * j.N + col];
-        if (j.xop_a) pre_ga[e] = j.gain_a[col];
-        if (j.xop_b) pre_gb[e] = j.gain_b[col];
-        if (j.n_peers > 0) {
-#pragma unroll
-          for (int p = 0; p < PRE_PEERS; ++p)
-            pre_peer[e][p] = j.peers[min(p, j.n_peers - 1) * j.peer_stride + (size_t)row * j.N + col];
+      for (int rq = 0; rq < QUADS; ++rq) {
+        if (rq * 4 >= M) break;
+        float4 v = tid < n_st ? pre_ss[rq] : make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int tile = tid + FUSED_THREADS; tile < n_st; tile += FUSED_THREADS) {
+          const float4 t4 = *reinterpret_cast<const float4*>(j.ssq + (size_t)tile * 16 + rq * 4);
+          v.x += t4.x; v.y += t4.y; v.z += t4.z; v.w += t4.w;
+        }
+        v.x = wave_sum_dpp(v.x); v.y = wave_sum_dpp(v.y); v.z = wave_sum_dpp(v.z); v.w = wave_sum_dpp(v.w);
+        if (lane == 0) {
+          float* dst = ssq + wave * 16 + rq * 4;
+          dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
         }
       }
     }
-  } else if (j.epi == EPI_QKV_ROPE) {
-    pre_pos = *j.pos_dev;
-    if (tid < 16 * TN * 8) {
-      const int pr = tid % (TN * 8);
-      const int jj = ((grp * (TN * 16) + 2 * pr) % j.d) >> 1;
-      pre_cos = j.cos_tab[(size_t)pre_pos * (j.d >> 1) + jj];
-      pre_sin = j.sin_tab[(size_t)pre_pos * (j.d >> 1) + jj];
-    }
-  }
-
-  if (kt0 < kt1) {
-    // buffer a holds the tiles of kt, buffer b those of kt + KB (where the range reaches that far): each is
-    // requested again, a turn ahead, as soon as it has been used.  Nothing is requested beyond the range: a load
-    // left in flight at the end (even one clamped onto the last tile, which the caches serve) is waited for by
-    // whatever the epilogue reads first, a memory round trip at the end of every workgroup.
-    int kt = kt0;
-    for (; kt + KA < kt1; kt += KA) {
-      fma(wa, xa, kt);
-      __builtin_amdgcn_sched_barrier(0);
-      load(wa, xa, kt + KA);
-      __builtin_amdgcn_sched_barrier(0);
-      fma(wb, xb, kt + KB);
-      __builtin_amdgcn_sched_barrier(0);
-      if (kt + KA + KB < kt1) load(wb, xb, kt + KA + KB);   // (uniform over the wavefront)
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    fma(wa, xa, kt);
-    __builtin_amdgcn_sched_barrier(0);
-    if (kt + KB < kt1) fma(wb, xb, kt + KB);
-  }
-
-  // cross-wave sums through LDS: red[wave][tile][col in tile][operand column], ssq[wave][row]
-  float* red = smem;                            // WAVES * TN * 16 * 17 floats
-  float* ssq = smem + WAVES * TN * 16 * 17;     // WAVES * 16 floats
-#pragma unroll
-  for (int t = 0; t < TN; ++t)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) red[((wave * TN + t) * 16 + 4 * q + r) * 17 + b] = acc[t][r];
-  if (j.normed) {
-    // the rows' sums of squares: this thread's tile (and, for streams of more than 512 tiles, the tiles beyond),
-    // then the wavefront, then (below) the eight wavefronts, always in this order
-#pragma unroll
-    for (int rq = 0; rq < 4; ++rq) {
-      if (rq * 4 >= M) break;
-      float4 v = tid < n_st ? pre_ss[rq] : make_float4(0.f, 0.f, 0.f, 0.f);
-      for (int tile = tid + FUSED_THREADS; tile < n_st; tile += FUSED_THREADS) {
-        const float4 t4 = *reinterpret_cast<const float4*>(j.ssq + (size_t)tile * 16 + rq * 4);
-        v.x += t4.x; v.y += t4.y; v.z += t4.z; v.w += t4.w;
-      }
-      v.x = wave_sum_dpp(v.x); v.y = wave_sum_dpp(v.y); v.z = wave_sum_dpp(v.z); v.w = wave_sum_dpp(v.w);
-      if (lane == 0) {
-        float* dst = ssq + wave * 16 + rq * 4;
-        dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
-      }
-    }
-  }
+  };
+  const char* const xbase = reinterpret_cast<const char*>(xop);
+  bool arrived;
+#define GEMV_PRODUCT(TN_) arrived = gemv_product<TN_, COH, WIDE, !COH && !CHAIN>(wr, xr, xbase, xlane, S * 64, KT, rot, wave, lane, smem, wait, before_x, behind_x)
+  if (tn == 1) GEMV_PRODUCT(1);
+  else if (tn == 2) GEMV_PRODUCT(2);
+  else if (tn == 3) GEMV_PRODUCT(3);
+  else GEMV_PRODUCT(4);
+#undef GEMV_PRODUCT
+  if (!arrived) return false;
   if (LATE && late && wave == 0) {
     // (its result has a word of its own: a wavefront that lags may still have to read the first wait's)
     const unsigned arrived = sync_wait(j.wait_on2, j.wait_flags2, j.wait_bias2, nullptr, 0u, 0u, j.wait_spins, lane, false);
@@ -518,20 +576,20 @@ __device__ __forceinline__ bool gemv_job(const GemvJob& j, const void* wp, const
 #pragma unroll
     for (int e = 0; e < E_RES; ++e) {
       const int idx = tid + e * FUSED_THREADS;
-      if (idx < TN * 256) pre_old[e] = j.x_old[(size_t)min((idx >> 4) & 15, j.M - 1) * j.N + (nt0 + (idx >> 8)) * 16 + (idx & 15)];
+      if (e * 2 < tn && idx < tn * 256) pre_old[e] = j.x_old[(size_t)min((idx >> 4) & 15, M - 1) * j.N + (nt0 + (idx >> 8)) * 16 + (idx & 15)];
     }
   }
   auto out_of = [&](int t, int col16, int row) {  // finished output element: wave sums (high + low half), then 1/rms of the row
     float v = 0.f;
 #pragma unroll
-    for (int w = 0; w < WAVES; ++w) {
-      const float* r = red + ((w * TN + t) * 16 + col16) * 17;
+    for (int w = 0; w < FUSED_WAVES; ++w) {
+      const float* r = smem + ((w * tn + t) * 16 + col16) * 17;
       v += WIDE ? r[row] : r[row] + r[row + 8];
     }
     if (j.normed) {
       float s = 0.f;
 #pragma unroll
-      for (int w = 0; w < WAVES; ++w) s += ssq[w * 16 + row];
+      for (int w = 0; w < FUSED_WAVES; ++w) s += ssq[w * 16 + row];
       v *= 1.0f / sqrtf(s / (float)j.K + j.eps);
     }
     return v;
@@ -540,10 +598,10 @@ __device__ __forceinline__ bool gemv_job(const GemvJob& j, const void* wp, const
   if (j.epi == EPI_SWIGLU) {
     // tile columns 0..7 = gate columns 8nt..8nt+7, columns 8..15 = the matching up columns
     const int I = j.N >> 1;
-    if (tid < TN * 128) {   // (whole wavefronts: the lanes of a column pair store together)
+    if (tid < tn * 128) {   // (whole wavefronts: the lanes of a column pair store together)
       const int t = tid >> 7, row = (tid >> 3) & 15, c8 = tid & 7;
       const int col = (nt0 + t) * 8 + c8;
-      const bool ok = row < j.M && col < I;   // (I is even: a pair is in or out as a whole)
+      const bool ok = row < M && col < I;   // (I is even: a pair is in or out as a whole)
       float v = 0.f;
       if (ok) {
         const float g = out_of(t, c8, row), u = out_of(t, c8 + 8, row);
@@ -560,10 +618,10 @@ __device__ __forceinline__ bool gemv_job(const GemvJob& j, const void* wp, const
 #pragma unroll
     for (int e = 0; e < E_RES; ++e) {
       const int idx = tid + e * FUSED_THREADS;
-      if (idx >= TN * 256) break;   // (uniform over a wavefront: TN * 256 is a multiple of 64)
+      if (e * 2 >= tn || idx >= tn * 256) break;   // (uniform over a wavefront: tn * 256 is a multiple of 64)
       const int t = idx >> 8, row = (idx >> 4) & 15, col16 = idx & 15;
       const int col = (nt0 + t) * 16 + col16;
-      const bool ok = row < j.M;
+      const bool ok = row < M;
       float v = 0.f;
       if (ok) {
         v = pre_old[e] + out_of(t, col16, row);
@@ -589,50 +647,46 @@ __device__ __forceinline__ bool gemv_job(const GemvJob& j, const void* wp, const
     return true;
   }
 
-  // EPI_QKV_ROPE: TN*8 adjacent pairs in this workgroup's columns, all inside one head
-  if (tid < 16 * TN * 8) {
-    const int row = tid / (TN * 8), pr = tid % (TN * 8);
-    if (row < j.M) {
-      const int col = grp * (TN * 16) + 2 * pr;
-      const int c16 = (2 * pr) & 15, t = (2 * pr) >> 4;
-      float e = out_of(t, c16, row), o = out_of(t, c16 + 1, row);
-      const int pos = pre_pos;
-      const int head = col / j.d, jj = (col % j.d) >> 1;
-      if (head < j.nq + j.nkv) {
-        const float c = pre_cos, sn = pre_sin;
-        const float re = e * c - o * sn, ro = e * sn + o * c;
-        e = re;
-        o = ro;
-      }
-      if (head < j.nq) {
-        uint32_t eh, el, oh, ol;
-        split_bf16(e, eh, el);
-        split_bf16(o, oh, ol);
-        const size_t at = (size_t)row * j.nq * j.d + col;
-        store_u32(reinterpret_cast<uint32_t*>(j.q_out + at), eh | (oh << 16));
-        store_u32(reinterpret_cast<uint32_t*>(j.q_out + (size_t)FUSED_LOW_ROW * j.nq * j.d + at), el | (ol << 16));
-      } else if (head < j.nq + j.nkv) {
-        const int kvh = head - j.nq;
-        store_u32(reinterpret_cast<uint32_t*>(j.cache_k + (((size_t)row * j.nkv + kvh) * j.max_seq + pos) * j.d + 2 * jj),
-                  pack_bf16(e, o));
-      } else {
-        const int kvh = head - j.nq - j.nkv;
-        bf16_t* vt = j.cache_v + (((size_t)row * j.nkv + kvh) * j.d + 2 * jj) * j.max_seq + pos;
-        store_b16(vt, f32_to_bf16(e));
-        store_b16(vt + j.max_seq, f32_to_bf16(o));
-      }
+  // EPI_QKV_ROPE: 8 tn adjacent pairs in this workgroup's columns, each tile inside one head
+  const int col = nt0 * 16 + 2 * qkv_pair, head = col / D;
+  if (qkv_row < M) {
+    const int row = qkv_row;
+    const int c16 = (2 * qkv_pair) & 15, t = qkv_pair >> 3, jj = (col % D) >> 1;
+    float e = out_of(t, c16, row), o = out_of(t, c16 + 1, row);
+    if (head < j.nq + j.nkv) {
+      const float re = e * pre_cos - o * pre_sin, ro = e * pre_sin + o * pre_cos;
+      e = re;
+      o = ro;
+    }
+    if (head < j.nq) {
+      uint32_t eh, el, oh, ol;
+      split_bf16(e, eh, el);
+      split_bf16(o, oh, ol);
+      const size_t at = (size_t)row * j.nq * D + col;
+      store_u32(reinterpret_cast<uint32_t*>(j.q_out + at), eh | (oh << 16));
+      store_u32(reinterpret_cast<uint32_t*>(j.q_out + (size_t)FUSED_LOW_ROW * j.nq * D + at), el | (ol << 16));
+    } else if (head < j.nq + j.nkv) {
+      const int kvh = head - j.nq;
+      store_u32(reinterpret_cast<uint32_t*>(j.cache_k + (((size_t)row * j.nkv + kvh) * j.max_seq + pos) * D + 2 * jj),
+                pack_bf16(e, o));
+    } else {
+      const int kvh = head - j.nq - j.nkv;
+      bf16_t* vt = j.cache_v + (((size_t)row * j.nkv + kvh) * D + 2 * jj) * j.max_seq + pos;
+      store_b16(vt, f32_to_bf16(e));
+      store_b16(vt + j.max_seq, f32_to_bf16(o));
     }
   }
   if (CHAIN) gemv_signal_done(j, lb);
   // the last position of a block: the block behind it is cleared for the next step (see clear_block; nothing of this step reads it)
-  if (tid < 16 * TN * 8 && tid / (TN * 8) < j.M && pre_pos % CACHE_BLOCK == CACHE_BLOCK - 1) {
-    const int row = tid / (TN * 8), col = grp * (TN * 16) + 2 * (tid % (TN * 8)), kvh = col / j.d - j.nq - j.nkv;
+  if (qkv_row < M && pos % CACHE_BLOCK == CACHE_BLOCK - 1) {
+    const int kvh = head - j.nq - j.nkv;
     if (kvh >= 0) {
-      bf16_t* const next = j.cache_v + (((size_t)row * j.nkv + kvh) * j.d + col % j.d) * j.max_seq + pre_pos + 1;
-      clear_block(next, pre_pos + 1, j.max_seq);
-      clear_block(next + j.max_seq, pre_pos + 1, j.max_seq);
+      bf16_t* const next = j.cache_v + (((size_t)qkv_row * j.nkv + kvh) * D + col % D) * j.max_seq + pos + 1;
+      clear_block(next, pos + 1, j.max_seq);
+      clear_block(next + j.max_seq, pos + 1, j.max_seq);
     }
   }
+#endif
   return true;
 }
 
@@ -662,25 +716,11 @@ __device__ __forceinline__ void attn_signal_done(const AttnJob& a, int ordinal) 
 }
 
 // Returns false if the job's wait gave up (nothing stored, error word raised).
-template <int D, int G>
-__device__ __forceinline__ bool attn_job(const AttnJob& a, int lb, float* smem, unsigned* s_flag, unsigned long long* t_ready) {
+template <int D, int G, bool CHAIN>
+__device__ __forceinline__ bool attn_job(const AttnJob& a, int lb, int chain_pos, float* smem, unsigned* s_flag, unsigned long long* t_ready) {
   constexpr int DS = D / 32, DT = D / 16;
   const int tid0 = opaque_tid();
   const int wave = __builtin_amdgcn_readfirstlane(tid0 >> 6);
-  if (a.wait_on) {
-    // chained step: q and the new cache rows come from the QKV projection of the same launch (see gemv_job)
-    if (wave == 0) {
-      const unsigned arrived = sync_wait(a.wait_on, a.wait_flags, a.wait_bias, nullptr, 0u, 0u, a.wait_spins, tid0 & 63, false);
-      if (tid0 == 0) {
-        *s_flag = arrived;
-        if (!arrived && a.err_word) __hip_atomic_store(a.err_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-      }
-    }
-    __syncthreads();
-    if (*s_flag == 0u) return false;
-    __syncthreads();   // (s_flag is written again below)
-  }
-  if (t_ready && tid0 == 0) *t_ready = wall_clock64();
   const int b = tid0 & 15, q = (tid0 & 63) >> 4;   // (valid up to the end of the key loop: see below)
   const int sp = lb % a.n_splits, kvh = (lb / a.n_splits) % a.nkv, bi = lb / (a.n_splits * a.nkv);
   const int pbeg = sp * a.split_len;
@@ -703,11 +743,28 @@ __device__ __forceinline__ bool attn_job(const AttnJob& a, int lb, float* smem, 
       vreg[dt] = make_uint4(lo.x, lo.y, hi.x, hi.y);
     }
   };
-  // The wave's first key block and the queries are requested before the position is known (one memory round
-  // trip instead of two; a block beyond the new token is masked or never used).
+  // The wave's first key block is requested before anything is waited for.  Chained step: where all of it lies in cache lines that the QKV
+  // projection of this launch does not write (the new position's V elements share a line with the 64 positions around it, and a line read too
+  // early would be found in this XCD's L2 afterwards, without them).  Separate launches: before the position is known (one
+  // memory round trip instead of two; a block beyond the new token is masked or never used).
   const int kb0 = pbeg + 32 * wave;
-  const bool early = kb0 + 32 <= a.max_seq;
+  const bool early = CHAIN ? kb0 + 32 <= (chain_pos & ~(CACHE_BLOCK - 1)) : kb0 + 32 <= a.max_seq;
   if (early) load_kv(kb0);
+  if (CHAIN && a.wait_on) {
+    __builtin_amdgcn_sched_barrier(0);
+    // chained step: q and the new cache rows come from the QKV projection of the same launch (see gemv_job)
+    if (wave == FUSED_WAVES - 1) {
+      const unsigned arrived = sync_wait(a.wait_on, a.wait_flags, a.wait_bias, nullptr, 0u, 0u, a.wait_spins, tid0 & 63, false);
+      if ((tid0 & 63) == 0) {
+        *s_flag = arrived;
+        if (!arrived && a.err_word) __hip_atomic_store(a.err_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      }
+    }
+    __syncthreads();
+    if (*s_flag == 0u) return false;
+    __syncthreads();   // (s_flag is written again below)
+  }
+  if (t_ready && tid0 == 0) *t_ready = wall_clock64();
   const uint4 zero4 = make_uint4(0, 0, 0, 0);
   static_assert(G <= 8, "high and low parts of the heads of a kv head share one 16-column operand");
   const int hsel = b & 7;             // head of this lane's operand column
@@ -721,7 +778,7 @@ __device__ __forceinline__ bool attn_job(const AttnJob& a, int lb, float* smem, 
       qreg[s] = hsel < G ? v : zero4;
     }
   }
-  const int n_pos = *a.pos_dev + 1;
+  const int n_pos = (CHAIN ? chain_pos : *a.pos_dev) + 1;
   if (pbeg >= n_pos) return true;  // nothing visible in this split: the workgroup leaves, no ticket taken
   const int pend = min(n_pos, pbeg + a.split_len);
   f32x4_t oacc[DT];
@@ -942,7 +999,7 @@ __global__ __launch_bounds__(FUSED_THREADS, 4) void fused_decode_kernel(const vo
   const kernarg_ptr_t ka = (kernarg_ptr_t)__builtin_amdgcn_kernarg_segment_ptr();
   if ((kb & FUSED_KIND_MASK) == (unsigned)JOB_ATTN) {
     const AttnJob& aj = *(const AttnJob*)(ka + offsetof(FusedKernelParams, fa) + offsetof(FusedArgs, a));
-    (void)attn_job<D, G>(aj, lb, smem, s_flag, nullptr);
+    (void)attn_job<D, G, false>(aj, lb, 0, smem, s_flag, nullptr);
   } else {
     const GemvJob& j = *(const GemvJob*)(ka + offsetof(FusedKernelParams, fa) + offsetof(FusedArgs, g) + (size_t)job * sizeof(GemvJob));
     const unsigned slot = kb >> FUSED_KIND_SLOT_SHIFT;   // which preloaded pointer pair: 0, 1, or 3 = none
@@ -956,24 +1013,14 @@ __global__ __launch_bounds__(FUSED_THREADS, 4) void fused_decode_kernel(const vo
     // more than 8 rows: high and low operand parts are two MFMA operands (else they share one)
     // (the one wait of these launches is for the attention output, read with coherent loads; every other operand
     // was complete before the launch: requested at once)
-#define FUSED_GEMV(U_, TN_, COH_)                                                                                  \
-  do {                                                                                                             \
-    if (M > 8) (void)gemv_job<U_, TN_, COH_, true, false>(j, wp, xop, KT, group0, M, lb, smem, s_flag, nullptr, nullptr);  \
-    else (void)gemv_job<U_, TN_, COH_, false, false>(j, wp, xop, KT, group0, M, lb, smem, s_flag, nullptr, nullptr);       \
+    const int pos = j.epi == EPI_QKV_ROPE ? *j.pos_dev : 0;
+#define FUSED_GEMV(COH_)                                                                                                          \
+  do {                                                                                                                            \
+    if (M > 8) (void)gemv_job<D, COH_, true, false>(j, wp, xop, KT, group0, M, (int)tn, lb, pos, smem, s_flag, nullptr, nullptr);  \
+    else (void)gemv_job<D, COH_, false, false>(j, wp, xop, KT, group0, M, (int)tn, lb, pos, smem, s_flag, nullptr, nullptr);       \
   } while (0)
-    if (kb & FUSED_KIND_WAITS) {
-      if (tn == 4) FUSED_GEMV(1, 4, true);
-      else if (tn == 2) FUSED_GEMV(FUSED_U2, 2, true);
-      else FUSED_GEMV(FUSED_U, 1, true);
-    } else if (tn == 4) {
-      FUSED_GEMV(1, 4, false);
-    } else if (tn == 3) {
-      FUSED_GEMV(1, 3, false);
-    } else if (tn == 2) {
-      FUSED_GEMV(FUSED_U2, 2, false);
-    } else {
-      FUSED_GEMV(FUSED_U, 1, false);
-    }
+    if (kb & FUSED_KIND_WAITS) FUSED_GEMV(true);
+    else FUSED_GEMV(false);
 #undef FUSED_GEMV
   }
 }
@@ -994,16 +1041,16 @@ __global__ __launch_bounds__(FUSED_THREADS, 4) void fused_decode_kernel(const vo
 // A slot's item list is read in chunks of 32 items into LDS; an item carries what the first requests need.
 // ------------------------------------------------------------------------------------------------
 #define FUSED_CHAIN_CHUNK 32
-#define FUSED_KIND_COH 32u
 static_assert(sizeof(StepItem) == 32, "the kernel reads an item as two 16-byte words");
 template <int D, int G>
 __global__ __launch_bounds__(FUSED_THREADS, 4) void fused_chain_kernel(const StepItem* __restrict__ items, int n_items,
                                                                       const GemvJob* __restrict__ gemv_jobs,
-                                                                      const AttnJob* __restrict__ attn_jobs, float* x_out,
-                                                                      unsigned long long* timeline) {
+                                                                      const AttnJob* __restrict__ attn_jobs, const int* pos_dev,
+                                                                      float* x_out, unsigned long long* timeline) {
   extern __shared__ float smem[];
   __shared__ unsigned s_flag[2];   // results of a job's first and second wait
   __shared__ unsigned s_claim, s_claim_n;
+  __shared__ int s_pos;
   __shared__ uint4 s_items[2 * FUSED_CHAIN_CHUNK];
   __shared__ uint4 s_surplus[2 * FUSED_CLAIM_MAX];
   // the job tables are read-only for the launch: scalar loads (constant address space), as for kernel arguments
@@ -1014,7 +1061,10 @@ __global__ __launch_bounds__(FUSED_THREADS, 4) void fused_chain_kernel(const Ste
   const uint4* mine = reinterpret_cast<const uint4*>(items + (size_t)blockIdx.x * n_items);
   // (whether the slot is inside a surplus list is kept in LDS, not in a register that would stay live across the
   // jobs' code: the kernel is at its register limit)
-  if (threadIdx.x == 0) s_claim_n = 0u;
+  if (threadIdx.x == 0) {
+    s_claim_n = 0u;
+    s_pos = *pos_dev;   // (advanced by the step's last job, which ends behind every reader)
+  }
   for (int it = 0; it < n_items; ++it) {
     const int ic = it % FUSED_CHAIN_CHUNK;
     if (ic == 0) {
@@ -1061,7 +1111,8 @@ __global__ __launch_bounds__(FUSED_THREADS, 4) void fused_chain_kernel(const Ste
     if (tl && threadIdx.x == 0) tl[0] = wall_clock64();
     bool ok;
     if ((kb & FUSED_KIND_MASK) == (unsigned)JOB_ATTN) {
-      ok = attn_job<D, G>(*(const AttnJob*)(aj + (size_t)job * sizeof(AttnJob)), lb, smem, s_flag, tl ? tl + 1 : nullptr);
+      ok = attn_job<D, G, true>(*(const AttnJob*)(aj + (size_t)job * sizeof(AttnJob)), lb, __builtin_amdgcn_readfirstlane(s_pos), smem,
+                                s_flag, tl ? tl + 1 : nullptr);
     } else {
       const GemvJob& j = *(const GemvJob*)(gj + (size_t)job * sizeof(GemvJob));
       const unsigned long long wpu = (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)i0.x) |
@@ -1076,25 +1127,9 @@ __global__ __launch_bounds__(FUSED_THREADS, 4) void fused_chain_kernel(const Ste
       const int KT = (int)(geo & 0xFFFFu), group0 = (int)(geo >> 16);
       const int M = (int)(((unsigned)__builtin_amdgcn_readfirstlane((int)i1.z) >> 8) & 0xFFu);
       const unsigned tn = ((kb >> FUSED_KIND_TN_SHIFT) & 3u) + 1u;
-#define CHAIN_GEMV(U_, TN_, COH_)                                                                                   \
-  do {                                                                                                              \
-    if (M > 8) ok = gemv_job<U_, TN_, COH_, true, true>(j, wp, xop, KT, group0, M, lb, smem, s_flag, x_out, tl ? tl + 1 : nullptr);   \
-    else ok = gemv_job<U_, TN_, COH_, false, true>(j, wp, xop, KT, group0, M, lb, smem, s_flag, x_out, tl ? tl + 1 : nullptr);        \
-  } while (0)
-      if (kb & FUSED_KIND_COH) {
-        if (tn == 4) CHAIN_GEMV(1, 4, true);
-        else if (tn == 2) CHAIN_GEMV(FUSED_U2, 2, true);
-        else CHAIN_GEMV(FUSED_U, 1, true);
-      } else if (tn == 4) {
-        CHAIN_GEMV(1, 4, false);
-      } else if (tn == 3) {
-        CHAIN_GEMV(1, 3, false);
-      } else if (tn == 2) {
-        CHAIN_GEMV(FUSED_U2, 2, false);
-      } else {
-        CHAIN_GEMV(FUSED_U, 1, false);
-      }
-#undef CHAIN_GEMV
+      const int pos = __builtin_amdgcn_readfirstlane(s_pos);
+      if (M > 8) ok = gemv_job<D, false, true, true>(j, wp, xop, KT, group0, M, (int)tn, lb, pos, smem, s_flag, x_out, tl ? tl + 1 : nullptr);
+      else ok = gemv_job<D, false, false, true>(j, wp, xop, KT, group0, M, (int)tn, lb, pos, smem, s_flag, x_out, tl ? tl + 1 : nullptr);
     }
     if (!ok) break;      // (the same for the whole workgroup)
     __syncthreads();     // the job's LDS is free again; the item chunk may be overwritten
@@ -1173,6 +1208,7 @@ static bool gemv_job_valid(const GemvJob& j) {
   if (j.wait_on2 && !j.wait_on) return false;
   if (j.done_ctr && j.done_target == 0) return false;
   if (j.epi == EPI_RESIDUAL && ((j.xop_a && !j.gain_a) || (j.xop_b && !j.gain_b) || !j.x_old || !j.x_new)) return false;
+  if (j.epi == EPI_QKV_ROPE && tn == 3) return false;
   if (j.epi == EPI_SWIGLU && (!j.act || ((j.N / 2) & 1))) return false;
   return j.epi == EPI_RESIDUAL || j.epi == EPI_SWIGLU || j.epi == EPI_QKV_ROPE;
 }
@@ -1182,11 +1218,9 @@ hipError_t fused_chain_item(const GemvJob& j, int job_index, int lb, StepItem* o
   const int tn = j.tn >= 2 ? j.tn : 1, kt = j.K >> 5;
   if (kt > 0xFFFF || j.group0 < 0 || j.group0 > 0xFFFF || lb < 0 || lb > 0xFFFF || job_index < 0 || job_index > 0xFFFF)
     return hipErrorInvalidValue;
-  const bool coh = j.coherent_x != 0;
-  if (tn == 3 && coh) return hipErrorInvalidValue;
   StepItem it{};
   it.wp = j.wp; it.xb = j.xb; it.kt = (uint16_t)kt; it.group0 = (uint16_t)j.group0; it.lb = (uint16_t)lb; it.job = (uint16_t)job_index;
-  it.kind = (uint8_t)((unsigned)JOB_GEMV | ((unsigned)(tn - 1) << FUSED_KIND_TN_SHIFT) | (coh ? FUSED_KIND_COH : 0u));
+  it.kind = (uint8_t)((unsigned)JOB_GEMV | ((unsigned)(tn - 1) << FUSED_KIND_TN_SHIFT));
   it.M = (uint8_t)j.M;
   *out = it;
   return hipSuccess;
@@ -1273,9 +1307,7 @@ static hipError_t launch_fused_d(const FusedArgs& fa, int g, dim3 grid, hipStrea
 
 // LDS a job needs: the attention job's merge area or the GEMV job's cross-wave sums
 size_t fused_attn_lds_bytes(int d, int g) { return (size_t)(2 * FUSED_WAVES * 16 + FUSED_WAVES * g * d + g * 64) * 4; }
-size_t fused_gemv_lds_bytes() {
-  return (size_t)(FUSED_WAVES * 4 * 16 * 17 + FUSED_WAVES * 16) * 4;   // sized for four-tile workgroups
-}
+size_t fused_gemv_lds_bytes() { return (size_t)(FUSED_WAVES * 4 * 16 * 17 + FUSED_WAVES * 16) * 4; }   // sized for four-tile workgroups
 
 // dynamic LDS above 64 KiB has to be allowed per kernel, once (outside any stream capture)
 template <int D>
@@ -1296,11 +1328,11 @@ hipError_t fused_decode_prepare(int d, int g) {
 }
 
 template <int D, int GQ>
-static hipError_t launch_chain_dg(const StepItem* items, int n_items, const GemvJob* gj, const AttnJob* aj, float* x_out,
+static hipError_t launch_chain_dg(const StepItem* items, int n_items, const GemvJob* gj, const AttnJob* aj, const int* pos_dev, float* x_out,
                                   unsigned long long* tl, int n_slots, int lds_bytes, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   const dim3 grid(n_slots), block(FUSED_THREADS);
-  if (ev0 || ev1) hipExtLaunchKernelGGL((fused_chain_kernel<D, GQ>), grid, block, lds_bytes, s, ev0, ev1, 0, items, n_items, gj, aj, x_out, tl);
-  else hipLaunchKernelGGL((fused_chain_kernel<D, GQ>), grid, block, lds_bytes, s, items, n_items, gj, aj, x_out, tl);
+  if (ev0 || ev1) hipExtLaunchKernelGGL((fused_chain_kernel<D, GQ>), grid, block, lds_bytes, s, ev0, ev1, 0, items, n_items, gj, aj, pos_dev, x_out, tl);
+  else hipLaunchKernelGGL((fused_chain_kernel<D, GQ>), grid, block, lds_bytes, s, items, n_items, gj, aj, pos_dev, x_out, tl);
   return hipGetLastError();
 }
 template <int D>
@@ -1324,15 +1356,15 @@ int fused_chain_slots(int d, int g, int n_cu) {
 }
 
 hipError_t launch_fused_chain(const StepItem* items, int n_items, const GemvJob* gemv_jobs, const AttnJob* attn_jobs,
-                              float* x_out, unsigned long long* timeline, int n_slots, int lds_bytes, int d, int g,
+                              const int* pos_dev, float* x_out, unsigned long long* timeline, int n_slots, int lds_bytes, int d, int g,
                               hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-  if (!items || n_items <= 0 || n_slots <= 0 || lds_bytes <= 0 || lds_bytes > FUSED_MAX_LDS_BYTES) return hipErrorInvalidValue;
+  if (!items || !pos_dev || n_items <= 0 || n_slots <= 0 || lds_bytes <= 0 || lds_bytes > FUSED_MAX_LDS_BYTES) return hipErrorInvalidValue;
 #define CHAIN_LAUNCH(D_)                                                                                                    \
   switch (g) {                                                                                                              \
-    case 1: return launch_chain_dg<D_, 1>(items, n_items, gemv_jobs, attn_jobs, x_out, timeline, n_slots, lds_bytes, s, ev0, ev1);    \
-    case 2: return launch_chain_dg<D_, 2>(items, n_items, gemv_jobs, attn_jobs, x_out, timeline, n_slots, lds_bytes, s, ev0, ev1);    \
-    case 4: return launch_chain_dg<D_, 4>(items, n_items, gemv_jobs, attn_jobs, x_out, timeline, n_slots, lds_bytes, s, ev0, ev1);    \
-    case 8: return launch_chain_dg<D_, 8>(items, n_items, gemv_jobs, attn_jobs, x_out, timeline, n_slots, lds_bytes, s, ev0, ev1);    \
+    case 1: return launch_chain_dg<D_, 1>(items, n_items, gemv_jobs, attn_jobs, pos_dev, x_out, timeline, n_slots, lds_bytes, s, ev0, ev1);    \
+    case 2: return launch_chain_dg<D_, 2>(items, n_items, gemv_jobs, attn_jobs, pos_dev, x_out, timeline, n_slots, lds_bytes, s, ev0, ev1);    \
+    case 4: return launch_chain_dg<D_, 4>(items, n_items, gemv_jobs, attn_jobs, pos_dev, x_out, timeline, n_slots, lds_bytes, s, ev0, ev1);    \
+    case 8: return launch_chain_dg<D_, 8>(items, n_items, gemv_jobs, attn_jobs, pos_dev, x_out, timeline, n_slots, lds_bytes, s, ev0, ev1);    \
   }
   if (d == 128) { CHAIN_LAUNCH(128) }
   if (d == 64) { CHAIN_LAUNCH(64) }

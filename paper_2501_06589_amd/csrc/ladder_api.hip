@@ -1271,7 +1271,7 @@ int build_chain(ladder_ctx* c, int B) {
       } else {
         GemvJob& j = fa.g[k];
         Producer& me = prod[(size_t)producer_of(j.wp)];
-        j.wait_on = nullptr; j.wait_on2 = nullptr; j.coherent_x = 0;
+        j.wait_on = nullptr; j.wait_on2 = nullptr;
         if (d1 >= 0) { j.wait_on = prod[(size_t)d1].words; j.wait_flags = prod[(size_t)d1].flagged ? prod[(size_t)d1].blocks : 0u; }
         if (d2 >= 0) { j.wait_on2 = prod[(size_t)d2].words; j.wait_flags2 = prod[(size_t)d2].flagged ? prod[(size_t)d2].blocks : 0u; }
         j.wait_bias = c->wait_bias; j.wait_bias2 = c->wait_bias2; j.wait_spins = c->wait_spins; j.err_word = c->err_word_dev;
@@ -1444,7 +1444,7 @@ int fused_body(ladder_ctx* c, const void* emb, int B, hipStream_t s, float* x_ou
   const int gq = g.n_q_heads / g.n_kv_heads;
   if (c->chain) {
     HIP_TRY(c, events(e));
-    HIP_TRY(c, launch_fused_chain(c->chain_items_dev, c->chain_items, c->chain_gemv_dev, c->chain_attn_dev, x_out,
+    HIP_TRY(c, launch_fused_chain(c->chain_items_dev, c->chain_items, c->chain_gemv_dev, c->chain_attn_dev, c->pos_dev, x_out,
                                   c->timeline_on ? c->chain_tl_dev : nullptr, c->chain_slots, c->chain_lds, g.head_dim, gq,
                                   s, e[0], e[1]));
     if (c->prof) c->prof_pending.push_back({LADDER_K_FUSED_DECODE, e[0], e[1]});
