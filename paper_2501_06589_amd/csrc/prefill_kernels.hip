@@ -1139,11 +1139,11 @@ __device__ __forceinline__ float max_over_rows(float v) {
 // before rescaling would save another 0.5 % of a call, but the largest weight of a query is then no longer exactly 1 and its
 // bf16 rounding shows: attention output behind 4001 positions 1.297e-2 -> 1.312e-2 of its norm.)  The K rows are staged in the order that leaves a
 // lane eight neighbouring keys (row 16 t + i holds key 8 (i / 4) + 4 t + i % 4), so its share of V^T is one 16-byte read.
-// us per layer (before -> after): 16 x 2048 tokens, 16 q / 2 kv heads 556 -> 424 (650 TFLOP/s); 1 x 2048, 32 / 8 heads 156 -> 106;
-// 1 x 4001, 8 / 1 heads 202 -> 116; 1 x 100, 32 / 8 heads 12.8 -> 6.0 (direct kernel before).
+// us per layer (direct kernel -> now): 16 x 2048 tokens, 16 q / 2 kv heads 556 -> 389 (710 TFLOP/s); 1 x 2048, 32 / 8 heads 156 -> 73;
+// 1 x 4001, 8 / 1 heads 202 -> 93; 1 x 100, 32 / 8 heads 12.8 -> 6.0.
 // ------------------------------------------------------------------------------------------------
 template <int D, int HW, int QT>
-__global__ __launch_bounds__(256, 2) void attn_prefill_lds_kernel(AttnPrefillArgs a) {
+__global__ __launch_bounds__(256, 2) void attn_prefill_lds_kernel(AttnPrefillArgs a, int n_pairs) {
   constexpr int DS = D / 32, DT = D / 16;
   constexpr int QW = 4 / HW;                 // query sub-blocks (of QT * 16) per workgroup
   constexpr int KROW = D * 2 + 16;           // bytes per staged K row (key): 16-byte pad, conflict-free b128 reads
@@ -1154,8 +1154,15 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_lds_kernel(AttnPrefillArg
 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int b = lane & 15, q = lane >> 4;
-  const int qblk = (int)gridDim.x - 1 - (int)blockIdx.x;   // longest rows first
-  const int h = blockIdx.y * HW + wave % HW, bi = blockIdx.z;
+  // Workgroups are dispatched in block order, one to each of 256 CUs, then a second one and so on, and a causal one is as long as its
+  // queries are far back.  So: longest first over all (sequence, head group) pairs, and where all of them fit the chip at once (one query tile) every
+  // second row of 256 in reverse, so that the sum on each CU is about the same.  (Pairs vary fastest: the workgroups of one pair share an XCD's L2
+  // where the pairs are a multiple of 8.)
+  const int n_wg = (int)gridDim.x, id = (int)blockIdx.x, row = id >> 8;
+  const int rank = QT == 1 && (row & 1) ? (row << 8) + min(256, n_wg - (row << 8)) - 1 - (id & 255) : id;
+  const int pair = rank % n_pairs, hg = pair % (a.nq / HW), bi = pair / (a.nq / HW);
+  const int qblk = n_wg / n_pairs - 1 - rank / n_pairs;
+  const int h = hg * HW + wave % HW;
   const int kvh = h / (a.nq / a.nkv);
   const int t0 = (qblk * QW + wave / HW) * (QT * 16);       // this wavefront's first query
   const float scale2 = 1.4426950408889634f / sqrtf((float)D);   // scores to exponents of 2
@@ -1294,30 +1301,30 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_lds_kernel(AttnPrefillArg
   }
 }
 
-// 16-query tiles per wavefront: the fewest whose workgroups still fit the chip together (two per CU of 256), because a call is
-// then as long as its longest workgroup; where even three tiles make more workgroups, three (the K / V^T reads from LDS
-// are shared by more queries; four leave one wavefront per SIMD and took 1.45 instead of 0.55 ms on 16 x 2048 tokens).
-// Whole layer, us, with 1 / 2 / 3: 70B R = 8 shard, 1 x 1000 374 / 388 / 395, 2 layers 1 x 4001 3223 / 3277 / 3315; 8B 2 layers
-// 1 x 2048 1845 / 1830 / 1862, 1 layer 1 x 4000 1740 / 1728 / 1720, 2 x 8000 7612 / 7245 / 7295.
 template <int D, int QT>
-static hipError_t launch_attn_prefill_lds(const AttnPrefillArgs& a, hipStream_t s) {
-  const int g = a.nq / a.nkv;
-  const int hw = g >= 4 && g % 4 == 0 ? 4 : (g % 2 == 0 ? 2 : 1);
-  const int qrows = (4 / hw) * QT * 16;
-  const dim3 grid((a.T + qrows - 1) / qrows, a.nq / hw, a.B), block(256);
-  if (hw == 4) hipLaunchKernelGGL((attn_prefill_lds_kernel<D, 4, QT>), grid, block, 0, s, a);
-  else if (hw == 2) hipLaunchKernelGGL((attn_prefill_lds_kernel<D, 2, QT>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((attn_prefill_lds_kernel<D, 1, QT>), grid, block, 0, s, a);
+static hipError_t launch_attn_prefill_lds(const AttnPrefillArgs& a, int hw, int n_wg, int n_pairs, hipStream_t s) {
+  const dim3 grid(n_wg), block(256);
+  if (hw == 4) hipLaunchKernelGGL((attn_prefill_lds_kernel<D, 4, QT>), grid, block, 0, s, a, n_pairs);
+  else if (hw == 2) hipLaunchKernelGGL((attn_prefill_lds_kernel<D, 2, QT>), grid, block, 0, s, a, n_pairs);
+  else hipLaunchKernelGGL((attn_prefill_lds_kernel<D, 1, QT>), grid, block, 0, s, a, n_pairs);
   return hipGetLastError();
 }
 
+// 16-query tiles per wavefront: one, of which four workgroups are resident per CU, until they are more than a quarter beyond what the chip holds
+// (then the last ones run on a nearly empty chip); else two, which read K / V^T from LDS half as often (three: 5 - 14 % slower than two everywhere).
+// us, one / two tiles: 8B shape 1 x 1000 31 / 43, 1 x 2048 (1024 workgroups of one tile) 73 / 83, 1 x 2600 (1304) 104 / 109, 3 x 1000 (1512) 61 / 53, 1 x 8000
+// 837 / 658; 70B R = 8 1 x 4001 93 / 137, 2 x 5000 (1252) 186 / 208; R = 4 1 x 5000 (1252) 182 / 207, 1 x 6000 (1500) 281 / 255, 16 x 2048 481 / 389.
+// Longest first within each pair only, and one to three tiles by which fit twice per CU: 8B 1 x 2048 123, 4 x 1000 99 (61), R = 8 1 x 4001 126, R = 4 16 x 2048 460.
+#define ATTN_ONE_TILE_WORKGROUPS 1280
 template <int D>
 static hipError_t launch_attn_prefill_lds(const AttnPrefillArgs& a, hipStream_t s) {
   const int g = a.nq / a.nkv;
   const int hw = g >= 4 && g % 4 == 0 ? 4 : (g % 2 == 0 ? 2 : 1);
-  int qt = 1;
-  while (qt < 3 && (long)((a.T + (4 / hw) * qt * 16 - 1) / ((4 / hw) * qt * 16)) * (a.nq / hw) * a.B > 512) ++qt;
-  return qt == 1 ? launch_attn_prefill_lds<D, 1>(a, s) : qt == 2 ? launch_attn_prefill_lds<D, 2>(a, s) : launch_attn_prefill_lds<D, 3>(a, s);
+  const int n_pairs = a.nq / hw * a.B;
+  const auto workgroups = [&](int qt) { return (long long)((a.T + 64 / hw * qt - 1) / (64 / hw * qt)) * n_pairs; };
+  if (workgroups(2) > 0x7fffffffll) return hipErrorInvalidValue;
+  if (workgroups(1) <= ATTN_ONE_TILE_WORKGROUPS) return launch_attn_prefill_lds<D, 1>(a, hw, (int)workgroups(1), n_pairs, s);
+  return launch_attn_prefill_lds<D, 2>(a, hw, (int)workgroups(2), n_pairs, s);
 }
 
 hipError_t launch_attn_prefill(const AttnPrefillArgs& a, hipStream_t s) {
