@@ -194,6 +194,11 @@ struct AttnGenericArgs {
   size_t cache_stride;     // bytes
 };
 hipError_t launch_attn_generic(const AttnGenericArgs& a, bool is_bf16, hipStream_t s);
+// A layer of at most PLAIN_NORM_ROWS rows whose modules do not read each other's output, in three launches: { qkv, gate_up }, { attn, down }, and the
+// attention's output projection; whether the rule takes it
+bool plain_beside(const PlainGemmArgs& qkv, const AttnGenericArgs& attn, const PlainGemmArgs& gate_up, const PlainGemmArgs& down, bool is_bf16);
+hipError_t launch_plain_inputs(PlainGemmArgs a, PlainGemmArgs b, bool is_bf16, hipStream_t s);
+hipError_t launch_plain_attn_beside(const AttnGenericArgs& a, PlainGemmArgs b, bool is_bf16, hipStream_t s);
 
 // act[m][i] = silu(gate) * up from the partial products of the packed gate/up projection (tile columns 0..7 gate, 8..15 the matching up
 // columns), act bf16: parts f32 [n_parts][M][2I], slot s at parts + s * part_stride, summed in slot order

@@ -412,8 +412,8 @@ __device__ __forceinline__ void plain_product(const PlainGemmArgs& a, const T* x
 // 21.2 / 39.0 / 89.0; columns first 31.3 / 64.1 / 135.1, 44.5 / 89.7 / 181.2; this 21.0 / 42.5 / 92.5, 20.2 / 39.2 / 80.1).  Else columns
 // first (all blocks run side by side; hidden 1024, 32 rows: 176 against 181 us).
 constexpr unsigned PLAIN_GROUP = 64;
-__device__ __forceinline__ bool plain_tile(unsigned row_blocks, unsigned col_blocks, unsigned& m_blk, unsigned& col_blk) {
-  const unsigned total = row_blocks * col_blocks, total8 = total & ~7u, id = flat_block();
+__device__ __forceinline__ bool plain_tile(unsigned id, unsigned row_blocks, unsigned col_blocks, unsigned& m_blk, unsigned& col_blk) {
+  const unsigned total = row_blocks * col_blocks, total8 = total & ~7u;
   if (id >= total) return false;
   if (total <= 512) {
     m_blk = id / col_blocks;
@@ -431,7 +431,7 @@ __device__ __forceinline__ bool plain_tile(unsigned row_blocks, unsigned col_blo
 // NM = 2: gate and up in one sweep over K, and more loads in flight in the other projections too.  (Two workgroups per CU: without the bound the rows that fp32 sums and norms itself cost two registers too many
 // for that; three layers of 264 - 512 workgroups of four rows, hidden 512 and 1024, 2 - 7 % slower than it was as separate kernels, with it 14 - 20 % faster.)
 template <typename T, int MR, bool VEC, int KC, bool NORM, int NM>
-__global__ __launch_bounds__(256, 2) void plain_gemm_kernel(PlainGemmArgs a) {
+__device__ __forceinline__ void plain_gemm_block(const PlainGemmArgs& a, unsigned id) {
   __shared__ __attribute__((aligned(16))) float xs[MR][KC];
   __shared__ float red[4 * NM][MR][64];
   __shared__ float sum[2][MR][64];
@@ -439,10 +439,10 @@ __global__ __launch_bounds__(256, 2) void plain_gemm_kernel(PlainGemmArgs a) {
   const int t = threadIdx.x, shard = blockIdx.z;
   unsigned m_blk, col_blk;
   if (MR == 1) {   // (a single row: m_blk is 0 inside the grid; written this way the tiny fp32 model's steps take 558 us, as one comparison 568)
-    m_blk = flat_block() / (unsigned)a.n_blocks;
-    col_blk = flat_block() % (unsigned)a.n_blocks;
+    m_blk = id / (unsigned)a.n_blocks;
+    col_blk = id % (unsigned)a.n_blocks;
     if (m_blk >= (unsigned)a.M) return;
-  } else if (!plain_tile(((unsigned)a.M + MR - 1) / MR, (unsigned)a.n_blocks, m_blk, col_blk)) {
+  } else if (!plain_tile(id, ((unsigned)a.M + MR - 1) / MR, (unsigned)a.n_blocks, m_blk, col_blk)) {
     return;
   }
   const int m0 = (int)m_blk * MR;
@@ -505,10 +505,35 @@ __global__ __launch_bounds__(256, 2) void plain_gemm_kernel(PlainGemmArgs a) {
   }
 }
 
+template <typename T, int MR, bool VEC, int KC, bool NORM, int NM>
+__global__ __launch_bounds__(256, 2) void plain_gemm_kernel(PlainGemmArgs a) {
+  plain_gemm_block<T, MR, VEC, KC, NORM, NM>(a, flat_block());
+}
+
+// The first projections of a layer's two modules in one launch, where neither reads what the other one writes: a's blocks, then b's.  Each launch of a
+// small model is as long as one workgroup's round trips (4 - 6 us), so what counts is how many follow one another.
+template <typename T, int MR, bool VEC>
+__global__ __launch_bounds__(256, 2) void plain_inputs_kernel(PlainGemmArgs a, PlainGemmArgs b) {
+  const unsigned id = blockIdx.x, n_a = (unsigned)a.n_blocks * (((unsigned)a.M + MR - 1) / MR);
+  if (id < n_a) plain_gemm_block<T, MR, VEC, 256, true, 2>(a, id);
+  else plain_gemm_block<T, MR, VEC, 256, true, 2>(b, id - n_a);
+}
+
+static int plain_col_blocks(const PlainGemmArgs& a) {
+  int n = 0;
+  for (int i = 0; i < (a.epilogue == PLAIN_SWIGLU ? 1 : a.n_mat); ++i) n += (a.N[i] + 63) / 64;
+  return n;
+}
+// four weights per load where every row of every matrix starts on such a boundary
+static bool plain_vec(const PlainGemmArgs& a) {
+  bool vec = (a.w_stride & 15) == 0;
+  for (int i = 0; i < a.n_mat; ++i) vec = vec && plain_four_at_once(a.w[i], a.N[i]);
+  return vec;
+}
+
 template <typename T, int MR>
 static hipError_t launch_plain_gemm_t(PlainGemmArgs a, bool vec, hipStream_t s) {
-  a.n_blocks = 0;
-  for (int i = 0; i < (a.epilogue == PLAIN_SWIGLU ? 1 : a.n_mat); ++i) a.n_blocks += (a.N[i] + 63) / 64;
+  a.n_blocks = plain_col_blocks(a);
   const long long blocks = (long long)a.n_blocks * (((long long)a.M + MR - 1) / MR);
   if (blocks > 0x7fffffff || a.n_shards > 65535) return hipErrorInvalidValue;
   const dim3 grid = flat_grid(blocks, a.n_shards);
@@ -555,9 +580,7 @@ hipError_t launch_stream_sum(const StreamSum& a, float* x_out, int rows, int H, 
 hipError_t launch_plain_gemm(const PlainGemmArgs& a, bool is_bf16, hipStream_t s) {
   if (a.M <= 0 || a.n_shards <= 0) return hipSuccess;
   if (a.gain && (a.M > PLAIN_NORM_ROWS || a.epilogue == PLAIN_OUT || (!a.in.emb && !a.in.base) || a.in.n_adds < 0 || a.in.n_adds > 2)) return hipErrorInvalidValue;
-  // four weights per load where every row of every matrix starts on such a boundary
-  bool vec = (a.w_stride & 15) == 0;
-  for (int i = 0; i < a.n_mat; ++i) vec = vec && plain_four_at_once(a.w[i], a.N[i]);
+  const bool vec = plain_vec(a);
   // rows per workgroup: one for a single row; four for a few; more re-use of the weights beyond
   const int mr = a.M == 1 ? 1 : a.M <= PLAIN_NORM_ROWS ? 4 : 16;
   if (is_bf16) return mr == 1 ? launch_plain_gemm_t<bf16_t, 1>(a, vec, s) : mr == 4 ? launch_plain_gemm_t<bf16_t, 4>(a, vec, s) : launch_plain_gemm_t<bf16_t, 16>(a, vec, s);
@@ -634,12 +657,11 @@ hipError_t launch_rope_append(const RopeAppendArgs& a, hipStream_t s) {
 // tiny fp32 model, one row behind 32 positions: 23 us per shard -> 5.7 for both.
 // ------------------------------------------------------------------------------------------------
 template <typename T, bool VEC>
-__global__ __launch_bounds__(256) void attn_generic_kernel(AttnGenericArgs a) {
+__device__ __forceinline__ void attn_generic_block(const AttnGenericArgs& a, unsigned unit) {
   __shared__ float qs[256];
   __shared__ __attribute__((aligned(16))) float ps[4][64];
   __shared__ float om[4][256], ms[4], ls[4];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const unsigned unit = flat_block();
   if (unit >= (unsigned)a.B * (unsigned)a.T * (unsigned)a.nq) return;
   const int row = (int)(unit / (unsigned)a.nq), h = (int)(unit % (unsigned)a.nq), shard = blockIdx.z;
   const int b = row / a.T, t = row % a.T;
@@ -709,6 +731,63 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(AttnGenericArgs a) {
     }
     store_f<T>(reinterpret_cast<T*>(a.o) + shard * a.q_stride + (size_t)row * a.nq * a.d + h * a.d + threadIdx.x, o / tot);
   }
+}
+
+template <typename T, bool VEC>
+__global__ __launch_bounds__(256) void attn_generic_kernel(AttnGenericArgs a) {
+  attn_generic_block<T, VEC>(a, flat_block());
+}
+
+// The attention of a layer and the last projection of its MLP in one launch (the MLP's first one has run beside the QKV projection)
+template <typename T, int MR, bool VEC_A, bool VEC_B>
+__global__ __launch_bounds__(256, 2) void plain_attn_beside_kernel(AttnGenericArgs a, PlainGemmArgs b) {
+  const unsigned id = blockIdx.x, n_a = (unsigned)a.B * (unsigned)a.T * (unsigned)a.nq;
+  if (id < n_a) attn_generic_block<T, VEC_A>(a, id);
+  else plain_gemm_block<T, MR, VEC_B, 256, false, 2>(b, id - n_a);
+}
+
+template <typename T, int MR>
+static hipError_t launch_plain_inputs_t(const PlainGemmArgs& a, const PlainGemmArgs& b, bool vec, dim3 grid, hipStream_t s) {
+  if (vec) hipLaunchKernelGGL((plain_inputs_kernel<T, MR, true>), grid, dim3(256), 0, s, a, b);
+  else hipLaunchKernelGGL((plain_inputs_kernel<T, MR, false>), grid, dim3(256), 0, s, a, b);
+  return hipGetLastError();
+}
+template <typename T, int MR>
+static hipError_t launch_plain_attn_beside_t(const AttnGenericArgs& a, const PlainGemmArgs& b, bool vec_a, bool vec_b, dim3 grid, hipStream_t s) {
+  if (vec_a && vec_b) hipLaunchKernelGGL((plain_attn_beside_kernel<T, MR, true, true>), grid, dim3(256), 0, s, a, b);
+  else if (vec_a) hipLaunchKernelGGL((plain_attn_beside_kernel<T, MR, true, false>), grid, dim3(256), 0, s, a, b);
+  else if (vec_b) hipLaunchKernelGGL((plain_attn_beside_kernel<T, MR, false, true>), grid, dim3(256), 0, s, a, b);
+  else hipLaunchKernelGGL((plain_attn_beside_kernel<T, MR, false, false>), grid, dim3(256), 0, s, a, b);
+  return hipGetLastError();
+}
+
+// Both launches together hold at most PLAIN_HELD_WORKGROUPS workgroups, two per CU; of a bf16 matrix whose weights come one by one (gain: the
+// caller has asked) the kernels by themselves know a better way
+bool plain_beside(const PlainGemmArgs& qkv, const AttnGenericArgs& attn, const PlainGemmArgs& gate_up, const PlainGemmArgs& down, bool is_bf16) {
+  const int rows = qkv.M, shards = qkv.n_shards;
+  if (rows < 1 || rows > PLAIN_NORM_ROWS || shards < 1 || !qkv.gain || !gate_up.gain || attn.d > 256) return false;
+  if (is_bf16 && !(plain_vec(qkv) && plain_vec(gate_up) && plain_vec(down))) return false;
+  const long long first = plain_workgroups(rows, plain_col_blocks(qkv) + plain_col_blocks(gate_up), shards);
+  const long long second = (long long)rows * attn.nq * shards + plain_workgroups(rows, plain_col_blocks(down), shards);
+  return first <= PLAIN_HELD_WORKGROUPS && second <= PLAIN_HELD_WORKGROUPS;
+}
+hipError_t launch_plain_inputs(PlainGemmArgs a, PlainGemmArgs b, bool is_bf16, hipStream_t s) {
+  if (a.M <= 0 || a.M > PLAIN_NORM_ROWS || b.M != a.M || a.n_shards <= 0 || b.n_shards != a.n_shards || !a.gain || !b.gain) return hipErrorInvalidValue;
+  a.n_blocks = plain_col_blocks(a);
+  b.n_blocks = plain_col_blocks(b);
+  const bool vec = plain_vec(a) && plain_vec(b), one = a.M == 1;
+  const dim3 grid((unsigned)((a.n_blocks + b.n_blocks) * (one ? 1 : (a.M + 3) / 4)), 1, (unsigned)a.n_shards);
+  if (is_bf16) return one ? launch_plain_inputs_t<bf16_t, 1>(a, b, vec, grid, s) : launch_plain_inputs_t<bf16_t, 4>(a, b, vec, grid, s);
+  return one ? launch_plain_inputs_t<float, 1>(a, b, vec, grid, s) : launch_plain_inputs_t<float, 4>(a, b, vec, grid, s);
+}
+hipError_t launch_plain_attn_beside(const AttnGenericArgs& a, PlainGemmArgs b, bool is_bf16, hipStream_t s) {
+  const int rows = a.B * a.T;
+  if (rows <= 0 || rows > PLAIN_NORM_ROWS || b.M != rows || a.n_shards <= 0 || b.n_shards != a.n_shards || a.d > 256) return hipErrorInvalidValue;
+  b.n_blocks = plain_col_blocks(b);
+  const bool vec_a = a.d % 4 == 0, vec_b = plain_vec(b), one = rows == 1;
+  const dim3 grid((unsigned)(rows * a.nq + b.n_blocks * (one ? 1 : (rows + 3) / 4)), 1, (unsigned)a.n_shards);
+  if (is_bf16) return one ? launch_plain_attn_beside_t<bf16_t, 1>(a, b, vec_a, vec_b, grid, s) : launch_plain_attn_beside_t<bf16_t, 4>(a, b, vec_a, vec_b, grid, s);
+  return one ? launch_plain_attn_beside_t<float, 1>(a, b, vec_a, vec_b, grid, s) : launch_plain_attn_beside_t<float, 4>(a, b, vec_a, vec_b, grid, s);
 }
 
 hipError_t launch_attn_generic(const AttnGenericArgs& a, bool is_bf16, hipStream_t s) {

@@ -436,35 +436,42 @@ size_t gu_rows_of(const ladder_config& g) {
   return most;
 }
 
-// one module of the plain path: three launches (attention) or two (MLP) for all computed shards, which leave a partial
-// sum each in out[shard][rows][hidden]; in: if non-null the rows the module reads are made from this sum (not read from y) and left in x_store
-int run_module_plain(ladder_ctx* c, int m, int B, int T, int pos0, float* out, hipStream_t s, const StreamSum* in = nullptr, float* x_store = nullptr) {
+// one module of the plain path for all computed shards, which leave a partial sum each in out[shard][rows][hidden]: its first projection, attention
+// (odd modules) and last projection; in: if non-null the rows the module reads are made from this sum (not read from y) and left in x_store
+struct PlainModule { PlainGemmArgs first; AttnGenericArgs attn; PlainGemmArgs last; };
+PlainModule plain_module(ladder_ctx* c, int m, int B, int T, int pos0, float* out, const StreamSum* in, float* x_store) {
   const ladder_config& g = c->cfg;
   const int rows = B * T, H = g.hidden, d = g.head_dim, nqd = g.n_q_heads * d, nkd = g.n_kv_heads * d, I = g.inter;
   const LayerStore& L = c->store[(size_t)((m - 1) / 2) * g.n_real_shards];   // shard 0; the others lie at fixed strides behind it
-  PlainGemmArgs a{};
+  PlainModule r{};
+  PlainGemmArgs& a = r.first;
   a.x = c->y[m & 1]; a.M = rows; a.K = H; a.n_shards = g.n_real_shards; a.w_stride = c->shard_bytes; a.held = c->plain_held;
   if (in) {
     a.in = *in; a.x_store = x_store; a.eps = g.rms_eps;
     a.gain = (m & 1) ? (const void*)c->gain_attn[(size_t)(m - 1) / 2] : (const void*)c->gain_mlp[(size_t)(m - 1) / 2];
   }
-  PlainGemmArgs last{};
+  PlainGemmArgs& last = r.last;
   last.M = rows; last.n_shards = g.n_real_shards; last.w_stride = c->shard_bytes; last.held = c->plain_held; last.n_mat = 1; last.N[0] = H;
   last.epilogue = PLAIN_OUT; last.out = out; last.out_stride = (size_t)rows * H;
   if (m & 1) {
     a.n_mat = 3; a.w[0] = L.wq; a.w[1] = L.wk; a.w[2] = L.wv; a.N[0] = nqd; a.N[1] = a.N[2] = nkd; a.epilogue = PLAIN_QKV;
     a.q_out = c->qbuf; a.q_stride = (size_t)rows * nqd; a.cache_k = L.cache_k; a.cache_v = L.cache_v; a.cache_stride = c->shard_kv_bytes;
     a.cos_tab = c->cos_tab; a.sin_tab = c->sin_tab; a.T = T; a.pos0 = pos0; a.nkv = g.n_kv_heads; a.d = d; a.max_seq = c->s_cap;
-    HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_plain_gemm(a, c->bf16, s); }));
-    AttnGenericArgs aa{c->qbuf, L.cache_k, L.cache_v, c->obuf, B, T, pos0, g.n_q_heads, g.n_kv_heads, d, c->s_cap, g.n_real_shards, (size_t)rows * nqd, c->shard_kv_bytes};
-    HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_attn_generic(aa, c->bf16, s); }));
+    r.attn = AttnGenericArgs{c->qbuf, L.cache_k, L.cache_v, c->obuf, B, T, pos0, g.n_q_heads, g.n_kv_heads, d, c->s_cap, g.n_real_shards, (size_t)rows * nqd, c->shard_kv_bytes};
     last.x = c->obuf; last.x_stride = (size_t)rows * nqd; last.K = nqd; last.w[0] = L.wo;
   } else {
     a.n_mat = 2; a.w[0] = L.wg; a.w[1] = L.wu; a.N[0] = a.N[1] = I; a.epilogue = PLAIN_SWIGLU; a.act = c->act; a.act_stride = (size_t)rows * I;
-    HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_plain_gemm(a, c->bf16, s); }));
     last.x = c->act; last.x_stride = (size_t)rows * I; last.K = I; last.w[0] = L.wd;
   }
-  HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_plain_gemm(last, c->bf16, s); }));
+  return r;
+}
+
+// ... in three launches (attention) or two (MLP)
+int run_module_plain(ladder_ctx* c, int m, int B, int T, int pos0, float* out, hipStream_t s, const StreamSum* in = nullptr, float* x_store = nullptr) {
+  const PlainModule p = plain_module(c, m, B, T, pos0, out, in, x_store);
+  HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_plain_gemm(p.first, c->bf16, s); }));
+  if (m & 1) HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_attn_generic(p.attn, c->bf16, s); }));
+  HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_plain_gemm(p.last, c->bf16, s); }));
   return LADDER_OK;
 }
 
@@ -695,11 +702,14 @@ int run_embed_norm(ladder_ctx* c, const void* emb, int rows, hipStream_t s) {
   return LADDER_OK;
 }
 
-// A call of few rows of the plain path on layers that run in order: five launches per layer instead of seven.  Reduce and norm are no kernels of their own:
+// A call of few rows of the plain path on layers that run in order.  Reduce and norm are no kernels of their own:
 // the first projection of a module makes the rows it reads (the last stored stream and the module outputs behind it), and one of
 // its workgroups per row block stores them for the modules that come.  What is read is there when it is read: module m's first projection
 // adds the outputs up to module m - lag, so the output of module m - 2, whose buffer module m's last projection overwrites, has been added.
-// tiny fp32 model, one row: 16 launches -> 11 (prompt of 32 and 8 steps 565 -> 484 us; hidden 512 726 -> 634, hidden 1024, two sequences 1383 -> 1287).
+// A layer is then five launches, each as long as its round trips whatever it holds (tiny fp32 model 4 - 6 us); where the layer's MLP does not
+// read its attention's output (lag 2), three: { QKV, gate/up }, { attention, down }, { O }.  Only gate/up stores the rows it makes then, x_{2l-2}, and the
+// layer behind adds one and two outputs to them, in the same order: same bits.
+// tiny fp32 model, prompt of 32 and 8 steps: sixteen launches per step 565 us, eleven 484, seven 306; hidden 512 (two shards) 686 -> 463, four sequences 936 -> 702; hidden 1024, bf16 908 -> 621.
 int forward_plain(ladder_ctx* c, const void* x_in, int B, int T, int pos0, float* x_out, hipStream_t s) {
   const ladder_config& g = c->cfg;
   const int rows = B * T;
@@ -718,6 +728,25 @@ int forward_plain(ladder_ctx* c, const void* x_in, int B, int T, int pos0, float
   for (int m = 1; m <= c->n_mod; ++m) {
     const int src = std::max(0, m - lag_of(c, m));
     add_up_to(src);
+    // (an emulated latency follows each module, so they run one after the other)
+    if ((m & 1) && lag_of(c, m + 1) == 2 && g.reduce_delay_us == 0) {
+      const PlainModule attn = plain_module(c, m, B, T, pos0, c->parts[1], &in, nullptr);
+      add_up_to(m - 1);
+      float* const store = in.n_adds || (m + 1 == c->n_mod && in.emb) ? buf[0] : nullptr;   // (as below)
+      const PlainModule mlp = plain_module(c, m + 1, B, T, pos0, c->parts[0], &in, store);
+      if (plain_beside(attn.first, attn.attn, mlp.first, mlp.last, c->bf16)) {
+        HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_plain_inputs(attn.first, mlp.first, c->bf16, s); }));
+        HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_plain_attn_beside(attn.attn, mlp.last, c->bf16, s); }));
+        HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_plain_gemm(attn.last, c->bf16, s); }));
+        if (store) {
+          in.emb = nullptr; in.base = store; stored = m - 1;
+          std::swap(buf[0], buf[1]);
+        }
+        ++m;
+        continue;
+      }
+      add_up_to(src);
+    }
     // (a call whose modules all read the embeddings, of one layer: the last one leaves them too, so that what writes x_out reads nothing of
     // x_in, which may lie in the same memory)
     float* const store = in.n_adds || (m == c->n_mod && in.emb) ? buf[0] : nullptr;

@@ -182,3 +182,26 @@ def test_input_and_output_in_the_same_memory(harness, wiring, dtype, n_layers, r
         for a, b in zip(want, got):
             assert torch.equal(a, b), place
     ctx.free()
+
+
+@pytest.mark.parametrize("dtype,hidden,nq,nkv,d,inter,rows,shards,n_std,n_layers", [
+    ("fp32", 264, 3, 3, 30, 345, 1, 2, 0, 3),      # weights and cache rows element by element
+    ("fp32", 264, 4, 2, 30, 96, 5, 2, 1, 3),       # behind a standard layer
+    ("fp32", 136, 2, 1, 64, 3840, 32, 1, 0, 2),    # QKV and gate/up: 512 workgroups together
+    ("fp32", 136, 2, 1, 64, 3841, 32, 1, 0, 2),    # and more
+    ("fp32", 136, 7, 7, 16, 64, 64, 1, 0, 2),      # attention and down: 496
+    ("fp32", 136, 8, 8, 16, 64, 64, 1, 0, 2),      # 560
+    ("bf16", 256, 4, 2, 64, 352, 1, 1, 0, 1),
+    ("bf16", 264, 4, 2, 64, 345, 9, 2, 0, 2),      # (bf16 weights one by one: reduce kernel)
+])
+def test_modules_beside_each_other(harness, dtype, hidden, nq, nkv, d, inter, rows, shards, n_std, n_layers):
+    """A layer's modules share launches where the MLP does not read the attention's output and two workgroups per CU hold them; with an emulated
+    latency they run one after the other: the same bits, and the right ones."""
+    w = BASE.with_(name="beside", dtype=dtype, n_layers=n_layers, hidden=hidden, n_q_heads=nq, n_kv_heads=nkv, head_dim=d, inter=inter, prefill=rows,
+                   tp_degree=shards + 1, n_real_shards=shards, peer_pool=2)
+    tensors = harness.make_tensors(w)
+    runs = [harness.run_case(w, tensors=tensors, gpu_only=delay > 0, n_standard_layers=n_std, kernel_path=ladder.LADDER_PATH_GENERIC,
+                             reduce_delay_us=delay) for delay in (0, 5)]
+    assert max(runs[0].errs) < (1e-4 if dtype == "fp32" else 0.0029 * (2 * n_layers) ** 0.5 * 5.8), runs[0].errs
+    for a, b in zip(*(r.gpu for r in runs)):
+        assert np.array_equal(a, b)
