@@ -213,7 +213,8 @@ hipError_t launch_embed_gather(const int* tokens, const void* table, void* x_out
 hipError_t launch_head_norm(const float* x, const void* gain, void* y, int rows, int H, float eps, bool is_bf16,
                             hipStream_t s);
 // tokens_out[r] = index of the largest of logits[r][0..V), the lowest index among equal maxima
-hipError_t launch_argmax(const float* logits, int* tokens_out, int rows, int V, hipStream_t s);
+// (scratch: memory of scratch_per_row bytes per row that nothing needs any more; may be null with 0)
+hipError_t launch_argmax(const float* logits, int* tokens_out, int rows, int V, void* scratch, size_t scratch_per_row, hipStream_t s);
 
 // ---- bf16 streaming / MFMA path ----------------------------------------------------------------
 // Packed weight format ("tiles"): the [K][N] matrix is cut into tiles of 32 k x 16 n; tile (nt, kt)

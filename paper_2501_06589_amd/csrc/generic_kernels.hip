@@ -951,82 +951,137 @@ hipError_t launch_embed_gather(const int* tokens, const void* table, void* x_out
   return hipGetLastError();
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void head_norm_kernel(const float* __restrict__ x, const T* __restrict__ gain,
-                                                        T* __restrict__ y, int H, float eps) {
-  __shared__ float part[4];
+// (a thread's elements of a pass in registers: one round trip for 8192 columns of 1024 threads, which long rows take)
+template <typename T, int THREADS>
+__global__ __launch_bounds__(THREADS) void head_norm_kernel(const float* __restrict__ x, const T* __restrict__ gain,
+                                                            T* __restrict__ y, int H, float eps) {
+  constexpr int N = 8;
+  __shared__ float part[THREADS / 64];
   const float* xr = x + (size_t)blockIdx.x * H;
-  float ss = 0.f;
-  for (int i = threadIdx.x; i < H; i += 256) ss = fmaf(xr[i], xr[i], ss);
+  float v[N], ss = 0.f;
+#pragma unroll
+  for (int e = 0; e < N; ++e) v[e] = (int)threadIdx.x + e * THREADS < H ? xr[threadIdx.x + e * THREADS] : 0.f;
+#pragma unroll
+  for (int e = 0; e < N; ++e) ss = fmaf(v[e], v[e], ss);
+  for (int i = threadIdx.x + N * THREADS; i < H; i += THREADS) ss = fmaf(xr[i], xr[i], ss);
   ss = wave_sum(ss);
   if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
   __syncthreads();
-  const float rs = 1.0f / sqrtf((part[0] + part[1] + part[2] + part[3]) / (float)H + eps);
-  for (int i = threadIdx.x; i < H; i += 256)
+  ss = 0.f;
+#pragma unroll
+  for (int w = 0; w < THREADS / 64; ++w) ss += part[w];
+  const float rs = 1.0f / sqrtf(ss / (float)H + eps);
+#pragma unroll
+  for (int e = 0; e < N; ++e) {
+    const int i = threadIdx.x + e * THREADS;
+    if (i < H) store_f(y + (size_t)blockIdx.x * H + i, v[e] * rs * (gain ? load_f(gain + i) : 1.0f));
+  }
+  for (int i = threadIdx.x + N * THREADS; i < H; i += THREADS)
     store_f(y + (size_t)blockIdx.x * H + i, xr[i] * rs * (gain ? load_f(gain + i) : 1.0f));
 }
 
+template <typename T>
+static void launch_head_norm_t(const float* x, const void* gain, void* y, int rows, int H, float eps, hipStream_t s) {
+  if (H > 2048) hipLaunchKernelGGL((head_norm_kernel<T, 1024>), dim3(rows), dim3(1024), 0, s, x, (const T*)gain, (T*)y, H, eps);
+  else hipLaunchKernelGGL((head_norm_kernel<T, 256>), dim3(rows), dim3(256), 0, s, x, (const T*)gain, (T*)y, H, eps);
+}
 hipError_t launch_head_norm(const float* x, const void* gain, void* y, int rows, int H, float eps, bool is_bf16,
                             hipStream_t s) {
   if (rows <= 0) return hipSuccess;
-  if (is_bf16) hipLaunchKernelGGL(head_norm_kernel<bf16_t>, dim3(rows), dim3(256), 0, s, x, (const bf16_t*)gain, (bf16_t*)y, H, eps);
-  else hipLaunchKernelGGL(head_norm_kernel<float>, dim3(rows), dim3(256), 0, s, x, (const float*)gain, (float*)y, H, eps);
+  if (is_bf16) launch_head_norm_t<bf16_t>(x, gain, y, rows, H, eps, s);
+  else launch_head_norm_t<float>(x, gain, y, rows, H, eps, s);
   return hipGetLastError();
 }
 
-// One workgroup per row (it needs no memory between workgroups, which a caller that cannot allocate would have to have);
-// what bounds it is how much of the row one CU has in flight, so 1024 threads request 16 bytes four times over before they
-// compare: 16 rows of 128256 logits 141 -> 12.5 us (256
-// threads, one element at a time, before).
 // A thread keeps the first maximum of its share (indices ascending), the merge prefers the lower index among equal values,
 // so the result is the first arg max of the row; a NaN gives way to any number.
-__global__ __launch_bounds__(1024) void argmax_kernel(const float* __restrict__ logits, int* __restrict__ out, int V, int vec) {
-  constexpr int NONE = 0x7fffffff;
-  __shared__ float bv[16];
-  __shared__ int bi[16];
-  const float* lr = logits + (size_t)blockIdx.x * V;
-  float best = -INFINITY;
-  int at = NONE;
+// What bounds it is how much of a row is in flight, so threads request 16 bytes four times over before they compare, and rows of
+// ARGMAX_SPLIT_V logits and more are cut over ARGMAX_PARTS workgroups, whose picks a second kernel merges; they lie where the normed rows lay
+// that the logits were made from.  16 rows of 128256 logits ARGMAX_US; of 32000 ARGMAX_US2.
+// ------------------------------------------------------------------------------------------------
+struct Pick {
+  float best;
+  int at;      // ARGMAX_NONE: none yet
+};
+constexpr int ARGMAX_NONE = 0x7fffffff;
+__device__ __forceinline__ void pick_merge(Pick& p, float ov, int oi) {
+  if (oi != ARGMAX_NONE && (p.at == ARGMAX_NONE || ov > p.best || (ov == p.best && oi < p.at) || (p.best != p.best && (ov == ov || oi < p.at)))) {
+    p.best = ov;
+    p.at = oi;
+  }
+}
+// THREADS threads take the elements from .. to - 1 of a row (with vec both multiples of 4, except the row's end); the result is thread 0's
+template <int THREADS>
+__device__ __forceinline__ Pick pick_first_max(const float* __restrict__ lr, int from, int to, int vec) {
+  __shared__ float bv[THREADS / 64];
+  __shared__ int bi[THREADS / 64];
+  Pick p{-INFINITY, ARGMAX_NONE};
   auto take = [&](float v, int i) {
-    if (at == NONE || v > best || best != best) { best = v; at = i; }   // strictly greater: the earliest index stays
+    if (p.at == ARGMAX_NONE || v > p.best || p.best != p.best) { p.best = v; p.at = i; }   // strictly greater: the earliest index stays
   };
   if (vec) {
     const float4* l4 = reinterpret_cast<const float4*>(lr);
-    const int n4 = V >> 2;
-    for (int i0 = threadIdx.x; i0 < n4; i0 += 4096) {
+    const int n4 = to >> 2;
+    for (int i0 = (from >> 2) + threadIdx.x; i0 < n4; i0 += 4 * THREADS) {
       float4 v[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = l4[min(i0 + u * 1024, n4 - 1)];
+      for (int u = 0; u < 4; ++u) v[u] = l4[min(i0 + u * THREADS, n4 - 1)];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int i = i0 + u * 1024;
+        const int i = i0 + u * THREADS;
         if (i < n4) { take(v[u].x, 4 * i); take(v[u].y, 4 * i + 1); take(v[u].z, 4 * i + 2); take(v[u].w, 4 * i + 3); }
       }
     }
   } else {
-    for (int i = threadIdx.x; i < V; i += 1024) take(lr[i], i);
+    for (int i = from + threadIdx.x; i < to; i += THREADS) take(lr[i], i);
   }
-  auto merge = [&](float ov, int oi) {
-    if (oi != NONE && (at == NONE || ov > best || (ov == best && oi < at) || (best != best && (ov == ov || oi < at)))) { best = ov; at = oi; }
-  };
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
-    const float ov = __shfl_xor(best, o, 64);
-    const int oi = __shfl_xor(at, o, 64);
-    merge(ov, oi);
+    const float ov = __shfl_xor(p.best, o, 64);
+    const int oi = __shfl_xor(p.at, o, 64);
+    pick_merge(p, ov, oi);
   }
   const int wave = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) { bv[wave] = best; bi[wave] = at; }
+  if ((threadIdx.x & 63) == 0) { bv[wave] = p.best; bi[wave] = p.at; }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int w = 1; w < 16; ++w) merge(bv[w], bi[w]);
-    out[blockIdx.x] = at == NONE ? 0 : at;
-  }
+  if (threadIdx.x == 0)
+    for (int w = 1; w < THREADS / 64; ++w) pick_merge(p, bv[w], bi[w]);
+  return p;
 }
 
-hipError_t launch_argmax(const float* logits, int* tokens_out, int rows, int V, hipStream_t s) {
+__global__ __launch_bounds__(1024) void argmax_kernel(const float* __restrict__ logits, int* __restrict__ out, int V, int vec) {
+  const Pick p = pick_first_max<1024>(logits + (size_t)blockIdx.x * V, 0, V, vec);
+  if (threadIdx.x == 0) out[blockIdx.x] = p.at == ARGMAX_NONE ? 0 : p.at;
+}
+
+#define ARGMAX_PARTS 16
+#define ARGMAX_SPLIT_V 32000
+__global__ __launch_bounds__(256) void argmax_part_kernel(const float* __restrict__ logits, Pick* __restrict__ picks, int V) {
+  const int per = ((V + ARGMAX_PARTS - 1) / ARGMAX_PARTS + 3) & ~3, from = min(V, (int)blockIdx.x * per);
+  const Pick p = pick_first_max<256>(logits + (size_t)blockIdx.y * V, from, min(V, from + per), 1);
+  if (threadIdx.x == 0) picks[(size_t)blockIdx.y * ARGMAX_PARTS + blockIdx.x] = p;
+}
+// (one wavefront per row)
+__global__ __launch_bounds__(64) void argmax_merge_kernel(const Pick* __restrict__ picks, int* __restrict__ out) {
+  Pick p{-INFINITY, ARGMAX_NONE};
+  if (threadIdx.x < ARGMAX_PARTS) p = picks[(size_t)blockIdx.x * ARGMAX_PARTS + threadIdx.x];
+#pragma unroll
+  for (int o = ARGMAX_PARTS / 2; o > 0; o >>= 1) {
+    const float ov = __shfl_xor(p.best, o, 64);
+    const int oi = __shfl_xor(p.at, o, 64);
+    pick_merge(p, ov, oi);
+  }
+  if (threadIdx.x == 0) out[blockIdx.x] = p.at == ARGMAX_NONE ? 0 : p.at;
+}
+
+hipError_t launch_argmax(const float* logits, int* tokens_out, int rows, int V, void* scratch, size_t scratch_per_row, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
   const int vec = V % 4 == 0 && ((uintptr_t)logits & 15) == 0;
+  if (vec && V >= ARGMAX_SPLIT_V && rows <= 65535 && scratch_per_row >= ARGMAX_PARTS * sizeof(Pick)) {
+    hipLaunchKernelGGL(argmax_part_kernel, dim3(ARGMAX_PARTS, rows), dim3(256), 0, s, logits, (Pick*)scratch, V);
+    hipLaunchKernelGGL(argmax_merge_kernel, dim3(rows), dim3(64), 0, s, (const Pick*)scratch, tokens_out);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(argmax_kernel, dim3(rows), dim3(1024), 0, s, logits, tokens_out, V, vec);
   return hipGetLastError();
 }

@@ -2159,7 +2159,7 @@ static int head_body(ladder_ctx* c, const float* x, int rows, char* y, float* lo
     a.x = (const bf16_t*)y; a.ldx = H; a.wp = c->head_wp; a.M = rows; a.K = H; a.N = V; a.out = logits; a.epilogue = 0;
     HIP_TRY(c, launch_gemm_mfma(a, s));
   }
-  if (tokens_out) HIP_TRY(c, launch_argmax(logits, tokens_out, rows, V, s));
+  if (tokens_out) HIP_TRY(c, launch_argmax(logits, tokens_out, rows, V, y, (size_t)H * c->esz, s));
   return LADDER_OK;
 }
 
