@@ -209,8 +209,8 @@ hipError_t launch_swiglu_parts(const float* parts, int n_parts, size_t part_stri
 // *bad_id (host-visible memory, may be null) to 1
 hipError_t launch_embed_gather(const int* tokens, const void* table, void* x_out, int rows, int H, int vocab,
                                unsigned* bad_id, bool is_bf16, hipStream_t s);
-// y[r][:] = x[r][:] / sqrt(mean(x[r]^2) + eps) * gain   (gain may be null = 1); y: T
-hipError_t launch_head_norm(const float* x, const void* gain, void* y, int rows, int H, float eps, bool is_bf16,
+// y[r][:] = x[r][:] / sqrt(mean(x[r]^2) + eps) * gain   (gain may be null = 1); y: T [rows][H], or (tiled, H % 8 == 0) [H / 8][rows][8]
+hipError_t launch_head_norm(const float* x, const void* gain, void* y, int rows, int H, float eps, bool tiled, bool is_bf16,
                             hipStream_t s);
 // tokens_out[r] = index of the largest of logits[r][0..V), the lowest index among equal maxima
 // (scratch: memory of scratch_per_row bytes per row that nothing needs any more; may be null with 0)
@@ -231,8 +231,9 @@ static inline size_t packed_tiles_bytes(int K, int N) {
 hipError_t launch_repack_tiles(const bf16_t* src, void* dst, int K, int N, int N_total, int col0, int mode, hipStream_t s);
 
 struct GemvArgs {
-  const bf16_t* x;         // bf16 [M][ldx]
+  const bf16_t* x;         // bf16 [M][ldx], or (x_tiled) [K / 8][M][8]: what a wavefront reads of a k tile is one piece of memory
   int ldx;
+  int x_tiled;
   const void* wp;          // packed tiles, N_total columns, K rows
   int M, K, N;             // N = packed column count (multiple of 16 after padding)
   int ksplit;              // workgroups along K; out slot = slot0 + ks

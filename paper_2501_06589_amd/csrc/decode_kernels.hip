@@ -50,7 +50,9 @@ hipError_t launch_repack_tiles(const bf16_t* src, void* dst, int K, int N, int N
 // HBM-bound: every weight byte is read once, as one coalesced 1 KiB tile per wavefront load
 // (non-temporal: the stream must not evict x from the caches), and goes straight into the A operand
 // of a 16x16x32 bf16 MFMA; the B operand is the matching 16 rows x 32 k slice of x (rows >= M zeroed),
-// read from L1/L2 once per k tile and shared by the wave's TN column tiles.  A workgroup owns TN
+// read from L1/L2 once per k tile and shared by the wave's TN column tiles (where the producer can lay it out so, x_tiled, as
+// one piece of memory instead of 64 bytes from each row: head of 128256 logits, hidden 4096, 16 rows 199 -> 185 us, 4096 x 32000 59.8 -> 54.9; four
+// rows and fewer no different.  Four column tiles instead, which read it half as often: 16 rows 199 / 204, one row 168 / 189).  A workgroup owns TN
 // adjacent 16-column tiles and a K range; its WAVES wavefronts split that range and add up through
 // LDS in a fixed order (wave 0.., then the ksplit slots by the consumer).
 // Latency hiding is explicit: two register buffers of U k-tiles each, the next batch is always in
@@ -81,7 +83,8 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_mfma_kernel(GemvArgs a) {
 
   const u32x4_t* wptr = reinterpret_cast<const u32x4_t*>(a.wp) + ((size_t)nt0 * KT) * 64 + lane;
   const bool rowok = b < a.M;
-  const bf16_t* xptr = a.x + (size_t)min(b, a.M - 1) * a.ldx + q * 8;
+  const int x_kt = a.x_tiled ? 32 * a.M : 32;   // elements per k tile
+  const bf16_t* xptr = a.x + (a.x_tiled ? (size_t)(q * a.M + min(b, a.M - 1)) * 8 : (size_t)min(b, a.M - 1) * a.ldx + q * 8);
   u32x4_t wa[TN][U], wb[TN][U], xa[U], xb[U];
   auto load = [&](u32x4_t (&wv)[TN][U], u32x4_t (&xv)[U], int kt) {
 #pragma unroll
@@ -89,7 +92,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_mfma_kernel(GemvArgs a) {
       const int ktc = min(kt + u, kt1 - 1);
 #pragma unroll
       for (int j = 0; j < TN; ++j) wv[j][u] = __builtin_nontemporal_load(wptr + ((size_t)j * KT + ktc) * 64);
-      xv[u] = *reinterpret_cast<const u32x4_t*>(xptr + (size_t)ktc * 32);
+      xv[u] = *reinterpret_cast<const u32x4_t*>(xptr + (size_t)ktc * x_kt);
     }
   };
   auto fma = [&](const u32x4_t (&wv)[TN][U], const u32x4_t (&xv)[U], int kt) {

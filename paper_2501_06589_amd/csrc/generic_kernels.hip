@@ -954,8 +954,9 @@ hipError_t launch_embed_gather(const int* tokens, const void* table, void* x_out
 // (a thread's elements of a pass in registers: one round trip for 8192 columns of 1024 threads, which long rows take)
 template <typename T, int THREADS>
 __global__ __launch_bounds__(THREADS) void head_norm_kernel(const float* __restrict__ x, const T* __restrict__ gain,
-                                                            T* __restrict__ y, int H, float eps) {
+                                                            T* __restrict__ y, int H, float eps, int tiled) {
   constexpr int N = 8;
+  const auto at = [&](int i) { return tiled ? ((size_t)(i >> 3) * gridDim.x + blockIdx.x) * 8 + (i & 7) : (size_t)blockIdx.x * H + i; };
   __shared__ float part[THREADS / 64];
   const float* xr = x + (size_t)blockIdx.x * H;
   float v[N], ss = 0.f;
@@ -974,22 +975,23 @@ __global__ __launch_bounds__(THREADS) void head_norm_kernel(const float* __restr
 #pragma unroll
   for (int e = 0; e < N; ++e) {
     const int i = threadIdx.x + e * THREADS;
-    if (i < H) store_f(y + (size_t)blockIdx.x * H + i, v[e] * rs * (gain ? load_f(gain + i) : 1.0f));
+    if (i < H) store_f(y + at(i), v[e] * rs * (gain ? load_f(gain + i) : 1.0f));
   }
   for (int i = threadIdx.x + N * THREADS; i < H; i += THREADS)
-    store_f(y + (size_t)blockIdx.x * H + i, xr[i] * rs * (gain ? load_f(gain + i) : 1.0f));
+    store_f(y + at(i), xr[i] * rs * (gain ? load_f(gain + i) : 1.0f));
 }
 
 template <typename T>
-static void launch_head_norm_t(const float* x, const void* gain, void* y, int rows, int H, float eps, hipStream_t s) {
-  if (H > 2048) hipLaunchKernelGGL((head_norm_kernel<T, 1024>), dim3(rows), dim3(1024), 0, s, x, (const T*)gain, (T*)y, H, eps);
-  else hipLaunchKernelGGL((head_norm_kernel<T, 256>), dim3(rows), dim3(256), 0, s, x, (const T*)gain, (T*)y, H, eps);
+static void launch_head_norm_t(const float* x, const void* gain, void* y, int rows, int H, float eps, bool tiled, hipStream_t s) {
+  if (H > 2048) hipLaunchKernelGGL((head_norm_kernel<T, 1024>), dim3(rows), dim3(1024), 0, s, x, (const T*)gain, (T*)y, H, eps, tiled ? 1 : 0);
+  else hipLaunchKernelGGL((head_norm_kernel<T, 256>), dim3(rows), dim3(256), 0, s, x, (const T*)gain, (T*)y, H, eps, tiled ? 1 : 0);
 }
-hipError_t launch_head_norm(const float* x, const void* gain, void* y, int rows, int H, float eps, bool is_bf16,
+hipError_t launch_head_norm(const float* x, const void* gain, void* y, int rows, int H, float eps, bool tiled, bool is_bf16,
                             hipStream_t s) {
   if (rows <= 0) return hipSuccess;
-  if (is_bf16) launch_head_norm_t<bf16_t>(x, gain, y, rows, H, eps, s);
-  else launch_head_norm_t<float>(x, gain, y, rows, H, eps, s);
+  if (tiled && (H & 7)) return hipErrorInvalidValue;
+  if (is_bf16) launch_head_norm_t<bf16_t>(x, gain, y, rows, H, eps, tiled, s);
+  else launch_head_norm_t<float>(x, gain, y, rows, H, eps, tiled, s);
   return hipGetLastError();
 }
 
@@ -997,7 +999,8 @@ hipError_t launch_head_norm(const float* x, const void* gain, void* y, int rows,
 // so the result is the first arg max of the row; a NaN gives way to any number.
 // What bounds it is how much of a row is in flight, so threads request 16 bytes four times over before they compare, and rows of
 // ARGMAX_SPLIT_V logits and more are cut over ARGMAX_PARTS workgroups, whose picks a second kernel merges; they lie where the normed rows lay
-// that the logits were made from.  16 rows of 128256 logits ARGMAX_US; of 32000 ARGMAX_US2.
+// that the logits were made from.  16 rows of 128256 logits, one workgroup per row / cut: 12.5 / 4.9 + 4.6 us as the profiler has them, the whole
+// head 205 / 193 with the norm's 1024 threads; 32000 logits, one row, 54.3 / 50.5; below that a row is one round trip either way.
 // ------------------------------------------------------------------------------------------------
 struct Pick {
   float best;

@@ -2144,14 +2144,16 @@ static int head_body(ladder_ctx* c, const float* x, int rows, char* y, float* lo
   const ladder_config& g = c->cfg;
   const int H = g.hidden, V = c->vocab_local;
   hipStream_t s = c->main;
-  HIP_TRY(c, launch_head_norm(x, c->head_gain, y, rows, H, g.rms_eps, c->bf16, s));
+  // what the skinny GEMM takes: whole pairs of tiles, and so many that K is not split
+  const bool skinny = c->head_fast && rows <= 16 && (V & 31) == 0 && gemv_plan(V, H, true).ksplit == 1;
+  HIP_TRY(c, launch_head_norm(x, c->head_gain, y, rows, H, g.rms_eps, skinny, c->bf16, s));
   if (!c->head_fast) {
     PlainGemmArgs a{};
     a.x = y; a.M = rows; a.K = H; a.n_shards = 1; a.held = PLAIN_HELD_WORKGROUPS; a.n_mat = 1; a.w[0] = c->head_w; a.N[0] = V; a.epilogue = PLAIN_OUT; a.out = logits;
     HIP_TRY(c, launch_plain_gemm(a, c->bf16, s));
-  } else if (rows <= 16 && (V & 31) == 0 && gemv_plan(V, H, true).ksplit == 1) {   // (what the skinny GEMM takes: whole pairs of tiles, and so many that K is not split)
+  } else if (skinny) {
     GemvArgs a{};
-    a.x = (const bf16_t*)y; a.ldx = H; a.wp = c->head_wp; a.M = rows; a.K = H; a.N = V; a.ksplit = 1;
+    a.x = (const bf16_t*)y; a.ldx = H; a.x_tiled = 1; a.wp = c->head_wp; a.M = rows; a.K = H; a.N = V; a.ksplit = 1;
     a.out = logits; a.out_stride = (size_t)rows * V; a.slot0 = 0; a.epilogue = 0;
     HIP_TRY(c, launch_gemv(a, s));
   } else {

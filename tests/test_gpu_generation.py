@@ -129,3 +129,34 @@ def test_token_id_outside_the_table_is_reported_by_the_next_call(harness):
     torch.cuda.synchronize()
     assert ctx.position() == (4, 2)
     ctx.free()
+
+
+@pytest.mark.parametrize("rows,vocab", [(1, 31988), (3, 32000), (16, 32000), (17, 32032), (5, 32004), (16, 100000)])
+def test_arg_max_of_long_rows(rows, vocab):
+    """Rows at and beyond the length from which sixteen workgroups share one: the first of equal maxima wins across the parts' borders; the
+    logits, of rows in either layout, against float64."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    H = 256
+    g = torch.Generator().manual_seed(rows + vocab)
+    cfg = ladder.make_config(n_layers=1, hidden=H, n_q_heads=2, n_kv_heads=1, head_dim=64, inter=352, max_batch=17, max_seq=128, max_tokens=1,
+                             dtype=ladder.LADDER_BF16)
+    ctx = ladder.Ladder(cfg)
+    w = (torch.randn(H, vocab, generator=g) * 0.02)
+    per = (-(-vocab // 16) + 3) // 4 * 4
+    x = torch.randn(rows, H, generator=g)
+    twin = (x[0] / x[0].norm()).to(torch.bfloat16).float()     # equal columns: row 0's maximum on both sides of a part's border and at the end
+    for at in (per - 1, per, vocab - 1):
+        w[:, at] = twin
+    w = w.to(torch.bfloat16)
+    gain = torch.ones(H, dtype=torch.bfloat16)
+    ctx.load_head(torch.zeros(vocab, H, dtype=torch.bfloat16).cuda(), gain.cuda(), w.cuda())
+    logits, tokens = ctx.head(x.cuda())
+    xd = x.double()
+    y = (xd / torch.sqrt((xd * xd).mean(-1, keepdim=True) + cfg.rms_eps)).to(torch.bfloat16).double()
+    want = y @ w.double()
+    # (each logit's 256 products are exact in fp32; their sum is rounded 256 times at most)
+    assert (logits.cpu().double() - want).abs().max() < 256 * 2.0 ** -24 * (y.abs() @ w.double().abs()).max()
+    assert np.array_equal(tokens.cpu().numpy(), np.argmax(logits.cpu().numpy(), axis=-1))
+    assert int(tokens[0]) == per - 1
+    ctx.free()
