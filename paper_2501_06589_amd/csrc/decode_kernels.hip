@@ -235,10 +235,10 @@ __global__ __launch_bounds__(256, 3) void attn_decode_kernel(AttnDecodeArgs a) {
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int s = 0; s < DS; ++s)
-        x.k[t][s] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(kb + (size_t)(blk * 32 + 4 * t) * D + s * 32));
+        x.k[t][s] = *reinterpret_cast<const u32x4_t*>(kb + (size_t)(blk * 32 + 4 * t) * D + s * 32);
 #pragma unroll
     for (int t = 0; t < DT; ++t)
-      x.v[t] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(vb + (size_t)t * 16 * a.max_seq + blk * 32));
+      x.v[t] = *reinterpret_cast<const u32x4_t*>(vb + (size_t)t * 16 * a.max_seq + blk * 32);
   };
   auto compute = [&](Block& x, int blk) {
     const int ahead = p1 - (p0 + blk * 32);
