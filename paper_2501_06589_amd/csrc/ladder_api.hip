@@ -801,8 +801,14 @@ int forward_body(ladder_ctx* c, const void* x_in, int B, int T, int pos0, bool d
   const bool independent = c->cfg.wiring == LADDER_WIRING_LADDER && c->cfg.n_standard_layers == 0 && c->cfg.n_layers > 1 &&
                            (c->cfg.n_layers >= 4 || all_bytes * (200.0 + rows) >= 230e9);
   const bool pays = !c->fast || T == 1 || (rows <= 64 && c->cfg.reduce_delay_us > 0) ? rows <= 64 : rows <= (independent ? FEW_ROWS : 64) && (rows <= 256 || rows > 512) && layer_bytes * (200.0 + rows) >= 32e9;
+  // (a decode step of a short layer in order all the same: a launch takes longer than the bytes it reads there, and the events between two
+  // streams are launches more.  Weights and cache of a layer, MB, and us of 8 steps, in order / side by side: 1.2B (4 layers), batch 20 behind 200 and 1000
+  // positions, 110, 1938 / 2190, 176, 2473 / 2400; batch 40 behind 300, 143, 2208 / 2240; batch 64 behind 300, 173, 2531 / 2320; 70B R = 8 (3), batch 20
+  // behind 100, 215, 1970 / 1950.)
+  const double cache_bytes = 2.0 * c->cfg.n_kv_heads * c->cfg.head_dim * c->esz * c->cfg.n_real_shards * rows * c->pos;
+  const bool step_of_short_layer = c->fast && T == 1 && decode && c->cfg.reduce_delay_us == 0 && layer_bytes + cache_bytes < 140e6;
   const bool small = rows <= 64 && !st && !brief;
-  const bool overlap = pays && !st && !brief && c->cfg.overlap_modules != 0;
+  const bool overlap = pays && !st && !brief && !step_of_short_layer && c->cfg.overlap_modules != 0;
   const bool side = small && c->cfg.overlap_modules == 0 && c->cfg.reduce_on_side_stream != 0;
   // the plain path, up to PLAIN_NORM_ROWS rows: module inputs made where they are multiplied, by every column block anew, which
   // pays while that is little beside a block's 64 columns of weights (four rows per block beyond one).  It rounds otherwise than a reduce and
