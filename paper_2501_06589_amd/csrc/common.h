@@ -83,6 +83,9 @@ struct ReduceNormArgs {
   float eps;
 };
 hipError_t launch_reduce_norm(const ReduceNormArgs& a, bool is_bf16, hipStream_t s);
+// a, then b on the same rows in place (bf16; no embeddings, no other source; a leaves no copy, b no step)
+bool reduce_norm_two_fits(int H);
+hipError_t launch_reduce_norm_two(const ReduceNormArgs& a, const ReduceNormArgs& b, hipStream_t s);
 
 // out_a[r][:] = rmsnorm(emb[r][:]) * gain_a, out_b likewise (or null), all bf16 [rows][H], on 16-byte boundaries except emb (8); H <= 16384, a multiple of 8
 #define EMBED_NORM_MAX_H 16384
@@ -309,6 +312,9 @@ struct GemmArgs {
   size_t out_stride;       // elements
 };
 hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s);
+// two products that do not depend on each other in one launch, where there is a kernel for their tiles (gemm_pairs)
+bool gemm_pairs(const GemmArgs& a, const GemmArgs& b);
+hipError_t launch_gemm_pair(const GemmArgs& a, const GemmArgs& b, hipStream_t s);
 // epilogue 0: the number of workgroups along K (1 .. max_split) that suits an M x N x K product
 // (extra_us: what taking a split at all costs beside the product)
 int gemm_ksplit(int M, int N, int K, int max_split, float extra_us);

@@ -30,6 +30,10 @@ template <> __device__ __forceinline__ void store4<bf16_t>(bf16_t* p, const floa
 // (Algorithm 1) with the AllReduce written as a sum over rank partial sums (Eq. 2).
 // One workgroup per row; the summation order is fixed: x, parts 0.., peers 0.. .
 // ------------------------------------------------------------------------------------------------
+// The squares of four columns, in an order that is written out: left to the compiler, two kernels around it may round differently, and the schedules
+// that call for one or the other are to give the same bits.
+__device__ __forceinline__ float squares4(const float (&v)[4]) { return fmaf(v[3], v[3], fmaf(v[2], v[2], fmaf(v[0], v[0], v[1] * v[1]))); }
+
 // STEP: x_out takes the step (a.x_step), for which the old values stay in registers past the sums; a branch of one kernel cost every
 // reduce of a wide decode step 0.2 - 0.3 us (1.2B, 4 layers, 50 sequences, 8 steps 2692 -> 2675 us).
 template <typename T, bool STEP>
@@ -60,7 +64,7 @@ __global__ void reduce_norm_kernel(ReduceNormArgs a) {
     } else if (a.x_out) {
       store4<float>(a.x_out + (size_t)row * H + i, v);
     }
-    ss += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+    ss += squares4(v);
   }
   if (!a.out_a && !a.out_b) return;
   __shared__ float red[16];
@@ -100,6 +104,85 @@ hipError_t launch_reduce_norm(const ReduceNormArgs& a, bool is_bf16, hipStream_t
   auto* const kernel = is_bf16 ? (step ? reduce_norm_kernel<bf16_t, true> : reduce_norm_kernel<bf16_t, false>)
                                : (step ? reduce_norm_kernel<float, true> : reduce_norm_kernel<float, false>);
   hipLaunchKernelGGL(kernel, dim3(a.rows), dim3(threads), 0, s, a);
+  return hipGetLastError();
+}
+
+// Two reduces of a stream in one pass (modules m and m + 1, whose outputs are both there): a's partial sums and peers, whose rows a's outputs are made
+// from, then b's; the rows stay in registers (C pieces of 4 columns per thread) and only the second ones are stored.  Same order of sums as one by one.
+template <typename T, int C>
+__global__ __launch_bounds__(1024) void reduce_norm_two_kernel(ReduceNormArgs a, ReduceNormArgs b) {
+  const int H = a.H, step = blockDim.x * 4;
+  const size_t row = (size_t)blockIdx.x * H;
+  __shared__ float red[2][16];
+  float v[2][C][4], ss[2] = {0.f, 0.f};
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const int i = threadIdx.x * 4 + c * step;
+    if (i >= H) break;
+    float x[4];
+    load4<float>(a.x + row + i, x);
+    auto add = [&](const ReduceNormArgs& r) {
+      auto pieces = [&](int n, auto load) {   // (four requested before the first is added)
+        for (int s0 = 0; s0 < n; s0 += 4) {
+          float t[4][4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (s0 + j < n) load(s0 + j, t[j]);
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (s0 + j < n)
+              for (int e = 0; e < 4; ++e) x[e] += t[j][e];
+        }
+      };
+      pieces(r.n_parts, [&](int s, float (&t)[4]) { load4<float>(r.parts + s * r.part_stride + row + i, t); });
+      pieces(r.n_peers, [&](int s, float (&t)[4]) { load4<T>(reinterpret_cast<const T*>(r.peers) + s * r.peer_stride + row + i, t); });
+    };
+    add(a);
+    for (int e = 0; e < 4; ++e) v[0][c][e] = x[e];
+    ss[0] += squares4(x);
+    add(b);
+    for (int e = 0; e < 4; ++e) v[1][c][e] = x[e];
+    ss[1] += squares4(x);
+    store4<float>(b.x + row + i, x);
+    if (b.x_out) store4<float>(b.x_out + row + i, x);
+  }
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    ss[k] = wave_sum(ss[k]);
+    if (lane == 0) red[k][wave] = ss[k];
+  }
+  __syncthreads();
+  auto give = [&](const float (&w)[C][4], const float* sums, void* out, const void* gain) {
+    if (!out) return;
+    float tot = 0.f;
+    for (int k = 0; k < nw; ++k) tot += sums[k];
+    const float rs = 1.0f / sqrtf(tot / (float)H + a.eps);
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const int i = threadIdx.x * 4 + c * step;
+      if (i >= H) break;
+      float g[4] = {1.f, 1.f, 1.f, 1.f}, y[4];
+      if (gain) load4<T>(reinterpret_cast<const T*>(gain) + i, g);
+      for (int e = 0; e < 4; ++e) y[e] = w[c][e] * rs * g[e];
+      store4<T>(reinterpret_cast<T*>(out) + row + i, y);
+    }
+  };
+  give(v[0], red[0], a.out_a, a.gain_a);
+  give(v[0], red[0], a.out_b, a.gain_b);
+  give(v[1], red[1], b.out_a, b.gain_a);
+  give(v[1], red[1], b.out_b, b.gain_b);
+}
+
+// (the threads per row of launch_reduce_norm: the same sums)
+bool reduce_norm_two_fits(int H) { return H % 4 == 0 && H <= 2 * 4 * (H >= 4096 ? 1024 : 256) * (H >= 4096 ? 1 : 2); }
+hipError_t launch_reduce_norm_two(const ReduceNormArgs& a, const ReduceNormArgs& b, hipStream_t s) {
+  if (a.rows <= 0) return hipSuccess;
+  if (!reduce_norm_two_fits(a.H) || a.H != b.H || a.rows != b.rows || a.x != b.x || a.emb || b.emb || a.x_src || b.x_src || a.x_out || b.x_step) return hipErrorInvalidValue;
+  const int threads = a.H >= 4096 ? 1024 : 256;
+  if (a.H <= 4 * threads) hipLaunchKernelGGL((reduce_norm_two_kernel<bf16_t, 1>), dim3(a.rows), dim3(threads), 0, s, a, b);
+  else if (a.H <= 8 * threads) hipLaunchKernelGGL((reduce_norm_two_kernel<bf16_t, 2>), dim3(a.rows), dim3(threads), 0, s, a, b);
+  else hipLaunchKernelGGL((reduce_norm_two_kernel<bf16_t, 4>), dim3(a.rows), dim3(threads), 0, s, a, b);
   return hipGetLastError();
 }
 

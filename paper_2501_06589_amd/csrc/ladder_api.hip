@@ -380,6 +380,15 @@ size_t row_slots_of(const ladder_config& g) {
 
 int max_slots(int rows) { return std::min(FEW_ROWS_SLOTS, FEW_ROWS_SLOTS * FEW_ROWS_FULL / rows); }
 
+// one projection of 17 .. FEW_ROWS rows that leaves partial products, a.ksplit slots of them, in out[slot][rows][N]
+GemmArgs few_rows_args(const char* x, int ldx, const char* wp, int rows, int K, int N, float* out, const float* row_scale) {
+  GemmArgs a{};
+  a.x = (const bf16_t*)x; a.ldx = ldx; a.wp = wp; a.M = rows; a.K = K; a.N = N; a.out = out; a.epilogue = 0; a.row_scale = row_scale;
+  a.ksplit = gemm_ksplit(rows, N, K, max_slots(rows), 0.f);
+  a.out_stride = (size_t)rows * N;
+  return a;
+}
+
 // one projection of a call of at most FEW_ROWS rows: out[slot][rows][N], returns the number of slots written
 int run_few_rows(ladder_ctx* c, const char* x, int ldx, const char* wp, int rows, int K, int N, float* out, hipStream_t s,
                  int* slots, const float* row_scale = nullptr) {
@@ -392,10 +401,7 @@ int run_few_rows(ladder_ctx* c, const char* x, int ldx, const char* wp, int rows
     HIP_TRY(c, timed(c, LADDER_K_GEMV, s, [&] { return launch_gemv(a, s); }));
     return LADDER_OK;
   }
-  GemmArgs a{};
-  a.x = (const bf16_t*)x; a.ldx = ldx; a.wp = wp; a.M = rows; a.K = K; a.N = N; a.out = out; a.epilogue = 0; a.row_scale = row_scale;
-  a.ksplit = gemm_ksplit(rows, N, K, max_slots(rows), 0.f);
-  a.out_stride = (size_t)rows * N;
+  const GemmArgs a = few_rows_args(x, ldx, wp, rows, K, N, out, row_scale);
   *slots = a.ksplit;
   HIP_TRY(c, timed(c, LADDER_K_GEMM, s, [&] { return launch_gemm_mfma(a, s); }));
   return LADDER_OK;
@@ -475,13 +481,81 @@ int run_module_plain(ladder_ctx* c, int m, int B, int T, int pos0, float* out, h
   return LADDER_OK;
 }
 
+// The pieces of the packed path's modules for calls of more than 16 rows.
+// QKV: partial products in c->qkv (epilogue 0: rotary and append follow, see run_rope_append), or rotary and append as its epilogue (epilogue 2)
+GemmArgs qkv_args(ladder_ctx* c, const LayerStore& L, const char* yin, const float* y_scale, int rows, int T, int pos0) {
+  const ladder_config& g = c->cfg;
+  const int H = g.hidden;
+  if (rows <= FEW_ROWS && (T == 1 || gemm_ksplit(rows, c->nqkv, H, max_slots(rows), SPLIT_KERNEL_US) > 1))
+    return few_rows_args(yin, H, L.pqkv, rows, H, c->nqkv, c->qkv, y_scale);
+  GemmArgs a{};
+  a.x = (const bf16_t*)yin; a.ldx = H; a.wp = L.pqkv; a.M = rows; a.K = H; a.N = c->nqkv; a.row_scale = y_scale; a.ksplit = 1;
+  if (T != 1) {
+    // rotary embedding and cache append are the GEMM's epilogue (no fp32 q|k|v round trip through memory)
+    a.epilogue = 2; a.q_out = (bf16_t*)c->qbuf; a.cache_k = (bf16_t*)L.cache_k; a.cache_v = (bf16_t*)L.cache_v;
+    a.cos_tab = c->cos_tab; a.sin_tab = c->sin_tab; a.T = T; a.pos0 = pos0; a.nq = g.n_q_heads; a.nkv = g.n_kv_heads; a.d = g.head_dim; a.max_seq = c->s_cap;
+  } else {   // (one token for each of more than FEW_ROWS sequences: in a decode step the position lives in device memory)
+    a.out = c->qkv; a.epilogue = 0;
+  }
+  return a;
+}
+
+int run_rope_append(ladder_ctx* c, const LayerStore& L, int slots, int B, int T, int pos0, const int* pos_dev, hipStream_t s) {
+  const ladder_config& g = c->cfg;
+  RopeAppendArgs ra{};
+  ra.qkv = c->qkv; ra.n_parts = slots; ra.part_stride = (size_t)B * T * c->nqkv;
+  ra.q_out = c->qbuf; ra.cache_k = L.cache_k; ra.cache_v = L.cache_v;
+  ra.cos_tab = c->cos_tab; ra.sin_tab = c->sin_tab;
+  ra.B = B; ra.T = T; ra.pos0 = pos0; ra.nq = g.n_q_heads; ra.nkv = g.n_kv_heads; ra.d = g.head_dim; ra.max_seq = c->s_cap; ra.pos_dev = pos_dev;
+  HIP_TRY(c, timed(c, LADDER_K_ROPE_APPEND, s, [&] { return launch_rope_append(ra, s); }));
+  return LADDER_OK;
+}
+
+int run_attention(ladder_ctx* c, const LayerStore& L, int B, int T, int pos0, const int* pos_dev, hipStream_t s) {
+  const ladder_config& g = c->cfg;
+  const int d = g.head_dim, nq = g.n_q_heads, nkv = g.n_kv_heads;
+  if (T == 1) {
+    AttnDecodeArgs aa{};
+    aa.q = (const bf16_t*)c->qbuf; aa.cache_k = (const bf16_t*)L.cache_k; aa.cache_v = (const bf16_t*)L.cache_v;
+    aa.part_o = c->att_o; aa.part_ml = c->att_ml; aa.o = (bf16_t*)c->obuf;
+    aa.B = B; aa.nq = nq; aa.nkv = nkv; aa.d = d; aa.max_seq = c->s_cap; aa.n_pos = pos0 + 1;
+    // launch shape fixed by the cache capacity (not the current position) so that a captured step
+    // stays valid as the sequence grows
+    aa.n_splits = attn_decode_splits(B, nkv, g.max_seq); aa.pos_dev = pos_dev;
+    HIP_TRY(c, timed(c, LADDER_K_ATTN_DECODE, s, [&] { return launch_attn_decode(aa, s); }));
+  } else {
+    AttnPrefillArgs aa{(const bf16_t*)c->qbuf, (const bf16_t*)L.cache_k, (const bf16_t*)L.cache_v,
+                       (bf16_t*)c->obuf, B, T, pos0, nq, nkv, d, c->s_cap};
+    HIP_TRY(c, timed(c, LADDER_K_ATTN_PREFILL, s, [&] { return launch_attn_prefill(aa, s); }));
+  }
+  return LADDER_OK;
+}
+
+// gate/up: the SwiGLU product in c->act (epilogue 1), or partial products in c->gu (epilogue 0: run_swiglu_parts follows)
+GemmArgs gate_up_args(ladder_ctx* c, const LayerStore& L, const char* yin, const float* y_scale, int rows) {
+  const ladder_config& g = c->cfg;
+  GemmArgs a{};
+  a.x = (const bf16_t*)yin; a.ldx = g.hidden; a.wp = L.pgu; a.M = rows; a.K = g.hidden; a.N = 2 * g.inter; a.row_scale = y_scale;
+  a.ksplit = gate_up_ksplit(g, rows);
+  if (a.ksplit > 1) { a.out = c->gu; a.epilogue = 0; a.out_stride = (size_t)rows * 2 * g.inter; }
+  else { a.act = (bf16_t*)c->act; a.epilogue = 1; }
+  return a;
+}
+
+int run_swiglu_parts(ladder_ctx* c, const GemmArgs& gate_up, hipStream_t s) {
+  HIP_TRY(c, timed(c, LADDER_K_OTHER, s, [&] {
+    return launch_swiglu_parts(c->gu, gate_up.ksplit, gate_up.out_stride, (bf16_t*)c->act, gate_up.M, c->cfg.inter, s);
+  }));
+  return LADDER_OK;
+}
+
 // ---------------------------------------------------------------------------------------------
 // one module's compute on the main stream; writes parts[m%2] and returns the number of slots written, or (fuse)
 // updates the residual itself and returns -1 slots: then no reduce follows
 // ---------------------------------------------------------------------------------------------
 int run_module(ladder_ctx* c, int m, int B, int T, int pos0, bool decode, hipStream_t s, int* n_slots, bool fuse, const void* emb, StreamCopy copy) {
   const ladder_config& g = c->cfg;
-  const int rows = B * T, H = g.hidden, d = g.head_dim, nq = g.n_q_heads, nkv = g.n_kv_heads, I = g.inter;
+  const int rows = B * T, H = g.hidden, nqd = g.n_q_heads * g.head_dim, I = g.inter;
   const int layer = (m - 1) / 2, par = m & 1;
   const bool is_attn = (m & 1) == 1;
   const char* yin = c->y[par];
@@ -491,54 +565,24 @@ int run_module(ladder_ctx* c, int m, int B, int T, int pos0, bool decode, hipStr
     *n_slots = g.n_real_shards;
     return run_module_plain(c, m, B, T, pos0, pout, s);
   }
-  const bool few = rows <= FEW_ROWS;
   // a decode step of the bf16 path reads the position from device memory, so that a captured one stays valid; a prefill of one
   // token starts at position 0 wherever the context stood before
   const int* pos_dev = decode ? c->pos_dev : nullptr;
-  int slots = 0;
+  int slots = 0, rc;
   for (int r = 0; r < g.n_real_shards; ++r) {
-    LayerStore& L = c->store[(size_t)layer * g.n_real_shards + r];
+    const LayerStore& L = c->store[(size_t)layer * g.n_real_shards + r];
     if (is_attn) {
       int qkv_slots = 1;
-      if (few && (T == 1 || rows <= 16 || gemm_ksplit(rows, c->nqkv, H, max_slots(rows), SPLIT_KERNEL_US) > 1)) {
-        const int rc = run_few_rows(c, yin, H, L.pqkv, rows, H, c->nqkv, c->qkv, s, &qkv_slots, c->y_scale[par]);
-        if (rc) return rc;
+      if (rows <= 16) {
+        if ((rc = run_few_rows(c, yin, H, L.pqkv, rows, H, c->nqkv, c->qkv, s, &qkv_slots, c->y_scale[par]))) return rc;
       } else {
-        GemmArgs a{};
-        a.x = (const bf16_t*)yin; a.ldx = H; a.wp = L.pqkv; a.M = rows; a.K = H; a.N = c->nqkv; a.row_scale = c->y_scale[par];
-        if (T != 1) {
-          // rotary embedding and cache append are the GEMM's epilogue (no fp32 q|k|v round trip through memory)
-          a.epilogue = 2; a.q_out = (bf16_t*)c->qbuf; a.cache_k = (bf16_t*)L.cache_k; a.cache_v = (bf16_t*)L.cache_v;
-          a.cos_tab = c->cos_tab; a.sin_tab = c->sin_tab; a.T = T; a.pos0 = pos0; a.nq = nq; a.nkv = nkv; a.d = d; a.max_seq = c->s_cap;
-          qkv_slots = 0;
-        } else {   // (one token for each of more than FEW_ROWS sequences: in a decode step the position lives in device memory)
-          a.out = c->qkv; a.epilogue = 0;
-        }
+        const GemmArgs a = qkv_args(c, L, yin, c->y_scale[par], rows, T, pos0);
+        qkv_slots = a.epilogue == 2 ? 0 : a.ksplit;
         HIP_TRY(c, timed(c, LADDER_K_GEMM, s, [&] { return launch_gemm_mfma(a, s); }));
       }
-      RopeAppendArgs ra{};
-      ra.qkv = c->qkv; ra.n_parts = qkv_slots; ra.part_stride = (size_t)rows * c->nqkv;
-      ra.q_out = c->qbuf; ra.cache_k = L.cache_k; ra.cache_v = L.cache_v;
-      ra.cos_tab = c->cos_tab; ra.sin_tab = c->sin_tab;
-      ra.B = B; ra.T = T; ra.pos0 = pos0; ra.nq = nq; ra.nkv = nkv; ra.d = d; ra.max_seq = c->s_cap; ra.pos_dev = pos_dev;
-      if (qkv_slots > 0) HIP_TRY(c, timed(c, LADDER_K_ROPE_APPEND, s, [&] { return launch_rope_append(ra, s); }));
-      if (T == 1) {
-        AttnDecodeArgs aa{};
-        aa.q = (const bf16_t*)c->qbuf; aa.cache_k = (const bf16_t*)L.cache_k; aa.cache_v = (const bf16_t*)L.cache_v;
-        aa.part_o = c->att_o; aa.part_ml = c->att_ml; aa.o = (bf16_t*)c->obuf;
-        aa.B = B; aa.nq = nq; aa.nkv = nkv; aa.d = d; aa.max_seq = c->s_cap; aa.n_pos = pos0 + 1;
-        // launch shape fixed by the cache capacity (not the current position) so that a captured step
-        // stays valid as the sequence grows
-        aa.n_splits = attn_decode_splits(B, nkv, g.max_seq); aa.pos_dev = pos_dev;
-        HIP_TRY(c, timed(c, LADDER_K_ATTN_DECODE, s, [&] { return launch_attn_decode(aa, s); }));
-      } else {
-        AttnPrefillArgs aa{(const bf16_t*)c->qbuf, (const bf16_t*)L.cache_k, (const bf16_t*)L.cache_v,
-                           (bf16_t*)c->obuf, B, T, pos0, nq, nkv, d, c->s_cap};
-        HIP_TRY(c, timed(c, LADDER_K_ATTN_PREFILL, s, [&] { return launch_attn_prefill(aa, s); }));
-      }
-      const int nqd = nq * d;
-      const int rc = run_last_projection(c, m, c->obuf, L.po, rows, nqd, pout + slots * pstride, fuse, emb, copy, s, &slots);
-      if (rc) return rc;
+      if (qkv_slots > 0 && (rc = run_rope_append(c, L, qkv_slots, B, T, pos0, pos_dev, s))) return rc;
+      if ((rc = run_attention(c, L, B, T, pos0, pos_dev, s))) return rc;
+      if ((rc = run_last_projection(c, m, c->obuf, L.po, rows, nqd, pout + slots * pstride, fuse, emb, copy, s, &slots))) return rc;
     } else {
       if (rows <= 16) {
         GemvArgs a{};
@@ -546,19 +590,44 @@ int run_module(ladder_ctx* c, int m, int B, int T, int pos0, bool decode, hipStr
         a.act = (bf16_t*)c->act; a.epilogue = 1;
         HIP_TRY(c, timed(c, LADDER_K_GEMV, s, [&] { return launch_gemv(a, s); }));
       } else {
-        GemmArgs a{};
-        a.x = (const bf16_t*)yin; a.ldx = H; a.wp = L.pgu; a.M = rows; a.K = H; a.N = 2 * I; a.row_scale = c->y_scale[par];
-        const int gu_slots = gate_up_ksplit(g, rows);
-        if (gu_slots > 1) { a.out = c->gu; a.epilogue = 0; a.ksplit = gu_slots; a.out_stride = (size_t)rows * 2 * I; }
-        else { a.act = (bf16_t*)c->act; a.epilogue = 1; }
+        const GemmArgs a = gate_up_args(c, L, yin, c->y_scale[par], rows);
         HIP_TRY(c, timed(c, LADDER_K_GEMM, s, [&] { return launch_gemm_mfma(a, s); }));
-        if (gu_slots > 1) HIP_TRY(c, timed(c, LADDER_K_OTHER, s, [&] { return launch_swiglu_parts(c->gu, gu_slots, (size_t)rows * 2 * I, (bf16_t*)c->act, rows, I, s); }));
+        if (a.epilogue == 0 && (rc = run_swiglu_parts(c, a, s))) return rc;
       }
-      const int rc = run_last_projection(c, m, c->act, L.pd, rows, I, pout + slots * pstride, fuse, emb, copy, s, &slots);
-      if (rc) return rc;
+      if ((rc = run_last_projection(c, m, c->act, L.pd, rows, I, pout + slots * pstride, fuse, emb, copy, s, &slots))) return rc;
     }
   }
   *n_slots = fuse ? -1 : slots;
+  return LADDER_OK;
+}
+
+// Both modules of a layer that do not read each other's output (lag 2), 17 .. 256 rows, one shard: { QKV, gate/up }, rotary + append, attention, { O, down } (and
+// the caller's reduce of both); products whose tiles have no kernel together in a launch each.  n_slots: of the attention module, of the MLP
+int run_layer_beside(ladder_ctx* c, int l, int B, int T, int pos0, bool decode, hipStream_t s, int n_slots[2]) {
+  const ladder_config& g = c->cfg;
+  const int rows = B * T, nqd = g.n_q_heads * g.head_dim;
+  const LayerStore& L = c->store[(size_t)(l - 1)];
+  const int* pos_dev = decode ? c->pos_dev : nullptr;
+  int rc;
+  auto two = [&](const GemmArgs& a, const GemmArgs& b) -> int {
+    if (gemm_pairs(a, b)) {
+      HIP_TRY(c, timed(c, LADDER_K_GEMM, s, [&] { return launch_gemm_pair(a, b, s); }));
+    } else {
+      HIP_TRY(c, timed(c, LADDER_K_GEMM, s, [&] { return launch_gemm_mfma(a, s); }));
+      HIP_TRY(c, timed(c, LADDER_K_GEMM, s, [&] { return launch_gemm_mfma(b, s); }));
+    }
+    return LADDER_OK;
+  };
+  const GemmArgs qkv = qkv_args(c, L, c->y[1], c->y_scale[1], rows, T, pos0), gu = gate_up_args(c, L, c->y[0], c->y_scale[0], rows);
+  if ((rc = two(qkv, gu))) return rc;
+  if (gu.epilogue == 0 && (rc = run_swiglu_parts(c, gu, s))) return rc;
+  if (qkv.epilogue == 0 && (rc = run_rope_append(c, L, qkv.ksplit, B, T, pos0, pos_dev, s))) return rc;
+  if ((rc = run_attention(c, L, B, T, pos0, pos_dev, s))) return rc;
+  const GemmArgs o = few_rows_args(c->obuf, nqd, L.po, rows, nqd, g.hidden, c->parts[1], nullptr);
+  const GemmArgs dn = few_rows_args(c->act, g.inter, L.pd, rows, g.inter, g.hidden, c->parts[0], nullptr);
+  if ((rc = two(dn, o))) return rc;
+  n_slots[0] = o.ksplit;
+  n_slots[1] = dn.ksplit;
   return LADDER_OK;
 }
 
@@ -655,7 +724,7 @@ int emulate_collective(ladder_ctx* c, int m, hipStream_t s) {
   return LADDER_OK;
 }
 
-int run_reduce(ladder_ctx* c, int m, int rows, int n_slots, const void* emb, StreamCopy copy, hipStream_t s) {
+ReduceNormArgs reduce_args(ladder_ctx* c, int m, int rows, int n_slots, const void* emb, StreamCopy copy) {
   const ladder_config& g = c->cfg;
   ReduceNormArgs a{};
   a.x = c->x; a.emb = emb; a.rows = rows; a.H = g.hidden; a.eps = g.rms_eps;
@@ -678,6 +747,11 @@ int run_reduce(ladder_ctx* c, int m, int rows, int n_slots, const void* emb, Str
     else { a.out_b = out; a.gain_b = gain; }
   }
   a.x_out = copy.at; a.x_step = copy.step;
+  return a;
+}
+
+int run_reduce(ladder_ctx* c, int m, int rows, int n_slots, const void* emb, StreamCopy copy, hipStream_t s) {
+  const ReduceNormArgs a = reduce_args(c, m, rows, n_slots, emb, copy);
   const int rc = emulate_collective(c, m, s);
   if (rc) return rc;
   HIP_TRY(c, timed(c, LADDER_K_REDUCE_NORM, s, [&] { return launch_reduce_norm(a, c->bf16, s); }));
@@ -801,8 +875,8 @@ int forward_body(ladder_ctx* c, const void* x_in, int B, int T, int pos0, bool d
   const bool independent = c->cfg.wiring == LADDER_WIRING_LADDER && c->cfg.n_standard_layers == 0 && c->cfg.n_layers > 1 &&
                            (c->cfg.n_layers >= 4 || all_bytes * (200.0 + rows) >= 230e9);
   const bool pays = !c->fast || T == 1 || (rows <= 64 && c->cfg.reduce_delay_us > 0) ? rows <= 64 : rows <= (independent ? FEW_ROWS : 64) && (rows <= 256 || rows > 512) && layer_bytes * (200.0 + rows) >= 32e9;
-  // (a decode step of a short layer in order all the same: a launch takes longer than the bytes it reads there, and the events between two
-  // streams are launches more.  Weights and cache of a layer, MB, and us of 8 steps, in order / side by side: 1.2B (4 layers), batch 20 behind 200 and 1000
+  // (a decode step of a short layer in order all the same, where its modules cannot share launches (see below): a launch takes longer than the bytes it
+  // reads there, and the events between two streams are launches more.  Weights and cache of a layer, MB, and us of 8 steps, in order / side by side: 1.2B (4 layers), batch 20 behind 200 and 1000
   // positions, 110, 1938 / 2190, 176, 2473 / 2400; batch 40 behind 300, 143, 2208 / 2240; batch 64 behind 300, 173, 2531 / 2320; 70B R = 8 (3), batch 20
   // behind 100, 215, 1970 / 1950.)
   const double cache_bytes = 2.0 * c->cfg.n_kv_heads * c->cfg.head_dim * c->esz * c->cfg.n_real_shards * rows * c->pos;
@@ -838,6 +912,27 @@ int forward_body(ladder_ctx* c, const void* x_in, int B, int T, int pos0, bool d
   const bool fuse = c->fast && rows > FEW_ROWS && c->cfg.n_real_shards == 1 && c->cfg.reduce_delay_us == 0;
   // module 1's residual update reads the embeddings themselves: a copy of them in the stream's buffer is 10 bytes per element more
   const bool emb_in_place = fuse && !st && c->cfg.hidden <= EMBED_NORM_MAX_H;
+  // Calls of 17 - 256 rows that would run in order, in five launches per layer where neither module reads the other's output (see run_layer_beside): what
+  // bounds a short layer is how many launches follow one another.  In order / beside, us: 1.2B (4 layers) 60 rows 247 / 172, 100 241 / 200, (2) 128 130 / 109, 250
+  // 154 / 141; 70B R = 8 (2) 17 156 / 142, 120 207 / 186, 230 300 / 280; one layer: 8B 100 141 / 133, 200 196 / 193, R = 4 240 217 / 202; steps of many sequences (2):
+  // 1.2B 128 behind 300 positions 1775 / 1657, R = 8 100 1685 / 1561, R = 4 128 behind 1000 3009 / 2845, 8B 100 2577 / 2592, 200 4018 / 4008.  Two streams keep what
+  // they take, side by side / beside: 8B (4) 50 rows 414 / 422, 100 457 / 483, 1.2B (4) 150 255 / 271, R = 4 40 414 / 426; steps of up to 64 sequences 8B 64 behind 1024
+  // (2) 2844 / 2849, R = 8 64 behind 2000 (3) 2313 / 2398, R = 4 64 behind 700 2954 / 3096; but not the steps of layers below 150 MB: 1.2B 20 sequences behind 200 (4)
+  // 1931 / 1648 (in order), 40 behind 1500 3817 / 3706, 64 behind 1000 (3) 2805 / 2673, 20 behind 3000 3572 / 3344.
+  const bool beside = c->fast && rows > 16 && rows <= 256 && !st && c->cfg.n_real_shards == 1 && c->cfg.reduce_delay_us == 0 && c->cfg.overlap_modules != 0 &&
+                      c->cfg.wiring != LADDER_WIRING_STANDARD && c->cfg.n_standard_layers == 0 && c->cfg.n_layers > 0 && reduce_norm_two_fits(c->cfg.hidden) &&
+                      (!overlap || (T == 1 && layer_bytes < 150e6));
+  if (beside) {
+    int rc = run_reduce(c, 0, rows, 0, x_in, {nullptr, false}, s0);
+    for (int l = 1; rc == LADDER_OK && l <= c->cfg.n_layers; ++l) {
+      int n[2];
+      if ((rc = run_layer_beside(c, l, B, T, pos0, decode, s0, n))) return rc;
+      const ReduceNormArgs first = reduce_args(c, 2 * l - 1, rows, n[0], nullptr, {nullptr, false});
+      const ReduceNormArgs second = reduce_args(c, 2 * l, rows, n[1], nullptr, {l == c->cfg.n_layers ? (float*)x_out : nullptr, false});
+      HIP_TRY(c, timed(c, LADDER_K_REDUCE_NORM, s0, [&] { return launch_reduce_norm_two(first, second, s0); }));
+    }
+    return rc;
+  }
   int rc = emb_in_place ? run_embed_norm(c, x_in, rows, s0) : st ? run_stage_in(c, *st, rows, s0) : run_reduce(c, 0, rows, 0, x_in, {c->n_mod == 0 ? (float*)x_out : nullptr, false}, s0);
   if (rc) return rc;
   if (overlap && c->n_mod >= 2) {  // fork: the MLP stream starts once x_0 and its normed copies exist

@@ -793,7 +793,7 @@ static hipError_t launch_gemm_duo(const GemmArgs& a, hipStream_t s) {
 // blocks they are 5 - 13 % slower.  A rotated start of the K sweep: no change.
 // ------------------------------------------------------------------------------------------------
 template <int BM, int BN, int WR, int WC, int S>
-__global__ __launch_bounds__(WR * WC * 64) void gemm_ring_kernel(GemmArgs a) {
+__device__ __forceinline__ void gemm_ring_tile(const GemmArgs& a, int block, int nblk) {
   constexpr int WAVES = WR * WC, MT = BM / WR / 16, JT = BN / WC / 16;
   constexpr int XB = BM * 128, WB = BN * 128;             // bytes per stage of 64 k
   constexpr int XL = BM / 8 / WAVES, WL = BN / 8 / WAVES; // 1 KiB loads per wave and stage
@@ -808,8 +808,8 @@ __global__ __launch_bounds__(WR * WC * 64) void gemm_ring_kernel(GemmArgs a) {
   const int wr = wave / WC, wc = wave % WC;
   const int KT = a.K >> 5, ST = (KT + 1) >> 1, NT = a.N >> 4;
   const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
-  const int nblk = gridDim.x, nblk8 = nblk & ~7;   // XCD-aware order, as in gemm_duo_kernel
-  int bid = (int)blockIdx.x < nblk8 ? ((int)blockIdx.x & 7) * (nblk8 >> 3) + ((int)blockIdx.x >> 3) : (int)blockIdx.x;
+  const int nblk8 = nblk & ~7;   // XCD-aware order, as in gemm_duo_kernel
+  int bid = block < nblk8 ? (block & 7) * (nblk8 >> 3) + (block >> 3) : block;
   const int ks = bid / (tiles_m * tiles_n);
   bid -= ks * (tiles_m * tiles_n);
   const int per_group = GEMM_GROUP_M * tiles_n;
@@ -933,6 +933,35 @@ __global__ __launch_bounds__(WR * WC * 64) void gemm_ring_kernel(GemmArgs a) {
 }
 
 template <int BM, int BN, int WR, int WC, int S>
+__global__ __launch_bounds__(WR * WC * 64) void gemm_ring_kernel(GemmArgs a) {
+  gemm_ring_tile<BM, BN, WR, WC, S>(a, (int)blockIdx.x, (int)gridDim.x);
+}
+
+// Two products that do not depend on each other in one launch (a's workgroups first): what a short product leaves of the chip at its start and
+// end, the other one fills.  The tiles and splits are those that each takes by itself: same bits.
+template <int BM_, int BN_, int WR_, int WC_, int S_>
+struct RingTile {
+  static constexpr int BM = BM_, BN = BN_, WR = WR_, WC = WC_, S = S_, LDS = S_ * (BM_ + BN_) * 128;
+  static_assert(WR_ * WC_ == 8, "512 threads");
+  static int workgroups(const GemmArgs& g) { return (g.M + BM - 1) / BM * ((g.N + BN - 1) / BN) * g.ksplit; }
+};
+template <typename A, typename B>
+__global__ __launch_bounds__(512) void gemm_ring_pair_kernel(GemmArgs a, GemmArgs b, int n_a) {
+  if ((int)blockIdx.x < n_a) gemm_ring_tile<A::BM, A::BN, A::WR, A::WC, A::S>(a, (int)blockIdx.x, n_a);
+  else gemm_ring_tile<B::BM, B::BN, B::WR, B::WC, B::S>(b, (int)blockIdx.x - n_a, (int)gridDim.x - n_a);
+}
+template <typename A, typename B>
+static hipError_t launch_ring_pair(const GemmArgs& a, const GemmArgs& b, hipStream_t s) {
+  constexpr int LDS = A::LDS > B::LDS ? A::LDS : B::LDS;
+  static bool prepared[64] = {};
+  const hipError_t e = allow_lds(reinterpret_cast<const void*>(gemm_ring_pair_kernel<A, B>), LDS, prepared);
+  if (e != hipSuccess) return e;
+  const int n_a = A::workgroups(a);
+  hipLaunchKernelGGL((gemm_ring_pair_kernel<A, B>), dim3(n_a + B::workgroups(b)), dim3(512), LDS, s, a, b, n_a);
+  return hipGetLastError();
+}
+
+template <int BM, int BN, int WR, int WC, int S>
 static hipError_t launch_gemm_ring_t(const GemmArgs& a, hipStream_t s) {
   constexpr int LDS = S * (BM + BN) * 128;
   static bool prepared[64] = {};
@@ -954,8 +983,8 @@ int gemm_ssq_parts(const GemmArgs& a) {
 
 int gemm_ksplit(int M, int N, int K, int max_split, float extra_us) { return gemm_best_split(M, N, K, max_split, extra_us); }
 
-hipError_t launch_gemm_mfma(const GemmArgs& given, hipStream_t s) {
-  GemmArgs a = given;
+// what a product must have, whatever tile it takes (a.ksplit: at least 1 behind it)
+static hipError_t check_gemm(GemmArgs& a) {
   if (a.M <= 0 || (a.K & 31) || (a.N & 15) || a.K < 32) return hipErrorInvalidValue;
   if (a.ksplit < 1) a.ksplit = 1;
   if (a.ksplit > 1) {
@@ -970,6 +999,13 @@ hipError_t launch_gemm_mfma(const GemmArgs& given, hipStream_t s) {
   if (a.epilogue == 3 && (!a.x_res || a.n_peers < 0 || (a.n_peers > 0 && !a.peers) || (a.xh_b && !a.xh_a) || (a.ssq_part && !a.xh_a) ||
                           (a.xh_a && !a.gain_a) || (a.xh_b && !a.gain_b)))
     return hipErrorInvalidValue;
+  return hipSuccess;
+}
+
+hipError_t launch_gemm_mfma(const GemmArgs& given, hipStream_t s) {
+  GemmArgs a = given;
+  const hipError_t ok = check_gemm(a);
+  if (ok != hipSuccess) return ok;
   const int tile = gemm_best_tile(shape_of(a), a.ksplit, nullptr);
   if (a.epilogue == 3 && (tile == TILE_64x64 || (tile == TILE_256x256 && a.n_peers > 0))) return hipErrorInvalidValue;   // (their kernels do not have it)
   switch (tile) {
@@ -982,6 +1018,44 @@ hipError_t launch_gemm_mfma(const GemmArgs& given, hipStream_t s) {
     case TILE_DUO_128: return launch_gemm_duo<2>(a, s);
     case TILE_DUO_192: return launch_gemm_duo<3>(a, s);
     default: return launch_gemm_duo<4>(a, s);
+  }
+}
+
+// The pairs of tiles that two products of up to 128 rows take (and most of up to 256), the second one's tile the larger: its workgroups take longest, so
+// they go first
+static int pair_of(const GemmArgs& a, const GemmArgs& b, bool* swap) {
+  if (a.epilogue == 3 || b.epilogue == 3) return -1;
+  int ta = gemm_best_tile(shape_of(a), std::max(1, a.ksplit), nullptr), tb = gemm_best_tile(shape_of(b), std::max(1, b.ksplit), nullptr);
+  const auto rank = [](int t) { return t == TILE_64x64 ? 0 : t == TILE_128x64 ? 1 : t == TILE_128x128 ? 2 : -1; };
+  ta = rank(ta);
+  tb = rank(tb);
+  if (ta < 0 || tb < 0) return -1;
+  *swap = ta > tb;
+  return *swap ? tb * 3 + ta : ta * 3 + tb;
+}
+bool gemm_pairs(const GemmArgs& a, const GemmArgs& b) {
+  bool swap;
+  return pair_of(a, b, &swap) >= 0;
+}
+hipError_t launch_gemm_pair(const GemmArgs& given_a, const GemmArgs& given_b, hipStream_t s) {
+  GemmArgs a = given_a, b = given_b;
+  hipError_t e = check_gemm(a);
+  if (e == hipSuccess) e = check_gemm(b);
+  if (e != hipSuccess) return e;
+  bool swap = false;
+  const int pair = pair_of(a, b, &swap);
+  if (swap) std::swap(a, b);
+  typedef RingTile<64, 64, 2, 4, 6> Small;
+  typedef RingTile<128, 64, 4, 2, 5> Tall;
+  typedef RingTile<128, 128, 2, 4, 5> Large;
+  switch (pair) {
+    case 0: return launch_ring_pair<Small, Small>(a, b, s);
+    case 1: return launch_ring_pair<Tall, Small>(b, a, s);
+    case 2: return launch_ring_pair<Large, Small>(b, a, s);
+    case 4: return launch_ring_pair<Tall, Tall>(a, b, s);
+    case 5: return launch_ring_pair<Large, Tall>(b, a, s);
+    case 8: return launch_ring_pair<Large, Large>(a, b, s);
+    default: return hipErrorInvalidValue;
   }
 }
 

@@ -1,10 +1,11 @@
 """GPU: the projections of calls of few and medium rows (ring GEMM, split K, partial products added up by the next kernel) at
 the edges of their tiles, splits and row ranges, against the CPU oracle."""
+import numpy as np
 import pytest
 import torch
 
 import wide_attention
-from paper_2501_06589_amd import inputs
+from paper_2501_06589_amd import inputs, ladder
 
 pytestmark = pytest.mark.gpu
 
@@ -182,3 +183,19 @@ def test_same_bits_in_contexts_of_any_capacity(harness, shape):
         own.free()
         assert torch.equal(want, got), rows
     big.free()
+
+
+# (rows, prompt or step, wiring): pairs of small tiles, small and tall, tall and large ones, SwiGLU from partial products, one token for each of many sequences
+@pytest.mark.parametrize("batch,prefill", [(1, 17), (2, 32), (1, 65), (1, 128), (3, 67), (1, 256), (1, 257), (17, 1), (40, 1), (200, 1)])
+@pytest.mark.parametrize("wiring", [ladder.LADDER_WIRING_LADDER, ladder.LADDER_WIRING_PARALLEL])
+@pytest.mark.parametrize("hidden,inter", [(512, 1056), (4160, 416)])
+def test_modules_that_share_launches_leave_the_same_bits(harness, batch, prefill, wiring, hidden, inter):
+    """17 to 256 rows: the two modules' products in a launch each time and both residual updates in one, against one after the other on one stream:
+    the same bits, and the right ones."""
+    w = WIDE.with_(name="beside", n_layers=2, hidden=hidden, inter=inter, n_q_heads=4, n_kv_heads=2, head_dim=64, batch=batch, prefill=prefill,
+                   tp_degree=3, n_real_shards=1, peer_pool=2)
+    tensors = harness.make_tensors(w)
+    runs = [harness.run_case(w, tensors=tensors, gpu_only=not on, decode_steps=1, wiring=wiring, overlap_modules=on, reduce_on_side_stream=0) for on in (1, 0)]
+    assert max(runs[0].errs) < TOL, runs[0].errs
+    for a, b in zip(*(r.gpu for r in runs)):
+        assert np.array_equal(a, b)
