@@ -202,6 +202,10 @@ hipError_t launch_attn_generic(const AttnGenericArgs& a, bool is_bf16, hipStream
 bool plain_beside(const PlainGemmArgs& qkv, const AttnGenericArgs& attn, const PlainGemmArgs& gate_up, const PlainGemmArgs& down, bool is_bf16);
 hipError_t launch_plain_inputs(PlainGemmArgs a, PlainGemmArgs b, bool is_bf16, hipStream_t s);
 hipError_t launch_plain_attn_beside(const AttnGenericArgs& a, PlainGemmArgs b, bool is_bf16, hipStream_t s);
+// ... or in two for a single row, { qkv, gate_up }, { attn + its output projection, down }, where plain_attn_out_fits
+#define PLAIN_ATTN_OUT_POSITIONS 256   // times heads: a chunk of 64 for each of four wavefronts
+bool plain_attn_out_fits(const AttnGenericArgs& a, const PlainGemmArgs& o, const PlainGemmArgs& down, bool is_bf16);
+hipError_t launch_plain_attn_out(const AttnGenericArgs& a, PlainGemmArgs o, PlainGemmArgs b, bool is_bf16, hipStream_t s);
 
 // act[m][i] = silu(gate) * up from the partial products of the packed gate/up projection (tile columns 0..7 gate, 8..15 the matching up
 // columns), act bf16: parts f32 [n_parts][M][2I], slot s at parts + s * part_stride, summed in slot order

@@ -404,9 +404,13 @@ __device__ __forceinline__ void stream_rows(const StreamSum& a, int H, int m0, i
 // rows m0 .. m0 + MR - 1 of x times columns n .. n + 3 (per lane) of the NM matrices w; the sums over all K end up in `sum` [NM][MR][64].
 // NORM: the rows are those of a.in times the gain; the factor 1/rms commutes with the product and is applied to the sums; store: this
 // workgroup leaves the rows in a.x_store.
-template <typename T, int MR, bool VEC, int KC, int NM, bool NORM>
+// made: nothing, or what leaves a single row of at most KC elements in xs[0] (beside the weights that have been requested) instead of x.
+struct PlainRowsGiven {};
+template <typename T, int MR, bool VEC, int KC, int NM, bool NORM, typename F>
 __device__ __forceinline__ void plain_product(const PlainGemmArgs& a, const T* x, int m0, const T* const (&w)[NM], int N, int n0, bool store, float (*xs)[KC],
-                                              float (*red)[MR][64], float (*sum)[MR][64], float (*red_ss)[4]) {
+                                              float (*red)[MR][64], float (*sum)[MR][64], float (*red_ss)[4], const F& made) {
+  constexpr bool MADE = !__is_same(F, PlainRowsGiven);
+  static_assert(!MADE || (MR == 1 && !NORM), "one row, as it is");
   const int M = a.M, K = a.K;
   const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
   const int c4 = (lane & 15) * 4, kg = t >> 4;
@@ -434,6 +438,8 @@ __device__ __forceinline__ void plain_product(const PlainGemmArgs& a, const T* x
         xs[m][t] = ok ? v[m] * gain : 0.f;
         ss[m] += ok ? v[m] * v[m] : 0.f;
       }
+    } else if constexpr (MADE) {
+      made(xs[0]);
     } else {
       if (k0 > 0) __syncthreads();   // the previous pass has been read
 #pragma unroll
@@ -513,8 +519,8 @@ __device__ __forceinline__ bool plain_tile(unsigned id, unsigned row_blocks, uns
 
 // NM = 2: gate and up in one sweep over K, and more loads in flight in the other projections too.  (Two workgroups per CU: without the bound the rows that fp32 sums and norms itself cost two registers too many
 // for that; three layers of 264 - 512 workgroups of four rows, hidden 512 and 1024, 2 - 7 % slower than it was as separate kernels, with it 14 - 20 % faster.)
-template <typename T, int MR, bool VEC, int KC, bool NORM, int NM>
-__device__ __forceinline__ void plain_gemm_block(const PlainGemmArgs& a, unsigned id) {
+template <typename T, int MR, bool VEC, int KC, bool NORM, int NM, typename F = PlainRowsGiven>
+__device__ __forceinline__ void plain_gemm_block(const PlainGemmArgs& a, unsigned id, const F& made = F()) {
   __shared__ __attribute__((aligned(16))) float xs[MR][KC];
   __shared__ float red[4 * NM][MR][64];
   __shared__ float sum[2][MR][64];
@@ -537,13 +543,13 @@ __device__ __forceinline__ void plain_gemm_block(const PlainGemmArgs& a, unsigne
   const bool store = NORM && a.x_store && col_blk == 0 && shard == 0;
   if (NM == 2 && a.epilogue == PLAIN_SWIGLU) {
     const T* const w[2] = {weights(0), weights(1)};
-    plain_product<T, MR, VEC, KC, 2, NORM>(a, x, m0, w, N, n0, store, xs, red, sum, red_ss);
+    plain_product<T, MR, VEC, KC, 2, NORM>(a, x, m0, w, N, n0, store, xs, red, sum, red_ss, made);
   } else {
     const T* const w[1] = {weights(mat)};
-    plain_product<T, MR, VEC, KC, 1, NORM>(a, x, m0, w, N, n0, store, xs, red, sum, red_ss);
+    plain_product<T, MR, VEC, KC, 1, NORM>(a, x, m0, w, N, n0, store, xs, red, sum, red_ss, made);
     if (a.epilogue == PLAIN_SWIGLU) {
       const T* const up[1] = {weights(1)};
-      plain_product<T, MR, VEC, KC, 1, NORM>(a, x, m0, up, N, n0, false, xs, red, sum + 1, red_ss);
+      plain_product<T, MR, VEC, KC, 1, NORM>(a, x, m0, up, N, n0, false, xs, red, sum + 1, red_ss, made);
     }
   }
   if (a.epilogue == PLAIN_OUT) {
@@ -829,6 +835,109 @@ __global__ __launch_bounds__(256, 2) void plain_attn_beside_kernel(AttnGenericAr
   else plain_gemm_block<T, MR, VEC_B, 256, false, 2>(b, id - n_a);
 }
 
+// One row's attention over all nq (1, 2 or 4) heads of a computed shard, as every workgroup of its output projection needs it: out[nq * d], rounded to T
+// as the stored one is.  The wavefronts are dealt out over the heads and then over chunks of 64 positions; a chunk as in attn_generic_block.
+template <typename T, bool VEC>
+__device__ __forceinline__ void attn_one_row(const AttnGenericArgs& a, int shard, float* out) {
+  __shared__ float qs[256];
+  __shared__ __attribute__((aligned(16))) float ps[4][64];
+  __shared__ float om[4][256], ms[4], ls[4];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nqd = a.nq * a.d;
+  const int h = wave % a.nq, first = wave / a.nq, stride = 4 / a.nq;
+  const int n_vis = a.pos0 + 1;
+  const T* kb = reinterpret_cast<const T*>(reinterpret_cast<const char*>(a.cache_k) + shard * a.cache_stride) + (size_t)(h / (a.nq / a.nkv)) * a.max_seq * a.d;
+  const T* vb = reinterpret_cast<const T*>(reinterpret_cast<const char*>(a.cache_v) + shard * a.cache_stride) + (size_t)(h / (a.nq / a.nkv)) * a.max_seq * a.d;
+  if ((int)threadIdx.x < nqd) qs[threadIdx.x] = load_f<T>(reinterpret_cast<const T*>(a.q) + shard * a.q_stride + threadIdx.x);
+  __syncthreads();
+  const float* const qh = qs + h * a.d;
+  const float scale = 1.0f / sqrtf((float)a.d);
+  float acc[4] = {0.f, 0.f, 0.f, 0.f};
+  float mx = -INFINITY, l = 0.f;
+  for (int c0 = first * 64; c0 < n_vis; c0 += stride * 64) {
+    const int n = min(64, n_vis - c0);
+    float sc = -INFINITY;
+    if (lane < n) {
+      const T* kr = kb + (size_t)(c0 + lane) * a.d;
+      float part[4] = {0.f, 0.f, 0.f, 0.f};
+      if (VEC) {
+#pragma unroll 8
+        for (int i = 0; i < a.d; i += 4) {
+          float kv[4];
+          load4<T>(kr + i, kv);
+          for (int e = 0; e < 4; ++e) part[e] = fmaf(qh[i + e], kv[e], part[e]);
+        }
+      } else {
+        for (int i = 0; i < a.d; ++i) part[i & 3] = fmaf(qh[i], load_f<T>(kr + i), part[i & 3]);
+      }
+      sc = ((part[0] + part[1]) + (part[2] + part[3])) * scale;
+    }
+    const float mn = fmaxf(mx, wave_max(sc));
+    const float ref = mn == -INFINITY ? 0.f : mn;   // (scores that are all -inf weigh nothing, they must not become NaN)
+    const float corr = expf(mx - ref), p = lane < n ? expf(sc - ref) : 0.f;
+    l = l * corr + wave_sum(p);
+    mx = mn;
+    ps[wave][lane] = p;
+    __builtin_amdgcn_wave_barrier();   // (the wavefront's own LDS accesses stay in order)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int i = lane + 64 * e;
+      if (i >= a.d) continue;
+      const T* vr = vb + (size_t)i * a.max_seq + c0;   // (the capacity and c0 are multiples of 64)
+      float o[4] = {0.f, 0.f, 0.f, 0.f};
+      int j = 0;
+#pragma unroll 8
+      for (; j + 4 <= n; j += 4) {
+        float v[4];
+        load4<T>(vr + j, v);
+        for (int u = 0; u < 4; ++u) o[u] = fmaf(ps[wave][j + u], v[u], o[u]);
+      }
+      for (; j < n; ++j) o[0] = fmaf(ps[wave][j], load_f<T>(vr + j), o[0]);
+      acc[e] = acc[e] * corr + ((o[0] + o[1]) + (o[2] + o[3]));
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (lane + 64 * e < a.d) om[wave][lane + 64 * e] = acc[e];
+  if (lane == 0) { ms[wave] = mx; ls[wave] = l; }
+  __syncthreads();
+  const int t = threadIdx.x;
+  float res = 0.f;
+  if (t < nqd) {
+    const int head = t / a.d, dim = t % a.d;
+    float m = ms[head], o = 0.f, tot = 0.f;   // (the head's first wavefront always has a chunk)
+    for (int w = head + a.nq; w < 4; w += a.nq) m = fmaxf(m, ms[w]);
+    const float ref = m == -INFINITY ? 0.f : m;
+    for (int w = head; w < 4; w += a.nq) {
+      const float f = expf(ms[w] - ref);
+      o += om[w][dim] * f;
+      tot += ls[w] * f;
+    }
+    T r;
+    store_f<T>(&r, o / tot);
+    res = load_f<T>(&r);
+  }
+  out[t] = res;   // (a pass of 256 elements: zeros behind the row)
+}
+
+// One row: the attention and its output projection (every workgroup of o makes the attention's output itself, which is little where the cache is short) beside the
+// last projection of the MLP
+template <typename T, bool VEC_A, bool VEC>
+__global__ __launch_bounds__(256, 2) void plain_attn_out_kernel(AttnGenericArgs a, PlainGemmArgs o, PlainGemmArgs b) {
+  const unsigned id = blockIdx.x;
+  if (id < (unsigned)o.n_blocks)
+    plain_gemm_block<T, 1, VEC, 256, false, 1>(o, id, [&](float* xs) { attn_one_row<T, VEC_A>(a, blockIdx.z, xs); });
+  else plain_gemm_block<T, 1, VEC, 256, false, 2>(b, id - (unsigned)o.n_blocks);
+}
+template <typename T>
+static hipError_t launch_plain_attn_out_t(const AttnGenericArgs& a, const PlainGemmArgs& o, const PlainGemmArgs& b, bool vec_a, bool vec, dim3 grid, hipStream_t s) {
+  if (vec_a && vec) hipLaunchKernelGGL((plain_attn_out_kernel<T, true, true>), grid, dim3(256), 0, s, a, o, b);
+  else if (vec_a) hipLaunchKernelGGL((plain_attn_out_kernel<T, true, false>), grid, dim3(256), 0, s, a, o, b);
+  else if (vec) hipLaunchKernelGGL((plain_attn_out_kernel<T, false, true>), grid, dim3(256), 0, s, a, o, b);
+  else hipLaunchKernelGGL((plain_attn_out_kernel<T, false, false>), grid, dim3(256), 0, s, a, o, b);
+  return hipGetLastError();
+}
+
 template <typename T, int MR>
 static hipError_t launch_plain_inputs_t(const PlainGemmArgs& a, const PlainGemmArgs& b, bool vec, dim3 grid, hipStream_t s) {
   if (vec) hipLaunchKernelGGL((plain_inputs_kernel<T, MR, true>), grid, dim3(256), 0, s, a, b);
@@ -853,6 +962,21 @@ bool plain_beside(const PlainGemmArgs& qkv, const AttnGenericArgs& attn, const P
   const long long first = plain_workgroups(rows, plain_col_blocks(qkv) + plain_col_blocks(gate_up), shards);
   const long long second = (long long)rows * attn.nq * shards + plain_workgroups(rows, plain_col_blocks(down), shards);
   return first <= PLAIN_HELD_WORKGROUPS && second <= PLAIN_HELD_WORKGROUPS;
+}
+// A single row whose heads' outputs are one pass of the projection, behind a cache of one chunk per wavefront, so that the sums are those of the attention by
+// itself (tiny fp32 model, prompt of 32 and 8 steps 306 -> 280 us; hidden 512 463 -> 407, bf16 458 -> 389; behind 300 positions, several chunks, 325 -> 361).
+bool plain_attn_out_fits(const AttnGenericArgs& a, const PlainGemmArgs& o, const PlainGemmArgs& down, bool is_bf16) {
+  if (a.B != 1 || a.T != 1 || (a.nq != 1 && a.nq != 2 && a.nq != 4) || a.nq * a.d > 256 || o.K != a.nq * a.d || o.M != 1 || down.M != 1) return false;
+  if (is_bf16 && !(plain_vec(o) && plain_vec(down))) return false;
+  return (long long)(a.pos0 + 1) * a.nq <= PLAIN_ATTN_OUT_POSITIONS && (long long)(plain_col_blocks(o) + plain_col_blocks(down)) * a.n_shards <= PLAIN_HELD_WORKGROUPS;
+}
+hipError_t launch_plain_attn_out(const AttnGenericArgs& a, PlainGemmArgs o, PlainGemmArgs b, bool is_bf16, hipStream_t s) {
+  if (!plain_attn_out_fits(a, o, b, is_bf16) || a.n_shards <= 0 || a.n_shards != o.n_shards || a.n_shards != b.n_shards) return hipErrorInvalidValue;
+  o.n_blocks = plain_col_blocks(o);
+  b.n_blocks = plain_col_blocks(b);
+  const bool vec_a = a.d % 4 == 0, vec = plain_vec(o) && plain_vec(b);
+  const dim3 grid((unsigned)(o.n_blocks + b.n_blocks), 1, (unsigned)a.n_shards);
+  return is_bf16 ? launch_plain_attn_out_t<bf16_t>(a, o, b, vec_a, vec, grid, s) : launch_plain_attn_out_t<float>(a, o, b, vec_a, vec, grid, s);
 }
 hipError_t launch_plain_inputs(PlainGemmArgs a, PlainGemmArgs b, bool is_bf16, hipStream_t s) {
   if (a.M <= 0 || a.M > PLAIN_NORM_ROWS || b.M != a.M || a.n_shards <= 0 || b.n_shards != a.n_shards || !a.gain || !b.gain) return hipErrorInvalidValue;

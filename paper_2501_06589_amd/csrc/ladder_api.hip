@@ -782,8 +782,8 @@ int run_embed_norm(ladder_ctx* c, const void* emb, int rows, hipStream_t s) {
 // adds the outputs up to module m - lag, so the output of module m - 2, whose buffer module m's last projection overwrites, has been added.
 // A layer is then five launches, each as long as its round trips whatever it holds (tiny fp32 model 4 - 6 us); where the layer's MLP does not
 // read its attention's output (lag 2), three: { QKV, gate/up }, { attention, down }, { O }.  Only gate/up stores the rows it makes then, x_{2l-2}, and the
-// layer behind adds one and two outputs to them, in the same order: same bits.
-// tiny fp32 model, prompt of 32 and 8 steps: sixteen launches per step 565 us, eleven 484, seven 306; hidden 512 (two shards) 686 -> 463, four sequences 936 -> 702; hidden 1024, bf16 908 -> 621.
+// layer behind adds one and two outputs to them, in the same order: same bits.  A single row behind a short cache in two, { attention + O, down } (see plain_attn_out_fits).
+// tiny fp32 model, prompt of 32 and 8 steps: sixteen launches per step 565 us, eleven 484, seven 306, five 280; hidden 512 (two shards) 686 -> 463, four sequences 936 -> 702; hidden 1024, bf16 908 -> 621.
 int forward_plain(ladder_ctx* c, const void* x_in, int B, int T, int pos0, float* x_out, hipStream_t s) {
   const ladder_config& g = c->cfg;
   const int rows = B * T;
@@ -810,8 +810,12 @@ int forward_plain(ladder_ctx* c, const void* x_in, int B, int T, int pos0, float
       const PlainModule mlp = plain_module(c, m + 1, B, T, pos0, c->parts[0], &in, store);
       if (plain_beside(attn.first, attn.attn, mlp.first, mlp.last, c->bf16)) {
         HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_plain_inputs(attn.first, mlp.first, c->bf16, s); }));
-        HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_plain_attn_beside(attn.attn, mlp.last, c->bf16, s); }));
-        HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_plain_gemm(attn.last, c->bf16, s); }));
+        if (plain_attn_out_fits(attn.attn, attn.last, mlp.last, c->bf16)) {
+          HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_plain_attn_out(attn.attn, attn.last, mlp.last, c->bf16, s); }));
+        } else {
+          HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_plain_attn_beside(attn.attn, mlp.last, c->bf16, s); }));
+          HIP_TRY(c, timed(c, LADDER_K_GENERIC, s, [&] { return launch_plain_gemm(attn.last, c->bf16, s); }));
+        }
         if (store) {
           in.emb = nullptr; in.base = store; stored = m - 1;
           std::swap(buf[0], buf[1]);

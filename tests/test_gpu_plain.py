@@ -205,3 +205,19 @@ def test_modules_beside_each_other(harness, dtype, hidden, nq, nkv, d, inter, ro
     assert max(runs[0].errs) < (1e-4 if dtype == "fp32" else 0.0029 * (2 * n_layers) ** 0.5 * 5.8), runs[0].errs
     for a, b in zip(*(r.gpu for r in runs)):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("nq,nkv,d", [(1, 1, 64), (2, 1, 64), (2, 2, 66), (4, 2, 64), (4, 4, 30), (2, 1, 130)])
+@pytest.mark.parametrize("cached", [1, 62, 63, 126, 127, 200, 254, 255])
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_attention_with_its_output_projection(harness, nq, nkv, d, cached, dtype):
+    """One row whose attention and output projection share a launch behind a short cache (256 positions times heads; heads of at most 256 elements
+    together), at the edges of that and of a wavefront's chunk: the same bits as the launches by themselves."""
+    w = BASE.with_(name="attn_out", dtype=dtype, hidden=264, n_q_heads=nq, n_kv_heads=nkv, head_dim=d, inter=96, prefill=0, kv_preload=cached,
+                   tp_degree=2, n_real_shards=2)
+    tensors = harness.make_tensors(w)
+    runs = [harness.run_case(w, tensors=tensors, kv_preload=cached, gpu_only=delay > 0, kernel_path=ladder.LADDER_PATH_GENERIC,
+                             reduce_delay_us=delay) for delay in (0, 5)]
+    assert max(runs[0].errs) < (1e-4 if dtype == "fp32" else 0.0029 * 2 ** 0.5 * 5.8), runs[0].errs
+    for a, b in zip(*(r.gpu for r in runs)):
+        assert np.array_equal(a, b)
