@@ -209,7 +209,15 @@ hipError_t launch_plain_attn_out(const AttnGenericArgs& a, PlainGemmArgs o, Plai
 
 // act[m][i] = silu(gate) * up from the partial products of the packed gate/up projection (tile columns 0..7 gate, 8..15 the matching up
 // columns), act bf16: parts f32 [n_parts][M][2I], slot s at parts + s * part_stride, summed in slot order
-hipError_t launch_swiglu_parts(const float* parts, int n_parts, size_t part_stride, bf16_t* act, int M, int I, hipStream_t s);
+struct SwigluPartsArgs {
+  const float* parts;
+  int n_parts;
+  size_t part_stride;      // elements
+  bf16_t* act;
+  int M, I;
+};
+hipError_t launch_swiglu_parts(const SwigluPartsArgs& a, hipStream_t s);
+hipError_t launch_rope_swiglu(const RopeAppendArgs& a, const SwigluPartsArgs& b, hipStream_t s);   // both in one launch
 
 // ---- generation head ----------------------------------------------------------------------------
 // x_out[r][:] = table[tokens[r]][:]  (T [rows][H]); an id outside [0, vocab) reads the nearest valid row and sets

@@ -34,10 +34,108 @@ template <> __device__ __forceinline__ void store4<bf16_t>(bf16_t* p, const floa
 // that call for one or the other are to give the same bits.
 __device__ __forceinline__ float squares4(const float (&v)[4]) { return fmaf(v[3], v[3], fmaf(v[2], v[2], fmaf(v[0], v[0], v[1] * v[1]))); }
 
+// f(s, N) for the pieces 0 .. n - 1 of a sum, four at a time: what N pieces read is requested before the first of them is added, in order.  One by one each was
+// a round trip to memory of its own (other XCDs have just written them), for each of up to eight partial products and seven peers.  With rotary + append and SwiGLU
+// in one launch where modules share launches, us, before / after: 1.2B (4 layers) prompt of 60 167 / 161, 20 sequences behind 200 positions, 8 steps 1695 / 1652; 70B R = 8 (2)
+// 40 behind 700 1465 / 1412, 900 rows 600 / 593; R = 4 (2) 230 rows 371 / 366; 1.2B (8) 3 x 333 and 8 steps 2959 / 2930; 8B (2) batch 64 2871 / 2866.
+template <int N> struct Pieces { static constexpr int n = N; };
+template <typename F>
+__device__ __forceinline__ void four_at_a_time(int n, const F& f) {
+  int s = 0;
+  for (; s + 4 <= n; s += 4) f(s, Pieces<4>());
+  if (n - s == 3) f(s, Pieces<3>());
+  else if (n - s == 2) f(s, Pieces<2>());
+  else if (n - s == 1) f(s, Pieces<1>());
+}
+
+// x += the partial sums and peers of r, for the columns col[] of the row that starts at element `row`
+template <typename T, int C>
+__device__ __forceinline__ void reduce_add(const ReduceNormArgs& r, size_t row, const int (&col)[C], float (&x)[C][4]) {
+  auto add = [&](int n, auto load) {
+    four_at_a_time(n, [&](int s, auto pieces) {
+      constexpr int N = decltype(pieces)::n;
+      float t[N][C][4];
+#pragma unroll
+      for (int j = 0; j < N; ++j)
+#pragma unroll
+        for (int c = 0; c < C; ++c) load(s + j, row + col[c], t[j][c]);
+#pragma unroll
+      for (int j = 0; j < N; ++j)
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+          for (int e = 0; e < 4; ++e) x[c][e] += t[j][c][e];
+    });
+  };
+  add(r.n_parts, [&](int s, size_t at, float (&t)[4]) { load4<float>(r.parts + s * r.part_stride + at, t); });
+  add(r.n_peers, [&](int s, size_t at, float (&t)[4]) { load4<T>(reinterpret_cast<const T*>(r.peers) + s * r.peer_stride + at, t); });
+}
+
 // STEP: x_out takes the step (a.x_step), for which the old values stay in registers past the sums; a branch of one kernel cost every
 // reduce of a wide decode step 0.2 - 0.3 us (1.2B, 4 layers, 50 sequences, 8 steps 2692 -> 2675 us).
+// The row stays in registers (C pieces of 4 columns per thread), and the gains are requested before the sums of squares meet.
+template <typename T, bool STEP, int C>
+__global__ __launch_bounds__(1024) void reduce_norm_kernel(ReduceNormArgs a) {
+  const int H = a.H, step = blockDim.x * 4;
+  const size_t row = (size_t)blockIdx.x * H;
+  const T* const emb = reinterpret_cast<const T*>(a.emb);
+  const float* const src = a.x_src ? a.x_src : a.x;
+  int col[C];   // (columns behind the row's end: its last ones again, not stored)
+  float v[C][4], old[C][4], g[2][C][4], ss = 0.f;
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    col[c] = min((int)threadIdx.x * 4 + c * step, H - 4);
+    if (emb) load4<T>(emb + row + col[c], v[c]);
+    else load4<float>(src + row + col[c], v[c]);
+    for (int e = 0; e < 4; ++e) old[c][e] = v[c][e];
+  }
+  reduce_add<T>(a, row, col, v);
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    if ((int)threadIdx.x * 4 + c * step >= H) break;
+    store4<float>(a.x + row + col[c], v[c]);
+    if (STEP) {
+      float t[4];
+      for (int e = 0; e < 4; ++e) t[e] = v[c][e] - old[c][e];
+      store4<float>(a.x_out + row + col[c], t);
+    } else if (a.x_out) {
+      store4<float>(a.x_out + row + col[c], v[c]);
+    }
+    ss += squares4(v[c]);
+  }
+  if (!a.out_a && !a.out_b) return;
+  auto gains = [&](const void* gain, float (&to)[C][4]) {
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      if (gain) load4<T>(reinterpret_cast<const T*>(gain) + col[c], to[c]);
+      else to[c][0] = to[c][1] = to[c][2] = to[c][3] = 1.f;
+    }
+  };
+  if (a.out_a) gains(a.gain_a, g[0]);
+  if (a.out_b) gains(a.gain_b, g[1]);
+  __shared__ float red[16];
+  ss = wave_sum(ss);
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+  if (lane == 0) red[wave] = ss;
+  __syncthreads();
+  float tot = 0.f;
+  for (int w = 0; w < nw; ++w) tot += red[w];
+  const float rs = 1.0f / sqrtf(tot / (float)H + a.eps);
+  auto give = [&](void* out, const float (&by)[C][4]) {
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      if ((int)threadIdx.x * 4 + c * step >= H) break;
+      float y[4];
+      for (int e = 0; e < 4; ++e) y[e] = v[c][e] * rs * by[c][e];
+      store4<T>(reinterpret_cast<T*>(out) + row + col[c], y);
+    }
+  };
+  if (a.out_a) give(a.out_a, g[0]);
+  if (a.out_b) give(a.out_b, g[1]);
+}
+
+// ... rows that are too long for that
 template <typename T, bool STEP>
-__global__ void reduce_norm_kernel(ReduceNormArgs a) {
+__global__ void reduce_norm_long_kernel(ReduceNormArgs a) {
   const int row = blockIdx.x;
   const int H = a.H;
   float* xr = a.x + (size_t)row * H;
@@ -97,13 +195,18 @@ __global__ void reduce_norm_kernel(ReduceNormArgs a) {
   }
 }
 
+template <typename T, bool STEP>
+static void launch_reduce_norm_t(const ReduceNormArgs& a, int threads, hipStream_t s) {
+  auto* const kernel = a.H <= 4 * threads ? reduce_norm_kernel<T, STEP, 1> : a.H <= 8 * threads ? reduce_norm_kernel<T, STEP, 2>
+                       : a.H <= 16 * threads ? reduce_norm_kernel<T, STEP, 4> : reduce_norm_long_kernel<T, STEP>;
+  hipLaunchKernelGGL(kernel, dim3(a.rows), dim3(threads), 0, s, a);
+}
 hipError_t launch_reduce_norm(const ReduceNormArgs& a, bool is_bf16, hipStream_t s) {
   if (a.rows <= 0) return hipSuccess;
   const int threads = a.H >= 4096 ? 1024 : 256;
   const bool step = a.x_out && a.x_step;
-  auto* const kernel = is_bf16 ? (step ? reduce_norm_kernel<bf16_t, true> : reduce_norm_kernel<bf16_t, false>)
-                               : (step ? reduce_norm_kernel<float, true> : reduce_norm_kernel<float, false>);
-  hipLaunchKernelGGL(kernel, dim3(a.rows), dim3(threads), 0, s, a);
+  if (is_bf16) step ? launch_reduce_norm_t<bf16_t, true>(a, threads, s) : launch_reduce_norm_t<bf16_t, false>(a, threads, s);
+  else step ? launch_reduce_norm_t<float, true>(a, threads, s) : launch_reduce_norm_t<float, false>(a, threads, s);
   return hipGetLastError();
 }
 
@@ -114,37 +217,25 @@ __global__ __launch_bounds__(1024) void reduce_norm_two_kernel(ReduceNormArgs a,
   const int H = a.H, step = blockDim.x * 4;
   const size_t row = (size_t)blockIdx.x * H;
   __shared__ float red[2][16];
+  int col[C];
   float v[2][C][4], ss[2] = {0.f, 0.f};
 #pragma unroll
   for (int c = 0; c < C; ++c) {
-    const int i = threadIdx.x * 4 + c * step;
-    if (i >= H) break;
-    float x[4];
-    load4<float>(a.x + row + i, x);
-    auto add = [&](const ReduceNormArgs& r) {
-      auto pieces = [&](int n, auto load) {   // (four requested before the first is added)
-        for (int s0 = 0; s0 < n; s0 += 4) {
-          float t[4][4];
+    col[c] = min((int)threadIdx.x * 4 + c * step, H - 4);
+    load4<float>(a.x + row + col[c], v[0][c]);
+  }
+  reduce_add<T>(a, row, col, v[0]);
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
-            if (s0 + j < n) load(s0 + j, t[j]);
+  for (int c = 0; c < C; ++c)
+    for (int e = 0; e < 4; ++e) v[1][c][e] = v[0][c][e];
+  reduce_add<T>(b, row, col, v[1]);
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
-            if (s0 + j < n)
-              for (int e = 0; e < 4; ++e) x[e] += t[j][e];
-        }
-      };
-      pieces(r.n_parts, [&](int s, float (&t)[4]) { load4<float>(r.parts + s * r.part_stride + row + i, t); });
-      pieces(r.n_peers, [&](int s, float (&t)[4]) { load4<T>(reinterpret_cast<const T*>(r.peers) + s * r.peer_stride + row + i, t); });
-    };
-    add(a);
-    for (int e = 0; e < 4; ++e) v[0][c][e] = x[e];
-    ss[0] += squares4(x);
-    add(b);
-    for (int e = 0; e < 4; ++e) v[1][c][e] = x[e];
-    ss[1] += squares4(x);
-    store4<float>(b.x + row + i, x);
-    if (b.x_out) store4<float>(b.x_out + row + i, x);
+  for (int c = 0; c < C; ++c) {
+    if ((int)threadIdx.x * 4 + c * step >= H) break;
+    ss[0] += squares4(v[0][c]);
+    ss[1] += squares4(v[1][c]);
+    store4<float>(b.x + row + col[c], v[1][c]);
+    if (b.x_out) store4<float>(b.x_out + row + col[c], v[1][c]);
   }
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
 #pragma unroll
@@ -681,11 +772,11 @@ hipError_t launch_plain_gemm(const PlainGemmArgs& a, bool is_bf16, hipStream_t s
 // host-made table) and append of k, v to the cache (packed-weight path, bf16).  One thread per pair.
 // ------------------------------------------------------------------------------------------------
 template <typename T>
-__global__ void rope_append_kernel(RopeAppendArgs a) {
+__device__ __forceinline__ void rope_append_block(const RopeAppendArgs& a, unsigned block) {
   const int half = a.d >> 1;
   const int per_row = (a.nq + 2 * a.nkv) * half;
   const int rows = a.B * a.T;
-  const long long gid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  const long long gid = (long long)block * 256 + threadIdx.x;
   if (gid >= (long long)rows * per_row) return;
   const int row = (int)(gid / per_row);
   const int u = (int)(gid % per_row);
@@ -695,15 +786,25 @@ __global__ void rope_append_kernel(RopeAppendArgs a) {
   const int nqkv = (a.nq + 2 * a.nkv) * a.d;
   const int head = u / half, j = u % half;  // head index over q heads, then k heads, then v heads
   const int col = head * a.d + 2 * j;
+  const float c = a.cos_tab[(size_t)pos * half + j], sn = a.sin_tab[(size_t)pos * half + j];   // (v does not need them)
   float e = 0.f, o = 0.f;
-  for (int s = 0; s < a.n_parts; ++s) {
-    const float* p = a.qkv + s * a.part_stride + (size_t)row * nqkv + col;
-    e += p[0];
-    o += p[1];
-  }
+  four_at_a_time(a.n_parts, [&](int s, auto pieces) {
+    constexpr int N = decltype(pieces)::n;
+    float t[N][2];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      const float* p = a.qkv + (s + k) * a.part_stride + (size_t)row * nqkv + col;
+      t[k][0] = p[0];
+      t[k][1] = p[1];
+    }
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      e += t[k][0];
+      o += t[k][1];
+    }
+  });
   if (head < a.nq + a.nkv) {
-    const float c = a.cos_tab[(size_t)pos * half + j], sn = a.sin_tab[(size_t)pos * half + j];
-    const float re = e * c - o * sn, ro = e * sn + o * c;
+    const float re = fmaf(e, c, -(o * sn)), ro = fmaf(o, c, e * sn);   // (written out: every kernel around it gives the same bits)
     e = re;
     o = ro;
   }
@@ -730,11 +831,14 @@ __global__ void rope_append_kernel(RopeAppendArgs a) {
   store_f<T>(dst + 1, o);
 }
 
+__global__ __launch_bounds__(256) void rope_append_kernel(RopeAppendArgs a) { rope_append_block<bf16_t>(a, blockIdx.x); }
+
+static unsigned rope_append_blocks(const RopeAppendArgs& a) { return (unsigned)(((long long)a.B * a.T * (a.nq + 2 * a.nkv) * (a.d / 2) + 255) / 256); }
+
 hipError_t launch_rope_append(const RopeAppendArgs& a, hipStream_t s) {
-  const long long total = (long long)a.B * a.T * (a.nq + 2 * a.nkv) * (a.d / 2);
-  if (total <= 0) return hipSuccess;
-  const unsigned blocks = (unsigned)((total + 255) / 256);
-  hipLaunchKernelGGL(rope_append_kernel<bf16_t>, dim3(blocks), dim3(256), 0, s, a);
+  const unsigned blocks = rope_append_blocks(a);
+  if (!blocks) return hipSuccess;
+  hipLaunchKernelGGL(rope_append_kernel, dim3(blocks), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
@@ -1016,29 +1120,49 @@ hipError_t launch_attn_generic(const AttnGenericArgs& a, bool is_bf16, hipStream
 // ------------------------------------------------------------------------------------------------
 // SwiGLU of a split gate/up projection (packed-weight path).
 // Four activations per thread; the gate columns of eight activations and the matching up columns are neighbours.
-__global__ __launch_bounds__(256) void swiglu_parts_kernel(const float* __restrict__ parts, int n_parts, size_t part_stride,
-                                                           bf16_t* __restrict__ act, int M, int I) {
-  const long long gid = (long long)blockIdx.x * 256 + threadIdx.x;
-  const int i4 = I >> 2;
-  if (gid >= (long long)M * i4) return;
+__device__ __forceinline__ void swiglu_parts_block(const SwigluPartsArgs& a, unsigned block) {
+  const long long gid = (long long)block * 256 + threadIdx.x;
+  const int i4 = a.I >> 2;
+  if (gid >= (long long)a.M * i4) return;
   const int m = (int)(gid / i4), i = (int)(gid % i4) * 4;
-  const float* p = parts + (size_t)m * 2 * I + 16 * (i >> 3) + (i & 7);
-  float g[4] = {}, u[4] = {}, a[4];
-  for (int s = 0; s < n_parts; ++s) {
-    float t[4];
-    load4<float>(p + s * part_stride, t);
-    for (int e = 0; e < 4; ++e) g[e] += t[e];
-    load4<float>(p + s * part_stride + 8, t);
-    for (int e = 0; e < 4; ++e) u[e] += t[e];
-  }
-  for (int e = 0; e < 4; ++e) a[e] = g[e] / (1.0f + __expf(-g[e])) * u[e];
-  store4<bf16_t>(act + (size_t)m * I + i, a);
+  const float* p = a.parts + (size_t)m * 2 * a.I + 16 * (i >> 3) + (i & 7);
+  float g[4] = {}, u[4] = {}, y[4];
+  four_at_a_time(a.n_parts, [&](int s, auto pieces) {
+    constexpr int N = decltype(pieces)::n;
+    float t[N][2][4];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      load4<float>(p + (s + k) * a.part_stride, t[k][0]);
+      load4<float>(p + (s + k) * a.part_stride + 8, t[k][1]);
+    }
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+      for (int e = 0; e < 4; ++e) { g[e] += t[k][0][e]; u[e] += t[k][1][e]; }
+  });
+  for (int e = 0; e < 4; ++e) y[e] = g[e] / (1.0f + __expf(-g[e])) * u[e];
+  store4<bf16_t>(a.act + (size_t)m * a.I + i, y);
 }
 
-hipError_t launch_swiglu_parts(const float* parts, int n_parts, size_t part_stride, bf16_t* act, int M, int I, hipStream_t s) {
-  const long long total = (long long)M * (I >> 2);
-  if (total <= 0) return hipSuccess;
-  hipLaunchKernelGGL(swiglu_parts_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, parts, n_parts, part_stride, act, M, I);
+__global__ __launch_bounds__(256) void swiglu_parts_kernel(SwigluPartsArgs a) { swiglu_parts_block(a, blockIdx.x); }
+
+// Rotary + append and SwiGLU of a layer whose modules share launches: neither reads what the other writes, and each by itself is as long as its round trips
+__global__ __launch_bounds__(256) void rope_swiglu_kernel(RopeAppendArgs a, SwigluPartsArgs b, unsigned n_a) {
+  if (blockIdx.x < n_a) rope_append_block<bf16_t>(a, blockIdx.x);
+  else swiglu_parts_block(b, blockIdx.x - n_a);
+}
+
+static unsigned swiglu_parts_blocks(const SwigluPartsArgs& a) { return (unsigned)(((long long)a.M * (a.I >> 2) + 255) / 256); }
+
+hipError_t launch_swiglu_parts(const SwigluPartsArgs& a, hipStream_t s) {
+  const unsigned blocks = swiglu_parts_blocks(a);
+  if (!blocks) return hipSuccess;
+  hipLaunchKernelGGL(swiglu_parts_kernel, dim3(blocks), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+hipError_t launch_rope_swiglu(const RopeAppendArgs& a, const SwigluPartsArgs& b, hipStream_t s) {
+  const unsigned n_a = rope_append_blocks(a), n_b = swiglu_parts_blocks(b);
+  if (!(n_a + n_b)) return hipSuccess;
+  hipLaunchKernelGGL(rope_swiglu_kernel, dim3(n_a + n_b), dim3(256), 0, s, a, b, n_a);
   return hipGetLastError();
 }
 

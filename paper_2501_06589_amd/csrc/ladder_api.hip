@@ -500,14 +500,18 @@ GemmArgs qkv_args(ladder_ctx* c, const LayerStore& L, const char* yin, const flo
   return a;
 }
 
-int run_rope_append(ladder_ctx* c, const LayerStore& L, int slots, int B, int T, int pos0, const int* pos_dev, hipStream_t s) {
+RopeAppendArgs rope_append_args(ladder_ctx* c, const LayerStore& L, int slots, int B, int T, int pos0, const int* pos_dev) {
   const ladder_config& g = c->cfg;
   RopeAppendArgs ra{};
   ra.qkv = c->qkv; ra.n_parts = slots; ra.part_stride = (size_t)B * T * c->nqkv;
   ra.q_out = c->qbuf; ra.cache_k = L.cache_k; ra.cache_v = L.cache_v;
   ra.cos_tab = c->cos_tab; ra.sin_tab = c->sin_tab;
   ra.B = B; ra.T = T; ra.pos0 = pos0; ra.nq = g.n_q_heads; ra.nkv = g.n_kv_heads; ra.d = g.head_dim; ra.max_seq = c->s_cap; ra.pos_dev = pos_dev;
-  HIP_TRY(c, timed(c, LADDER_K_ROPE_APPEND, s, [&] { return launch_rope_append(ra, s); }));
+  return ra;
+}
+
+int run_rope_append(ladder_ctx* c, const RopeAppendArgs& a, hipStream_t s) {
+  HIP_TRY(c, timed(c, LADDER_K_ROPE_APPEND, s, [&] { return launch_rope_append(a, s); }));
   return LADDER_OK;
 }
 
@@ -542,10 +546,12 @@ GemmArgs gate_up_args(ladder_ctx* c, const LayerStore& L, const char* yin, const
   return a;
 }
 
-int run_swiglu_parts(ladder_ctx* c, const GemmArgs& gate_up, hipStream_t s) {
-  HIP_TRY(c, timed(c, LADDER_K_OTHER, s, [&] {
-    return launch_swiglu_parts(c->gu, gate_up.ksplit, gate_up.out_stride, (bf16_t*)c->act, gate_up.M, c->cfg.inter, s);
-  }));
+SwigluPartsArgs swiglu_parts_args(ladder_ctx* c, const GemmArgs& gate_up) {
+  return SwigluPartsArgs{c->gu, gate_up.ksplit, gate_up.out_stride, (bf16_t*)c->act, gate_up.M, c->cfg.inter};
+}
+
+int run_swiglu_parts(ladder_ctx* c, const SwigluPartsArgs& a, hipStream_t s) {
+  HIP_TRY(c, timed(c, LADDER_K_OTHER, s, [&] { return launch_swiglu_parts(a, s); }));
   return LADDER_OK;
 }
 
@@ -580,7 +586,7 @@ int run_module(ladder_ctx* c, int m, int B, int T, int pos0, bool decode, hipStr
         qkv_slots = a.epilogue == 2 ? 0 : a.ksplit;
         HIP_TRY(c, timed(c, LADDER_K_GEMM, s, [&] { return launch_gemm_mfma(a, s); }));
       }
-      if (qkv_slots > 0 && (rc = run_rope_append(c, L, qkv_slots, B, T, pos0, pos_dev, s))) return rc;
+      if (qkv_slots > 0 && (rc = run_rope_append(c, rope_append_args(c, L, qkv_slots, B, T, pos0, pos_dev), s))) return rc;
       if ((rc = run_attention(c, L, B, T, pos0, pos_dev, s))) return rc;
       if ((rc = run_last_projection(c, m, c->obuf, L.po, rows, nqd, pout + slots * pstride, fuse, emb, copy, s, &slots))) return rc;
     } else {
@@ -592,7 +598,7 @@ int run_module(ladder_ctx* c, int m, int B, int T, int pos0, bool decode, hipStr
       } else {
         const GemmArgs a = gate_up_args(c, L, yin, c->y_scale[par], rows);
         HIP_TRY(c, timed(c, LADDER_K_GEMM, s, [&] { return launch_gemm_mfma(a, s); }));
-        if (a.epilogue == 0 && (rc = run_swiglu_parts(c, a, s))) return rc;
+        if (a.epilogue == 0 && (rc = run_swiglu_parts(c, swiglu_parts_args(c, a), s))) return rc;
       }
       if ((rc = run_last_projection(c, m, c->act, L.pd, rows, I, pout + slots * pstride, fuse, emb, copy, s, &slots))) return rc;
     }
@@ -601,7 +607,7 @@ int run_module(ladder_ctx* c, int m, int B, int T, int pos0, bool decode, hipStr
   return LADDER_OK;
 }
 
-// Both modules of a layer that do not read each other's output (lag 2), 17 .. 256 rows, one shard: { QKV, gate/up }, rotary + append, attention, { O, down } (and
+// Both modules of a layer that do not read each other's output (lag 2), 17 .. 256 rows, one shard: { QKV, gate/up }, { rotary + append, SwiGLU of a split gate/up }, attention, { O, down } (and
 // the caller's reduce of both); products whose tiles have no kernel together in a launch each.  n_slots: of the attention module, of the MLP
 int run_layer_beside(ladder_ctx* c, int l, int B, int T, int pos0, bool decode, hipStream_t s, int n_slots[2]) {
   const ladder_config& g = c->cfg;
@@ -620,8 +626,11 @@ int run_layer_beside(ladder_ctx* c, int l, int B, int T, int pos0, bool decode, 
   };
   const GemmArgs qkv = qkv_args(c, L, c->y[1], c->y_scale[1], rows, T, pos0), gu = gate_up_args(c, L, c->y[0], c->y_scale[0], rows);
   if ((rc = two(qkv, gu))) return rc;
-  if (gu.epilogue == 0 && (rc = run_swiglu_parts(c, gu, s))) return rc;
-  if (qkv.epilogue == 0 && (rc = run_rope_append(c, L, qkv.ksplit, B, T, pos0, pos_dev, s))) return rc;
+  const RopeAppendArgs rope = rope_append_args(c, L, qkv.ksplit, B, T, pos0, pos_dev);
+  const SwigluPartsArgs swiglu = swiglu_parts_args(c, gu);
+  if (gu.epilogue == 0 && qkv.epilogue == 0) HIP_TRY(c, timed(c, LADDER_K_ROPE_APPEND, s, [&] { return launch_rope_swiglu(rope, swiglu, s); }));
+  else if (gu.epilogue == 0 && (rc = run_swiglu_parts(c, swiglu, s))) return rc;
+  else if (qkv.epilogue == 0 && (rc = run_rope_append(c, rope, s))) return rc;
   if ((rc = run_attention(c, L, B, T, pos0, pos_dev, s))) return rc;
   const GemmArgs o = few_rows_args(c->obuf, nqd, L.po, rows, nqd, g.hidden, c->parts[1], nullptr);
   const GemmArgs dn = few_rows_args(c->act, g.inter, L.pd, rows, g.inter, g.hidden, c->parts[0], nullptr);

